@@ -414,14 +414,14 @@ typedef struct {
     int32_t queue_batch;        /* gather batch of the queue kernel */
     int32_t queue_workgroups;   /* workgroups of the persistent launch */
     int32_t pad;
-    int64_t queue_tiles_per_step; /* tiles (256 particles x 1024 scan points) per step through the queues */
+    int64_t queue_tiles_per_step; /* tiles (at most 256 particles x 1024 scan points) per step through the queues */
 } mp_batch_info;
 
 /* Instances with the PLAIN scorer on a dense-field map get lik_layout =
  * GROUPED: in every correction iteration their likelihood passes run as one
- * persistent launch (a fixed grid of workgroups taking tiles of 256 particles
- * x 1024 scan points of all these instances, in instance order, from an
- * atomic work queue); the other instances launch their own
+ * persistent launch (a fixed grid of workgroups taking tiles of at most 256
+ * particles x 1024 scan points of all these instances, in instance order, from
+ * an atomic work queue); the other instances launch their own
  * likelihood kernels on their branch.  autotune != 0 times the queue kernel
  * for each gather batch (2, 4, 8) and keeps the fastest, and times the
  * likelihood launch of every other PLAIN instance for each (lik_layout,

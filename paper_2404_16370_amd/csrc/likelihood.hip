@@ -48,6 +48,7 @@ struct LikArgs {
     const float4* __restrict__ scan;    // ns x 3 float4 records
     float* __restrict__ partial;        // [chunk][29][N]
     int32_t n, ns, chunk_len, nchunks, nbx;
+    int32_t rounds;                     // grouped layout: rounds of 32 particles per workgroup
     float dmax2, cmax;
     float sig2, ib, r_floor, r_out;   // residual-field scorer: sigma_s^2, 1 / (1 + sigma_s^2), floor of r, r outside the gate
 };
@@ -356,20 +357,22 @@ __global__ __launch_bounds__(kLanes) void k_lik(LikArgs A) {
 }
 
 // Grouped layout: 16 lanes per particle.  A workgroup (8 waves) keeps a
-// chunk of 1024 scan records in LDS and takes 256 LSH-sorted particles, 32 at
-// a time; the 16 lanes of a particle walk its points with stride 16, so one
-// gather instruction of a wave touches the records of 4 particles x 16
-// consecutive (Morton-ordered) scan points: a few compact clusters of cells
-// instead of 64 scattered ones.  The 29 sums of a particle are reduced across
-// its 16 lanes by shuffles and written per (chunk, sorted position).
+// chunk of 1024 scan records in LDS and takes up to 256 LSH-sorted particles,
+// 32 at a time (see lik_rounds); the 16 lanes of a particle walk its points with
+// stride 16, so one gather instruction of a wave touches the records of 4
+// particles x 16 consecutive (Morton-ordered) scan points: a few compact
+// clusters of cells instead of 64 scattered ones.  The 29 sums of a particle
+// are reduced across its 16 lanes by shuffles and written per (chunk, sorted
+// position).
 constexpr int kGLanes = 16;
 constexpr int kGChunk = 1024;
 constexpr int kGThreads = 512;
-constexpr int kGParticles = 256;
+constexpr int kGSlots = kGThreads / kGLanes;   // particles a workgroup takes at a time
+constexpr int kGRounds = 8;          // most rounds of a workgroup
 
-// One tile of the grouped layout: scan chunk `chunk` (kGChunk points) against
-// the kGParticles particles of sorted block `pblk`; the whole workgroup takes
-// part (it stages the chunk in `tile`).
+// One tile of the grouped layout: scan chunk `chunk` (kGChunk points)
+// against the A.rounds * kGSlots particles of sorted block `pblk`; the whole
+// workgroup takes part (it stages the chunk in `tile`).
 template <int BACKEND, int BATCH, int SC>
 __device__ __forceinline__ void grp_tile(const LikArgs& A, const int chunk, const int pblk, float4* tile) {
     const int k0 = chunk * kGChunk;
@@ -392,10 +395,10 @@ __device__ __forceinline__ void grp_tile(const LikArgs& A, const int chunk, cons
     const int grp = threadIdx.x / kGLanes;   // particle slot in the workgroup (0..31)
     const int gl = threadIdx.x % kGLanes;    // lane within the particle's group
     const float a = A.map.gicp_a;
-    constexpr int kSlots = kGThreads / kGLanes;
     static_assert(kGChunk % (kGLanes * BATCH) == 0, "a batch never runs past the staged chunk");
-    for (int round = 0; round < kGParticles / kSlots; ++round) {
-        const int sp = pblk * kGParticles + round * kSlots + grp;   // sorted position
+    for (int round = 0; round < A.rounds; ++round) {
+        const int sp = (pblk * A.rounds + round) * kGSlots + grp;   // sorted position
+        if (sp - grp >= A.n) break;                                 // (uniform) no particle left
         int i = sp < A.n ? (A.order ? A.order[sp] : sp) : 0;
         const bool active = sp < A.n && i >= 0 && i < A.n;
         if (!active) i = 0;   // evaluated like particle 0, never written
@@ -651,6 +654,21 @@ static void lik_prepare_order(mp_filter f, int scorer, hipStream_t s) {
     mp_radix_sort_u32_inplace_parity(k0, v0, k1, v1, n, kBits, f->hist, s);
 }
 
+// Rounds of 32 particles that each workgroup of a grouped pass takes.  Two
+// workgroups fit a CU, so 512 run at once; a pass of fewer than kSplitGroups
+// workgroups gives each fewer particles (no sum depends on it; the price is
+// staging a chunk for fewer particles).  With 256 particles in every
+// workgroup, 4096 particles x 1024 points ran on 16 of the 256 CUs: 266 us a
+// launch, 39 us with 32; 16,384 x 2048 312 -> 125 us, 65,536 x 4096 944 -> 874
+// us (512 of its 1024 workgroups in flight, the last ones alone).
+constexpr int kSplitGroups = 1024;
+
+static int lik_rounds(int n, int nch) {
+    int rounds = kGRounds;
+    while (rounds > 1 && (int64_t)((n + kGSlots * rounds - 1) / (kGSlots * rounds)) * nch < kSplitGroups) rounds /= 2;
+    return rounds;
+}
+
 // scan-point chunks per particle tile and the chunk length
 static int lik_chunks(mp_filter f, int& clen) {
     const int n = f->n;
@@ -693,9 +711,10 @@ LikPlan lik_plan(mp_filter f) {
     const int n = f->n;
     const int ns = f->scan_n;
     P.grouped = lik_grouped(f) && P.scorer != MP_SCORER_SURROGATE;
-    const int nbx = P.grouped ? (n + kGParticles - 1) / kGParticles : (n + kLanes - 1) / kLanes;
     int clen = 0;
     P.nch = lik_chunks(f, clen);
+    const int rounds = lik_rounds(n, P.nch);
+    const int nbx = P.grouped ? (n + kGSlots * rounds - 1) / (kGSlots * rounds) : (n + kLanes - 1) / kLanes;
     f->lik_chunks = P.nch;
     f->lik_chunk_len = clen;
     f->partial.ensure(mp_lik_partial_bytes(f));
@@ -710,6 +729,7 @@ LikPlan lik_plan(mp_filter f) {
     A.chunk_len = std::max(1, clen);
     A.nchunks = P.nch;
     A.nbx = nbx;
+    A.rounds = rounds;
     A.dmax2 = f->p.d_max * f->p.d_max;
     A.cmax = f->p.c_max;
     A.sig2 = f->p.sigma_s * f->p.sigma_s;

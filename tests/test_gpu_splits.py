@@ -1,0 +1,40 @@
+"""Launch splits and pruned searches that must not change a result: every
+comparison here is bit for bit."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+from paper_2404_16370_amd import megapf as M
+from paper_2404_16370_amd import synth as S
+
+
+@pytest.fixture(scope="module")
+def room():
+    w = S.build_workload("room", map_points=100_000, scan_points=1100)
+    return dict(w=w, map=M.Map(w["map_xyz"], voxel=0.5))
+
+
+def _filter(room, n, poses, **kw):
+    p = dict(n_particles=n, k=8, lsh_bits=16, svgd_iters=1, window_c=16, d_max=1.0, seed=5)
+    p.update(kw)
+    return M.Filter(room["map"], M.mp_filter_default_params(**p), poses=poses)
+
+
+@pytest.mark.parametrize("ns", [40, 1024, 1100])
+def test_grouped_likelihood_does_not_depend_on_the_split(room, ns):
+    # 1, 2, 4 and 8 rounds of 32 particles per workgroup, ragged last rounds
+    R, t = room["w"]["traj"][0]
+    poses = S.gaussian_particles(270_001, S.pose8(R, t), 0.1, 0.3, 3)
+    ref = None
+    for n in (31, 32, 33, 9_999, 40_001, 100_000, 270_001):
+        f = _filter(room, n, poses[:n], lik_layout=M.MP_LIK_LAYOUT_GROUPED)
+        f.scan_upload(room["w"]["scans"][0][:ns])
+        f.debug_stage(M.MP_STAGE_LIK)
+        psi = f.debug_get("psi")
+        assert np.isfinite(psi).all() and psi[:, 7].max() > 0
+        if ref is not None:
+            m = min(len(ref), n)
+            assert np.array_equal(psi[:m], ref[:m])
+        ref = psi if ref is None or n > len(ref) else ref
+        f.close()
