@@ -8,7 +8,7 @@ for all timed steps are generated and copied to HBM before timing; the timed
 region covers mp_scan_upload (device-resident points) + mp_filter_step.
 
 Prints one JSON line.  `roofline` refers to the likelihood kernel (k_lik_grp),
-timed with HIP events on the stream it runs on; `cpu_baseline` times the CPU
+timed by the device clock (mp_stage_times); `cpu_baseline` times the CPU
 oracle on a bounded sample of the same workload on this host's cores.
 """
 import argparse
@@ -932,7 +932,7 @@ def main():
         e1.record()
         f.step(dT, cov)
         e2.record()
-        st = f.stage_times()   # synchronises on this step's events
+        st = f.stage_times()   # synchronises the device
         lik_ms.append(st["likelihood_core"][0])
         lik_n.append(st["likelihood_core"][1])
         up_ms.append(e0.elapsed_time(e1))

@@ -69,6 +69,8 @@ void DevMem::release() {
     bytes = 0;
 }
 
+constexpr size_t kStampMarks = 2;   // clock values of a scan upload before those of a step
+
 static inline hipStream_t as_stream(void* s) { return static_cast<hipStream_t>(s); }
 
 static bool is_device_ptr(const void* p) {
@@ -359,10 +361,6 @@ static void validate_params(const mp_filter_params& p) {
 
 static void destroy_filter(mp_filter f) {
     if (!f) return;
-    for (int st = 0; st < MP_NUM_STAGES; ++st) {
-        for (hipEvent_t e : f->ev0[st]) (void)hipEventDestroy(e);
-        for (hipEvent_t e : f->ev1[st]) (void)hipEventDestroy(e);
-    }
     if (f->map) f->map->users--;
     if (f->sur) f->sur->users--;
     delete f;
@@ -440,6 +438,12 @@ extern "C" mp_status mp_filter_init(mp_map map, const mp_filter_params* params, 
             f->post1.alloc(4 * N);
             f->flags.alloc(64);
             f->tlsh.alloc(32);
+            // one clock value per mark of a step: prediction, re-score, posterior, end; per iteration
+            // three list stages per table, three of the likelihood, SVGD (stages beyond 2^16 iterations' marks
+            // are not timed)
+            const size_t per = 3 * (size_t)std::max(1, params->lsh_tables) + 4;
+            f->stamps.alloc(sizeof(uint64_t) *
+                            (kStampMarks + 8 + per * (size_t)std::min(params->svgd_iters, 1 << 16)));
             f->stepinfo.alloc(16 * sizeof(double));
             f->red.alloc(sizeof(double) * (N + 3 * ((N + 255) / 256)) + sizeof(int) * ((N + 255) / 256) + 64);
             MP_HIP(hipMemsetAsync(f->flags.p, 0, 64, s));
@@ -509,34 +513,35 @@ extern "C" mp_status mp_scan_upload(mp_filter f, const float* xyz, const float* 
             }
             f->scan_orig.ensure(sizeof(float) * 12 * (size_t)n);
             f->orig_n = n;
-            f->ev_count[MP_STAGE_SCAN] = 0;
-            mp_tick(f, MP_STAGE_SCAN, true, s);
+            uint64_t* stamps = f->stamps.as<uint64_t>();
             // Walk order for the likelihood: Morton order of the points on a grid of half the
             // map voxel, so that consecutive points of one particle land in the same or
             // neighbouring voxels (the sum over points does not depend on the order).
             mp_scan_walk_order(f->scan_xyz.as<float>(), n, 0.5f * f->map->params.voxel, lo_bad, work, work + n,
                                f->scan_perm.as<int32_t>(), reinterpret_cast<int32_t*>(work + 2 * (size_t)n),
-                               f->scan_sort, s);
+                               f->scan_sort, stamps, s);
             mp_scan_records(f->scan_xyz.as<float>(), dcov, n, f->p.scan_k, f->p.cov_eps, f->scan_orig.as<float>(), s);
-            mp_scan_permute(f->scan_orig.as<float>(), f->scan_perm.as<int32_t>(), n, f->scan.as<float>(), s);
-            mp_tick(f, MP_STAGE_SCAN, false, s);
+            mp_scan_permute(f->scan_orig.as<float>(), f->scan_perm.as<int32_t>(), n, f->scan.as<float>(), stamps + 1,
+                            s);
+            f->scan_timed = true;
         }
         f->scan_n = n;
         f->last_stream = s;
     });
 }
 
-void mp_tick(mp_filter f, int st, bool begin, hipStream_t s) {
-    if (f->capturing) return;
-    const int k = f->ev_count[st];
-    auto& v = begin ? f->ev0[st] : f->ev1[st];
-    while ((int)v.size() <= k) {
-        hipEvent_t e;
-        MP_HIP(hipEventCreate(&e));
-        v.push_back(e);
+void mp_stage_begin(mp_filter f, int st) {
+    if (!f->timing) return;
+    uint64_t* base = f->stamps.as<uint64_t>();
+    int32_t slot = kStampMarks + (int32_t)f->marks.size();
+    if (sizeof(uint64_t) * ((size_t)slot + 2) > f->stamps.bytes) {   // (one slot is left for the end)
+        f->timing = false;
+        f->stamp = nullptr;
+        return;
     }
-    MP_HIP(hipEventRecord(v[k], s));
-    if (!begin) f->ev_count[st] = k + 1;
+    if (f->stamp) slot = f->marks.back().slot;   // the stage before launched nothing: both start here
+    f->marks.push_back({st, slot});
+    f->stamp = base + slot;
 }
 
 // host FP64 Cholesky of a 6x6 PSD matrix; false if not PSD
@@ -600,12 +605,10 @@ static void run_stage(mp_filter f, int st, int it, hipStream_t s) {
 // the likelihood and the lists' kernel values at the current (final) poses:
 // one likelihood pass and a refresh that only re-ranks the current lists
 static void rescore(mp_filter f, hipStream_t s) {
-    mp_tick(f, MP_STAGE_LIK, true, s);
+    mp_stage_begin(f, MP_STAGE_LIK);
     run_stage(f, MP_STAGE_LIK, f->p.svgd_iters, s);
-    mp_tick(f, MP_STAGE_LIK, false, s);
-    mp_tick(f, MP_STAGE_REFRESH, true, s);
+    mp_stage_begin(f, MP_STAGE_REFRESH);
     mp_launch_refresh(f, s, 0);
-    mp_tick(f, MP_STAGE_REFRESH, false, s);
 }
 
 void mp_reserve_step(mp_filter f) {
@@ -621,9 +624,8 @@ void mp_step_begin(mp_filter f, bool pred, const float dq[7], const float L[36],
     if (pred || f->dyn) {
         static const float ident[7] = {1, 0, 0, 0, 0, 0, 0};
         static const float zero[36] = {};
-        mp_tick(f, MP_STAGE_PREDICT, true, s);
+        mp_stage_begin(f, MP_STAGE_PREDICT);
         mp_launch_predict(f, pred ? dq : ident, pred ? L : zero, pred && noise, s);
-        mp_tick(f, MP_STAGE_PREDICT, false, s);
     }
 }
 
@@ -634,24 +636,29 @@ void mp_step_iter_nbr(mp_filter f, int it, hipStream_t s) {
     const int tables = std::max(1, f->p.lsh_tables);
     for (int l = 0; l < tables; ++l)
         for (int st : {MP_STAGE_LSH, MP_STAGE_SORT, MP_STAGE_REFRESH}) {
-            mp_tick(f, st, true, s);
+            mp_stage_begin(f, st);
             run_stage(f, st, it * tables + l, s);
-            mp_tick(f, st, false, s);
         }
 }
 
 void mp_step_iter_svgd(mp_filter f, int it, hipStream_t s) {
-    mp_tick(f, MP_STAGE_SVGD, true, s);
+    mp_stage_begin(f, MP_STAGE_SVGD);
     run_stage(f, MP_STAGE_SVGD, it, s);
-    mp_tick(f, MP_STAGE_SVGD, false, s);
 }
 
 void mp_step_end(mp_filter f, hipStream_t s) {
-    if (f->scan_n <= 0 || f->p.svgd_iters <= 0) return;
-    if (f->p.final_rescore) rescore(f, s);
-    mp_tick(f, MP_STAGE_POSTERIOR, true, s);
-    mp_launch_posterior(f, s);
-    mp_tick(f, MP_STAGE_POSTERIOR, false, s);
+    const bool corrected = f->scan_n > 0 && f->p.svgd_iters > 0;
+    if (corrected) {
+        if (f->p.final_rescore) rescore(f, s);
+        mp_stage_begin(f, MP_STAGE_POSTERIOR);
+    }
+    uint64_t* end = nullptr;
+    if (f->timing) {
+        f->marks.push_back({MP_MARK_END, (int32_t)(kStampMarks + f->marks.size())});
+        end = f->stamps.as<uint64_t>() + f->marks.back().slot;
+    }
+    if (corrected) mp_launch_posterior(f, s, end);
+    else if (end && f->marks.size() > 1) mp_launch_stamp(end, s);
 }
 
 void mp_step_launches(mp_filter f, bool pred, const float dq[7], const float L[36], bool noise, hipStream_t s) {
@@ -659,9 +666,8 @@ void mp_step_launches(mp_filter f, bool pred, const float dq[7], const float L[3
     if (f->scan_n > 0) {
         for (int it = 0; it < f->p.svgd_iters; ++it) {
             mp_step_iter_nbr(f, it, s);
-            mp_tick(f, MP_STAGE_LIK, true, s);
+            mp_stage_begin(f, MP_STAGE_LIK);
             run_stage(f, MP_STAGE_LIK, it, s);
-            mp_tick(f, MP_STAGE_LIK, false, s);
             mp_step_iter_svgd(f, it, s);
         }
     }
@@ -681,8 +687,7 @@ extern "C" mp_status mp_filter_step(mp_filter f, const float dT[7], const float 
         // every work buffer of the step is sized before anything is launched,
         // so that a failed allocation leaves the filter as it was
         mp_reserve_step(f);
-        for (int st = 0; st < MP_NUM_STAGES; ++st)
-            if (st != MP_STAGE_SCAN) f->ev_count[st] = 0;
+        f->marks.clear();
         // check of the learned scorer (before the step, on the current particles)
         f->sur_fallback = false;
         SurCheck& c = f->chk;
@@ -698,7 +703,17 @@ extern "C" mp_status mp_filter_step(mp_filter f, const float dT[7], const float 
                 ++c.fallback_steps;
             }
         }
-        mp_step_launches(f, dT != nullptr, dq, L, noise, s);
+        f->timing = true;
+        try {
+            mp_step_launches(f, dT != nullptr, dq, L, noise, s);
+        } catch (...) {
+            f->timing = false;
+            f->stamp = nullptr;
+            f->marks.clear();
+            throw;
+        }
+        f->timing = false;
+        f->stamp = nullptr;
         f->sur_fallback = false;
         f->frame++;
         f->last_stream = s;
@@ -760,16 +775,31 @@ extern "C" mp_status mp_posterior_query(mp_filter f, mp_posterior* out, float* p
 extern "C" mp_status mp_stage_times(mp_filter f, float* ms_out, int32_t* counts_out) {
     return guarded("mp_stage_times", [&]() {
         if (!f || !ms_out) mp_throw(MP_E_ARG, "null argument");
-        for (int st = 0; st < MP_NUM_STAGES; ++st) {
-            double tot = 0.0;
-            for (int k = 0; k < f->ev_count[st]; ++k) {
-                MP_HIP(hipEventSynchronize(f->ev1[st][k]));
-                float ms = 0.0f;
-                MP_HIP(hipEventElapsedTime(&ms, f->ev0[st][k], f->ev1[st][k]));
-                tot += ms;
+        int32_t counts[MP_NUM_STAGES] = {};
+        double ticks[MP_NUM_STAGES] = {};
+        if (f->scan_timed || !f->marks.empty()) {
+            std::vector<uint64_t> t(f->stamps.bytes / sizeof(uint64_t));
+            MP_HIP(hipDeviceSynchronize());
+            MP_HIP(hipMemcpy(t.data(), f->stamps.p, sizeof(uint64_t) * t.size(), hipMemcpyDeviceToHost));
+            auto add = [&](int st, uint64_t from, uint64_t to, bool count) {
+                ticks[st] += to > from ? (double)(to - from) : 0.0;
+                counts[st] += count ? 1 : 0;
+            };
+            if (f->scan_timed) add(MP_STAGE_SCAN, t[0], t[1], true);
+            for (size_t k = 0; k + 1 < f->marks.size(); ++k) {
+                const uint64_t from = t[f->marks[k].slot], to = t[f->marks[k + 1].slot];
+                const int st = f->marks[k].stage;
+                // the likelihood: walk order, then its kernel, then the solve
+                if (st == MP_STAGE_LIK_CORE || st == MP_MARK_SOLVE) add(MP_STAGE_LIK, from, to, false);
+                if (st != MP_MARK_SOLVE) add(st, from, to, true);
             }
-            ms_out[st] = (float)tot;
-            if (counts_out) counts_out[st] = f->ev_count[st];
+        }
+        int dev = 0, khz = 0;
+        MP_HIP(hipGetDevice(&dev));
+        MP_HIP(hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev));
+        for (int st = 0; st < MP_NUM_STAGES; ++st) {
+            ms_out[st] = (float)(ticks[st] / (double)std::max(1, khz));
+            if (counts_out) counts_out[st] = counts[st];
         }
     });
 }

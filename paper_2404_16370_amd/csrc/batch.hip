@@ -421,8 +421,7 @@ void step_impl(void* p) {
     MP_HIP(hipGraphLaunch(b->exec, c.s));
     for (size_t i = 0; i < n; ++i) {
         mp_filter f = b->f[i];
-        for (int st = 0; st < MP_NUM_STAGES; ++st)
-            if (st != MP_STAGE_SCAN) f->ev_count[st] = 0;
+        f->marks.clear();
         f->frame++;
         f->last_stream = c.s;
     }

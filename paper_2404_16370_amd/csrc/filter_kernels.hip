@@ -76,6 +76,7 @@ struct SvgdArgs {
     const float* __restrict__ kval;
     int32_t n, K;
     float sr, st;
+    uint64_t* stamp;   // stage clock, or null
 };
 
 __device__ inline float3 cross3(const float3 a, const float3 b) {
@@ -144,6 +145,7 @@ __device__ inline void jr_inv_t(const float3 om, const float3 rho, float beta, c
 // T_i <- T_i exp(phi_i) (Jacobi: all j at pre-update poses).
 template <bool EXACT, bool TRANSPORT>
 __global__ __launch_bounds__(256) void k_svgd(SvgdArgs A) {
+    mp_write_stamp(A.stamp);
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= A.n) return;
     mpdet::quat qi;
@@ -220,9 +222,11 @@ struct PredArgs {
     int32_t noise;
     uint32_t purpose;                 // generator purpose of z (prediction, or Gaussian initialisation)
     const StepDyn* __restrict__ dyn;  // captured step: frame, increment and noise from here
+    uint64_t* stamp;                  // stage clock, or null
 };
 
 __global__ __launch_bounds__(256) void k_predict(PredArgs A) {
+    mp_write_stamp(A.stamp);
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= A.n) return;
     if (A.dyn) {
@@ -341,9 +345,12 @@ struct PostArgs {
     float* __restrict__ prior_out;
     int32_t n, K, nb;
     double inv_tau, floor_p;
+    uint64_t* stamp;                // stage clock at the start, or null
+    uint64_t* stamp_end;            // and at the end of the last launch, or null
 };
 
 __global__ __launch_bounds__(kRB) void k_post_logits(PostArgs A) {
+    mp_write_stamp(A.stamp);
     const int i = blockIdx.x * kRB + threadIdx.x;
     double l = -INFINITY, ll = -INFINITY;
     if (i < A.n) {
@@ -471,7 +478,11 @@ __global__ __launch_bounds__(kRB) void k_post_neff_final(PostArgs A) {
     for (int b = threadIdx.x; b < A.nb; b += kRB) s += A.part[2 * A.nb + b];
     s = block_sum(s);
     if (threadIdx.x == 0) A.info[5] = 1.0 / s;
+    mp_write_stamp(A.stamp_end);
 }
+
+// the end of a step whose last kernel does not stamp it
+__global__ void k_stamp(uint64_t* p) { mp_write_stamp(p); }
 
 }  // namespace
 
@@ -486,6 +497,7 @@ void mp_launch_svgd(mp_filter f, hipStream_t s) {
     A.K = f->K;
     A.sr = f->p.sigma_r;
     A.st = f->p.sigma_t;
+    A.stamp = mp_take_stamp(f);
     const bool exact = f->p.svgd_grad == MP_SVGD_GRAD_EXACT;
     const bool transport = f->p.svgd_transport == MP_SVGD_TRANSPORT_ADJOINT;
     if (exact && transport) k_svgd<true, true><<<nblk(f->n), 256, 0, s>>>(A);
@@ -511,6 +523,7 @@ void mp_launch_predict(mp_filter f, const float dT[7], const float L[36], bool n
         for (int c = 0; c <= r; ++c) A.L[p++] = noise ? L[6 * r + c] : 0.0f;
     A.noise = noise ? 1 : 0;
     A.dyn = f->dyn;
+    A.stamp = mp_take_stamp(f);
     k_predict<<<nblk(f->n), 256, 0, s>>>(A);
     MP_CHECK_LAUNCH();
 }
@@ -556,7 +569,12 @@ void mp_copy_poses(mp_filter f, int from, int to, hipStream_t s) {
     MP_CHECK_LAUNCH();
 }
 
-void mp_launch_posterior(mp_filter f, hipStream_t s) {
+void mp_launch_stamp(uint64_t* p, hipStream_t s) {
+    k_stamp<<<1, 64, 0, s>>>(p);
+    MP_CHECK_LAUNCH();
+}
+
+void mp_launch_posterior(mp_filter f, hipStream_t s, uint64_t* stamp_end) {
     const int n = f->n;
     const int nb = (int)nblk(n, kRB);
     f->red.ensure(mp_post_scratch_bytes(f));
@@ -577,6 +595,8 @@ void mp_launch_posterior(mp_filter f, hipStream_t s) {
     A.nb = nb;
     A.inv_tau = 1.0 / (double)f->p.temperature;
     A.floor_p = (double)f->p.prior_floor;
+    A.stamp = mp_take_stamp(f);
+    A.stamp_end = stamp_end;
     k_post_logits<<<nb, kRB, 0, s>>>(A);
     k_post_max_final<<<1, kRB, 0, s>>>(A);
     k_post_expsum<<<nb, kRB, 0, s>>>(A);

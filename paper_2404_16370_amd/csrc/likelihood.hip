@@ -50,6 +50,7 @@ struct LikArgs {
     int32_t n, ns, chunk_len, nchunks, nbx;
     int32_t rounds;                     // grouped layout: rounds of 32 particles per workgroup
     float dmax2, cmax;
+    uint64_t* stamp;                    // stage clock, or null
     float sig2, ib, r_floor, r_out;   // residual-field scorer: sigma_s^2, 1 / (1 + sigma_s^2), floor of r, r outside the gate
 };
 
@@ -276,6 +277,7 @@ __device__ __forceinline__ void lik_record(const MapView& v, int32_t g, float4& 
 template <int BACKEND, int BATCH, int SC = MP_SCORER_PLAIN>
 __global__ __launch_bounds__(kLanes) void k_lik(LikArgs A) {
     __shared__ float4 tile[kTile * 3];
+    mp_write_stamp(A.stamp);
     const int nb = A.nbx * A.nchunks;
     const int logical = remap_xcd(blockIdx.x, nb);
     const int chunk = logical / A.nbx;
@@ -466,6 +468,7 @@ __device__ __forceinline__ void grp_tile(const LikArgs& A, const int chunk, cons
 template <int BACKEND, int BATCH, int SC>
 __global__ __launch_bounds__(kGThreads) void k_lik_grp(LikArgs A) {
     __shared__ float4 tile[kGChunk * 3];
+    mp_write_stamp(A.stamp);
     const int nb = A.nbx * A.nchunks;
     const int logical = remap_xcd(blockIdx.x, nb);
     const int chunk = logical / A.nbx;
@@ -539,9 +542,11 @@ struct SolveArgs {
     int32_t* __restrict__ how;   // N or null: 0 FP32 Cholesky, 1 FP64 re-solve, 2 both failed
     int32_t n, nchunks, ns;
     float cmax, lam_rel, lam_abs;
+    uint64_t* stamp;             // stage clock, or null
 };
 
 __global__ __launch_bounds__(256) void k_solve(SolveArgs A) {
+    mp_write_stamp(A.stamp);
     const int col = blockIdx.x * blockDim.x + threadIdx.x;   // partial column
     if (col >= A.n) return;
     const int i = A.order ? A.order[col] : col;
@@ -593,7 +598,9 @@ __global__ __launch_bounds__(256) void k_solve(SolveArgs A) {
 // Morton key (8 bits per axis over the map box, z y x interleaved from the
 // top bit) of each particle's translation, and the particle's index
 __global__ void k_walk_keys(const float4* __restrict__ poses, int n, float lo0, float lo1, float lo2, float s0,
-                            float s1, float s2, uint32_t* __restrict__ keys, int32_t* __restrict__ idx) {
+                            float s1, float s2, uint32_t* __restrict__ keys, int32_t* __restrict__ idx,
+                            uint64_t* __restrict__ stamp) {
+    mp_write_stamp(stamp);
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const float4 t = poses[2 * i + 1];
@@ -649,7 +656,7 @@ static void lik_prepare_order(mp_filter f, int scorer, hipStream_t s) {
     uint32_t* k1 = odd ? f->lkeys.as<uint32_t>() : f->tmp_keys.as<uint32_t>();
     int32_t* v1 = odd ? f->lorder.as<int32_t>() : f->tmp_vals.as<int32_t>();
     k_walk_keys<<<(n + 255) / 256, 256, 0, s>>>(f->poses[f->cur].as<float4>(), n, lo[0], lo[1], lo[2], sc[0], sc[1],
-                                                 sc[2], k0, v0);
+                                                 sc[2], k0, v0, mp_take_stamp(f));
     MP_CHECK_LAUNCH();
     mp_radix_sort_u32_inplace_parity(k0, v0, k1, v1, n, kBits, f->hist, s);
 }
@@ -734,6 +741,7 @@ LikPlan lik_plan(mp_filter f) {
     A.cmax = f->p.c_max;
     A.sig2 = f->p.sigma_s * f->p.sigma_s;
     A.ib = 1.0f / (1.0f + A.sig2);
+    A.stamp = nullptr;
     A.r_floor = 1e-2f;
     A.r_out = mp_residual_r_out(f->p.d_max, f->p.sigma_s, f->map->params.cov_eps);
     return P;
@@ -757,6 +765,7 @@ void lik_solve(mp_filter f, bool grouped, int nch, const int32_t* order, hipStre
     S.cmax = f->p.c_max;
     S.lam_rel = f->p.lambda_rel;
     S.lam_abs = f->p.lambda_abs;
+    S.stamp = mp_take_stamp(f);
     k_solve<<<(n + 255) / 256, 256, 0, s>>>(S);
     MP_CHECK_LAUNCH();
 }
@@ -765,6 +774,8 @@ void lik_solve(mp_filter f, bool grouped, int nch, const int32_t* order, hipStre
 void mp_launch_likelihood(mp_filter f, hipStream_t s) {
     LikPlan P = lik_plan(f);
     lik_prepare_order(f, P.scorer, s);
+    mp_stage_begin(f, MP_STAGE_LIK_CORE);
+    P.A.stamp = mp_take_stamp(f);
     const LikArgs& A = P.A;
     const int scorer = P.scorer;
     const int n = f->n;
@@ -776,11 +787,8 @@ void mp_launch_likelihood(mp_filter f, hipStream_t s) {
         nch = 1;
         f->lik_chunks = 1;
         f->lik_chunk_len = ns;
-        mp_tick(f, MP_STAGE_LIK_CORE, true, s);
-        mp_sur_likelihood(f, A.partial, s);
-        mp_tick(f, MP_STAGE_LIK_CORE, false, s);
+        mp_sur_likelihood(f, A.partial, A.stamp, s);
     } else if (ns > 0 && grouped) {
-        mp_tick(f, MP_STAGE_LIK_CORE, true, s);
         const unsigned grid = (unsigned)(A.nbx * nch);
         const bool dense = A.map.backend == MP_NNF_DENSE;
         if (scorer == MP_SCORER_SCOREFIELD) {
@@ -797,25 +805,21 @@ void mp_launch_likelihood(mp_filter f, hipStream_t s) {
             else k_lik_grp<MP_NNF_HASH, 2, MP_SCORER_PLAIN><<<grid, kGThreads, 0, s>>>(A);
         }
         MP_CHECK_LAUNCH();
-        mp_tick(f, MP_STAGE_LIK_CORE, false, s);
     } else if (ns > 0 && scorer == MP_SCORER_SCOREFIELD) {
-        mp_tick(f, MP_STAGE_LIK_CORE, true, s);
         if (A.map.backend == MP_NNF_DENSE)
             k_lik<MP_NNF_DENSE, 4, MP_SCORER_SCOREFIELD><<<nbx * nch, kLanes, 0, s>>>(A);
         else
             k_lik<MP_NNF_HASH, 4, MP_SCORER_SCOREFIELD><<<nbx * nch, kLanes, 0, s>>>(A);
         MP_CHECK_LAUNCH();
-        mp_tick(f, MP_STAGE_LIK_CORE, false, s);
     } else if (ns > 0) {
-        mp_tick(f, MP_STAGE_LIK_CORE, true, s);
         if (A.map.backend == MP_NNF_DENSE) launch_lik_batch<MP_NNF_DENSE>(f->p.lik_batch, nbx * nch, s, A);
         else launch_lik_batch<MP_NNF_HASH>(f->p.lik_batch, nbx * nch, s, A);
         MP_CHECK_LAUNCH();
-        mp_tick(f, MP_STAGE_LIK_CORE, false, s);
     } else {
         mp_fill_u32(A.partial, 0u, (size_t)kNumPartial * n, s);
         nch = 1;
     }
+    mp_stage_begin(f, MP_MARK_SOLVE);
     lik_solve(f, grouped, nch, A.order, s);
 }
 

@@ -126,6 +126,11 @@ struct SurCheck {
     float last = -1.0f;            // mean |delta s| of the last check
 };
 
+struct StageMark {
+    int32_t stage;   // MP_STAGE_* or MP_MARK_*
+    int32_t slot;    // its clock value in the filter's stamps
+};
+
 struct mp_filter_s {
     mp_map map = nullptr;
     mp_surrogate sur = nullptr;   // network of the SURROGATE scorer
@@ -171,13 +176,30 @@ struct mp_filter_s {
     DevMem scan_sort;         // radix-sort scratch of the walk order
     DevMem tlsh;              // 8 float
     DevMem stepinfo;          // posterior summary (doubles)
-    // stage timers: event pairs per stage and span, reused across steps
-    std::vector<hipEvent_t> ev0[MP_NUM_STAGES], ev1[MP_NUM_STAGES];
-    int ev_count[MP_NUM_STAGES] = {};
+    // stage timers of the last step (mp_stage_begin) and scan upload
+    DevMem stamps;            // device clock values: [0] scan start, [1] scan end, then one per mark
+    std::vector<StageMark> marks;
+    bool timing = false;      // a step is being launched eagerly: its stages are marked
+    uint64_t* stamp = nullptr;   // where the next kernel that starts a stage writes its clock
+    bool scan_timed = false;
 };
 
-// record the start (begin = true) or end of span `ev_count[st]` of stage st
-void mp_tick(mp_filter f, int st, bool begin, hipStream_t s);
+// Stage times.  The first kernel of a stage writes the device clock to the
+// stage's slot when it starts; a stage ends where the next one starts, and the
+// step's last kernel stamps its end.  (Event pairs around every stage cost
+// about 3.5 us of idle GPU each, 16 of them an iteration: 0.56 of the 1.92 ms
+// of a 4096-particle frame.)
+enum { MP_MARK_END = -1, MP_MARK_SOLVE = MP_NUM_STAGES };   // marks besides the stages
+void mp_stage_begin(mp_filter f, int st);
+// the slot the stage's first kernel stamps (null when no stage just began)
+inline uint64_t* mp_take_stamp(mp_filter f) {
+    uint64_t* p = f->stamp;
+    f->stamp = nullptr;
+    return p;
+}
+__device__ __forceinline__ void mp_write_stamp(uint64_t* p) {
+    if (p && blockIdx.x == 0 && threadIdx.x == 0) *p = (uint64_t)wall_clock64();
+}
 
 // ------------------------------------------------------------ launchers
 // sort / scan primitives (sort.hip)
@@ -194,8 +216,9 @@ size_t mp_radix_scratch_bytes(int64_t n);
 int mp_radix_passes(int64_t n, int bits);
 // as mp_radix_sort_u32 without the final copy: after an odd number of passes
 // the result is in (keys_alt, vals_alt)
+// (stamp: stage clock of the first launch, if any)
 void mp_radix_sort_u32_inplace_parity(uint32_t* keys, int32_t* vals, uint32_t* keys_alt, int32_t* vals_alt, int64_t n,
-                                      int bits, DevMem& scratch, hipStream_t s);
+                                      int bits, DevMem& scratch, hipStream_t s, uint64_t* stamp = nullptr);
 // device word of a 32-bit sort's scratch, zero after a good sort: 1 if a
 // workgroup stopped waiting for its predecessors' counts, 2 if a key's place
 // fell outside the output (its input changed while it ran); neither is
@@ -209,14 +232,18 @@ void mp_map_lookup_launch(const MapView& v, const float* xyz_dev, int64_t n, int
 // scan covariances (scan.hip)
 void mp_scan_records(const float* xyz_dev, const float* cov6_dev, int32_t n, int32_t k, float eps, float* rec_dev,
                      hipStream_t s);
-void mp_scan_permute(const float* rec_orig, const int32_t* perm, int32_t n, float* rec_out, hipStream_t s);
+// (stamp_end: raised to the device clock at which the launch's last workgroup ends)
+void mp_scan_permute(const float* rec_orig, const int32_t* perm, int32_t n, float* rec_out, uint64_t* stamp_end,
+                     hipStream_t s);
 // lo_bad_dev (4 floats): bounding-box minimum corner of the points, then 1 if any
 // point or covariance entry is not finite (else 0)
 void mp_scan_check(const float* xyz_dev, const float* cov6_dev, int32_t n, float* lo_bad_dev, hipStream_t s);
+// (stamps: [0] set to the device clock, [1] zeroed)
 // walk order of the likelihood: stable sort of the points by the Morton key of
 // their cell (edge `cell`); keys/keys_alt/perm_alt are n-entry work arrays
 void mp_scan_walk_order(const float* xyz_dev, int32_t n, float cell, const float* lo_bad_dev, uint32_t* keys,
-                        uint32_t* keys_alt, int32_t* perm, int32_t* perm_alt, DevMem& scratch, hipStream_t s);
+                        uint32_t* keys_alt, int32_t* perm, int32_t* perm_alt, DevMem& scratch, uint64_t* stamps,
+                        hipStream_t s);
 
 // filter stages
 void mp_launch_init_uniform(mp_filter f, const float lo[3], const float hi[3], hipStream_t s);
@@ -245,7 +272,8 @@ void mp_step_iter_nbr(mp_filter f, int it, hipStream_t s);
 void mp_step_iter_svgd(mp_filter f, int it, hipStream_t s);
 void mp_step_end(mp_filter f, hipStream_t s);
 void mp_launch_svgd(mp_filter f, hipStream_t s);
-void mp_launch_posterior(mp_filter f, hipStream_t s);
+void mp_launch_posterior(mp_filter f, hipStream_t s, uint64_t* stamp_end = nullptr);
+void mp_launch_stamp(uint64_t* p, hipStream_t s);
 void mp_launch_reset_lists(mp_filter f, hipStream_t s);
 // device fill (graph-safe replacement of hipMemsetAsync)
 void mp_fill_u32(void* p, uint32_t v, size_t n, hipStream_t s);
@@ -279,4 +307,4 @@ void mp_sur_grad_step(mp_surrogate S, int32_t n_real, bool update, float lr, flo
 // one Adam step on a batch drawn from the training set (step counter `step`)
 void mp_sur_train_step(mp_surrogate S, int32_t n_real, bool full, uint32_t step, float lr, float* loss_dev,
                        hipStream_t s);
-void mp_sur_likelihood(mp_filter f, float* partial, hipStream_t s);
+void mp_sur_likelihood(mp_filter f, float* partial, uint64_t* stamp, hipStream_t s);

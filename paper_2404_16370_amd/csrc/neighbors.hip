@@ -38,9 +38,11 @@ struct LshArgs {
     float lo[3], hi[3];
     uint64_t seed;
     const StepDyn* __restrict__ dyn;   // captured step: frame from here
+    uint64_t* stamp;                   // stage clock, or null
 };
 
 __global__ __launch_bounds__(256) void k_lsh(LshArgs A) {
+    mp_write_stamp(A.stamp);
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (A.dyn) A.frame = A.dyn->frame;
     // T^LSH is the same for every particle: one lane of the workgroup draws it
@@ -89,7 +91,8 @@ __global__ __launch_bounds__(256) void k_lsh(LshArgs A) {
 // s, found by an exponential then binary search on each side (a bucket of m
 // particles costs about 2 log2(m) reads per position).
 __global__ void k_bucket_bounds(const uint32_t* __restrict__ sc, int n, int32_t* __restrict__ head,
-                                int32_t* __restrict__ end) {
+                                int32_t* __restrict__ end, uint64_t* __restrict__ stamp) {
+    mp_write_stamp(stamp);
     const int s = blockIdx.x * blockDim.x + threadIdx.x;
     if (s >= n) return;
     const uint32_t c = sc[s];
@@ -173,7 +176,9 @@ struct TopK {
 };
 
 // rank[sorted[s]] = s
-__global__ void k_rank(const int32_t* __restrict__ sorted, int n, int32_t* __restrict__ rank) {
+__global__ void k_rank(const int32_t* __restrict__ sorted, int n, int32_t* __restrict__ rank,
+                       uint64_t* __restrict__ stamp) {
+    mp_write_stamp(stamp);
     const int s = blockIdx.x * blockDim.x + threadIdx.x;
     if (s >= n) return;
     const int i = sorted[s];
@@ -279,6 +284,7 @@ void mp_launch_lsh(mp_filter f, uint32_t frame, uint32_t it, hipStream_t s) {
     }
     A.seed = f->p.seed;
     A.dyn = f->dyn;
+    A.stamp = mp_take_stamp(f);
     k_lsh<<<nblk(f->n), 256, 0, s>>>(A);
     MP_CHECK_LAUNCH();
 }
@@ -288,19 +294,21 @@ void mp_launch_sort(mp_filter f, hipStream_t s) {
     // stable sort of (code, index) from the buffers the LSH kernel filled;
     // the result lands in (scodes, sorted) with no copy
     const bool odd = mp_radix_passes(n, f->p.lsh_bits) % 2 == 1;
+    uint64_t* stamp = mp_radix_passes(n, f->p.lsh_bits) > 0 ? mp_take_stamp(f) : nullptr;
     if (odd)
         mp_radix_sort_u32_inplace_parity(f->tmp_keys.as<uint32_t>(), f->tmp_vals.as<int32_t>(),
                                          f->scodes.as<uint32_t>(), f->sorted.as<int32_t>(), n, f->p.lsh_bits, f->hist,
-                                         s);
+                                         s, stamp);
     else
         mp_radix_sort_u32_inplace_parity(f->scodes.as<uint32_t>(), f->sorted.as<int32_t>(), f->tmp_keys.as<uint32_t>(),
-                                         f->tmp_vals.as<int32_t>(), n, f->p.lsh_bits, f->hist, s);
-    k_bucket_bounds<<<nblk(n), 256, 0, s>>>(f->scodes.as<uint32_t>(), n, f->head.as<int32_t>(), f->end.as<int32_t>());
+                                         f->tmp_vals.as<int32_t>(), n, f->p.lsh_bits, f->hist, s, stamp);
+    k_bucket_bounds<<<nblk(n), 256, 0, s>>>(f->scodes.as<uint32_t>(), n, f->head.as<int32_t>(), f->end.as<int32_t>(),
+                                            mp_take_stamp(f));
     MP_CHECK_LAUNCH();
 }
 
 void mp_launch_refresh(mp_filter f, hipStream_t s, int window) {
-    k_rank<<<nblk(f->n), 256, 0, s>>>(f->sorted.as<int32_t>(), f->n, f->rank.as<int32_t>());
+    k_rank<<<nblk(f->n), 256, 0, s>>>(f->sorted.as<int32_t>(), f->n, f->rank.as<int32_t>(), mp_take_stamp(f));
     MP_CHECK_LAUNCH();
     RefreshArgs A;
     A.poses = f->poses[f->cur].as<float4>();

@@ -245,13 +245,16 @@ __global__ void k_scan_given_cov(const float* __restrict__ xyz, const float* __r
 }
 
 __global__ void k_scan_permute(const float4* __restrict__ in, const int32_t* __restrict__ perm, int n,
-                               float4* __restrict__ out) {
+                               float4* __restrict__ out, uint64_t* __restrict__ stamp_end) {
     const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k >= n) return;
-    const int j = perm[k];
-    out[3 * k] = in[3 * j];
-    out[3 * k + 1] = in[3 * j + 1];
-    out[3 * k + 2] = in[3 * j + 2];
+    if (k < n) {
+        const int j = perm[k];
+        out[3 * k] = in[3 * j];
+        out[3 * k + 1] = in[3 * j + 1];
+        out[3 * k + 2] = in[3 * j + 2];
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) atomicMax((unsigned long long*)stamp_end, (unsigned long long)wall_clock64());
 }
 
 // Finiteness of the points (and covariances) and the minimum corner of the
@@ -306,8 +309,12 @@ __device__ inline uint32_t spread10(uint32_t v) {
 // 30-bit Morton (Z-order) key of each point's cell (edge `cell`, 1024 cells
 // per axis from the box corner, clamped) and the identity permutation
 __global__ void k_morton_keys(const float* __restrict__ xyz, int n, const float* __restrict__ lo_bad, float inv_cell,
-                              uint32_t* __restrict__ key, int32_t* __restrict__ idx) {
+                              uint32_t* __restrict__ key, int32_t* __restrict__ idx, uint64_t* __restrict__ stamps) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i == 0) {
+        stamps[0] = (uint64_t)wall_clock64();
+        stamps[1] = 0;
+    }
     if (i >= n) return;
     uint32_t c[3];
 #pragma unroll
@@ -321,10 +328,11 @@ __global__ void k_morton_keys(const float* __restrict__ xyz, int n, const float*
 
 }  // namespace
 
-void mp_scan_permute(const float* rec_orig, const int32_t* perm, int32_t n, float* rec_out, hipStream_t s) {
+void mp_scan_permute(const float* rec_orig, const int32_t* perm, int32_t n, float* rec_out, uint64_t* stamp_end,
+                     hipStream_t s) {
     if (n <= 0) return;
     k_scan_permute<<<(n + 255) / 256, 256, 0, s>>>(reinterpret_cast<const float4*>(rec_orig), perm, n,
-                                                    reinterpret_cast<float4*>(rec_out));
+                                                    reinterpret_cast<float4*>(rec_out), stamp_end);
     MP_CHECK_LAUNCH();
 }
 
@@ -351,9 +359,10 @@ void mp_scan_check(const float* xyz_dev, const float* cov6_dev, int32_t n, float
 }
 
 void mp_scan_walk_order(const float* xyz_dev, int32_t n, float cell, const float* lo_bad_dev, uint32_t* keys,
-                        uint32_t* keys_alt, int32_t* perm, int32_t* perm_alt, DevMem& scratch, hipStream_t s) {
+                        uint32_t* keys_alt, int32_t* perm, int32_t* perm_alt, DevMem& scratch, uint64_t* stamps,
+                        hipStream_t s) {
     if (n <= 0) return;
-    k_morton_keys<<<(n + 255) / 256, 256, 0, s>>>(xyz_dev, n, lo_bad_dev, 1.0f / cell, keys, perm);
+    k_morton_keys<<<(n + 255) / 256, 256, 0, s>>>(xyz_dev, n, lo_bad_dev, 1.0f / cell, keys, perm, stamps);
     MP_CHECK_LAUNCH();
     mp_radix_sort_u32(keys, perm, keys_alt, perm_alt, n, 30, scratch, s);
 }

@@ -265,6 +265,7 @@ struct OsHistArgs {
     uint32_t* __restrict__ part;     // [gridDim.x][kOsMaxPasses][256]
     uint32_t* __restrict__ clear;    // counters, flag and published words: zeroed
     int64_t clear_words;
+    uint64_t* stamp;                 // stage clock, or null
 };
 
 // Digit counts of every pass over all keys.  A thread takes 16 consecutive
@@ -272,6 +273,7 @@ struct OsHistArgs {
 // converged filter share codes over long runs).
 __global__ __launch_bounds__(kOsHistThreads) void k_os_hist(OsHistArgs A) {
     __shared__ uint32_t h[kOsMaxPasses * 256];
+    mp_write_stamp(A.stamp);
     const int64_t gt = (int64_t)blockIdx.x * kOsHistThreads + threadIdx.x;
     const int64_t gstride = (int64_t)gridDim.x * kOsHistThreads;
     for (int j = threadIdx.x; j < kOsMaxPasses * 256; j += kOsHistThreads) h[j] = 0;
@@ -496,7 +498,7 @@ size_t os_scratch_words(int64_t n) {
 // digit counts, one per 8-bit pass), ping-ponging with the alt arrays; the
 // result lands as in radix_sort.
 void onesweep_sort(uint32_t* keys, int32_t* vals, uint32_t* keys_alt, int32_t* vals_alt, int64_t n, int bits,
-                   DevMem& scratch, hipStream_t s, bool copy_back) {
+                   DevMem& scratch, hipStream_t s, bool copy_back, uint64_t* stamp = nullptr) {
     if (n <= 1 || bits <= 0) return;
     if (n > (int64_t)kStVal) mp_throw(MP_E_UNSUPPORTED, "radix sort of more than 2^30 - 1 keys");
     const int passes = std::min(kOsMaxPasses, (bits + 7) / 8);
@@ -514,6 +516,7 @@ void onesweep_sort(uint32_t* keys, int32_t* vals, uint32_t* keys_alt, int32_t* v
     H.part = part;
     H.clear = base;
     H.clear_words = kOsHead + (int64_t)passes * tiles * 256;
+    H.stamp = stamp;
     k_os_hist<<<nhist, kOsHistThreads, 0, s>>>(H);
     MP_CHECK_LAUNCH();
     uint32_t* ka = keys;
@@ -565,8 +568,8 @@ int mp_radix_passes(int64_t n, int bits) {
 }
 
 void mp_radix_sort_u32_inplace_parity(uint32_t* keys, int32_t* vals, uint32_t* keys_alt, int32_t* vals_alt, int64_t n,
-                                      int bits, DevMem& scratch, hipStream_t s) {
-    onesweep_sort(keys, vals, keys_alt, vals_alt, n, bits, scratch, s, false);
+                                      int bits, DevMem& scratch, hipStream_t s, uint64_t* stamp) {
+    onesweep_sort(keys, vals, keys_alt, vals_alt, n, bits, scratch, s, false, stamp);
 }
 
 uint32_t* mp_radix_wait_flag(DevMem& scratch) { return scratch.as<uint32_t>() + 4; }

@@ -765,6 +765,7 @@ struct SurLikArgs {
     int32_t n, ns;
     float cmax, r_scale, g_scale;
     float lo[3], inv[3];
+    uint64_t* stamp;                    // stage clock, or null
 };
 
 __device__ __forceinline__ float wave_sum(float v) {
@@ -778,6 +779,7 @@ __device__ __forceinline__ float wave_sum(float v) {
 // are reduced across the wave once per particle.
 __global__ __launch_bounds__(kInferThreads) void k_lik_sur(SurLikArgs A) {
     __shared__ uint4 simg[kImgBytes / 16];
+    mp_write_stamp(A.stamp);
     load_image(A.img, simg);
     const char* img = reinterpret_cast<const char*>(simg);
     const int lane = threadIdx.x & 63, m = lane & 31, h = lane >> 5;
@@ -1078,7 +1080,7 @@ void mp_sur_train_step(mp_surrogate S, int32_t n_real, bool full, uint32_t step,
     fused_step(S, n_real, true, full, step, true, lr, loss_dev, s);
 }
 
-void mp_sur_likelihood(mp_filter f, float* partial, hipStream_t s) {
+void mp_sur_likelihood(mp_filter f, float* partial, uint64_t* stamp, hipStream_t s) {
     mp_surrogate S = f->sur;
     SurLikArgs A;
     A.img = S->img.as<uint4>();
@@ -1086,6 +1088,7 @@ void mp_sur_likelihood(mp_filter f, float* partial, hipStream_t s) {
     A.order = f->sorted.as<int32_t>();
     A.scan = f->scan.as<float4>();
     A.partial = partial;
+    A.stamp = stamp;
     A.n = f->n;
     A.ns = f->scan_n;
     A.cmax = f->p.c_max;

@@ -38,3 +38,27 @@ def test_grouped_likelihood_does_not_depend_on_the_split(room, ns):
             assert np.array_equal(psi[:m], ref[:m])
         ref = psi if ref is None or n > len(ref) else ref
         f.close()
+
+
+@pytest.mark.parametrize("iters,tables,rescore,bits", [(1, 1, 0, 16), (3, 2, 1, 16), (2, 1, 0, 0)])
+def test_stage_times_cover_the_step(room, iters, tables, rescore, bits):
+    # bits = 0: the sort launches nothing but its bucket bounds
+    R, t = room["w"]["traj"][0]
+    f = _filter(room, 3000, S.gaussian_particles(3000, S.pose8(R, t), 0.1, 0.3, 3), svgd_iters=iters,
+                lsh_tables=tables, final_rescore=rescore, lsh_bits=bits)
+    f.scan_upload(room["w"]["scans"][0])
+    dT = np.array([1, 0, 0, 0, 0, 0, 0], np.float32)
+    for _ in range(3):
+        f.step(dT, np.eye(6, dtype=np.float32) * 1e-6)
+    st = f.stage_times()
+    want = dict(predict=1, lsh=iters * tables, sort=iters * tables, refresh=iters * tables + rescore,
+                likelihood=iters + rescore, likelihood_core=iters + rescore, svgd=iters, posterior=1, scan=1)
+    assert {k: v[1] for k, v in st.items()} == want
+    assert all(0.0 < v[0] < 100.0 for v in st.values()), st
+    assert st["likelihood_core"][0] < st["likelihood"][0]
+    # an empty scan: prediction only
+    f.scan_upload(np.zeros((0, 3), np.float32))
+    f.step(dT)
+    st = f.stage_times()
+    assert {k: v[1] for k, v in st.items() if k != "scan"} == {k: int(k == "predict") for k in want if k != "scan"}
+    assert st["predict"][0] > 0.0
