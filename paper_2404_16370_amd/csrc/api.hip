@@ -509,9 +509,11 @@ extern "C" mp_status mp_scan_upload(mp_filter f, const float* xyz, const float* 
             // the current records become the previous scan's (odometry)
             if (f->orig_n > 0) {
                 f->scan_orig.swap(f->prev_orig);
+                f->scan_idx.swap(f->prev_idx);
                 f->prev_n = f->orig_n;
             }
             f->scan_orig.ensure(sizeof(float) * 12 * (size_t)n);
+            f->scan_idx.ensure(mp_scan_index_bytes(n));
             f->orig_n = n;
             uint64_t* stamps = f->stamps.as<uint64_t>();
             // Walk order for the likelihood: Morton order of the points on a grid of half the
@@ -520,8 +522,8 @@ extern "C" mp_status mp_scan_upload(mp_filter f, const float* xyz, const float* 
             mp_scan_walk_order(f->scan_xyz.as<float>(), n, 0.5f * f->map->params.voxel, lo_bad, work, work + n,
                                f->scan_perm.as<int32_t>(), reinterpret_cast<int32_t*>(work + 2 * (size_t)n),
                                f->scan_sort, stamps, s);
-            mp_scan_records(f->scan_xyz.as<float>(), dcov, n, f->p.scan_k, f->p.cov_eps, f->scan_orig.as<float>(), s);
-            mp_scan_permute(f->scan_orig.as<float>(), f->scan_perm.as<int32_t>(), n, f->scan.as<float>(), stamps + 1,
+            mp_scan_records(f->scan_xyz.as<float>(), dcov, f->scan_perm.as<int32_t>(), n, f->p.scan_k, f->p.cov_eps,
+                            mp_scan_index(f->scan_idx, n), f->scan_orig.as<float>(), f->scan.as<float>(), stamps + 1,
                             s);
             f->scan_timed = true;
         }

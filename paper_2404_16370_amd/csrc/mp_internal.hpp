@@ -167,6 +167,7 @@ struct mp_filter_s {
     DevMem scan_orig;         // n x 12 float records in the caller's order
     DevMem scan_perm;         // n int32: walk position -> caller index
     DevMem scan_xyz;          // n x 3 float staging
+    DevMem scan_idx, prev_idx;   // spatial indexes of the current and the previous non-empty scan
     DevMem prev_orig;         // the previous non-empty scan's records (caller order), for odometry
     int32_t prev_n = 0;       // its points (0: none yet)
     int32_t orig_n = 0;       // points of the records in scan_orig (the last non-empty scan)
@@ -230,11 +231,21 @@ void mp_build_map(mp_map m, const float* xyz_dev, int64_t n, hipStream_t s);
 void mp_map_lookup_launch(const MapView& v, const float* xyz_dev, int64_t n, int32_t* gid_dev, hipStream_t s);
 
 // scan covariances (scan.hip)
-void mp_scan_records(const float* xyz_dev, const float* cov6_dev, int32_t n, int32_t k, float eps, float* rec_dev,
-                     hipStream_t s);
-// (stamp_end: raised to the device clock at which the launch's last workgroup ends)
-void mp_scan_permute(const float* rec_orig, const int32_t* perm, int32_t n, float* rec_out, uint64_t* stamp_end,
-                     hipStream_t s);
+// spatial index of a scan for neighbour searches: its points in walk order,
+// the boxes (2 float4) of every 64 of them and of every 16 blocks
+constexpr int kScanBlock = 64, kScanFan = 16;
+struct ScanIndex {
+    float4* pts;     // n: x, y, z, caller index (bits)
+    float4* box;     // 2 per block
+    float4* super;   // 2 per kScanFan blocks
+    int32_t blocks, supers;
+};
+size_t mp_scan_index_bytes(int32_t n);
+ScanIndex mp_scan_index(const DevMem& mem, int32_t n);
+// the index, then every point's record in the caller's order and in walk order
+// (stamp_end: raised to the device clock at which the last workgroup ends)
+void mp_scan_records(const float* xyz_dev, const float* cov6_dev, const int32_t* perm, int32_t n, int32_t k, float eps,
+                     const ScanIndex& X, float* rec_dev, float* walk_dev, uint64_t* stamp_end, hipStream_t s);
 // lo_bad_dev (4 floats): bounding-box minimum corner of the points, then 1 if any
 // point or covariance entry is not finite (else 0)
 void mp_scan_check(const float* xyz_dev, const float* cov6_dev, int32_t n, float* lo_bad_dev, hipStream_t s);

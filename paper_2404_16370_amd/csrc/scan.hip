@@ -4,7 +4,7 @@
 // mu is the point itself.  Without caller covariances, Sigma is the
 // GICP-normalised covariance I - (1-eps) n n^T of the point and its k nearest
 // other scan points: k-NN by FP32 squared distance (fixed fma order, ties to
-// the lower index; scan tiles staged in LDS, 16 lanes per point, 32 points per workgroup), FP64 mean and 1/(k+1)
+// the lower index; a spatial index skips what is too far, 16 lanes per point), FP64 mean and 1/(k+1)
 // covariance summed self-first in neighbour order, FP64 cyclic Jacobi with a
 // fixed operation order.  Fewer than 5 points give Sigma = I.
 //
@@ -13,12 +13,12 @@
 #include <hip/hip_runtime.h>
 
 #include "mp_internal.hpp"
+#include "mp_scan_index.hpp"
 
 namespace {
 
-constexpr int kB = 512;   // 32 points per workgroup share each staged tile
+constexpr int kB = 256;   // 16 points per workgroup
 constexpr int kKMax = 32;
-constexpr int kPtsTile = 2048;
 
 // Cyclic Jacobi on a symmetric 3x3 (row-major) and the eigenvector of the
 // smallest eigenvalue (lowest index on ties).  The rotation loop is unrolled
@@ -68,193 +68,261 @@ __device__ void jacobi_min_vec(double A[9], double nrm[3]) {
     nrm[2] = m == 0 ? V[6] : (m == 1 ? V[7] : V[8]);
 }
 
-// k nearest other scan points of each point, 16 lanes per point: lane l
-// keeps the KC best (d2, j) of the candidates j = l, l + 16, ... (ascending j
-// with a strict comparison, so equal distances stay in index order) that do
-// not exceed a bound on the group's k-th distance; the 16 sorted lists are
-// then merged by rounds of a (d2, j) minimum across the group.  Then the
-// FP64 Gaussian of the point and its neighbours.
-constexpr int kQLanes = 16;
-constexpr int kChunk = 32;   // candidates per lane between group-bound updates
+// raises *p to the device clock at which the workgroup ends
+__device__ __forceinline__ void stamp_last(uint64_t* p) {
+    __syncthreads();
+    if (threadIdx.x == 0) atomicMax((unsigned long long*)p, (unsigned long long)wall_clock64());
+}
 
-template <int KC>
-__global__ __launch_bounds__(kB) void k_scan_knn_cov(const float* __restrict__ xyz, int n, int k, float eps,
-                                                     float4* __restrict__ rec) {
-    __shared__ float3 tile[kPtsTile];
-    const int grp = threadIdx.x / kQLanes, gl = threadIdx.x % kQLanes;
-    const int i = blockIdx.x * (kB / kQLanes) + grp;
-    const bool active = i < n;   // uniform over the point's lanes
-    const float3 pi = active ? make_float3(xyz[3 * i], xyz[3 * i + 1], xyz[3 * i + 2]) : make_float3(0, 0, 0);
-    const int kk = min(k, n - 1);
-    float bd[KC];
-    int bj[KC];
+// ------------------------------------------------------------ spatial index of a scan
+// The scan in the likelihood's walk order (Morton order of its cells), as
+// (x, y, z, caller index) per point, with the bounding boxes of every block
+// of 64 consecutive points and of every 16 blocks: the neighbour searches
+// (here and in the odometry) skip a box when it lies farther away than what
+// they already hold.  One workgroup per 1024 points, one wave per block.
+constexpr int kIdxThreads = kScanBlock * kScanFan;
+
+__device__ __forceinline__ float wave_min(float v) {
 #pragma unroll
-    for (int m = 0; m < KC; ++m) {
-        bd[m] = __builtin_inff();
-        bj[m] = 0x7FFFFFFF;
+    for (int off = 32; off >= 1; off >>= 1) v = fminf(v, __shfl_xor(v, off, 64));
+    return v;
+}
+
+__global__ __launch_bounds__(kIdxThreads) void k_scan_index(const float* __restrict__ xyz,
+                                                            const int32_t* __restrict__ perm, int n, ScanIndex X) {
+    __shared__ float box[kScanFan][6];
+    const int w = blockIdx.x * kIdxThreads + threadIdx.x;
+    float b[6];   // lower corner, negated upper corner: both are minima
+#pragma unroll
+    for (int a = 0; a < 6; ++a) b[a] = __builtin_inff();
+    if (w < n) {
+        const int j = perm[w];
+        const float x = xyz[3 * j], y = xyz[3 * j + 1], z = xyz[3 * j + 2];
+        X.pts[w] = make_float4(x, y, z, __int_as_float(j));
+        b[0] = x; b[1] = y; b[2] = z;
+        b[3] = -x; b[4] = -y; b[5] = -z;
     }
+#pragma unroll
+    for (int a = 0; a < 6; ++a) b[a] = wave_min(b[a]);
+    const int v = threadIdx.x / kScanBlock;
+    if (threadIdx.x % kScanBlock == 0) {
+#pragma unroll
+        for (int a = 0; a < 6; ++a) box[v][a] = b[a];
+        const int blk = blockIdx.x * kScanFan + v;
+        if (blk < X.blocks) {
+            X.box[2 * blk] = make_float4(b[0], b[1], b[2], 0.0f);
+            X.box[2 * blk + 1] = make_float4(-b[3], -b[4], -b[5], 0.0f);
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int u = 1; u < kScanFan; ++u)
+#pragma unroll
+            for (int a = 0; a < 6; ++a) b[a] = fminf(b[a], box[u][a]);
+        X.super[2 * blockIdx.x] = make_float4(b[0], b[1], b[2], 0.0f);
+        X.super[2 * blockIdx.x + 1] = make_float4(-b[3], -b[4], -b[5], 0.0f);
+    }
+}
+
+// k nearest other scan points of each point, 16 lanes per point.  The lanes
+// test the boxes of the index 16 at a time, first those of 1024 points, then
+// the 16 blocks of each that may hold a neighbour; of a block that passes,
+// every lane takes four points.  Lane l keeps its KC best (d2, j) that do not
+// exceed a bound on the group's k-th distance; the 16 sorted lists are then
+// merged by rounds of a (d2, j) minimum across the group.  Then the FP64
+// Gaussian of the point and its neighbours.
+//
+// What bounds it: latency of the list upkeep, the merge and the FP64
+// eigen-solve, a few thousand instructions a point at two to four waves per
+// SIMD.  8192 points take 66 us and 65,536 224 us; a search through all n
+// points, staged in LDS, took 290 us and 4.6 ms.
+constexpr int kQLanes = 16;
+static_assert(kScanFan == kQLanes, "one lane per block of a box of 1024 points");
+
+// The candidates' order (distance, caller index) as one 64-bit key: distances
+// are non-negative, so their bits order as their values do.
+__device__ __forceinline__ uint64_t knn_key(float d2, int32_t j) {
+    return ((uint64_t)__float_as_uint(d2) << 32) | (uint32_t)j;
+}
+
+template <int ROT>
+__device__ __forceinline__ uint64_t row_min_step(uint64_t v) {
+    const uint64_t o = ((uint64_t)mp_row_ror<ROT>((uint32_t)(v >> 32)) << 32) | mp_row_ror<ROT>((uint32_t)v);
+    return o < v ? o : v;
+}
+
+// The loops that are not unrolled keep the code short: a launch over a few
+// hundred points spends its time fetching instructions for the first time.
+template <int KC>
+__global__ __launch_bounds__(kB) void k_scan_knn_cov(const float* __restrict__ xyz, ScanIndex X, int n, int k,
+                                                     float eps, float4* __restrict__ rec, float4* __restrict__ walk,
+                                                     uint64_t* __restrict__ stamp_end) {
+    __shared__ float nbr[kB / kQLanes][KC][3];
+    const int grp = threadIdx.x / kQLanes, gl = threadIdx.x % kQLanes;
+    const int w = blockIdx.x * (kB / kQLanes) + grp;
+    const bool active = w < n;   // uniform over the point's lanes
+    const float4 p4 = X.pts[active ? w : 0];
+    const float3 pi = make_float3(p4.x, p4.y, p4.z);
+    const int i = __float_as_int(p4.w);
+    const int kk = min(k, n - 1);
+    uint64_t best[KC];
+#pragma unroll
+    for (int m = 0; m < KC; ++m) best[m] = knn_key(__builtin_inff(), 0x7FFFFFFF);
     // lists needed per lane to bound the group's kk-th distance (kk <= KC)
     const int mb = kk > kQLanes ? 1 : 0;
     float bound = __builtin_inff();
-    // Seed the bound from the 16 (mb + 1) points nearest to i in scan order
-    // (sensor order keeps them close in space): each lane measures mb + 1 of
-    // them with the same arithmetic as the search below.
-    const int nseed = kQLanes * (mb + 1);
-    if (active && n - 1 >= nseed) {
-        const int start = max(0, min(i - nseed / 2, n - 1 - nseed));
-        float own = 0.0f;
-        for (int r = 0; r <= mb; ++r) {
-            int j = start + kQLanes * r + gl;
-            j += j >= i ? 1 : 0;
-            const float dx = xyz[3 * j] - pi.x, dy = xyz[3 * j + 1] - pi.y, dz = xyz[3 * j + 2] - pi.z;
-            own = fmaxf(own, __builtin_fmaf(dx, dx, __builtin_fmaf(dy, dy, dz * dz)));
+    // Seed the bound from the (up to 64) points nearest to this one in walk
+    // order: every lane measures up to four of them with the arithmetic of the
+    // search, and the largest of the lanes' best (second best for mb = 1)
+    // bounds the kk-th distance, as in the search below.
+    const int nseed = min(4, (n - 1) / kQLanes);
+    if (nseed > mb) {
+        const int start = max(0, min(w - kQLanes * nseed / 2, n - 1 - kQLanes * nseed));
+        float s0 = __builtin_inff(), s1 = __builtin_inff();
+        for (int r = 0; r < nseed; ++r) {
+            int q = start + kQLanes * r + gl;
+            q += q >= w ? 1 : 0;
+            const float d2 = mp_point_d2(X.pts[min(q, n - 1)], pi);
+            s1 = fminf(s1, fmaxf(s0, d2));
+            s0 = fminf(s0, d2);
         }
-#pragma unroll
-        for (int off = kQLanes / 2; off >= 1; off >>= 1) own = fmaxf(own, __shfl_xor(own, off, 64));
-        bound = own;
+        bound = mp_row_max(mb >= 1 ? s1 : s0);
     }
-    for (int base = 0; base < n; base += kPtsTile) {
-        const int cnt = min(kPtsTile, n - base);
-        __syncthreads();
-        for (int t = threadIdx.x; t < cnt; t += kB)
-            tile[t] = make_float3(xyz[3 * (base + t)], xyz[3 * (base + t) + 1], xyz[3 * (base + t) + 2]);
-        __syncthreads();
-        if (!active) continue;
-        for (int c0 = 0; c0 < cnt; c0 += kQLanes * kChunk) {
-            const int c1 = min(cnt, c0 + kQLanes * kChunk);
-            for (int t = c0 + gl; t < c1; t += kQLanes) {
-                const int j = base + t;
-                if (j == i) continue;
-                const float3 pj = tile[t];
-                const float dx = pj.x - pi.x, dy = pj.y - pi.y, dz = pj.z - pi.z;
-                const float d2 = __builtin_fmaf(dx, dx, __builtin_fmaf(dy, dy, dz * dz));
-                if (d2 < bd[KC - 1] && d2 <= bound) {
+    // the boxes, walked by the whole wave: a group without work idles along
+    for (int s0 = 0; s0 < X.supers; s0 += kQLanes) {
+        const int sup = s0 + gl;
+        uint32_t sm = mp_row_ballot(active && sup < X.supers &&
+                                    mp_box_d2(X.super + 2 * min(sup, X.supers - 1), pi) <= bound);
+        while (__any(sm != 0)) {
+            const int su = s0 + (sm ? __builtin_ctz(sm) : 0);
+            const int blk = su * kScanFan + gl;
+            uint32_t bm = mp_row_ballot(sm != 0 && blk < X.blocks &&
+                                        mp_box_d2(X.box + 2 * min(blk, X.blocks - 1), pi) <= bound);
+            sm &= sm - 1;
+            while (__any(bm != 0)) {
+                const int q0 = bm ? (su * kScanFan + __builtin_ctz(bm)) * kScanBlock + gl : n;
+                bm &= bm - 1;
+                float4 next = X.pts[min(q0, n - 1)];
+#pragma unroll 1
+                for (int r = 0; r < kScanBlock / kQLanes; ++r) {
+                    const int q = q0 + kQLanes * r;
+                    const float4 c = next;
+                    next = X.pts[min(q + kQLanes, n - 1)];
+                    const float d2 = mp_point_d2(c, pi);
+                    const uint64_t key = knn_key(d2, __float_as_int(c.w));
+                    if (q < n && q != w && d2 <= bound && key < best[KC - 1]) {
 #pragma unroll
-                    for (int m = KC - 1; m >= 1; --m) {
-                        const bool sh = d2 < bd[m - 1];
-                        const bool here = d2 < bd[m];
-                        bd[m] = sh ? bd[m - 1] : (here ? d2 : bd[m]);
-                        bj[m] = sh ? bj[m - 1] : (here ? j : bj[m]);
-                    }
-                    if (d2 < bd[0]) {
-                        bd[0] = d2;
-                        bj[0] = j;
+                        for (int m = KC - 1; m >= 0; --m) {
+                            const bool up = m > 0 && key < best[m > 0 ? m - 1 : 0];
+                            best[m] = up ? best[m > 0 ? m - 1 : 0] : (key < best[m] ? key : best[m]);
+                        }
                     }
                 }
+                // Group bound: every lane holds at least mb + 1 distinct candidates
+                // at or below its best[mb], so 16 (mb + 1) >= kk candidates lie at or
+                // below the maximum over the group, and so does every one of the
+                // final kk.  Candidates (and boxes) above it are never needed.
+                bound = fminf(bound, mp_row_max(__uint_as_float((uint32_t)((mb >= 1 ? best[1] : best[0]) >> 32))));
             }
-            // Group bound: every lane holds at least mb + 1 distinct candidates
-            // at or below its bd[mb], so 16 (mb + 1) >= kk candidates lie at or
-            // below the maximum over the group, and so does every one of the
-            // final kk.  Candidates above it are never needed (same lists as
-            // without the bound for the entries the merge takes).
-            float own = mb >= 1 ? bd[1] : bd[0];
-#pragma unroll
-            for (int off = kQLanes / 2; off >= 1; off >>= 1) own = fmaxf(own, __shfl_xor(own, off, 64));
-            bound = fminf(bound, own);
         }
     }
-    if (!active) return;
-    // merge: round r takes the smallest head of the group's lists and pops it
-    int nb[KC];
+    // merge: round r takes the smallest head of the group's lists and pops it;
+    // lane r % 16 fetches that neighbour
+    int mine[KC / kQLanes > 0 ? KC / kQLanes : 1];
 #pragma unroll
-    for (int r = 0; r < KC; ++r) {
-        float d = bd[0];
-        int j = bj[0];
+    for (int a = 0; a < KC; a += kQLanes) mine[a / kQLanes] = 0;
 #pragma unroll
-        for (int off = kQLanes / 2; off >= 1; off >>= 1) {
-            const float od = __shfl_xor(d, off, 64);
-            const int oj = __shfl_xor(j, off, 64);
-            const bool take = od < d || (od == d && oj < j);
-            d = take ? od : d;
-            j = take ? oj : j;
-        }
-        nb[r] = j;
-        if (bj[0] == j) {   // this lane held the minimum (indices are unique)
+    for (int a = 0; a < KC; a += kQLanes) {
+#pragma unroll 1
+        for (int r = a; r < min(kk, a + kQLanes); ++r) {
+            uint64_t v = best[0];
+            v = row_min_step<8>(v);
+            v = row_min_step<4>(v);
+            v = row_min_step<2>(v);
+            v = row_min_step<1>(v);
+            if (gl == r - a) mine[a / kQLanes] = (int32_t)(uint32_t)v;
+            if (best[0] == v) {   // this lane held the minimum (indices are unique)
 #pragma unroll
-            for (int m = 0; m + 1 < KC; ++m) {
-                bd[m] = bd[m + 1];
-                bj[m] = bj[m + 1];
-            }
-            bd[KC - 1] = __builtin_inff();
-            bj[KC - 1] = 0x7FFFFFFF;
-        }
-    }
-    if (gl != 0) return;
-    double c6[6];
-    if (kk + 1 < 5) {
-        c6[0] = 1; c6[1] = 0; c6[2] = 0; c6[3] = 1; c6[4] = 0; c6[5] = 1;
-    } else {
-        // unrolled over the list capacity so that nb is indexed by constants
-        // and stays in registers; sums in list order
-        double sm[3] = {(double)pi.x, (double)pi.y, (double)pi.z};
-#pragma unroll
-        for (int a = 0; a < KC; ++a) {
-            if (a < kk) {
-                const int j = nb[a];
-                sm[0] = sm[0] + (double)xyz[3 * j];
-                sm[1] = sm[1] + (double)xyz[3 * j + 1];
-                sm[2] = sm[2] + (double)xyz[3 * j + 2];
+                for (int m = 0; m + 1 < KC; ++m) best[m] = best[m + 1];
+                best[KC - 1] = knn_key(__builtin_inff(), 0x7FFFFFFF);
             }
         }
-        const double dn = (double)(kk + 1);
-        const double mu[3] = {sm[0] / dn, sm[1] / dn, sm[2] / dn};
-        double S[6] = {0, 0, 0, 0, 0, 0};
-        {
-            const double d0 = (double)pi.x - mu[0];
-            const double d1 = (double)pi.y - mu[1];
-            const double d2 = (double)pi.z - mu[2];
-            S[0] += d0 * d0; S[1] += d0 * d1; S[2] += d0 * d2;
-            S[3] += d1 * d1; S[4] += d1 * d2; S[5] += d2 * d2;
+        const int j = mine[a / kQLanes];
+        if (active && a + gl < kk) {
+            nbr[grp][a + gl][0] = xyz[3 * j];
+            nbr[grp][a + gl][1] = xyz[3 * j + 1];
+            nbr[grp][a + gl][2] = xyz[3 * j + 2];
         }
-#pragma unroll
-        for (int a = 0; a < KC; ++a) {
-            if (a < kk) {
-                const int j = nb[a];
-                const double d0 = (double)xyz[3 * j] - mu[0];
-                const double d1 = (double)xyz[3 * j + 1] - mu[1];
-                const double d2 = (double)xyz[3 * j + 2] - mu[2];
-                S[0] += d0 * d0; S[1] += d0 * d1; S[2] += d0 * d2;
-                S[3] += d1 * d1; S[4] += d1 * d2; S[5] += d2 * d2;
-            }
-        }
-        for (int a = 0; a < 6; ++a) S[a] /= dn;
-        double A[9] = {S[0], S[1], S[2], S[1], S[3], S[4], S[2], S[4], S[5]};
-        double nv[3];
-        jacobi_min_vec(A, nv);
-        const double a = 1.0 - (double)eps;
-        c6[0] = 1.0 - a * nv[0] * nv[0];
-        c6[1] = -a * nv[0] * nv[1];
-        c6[2] = -a * nv[0] * nv[2];
-        c6[3] = 1.0 - a * nv[1] * nv[1];
-        c6[4] = -a * nv[1] * nv[2];
-        c6[5] = 1.0 - a * nv[2] * nv[2];
-    }
-    rec[3 * i] = make_float4(pi.x, pi.y, pi.z, (float)c6[0]);
-    rec[3 * i + 1] = make_float4((float)c6[1], (float)c6[2], (float)c6[3], (float)c6[4]);
-    rec[3 * i + 2] = make_float4((float)c6[5], 0.0f, 0.0f, 0.0f);
-}
-
-__global__ void k_scan_given_cov(const float* __restrict__ xyz, const float* __restrict__ cov, int n,
-                                 float4* __restrict__ rec) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    const float* c = cov + 6 * (size_t)i;
-    rec[3 * i] = make_float4(xyz[3 * i], xyz[3 * i + 1], xyz[3 * i + 2], c[0]);
-    rec[3 * i + 1] = make_float4(c[1], c[2], c[3], c[4]);
-    rec[3 * i + 2] = make_float4(c[5], 0.0f, 0.0f, 0.0f);
-}
-
-__global__ void k_scan_permute(const float4* __restrict__ in, const int32_t* __restrict__ perm, int n,
-                               float4* __restrict__ out, uint64_t* __restrict__ stamp_end) {
-    const int k = blockIdx.x * blockDim.x + threadIdx.x;
-    if (k < n) {
-        const int j = perm[k];
-        out[3 * k] = in[3 * j];
-        out[3 * k + 1] = in[3 * j + 1];
-        out[3 * k + 2] = in[3 * j + 2];
     }
     __syncthreads();
-    if (threadIdx.x == 0) atomicMax((unsigned long long*)stamp_end, (unsigned long long)wall_clock64());
+    if (active && gl == 0) {
+        double c6[6];
+        if (kk + 1 < 5) {
+            c6[0] = 1; c6[1] = 0; c6[2] = 0; c6[3] = 1; c6[4] = 0; c6[5] = 1;
+        } else {
+            // sums in list order, the point itself first
+            double sm[3] = {(double)pi.x, (double)pi.y, (double)pi.z};
+#pragma unroll 1
+            for (int a = 0; a < kk; ++a) {
+                sm[0] = sm[0] + (double)nbr[grp][a][0];
+                sm[1] = sm[1] + (double)nbr[grp][a][1];
+                sm[2] = sm[2] + (double)nbr[grp][a][2];
+            }
+            const double dn = (double)(kk + 1);
+            const double mu[3] = {sm[0] / dn, sm[1] / dn, sm[2] / dn};
+            double S[6] = {0, 0, 0, 0, 0, 0};
+            double d0 = (double)pi.x - mu[0], d1 = (double)pi.y - mu[1], d2 = (double)pi.z - mu[2];
+#pragma unroll 1
+            for (int a = 0;; ++a) {
+                S[0] += d0 * d0; S[1] += d0 * d1; S[2] += d0 * d2;
+                S[3] += d1 * d1; S[4] += d1 * d2; S[5] += d2 * d2;
+                if (a == kk) break;
+                d0 = (double)nbr[grp][a][0] - mu[0];
+                d1 = (double)nbr[grp][a][1] - mu[1];
+                d2 = (double)nbr[grp][a][2] - mu[2];
+            }
+            for (int a = 0; a < 6; ++a) S[a] /= dn;
+            double A[9] = {S[0], S[1], S[2], S[1], S[3], S[4], S[2], S[4], S[5]};
+            double nv[3];
+            jacobi_min_vec(A, nv);
+            const double a = 1.0 - (double)eps;
+            c6[0] = 1.0 - a * nv[0] * nv[0];
+            c6[1] = -a * nv[0] * nv[1];
+            c6[2] = -a * nv[0] * nv[2];
+            c6[3] = 1.0 - a * nv[1] * nv[1];
+            c6[4] = -a * nv[1] * nv[2];
+            c6[5] = 1.0 - a * nv[2] * nv[2];
+        }
+        const float4 r0 = make_float4(pi.x, pi.y, pi.z, (float)c6[0]);
+        const float4 r1 = make_float4((float)c6[1], (float)c6[2], (float)c6[3], (float)c6[4]);
+        const float4 r2 = make_float4((float)c6[5], 0.0f, 0.0f, 0.0f);
+        rec[3 * i] = r0;
+        rec[3 * i + 1] = r1;
+        rec[3 * i + 2] = r2;
+        walk[3 * w] = r0;
+        walk[3 * w + 1] = r1;
+        walk[3 * w + 2] = r2;
+    }
+    stamp_last(stamp_end);
+}
+
+__global__ void k_scan_given_cov(const float* __restrict__ cov, ScanIndex X, int n, float4* __restrict__ rec,
+                                 float4* __restrict__ walk, uint64_t* __restrict__ stamp_end) {
+    const int w = blockIdx.x * blockDim.x + threadIdx.x;
+    if (w < n) {
+        const float4 p = X.pts[w];
+        const int i = __float_as_int(p.w);
+        const float* c = cov + 6 * (size_t)i;
+        const float4 r0 = make_float4(p.x, p.y, p.z, c[0]), r1 = make_float4(c[1], c[2], c[3], c[4]);
+        const float4 r2 = make_float4(c[5], 0.0f, 0.0f, 0.0f);
+        rec[3 * i] = r0;
+        rec[3 * i + 1] = r1;
+        rec[3 * i + 2] = r2;
+        walk[3 * w] = r0;
+        walk[3 * w + 1] = r1;
+        walk[3 * w + 2] = r2;
+    }
+    stamp_last(stamp_end);
 }
 
 // Finiteness of the points (and covariances) and the minimum corner of the
@@ -328,27 +396,37 @@ __global__ void k_morton_keys(const float* __restrict__ xyz, int n, const float*
 
 }  // namespace
 
-void mp_scan_permute(const float* rec_orig, const int32_t* perm, int32_t n, float* rec_out, uint64_t* stamp_end,
-                     hipStream_t s) {
-    if (n <= 0) return;
-    k_scan_permute<<<(n + 255) / 256, 256, 0, s>>>(reinterpret_cast<const float4*>(rec_orig), perm, n,
-                                                    reinterpret_cast<float4*>(rec_out), stamp_end);
-    MP_CHECK_LAUNCH();
+size_t mp_scan_index_bytes(int32_t n) {
+    const size_t b = (size_t)((n + kScanBlock - 1) / kScanBlock), u = (size_t)((n + kIdxThreads - 1) / kIdxThreads);
+    return sizeof(float4) * ((size_t)n + 2 * b + 2 * u);
 }
 
-void mp_scan_records(const float* xyz, const float* cov6, int32_t n, int32_t k, float eps, float* rec,
-                     hipStream_t s) {
+ScanIndex mp_scan_index(const DevMem& mem, int32_t n) {
+    ScanIndex X;
+    X.blocks = (n + kScanBlock - 1) / kScanBlock;
+    X.supers = (n + kIdxThreads - 1) / kIdxThreads;
+    X.pts = mem.as<float4>();
+    X.box = X.pts + n;
+    X.super = X.box + 2 * (size_t)X.blocks;
+    return X;
+}
+
+void mp_scan_records(const float* xyz, const float* cov6, const int32_t* perm, int32_t n, int32_t k, float eps,
+                     const ScanIndex& X, float* rec, float* walk, uint64_t* stamp_end, hipStream_t s) {
     if (n <= 0) return;
+    if (k > kKMax) mp_throw(MP_E_UNSUPPORTED, "scan_k above %d", kKMax);
+    k_scan_index<<<X.supers, kIdxThreads, 0, s>>>(xyz, perm, n, X);
+    MP_CHECK_LAUNCH();
+    float4* r4 = reinterpret_cast<float4*>(rec);
+    float4* w4 = reinterpret_cast<float4*>(walk);
     if (cov6) {
-        k_scan_given_cov<<<(n + 255) / 256, 256, 0, s>>>(xyz, cov6, n, reinterpret_cast<float4*>(rec));
+        k_scan_given_cov<<<(n + 255) / 256, 256, 0, s>>>(cov6, X, n, r4, w4, stamp_end);
     } else {
-        if (k > kKMax) mp_throw(MP_E_UNSUPPORTED, "scan_k above %d", kKMax);
         constexpr int per = kB / kQLanes;
         const unsigned grid = (unsigned)((n + per - 1) / per);
-        float4* r4 = reinterpret_cast<float4*>(rec);
-        if (k <= 8) k_scan_knn_cov<8><<<grid, kB, 0, s>>>(xyz, n, k, eps, r4);
-        else if (k <= 16) k_scan_knn_cov<16><<<grid, kB, 0, s>>>(xyz, n, k, eps, r4);
-        else k_scan_knn_cov<32><<<grid, kB, 0, s>>>(xyz, n, k, eps, r4);
+        if (k <= 8) k_scan_knn_cov<8><<<grid, kB, 0, s>>>(xyz, X, n, k, eps, r4, w4, stamp_end);
+        else if (k <= 16) k_scan_knn_cov<16><<<grid, kB, 0, s>>>(xyz, X, n, k, eps, r4, w4, stamp_end);
+        else k_scan_knn_cov<32><<<grid, kB, 0, s>>>(xyz, X, n, k, eps, r4, w4, stamp_end);
     }
     MP_CHECK_LAUNCH();
 }

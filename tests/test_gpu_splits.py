@@ -62,3 +62,32 @@ def test_stage_times_cover_the_step(room, iters, tables, rescore, bits):
     st = f.stage_times()
     assert {k: v[1] for k, v in st.items() if k != "scan"} == {k: int(k == "predict") for k in want if k != "scan"}
     assert st["predict"][0] > 0.0
+
+
+def _cloud(n, kind, seed=0):
+    rng = np.random.default_rng(seed)
+    if kind == "surface":       # a few planes, a few hundred metres apart, with noise
+        p = rng.uniform(-20, 20, (n, 3))
+        p[:, 2] = np.round(p[:, 2] / 10.0) * 10.0 + rng.normal(0, 0.01, n)
+        p[: n // 8] += np.array([300.0, 0.0, 0.0])
+    elif kind == "lattice":     # many equal distances, every point twice
+        p = np.round(rng.uniform(-3, 3, (n, 3)) / 0.25) * 0.25
+        p[n // 2:] = p[: n - n // 2]
+    else:                       # all in one cell of the walk order
+        p = rng.uniform(0, 0.2, (n, 3))
+    return np.ascontiguousarray(p[rng.permutation(n)], np.float32)
+
+
+@pytest.mark.parametrize("kind", ["surface", "lattice", "cell"])
+@pytest.mark.parametrize("n,k", [(1, 10), (2, 10), (16, 10), (17, 8), (33, 32), (64, 10), (65, 10), (1023, 20),
+                                 (1025, 10), (9000, 10), (5000, 32)])
+def test_scan_neighbours_of_the_indexed_search(room, O, n, k, kind):
+    scan = _cloud(n, kind, n + k)
+    f = _filter(room, 64, None, scan_k=k)
+    f.scan_upload(scan)
+    rec = f.debug_get("scan")
+    assert np.array_equal(rec[:, :3], scan)
+    _, cov, _ = O.scan_cov(scan, k=k, eps=1e-3)
+    assert np.array_equal(rec[:, 3:9], cov)
+    walk = f.debug_get("scan_walk")
+    assert np.array_equal(walk[np.lexsort(walk.T)], rec[np.lexsort(rec.T)])
