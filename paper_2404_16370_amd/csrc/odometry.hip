@@ -17,15 +17,21 @@
 // dT <- dT exp(psi) (FP64 pose, FP32 copy for the next evaluation).  After
 // the last update the terms are evaluated once more: Sigma^dT = scale H^-1.
 //
-// Launch shape per iteration: the neighbour search over a grid of (source
-// block, target block) pairs, each target block staged in LDS and read as
-// broadcasts, one source point per lane; a block's minimum goes into the
-// point's 64-bit key (distance bits, index) by an atomic minimum, which for
-// non-negative distances is the lowest distance and, among equal ones, the
-// lowest index, whatever the order of the blocks.  Then one lane per source
-// point forms its terms and each workgroup sums its points' terms in FP64 in
-// a fixed order; one workgroup adds the workgroups' sums in order and takes
-// the step.
+// One launch per iteration.  Every workgroup adds the sums that the
+// workgroups of the launch before left and takes the step itself (the same
+// operations in the same order, so all hold the same pose); then it matches
+// its source points, 16 lanes a point, through the spatial index of the
+// previous scan (boxes of 64 and of 1024 of its points), starting from the
+// point's match of the iteration before: a box farther away than the best
+// distance so far, or than d_max, holds no better match.  Then one lane per
+// source point forms its terms, and the workgroup leaves their FP64 sums,
+// added in a fixed order.
+//
+// What bounds it: latency (the sums and the step's FP64 chain, about 3 us,
+// then the dependent loads of the search).  An iteration takes 16 us on
+// 8192-point scans and 51 us on 65,536-point ones (130 us for the first,
+// which has no matches to start from); searching all targets for every point,
+// with the step and the terms in launches of their own, took 36 and 820 us.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -36,77 +42,50 @@
 #include "megapf.h"
 #include "mp_det.hpp"
 #include "mp_internal.hpp"
-#include "mp_solve.hpp"
+#include "mp_scan_index.hpp"
 
 namespace {
 
-constexpr int kNnThreads = 256;   // source points per search workgroup
-constexpr int kNnTargets = 256;   // target points per search workgroup (LDS)
-constexpr int kTB = 256;          // source points per terms workgroup
-constexpr int kOTerms = 29;       // H (21), b (6), cost, inlier count per source point
-constexpr int kSumGroups = 8;     // terms of a workgroup summed in 8 runs of kTB / 8 points
-constexpr uint64_t kNoMatch = ~0ull;
+constexpr int kOThreads = 512;
+constexpr int kOLanes = 16;                        // lanes per source point in the search
+constexpr int kOSlots = kOThreads / kOLanes;       // source points matched at a time
+constexpr int kOParts = 512;                       // most workgroups of a launch
+constexpr int kORounds = 4;                        // most rounds of a workgroup
+constexpr int kOTerms = 29;                        // H (21), b (6), cost, inlier count per source point
+constexpr int kOBlocks = 65536 / kScanBlock;       // boxes of the largest scan
+constexpr int kOSum = 16;                          // every sum is taken in this many parts, then over them
+static_assert(kOParts * kORounds * kOSlots >= 65536, "the largest scan");
+static_assert(kOTerms * kOSum <= kOThreads, "one thread per part of a sum");
 
 __device__ __forceinline__ float3 odo_point(const float* pose, const mpdet::mat3& Rm, const float4 r) {
     return mpdet::xform(Rm.m, make_float3(pose[4], pose[5], pose[6]), make_float3(r.x, r.y, r.z));
 }
 
-struct OdoNnArgs {
-    const float4* __restrict__ trec;   // previous scan records (3 float4 per point)
-    const float4* __restrict__ srec;   // current scan records
-    const float* __restrict__ pose;    // FP32 pose (qw, qx, qy, qz, tx, ty, tz, 0)
-    unsigned long long* __restrict__ key;   // ns: (distance bits << 32) | index, kNoMatch before the search
-    int32_t nt, ns;
-};
-
-__global__ __launch_bounds__(kNnThreads) void k_odo_nn(OdoNnArgs A) {
-    __shared__ float3 tile[kNnTargets];
-    const int j0 = blockIdx.y * kNnTargets;
-    const int cnt = min(kNnTargets, A.nt - j0);
-    for (int u = threadIdx.x; u < cnt; u += kNnThreads) {
-        const float4 r = A.trec[3 * (j0 + u)];
-        tile[u] = make_float3(r.x, r.y, r.z);
-    }
-    __syncthreads();
-    const int k = blockIdx.x * kNnThreads + threadIdx.x;
-    if (k >= A.ns) return;
-    const mpdet::mat3 Rm = mpdet::qmat(mpdet::quat{A.pose[0], A.pose[1], A.pose[2], A.pose[3]});
-    const float3 p = odo_point(A.pose, Rm, A.srec[3 * k]);
-    float bd = __builtin_inff();
-    int bj = j0;
-    for (int u = 0; u < cnt; ++u) {   // ascending j, strict <: the lower index wins ties
-        const float3 q = tile[u];
-        const float dx = q.x - p.x, dy = q.y - p.y, dz = q.z - p.z;
-        const float d2 = __builtin_fmaf(dx, dx, __builtin_fmaf(dy, dy, dz * dz));
-        if (d2 < bd) {
-            bd = d2;
-            bj = j0 + u;
-        }
-    }
-    // d2 >= +0 (a sum of squares, never -0): its bits order as the values do
-    atomicMin(A.key + k, ((unsigned long long)__float_as_uint(bd) << 32) | (uint32_t)bj);
-}
-
-struct OdoTermArgs {
-    const float4* __restrict__ trec;
-    const float4* __restrict__ srec;
-    const float* __restrict__ pose;
-    unsigned long long* __restrict__ key;   // read, then reset to kNoMatch for the next search
-    int32_t* __restrict__ nn;          // ns: target index or -1
-    double* __restrict__ part;         // per workgroup: kOTerms FP64 sums
-    int32_t ns;
+struct OdoArgs {
+    ScanIndex T;                       // the previous scan's index
+    const float4* __restrict__ trec;   // its records, caller order (3 float4 per point)
+    const float4* __restrict__ swalk;  // the current scan's records in walk order
+    const float4* __restrict__ spts;   // and its points with their caller index
+    int32_t* nn;                       // ns, caller order: target index or -1 (read and rewritten by each iteration)
+    const double* __restrict__ part_in;   // the iteration before: [kOTerms][kOParts] workgroup sums
+    double* __restrict__ part_out;
+    const double* __restrict__ pose_in;   // and its pose (7)
+    double* __restrict__ pose_out;
+    double init[7];                    // first iteration: the starting pose
+    double lam_rel, lam_abs;
+    int32_t ns, nparts, rounds, first;
     float dmax2;
 };
 
 // The GICP terms of one source point given its nearest target (zero for an
 // outlier); t[28] is the inlier count.
-__device__ __forceinline__ void odo_point_terms(const OdoTermArgs& A, const mpdet::mat3& Rm, const int k,
-                                                const int bj, float t[kOTerms]) {
-    const float4 s0 = A.srec[3 * k];
+__device__ __forceinline__ void odo_point_terms(const OdoArgs& A, const float* pose, const mpdet::mat3& Rm,
+                                                const int ws, const int bj, float t[kOTerms]) {
+    const float4 s0 = A.swalk[3 * ws];
     const float3 mu = make_float3(s0.x, s0.y, s0.z);
-    const float3 p = odo_point(A.pose, Rm, s0);
+    const float3 p = odo_point(pose, Rm, s0);
     const float4 t0 = A.trec[3 * bj], t1 = A.trec[3 * bj + 1], t2 = A.trec[3 * bj + 2];
-    const float4 s1 = A.srec[3 * k + 1], s2 = A.srec[3 * k + 2];
+    const float4 s1 = A.swalk[3 * ws + 1], s2 = A.swalk[3 * ws + 2];
     const float3 eb = mpdet::rot_t(Rm, make_float3(t0.x - p.x, t0.y - p.y, t0.z - p.z));
     // R^T T R: columns of T R, then R^T times them
     const float T[3][3] = {{t0.w, t1.x, t1.y}, {t1.x, t1.z, t1.w}, {t1.y, t1.w, t2.x}};
@@ -143,57 +122,99 @@ __device__ __forceinline__ void odo_point_terms(const OdoTermArgs& A, const mpde
     t[28] = 1.0f;
 }
 
-// One lane per source point: its match, its terms into LDS, then the
-// workgroup's FP64 sums in a fixed order (kSumGroups runs of consecutive
-// points per term, then the runs in order).
-__global__ __launch_bounds__(kTB) void k_odo_terms(OdoTermArgs A) {
-    __shared__ float tt[kOTerms][kTB];
-    __shared__ double run[kOTerms][kSumGroups];
-    const int k = blockIdx.x * kTB + threadIdx.x;
-    float t[kOTerms];
-    for (int m = 0; m < kOTerms; ++m) t[m] = 0.0f;
-    if (k < A.ns) {
-        const unsigned long long key = A.key[k];
-        A.key[k] = kNoMatch;
-        const float bd = __uint_as_float((uint32_t)(key >> 32));
-        const int bj = (int)(uint32_t)key;
-        const bool inl = key != kNoMatch && bd <= A.dmax2;
-        A.nn[k] = inl ? bj : -1;
-        if (inl) {
-            const mpdet::mat3 Rm = mpdet::qmat(mpdet::quat{A.pose[0], A.pose[1], A.pose[2], A.pose[3]});
-            odo_point_terms(A, Rm, k, bj, t);
-        }
-    }
-    for (int m = 0; m < kOTerms; ++m) tt[m][threadIdx.x] = t[m];
-    __syncthreads();
-    constexpr int kRun = kTB / kSumGroups;
-    for (int q = threadIdx.x; q < kOTerms * kSumGroups; q += kTB) {
-        const int m = q / kSumGroups, g = q % kSumGroups;
+// The sums of the workgroups of one launch: every term in kOSum parts, then
+// over the parts (a fixed order, the same in every workgroup).
+__device__ __forceinline__ void odo_total(const double* __restrict__ part, int nparts, double (*run)[kOSum],
+                                          double* tot) {
+    if (threadIdx.x < kOTerms * kOSum) {
+        const int m = threadIdx.x / kOSum, c = threadIdx.x % kOSum;
         double acc = 0.0;
-        for (int i = 0; i < kRun; ++i) acc += (double)tt[m][g * kRun + i];
-        run[m][g] = acc;
+        constexpr int kFly = 16;   // loads in flight together
+        for (int g0 = c; g0 < nparts; g0 += kFly * kOSum) {
+            double v[kFly];
+#pragma unroll
+            for (int u = 0; u < kFly; ++u) {
+                const int g = g0 + u * kOSum;
+                v[u] = part[m * kOParts + min(g, nparts - 1)];
+            }
+#pragma unroll
+            for (int u = 0; u < kFly; ++u) acc += g0 + u * kOSum < nparts ? v[u] : 0.0;
+        }
+        run[m][c] = acc;
     }
     __syncthreads();
     if (threadIdx.x < kOTerms) {
         double acc = 0.0;
-        for (int g = 0; g < kSumGroups; ++g) acc += run[threadIdx.x][g];
-        A.part[(size_t)blockIdx.x * kOTerms + threadIdx.x] = acc;
+        for (int c = 0; c < kOSum; ++c) acc += run[threadIdx.x][c];
+        tot[threadIdx.x] = acc;
     }
+    __syncthreads();
 }
 
-// SE(3) exponential of [omega; v] (FP64): unit quaternion + translation V v
+// x = -(H + diag(lam_rel H_ii + lam_abs))^-1 b by an L D L^T factorisation;
+// false if a pivot is not positive
+__device__ __forceinline__ bool odo_solve(const double* H, const double* b, double lam_rel, double lam_abs,
+                                          double x[6]) {
+    double L[6][6], D[6], inv[6];
+    bool ok = true;
+#pragma unroll
+    for (int j = 0; j < 6; ++j) {
+        const double h = H[j * 6 - j * (j - 1) / 2];   // H_jj of the packed upper triangle
+        double d = h + (lam_rel * h + lam_abs);
+#pragma unroll
+        for (int k = 0; k < j; ++k) d -= L[j][k] * L[j][k] * D[k];
+        ok = ok && d > 0.0;
+        D[j] = d;
+        inv[j] = 1.0 / d;
+#pragma unroll
+        for (int i = j + 1; i < 6; ++i) {
+            double t = H[j * 6 - j * (j - 1) / 2 + (i - j)];
+#pragma unroll
+            for (int k = 0; k < j; ++k) t -= L[i][k] * L[j][k] * D[k];
+            L[i][j] = t * inv[j];
+        }
+    }
+    double y[6];
+#pragma unroll
+    for (int i = 0; i < 6; ++i) {
+        double t = -b[i];
+#pragma unroll
+        for (int k = 0; k < i; ++k) t -= L[i][k] * y[k];
+        y[i] = t;
+    }
+#pragma unroll
+    for (int i = 5; i >= 0; --i) {
+        double t = y[i] * inv[i];
+#pragma unroll
+        for (int k = i + 1; k < 6; ++k) t -= L[k][i] * x[k];
+        x[i] = t;
+    }
+    return ok;
+}
+
+// SE(3) exponential of [omega; v] (FP64): unit quaternion + translation V v,
+// V = I + A w^ + B w^2
 __device__ void se3_exp_d(const double xi[6], double T[7]) {
     const double* w = xi;
     const double* v = xi + 3;
     const double th2 = w[0] * w[0] + w[1] * w[1] + w[2] * w[2];
-    const double th = sqrt(th2);
-    double A, B, hs, hc;
-    if (th < 1e-5) {   // series of (1 - cos)/th^2, (th - sin)/th^3, sin(th/2)/th, cos(th/2)
-        A = 0.5 - th2 / 24.0;
-        B = 1.0 / 6.0 - th2 / 120.0;
-        hs = 0.5 - th2 / 48.0;
-        hc = 1.0 - th2 / 8.0;
+    double A, B, hs, hc;   // (1 - cos)/th^2, (th - sin)/th^3, sin(th/2)/th, cos(th/2)
+    if (th2 < 0.25) {      // Taylor series: the first term left out is below 1e-17 of the sum
+        const double h2 = 0.25 * th2;   // (th/2)^2
+        double s = 1.0, c = 1.0, b = 1.0;
+#pragma unroll
+        for (int n = 8; n >= 1; --n) {
+            const double e = 2.0 * n;
+            s = 1.0 - (s * h2) * (1.0 / (e * (e + 1.0)));
+            c = 1.0 - (c * h2) * (1.0 / (e * (e - 1.0)));
+            b = 1.0 - (b * th2) * (1.0 / ((e + 2.0) * (e + 3.0)));
+        }
+        hs = 0.5 * s;
+        hc = c;
+        A = 0.5 * s * s;
+        B = b * (1.0 / 6.0);
     } else {
+        const double th = sqrt(th2);
         A = (1.0 - cos(th)) / th2;
         B = (th - sin(th)) / (th2 * th);
         hs = sin(0.5 * th) / th;
@@ -208,69 +229,172 @@ __device__ void se3_exp_d(const double xi[6], double T[7]) {
     for (int k = 0; k < 3; ++k) T[4 + k] = v[k] + A * c1[k] + B * c2[k];
 }
 
-struct OdoStepArgs {
-    const double* __restrict__ part;   // nparts x kOTerms workgroup sums
-    double* __restrict__ pose64;   // 7
-    float* __restrict__ pose32;    // 8
-    double* __restrict__ out;      // final: H 21, b 6, cost, inliers, cov 36, ok
-    int32_t nparts, final_eval;
-    double lam_rel, lam_abs, cov_scale;
-};
+// P <- P exp(psi) with the damped step of the sums `tot`
+__device__ void odo_step(const double* tot, double lam_rel, double lam_abs, const double* P, double out[7]) {
+    double psi[6];
+    if (!odo_solve(tot, tot + 21, lam_rel, lam_abs, psi))
+        for (int m = 0; m < 6; ++m) psi[m] = 0.0;
+    double D[7];
+    se3_exp_d(psi, D);
+    // Hamilton product and P's rotation applied to D's translation
+    const double q[4] = {P[0] * D[0] - P[1] * D[1] - P[2] * D[2] - P[3] * D[3],
+                         P[0] * D[1] + P[1] * D[0] + P[2] * D[3] - P[3] * D[2],
+                         P[0] * D[2] - P[1] * D[3] + P[2] * D[0] + P[3] * D[1],
+                         P[0] * D[3] + P[1] * D[2] - P[2] * D[1] + P[3] * D[0]};
+    const double w = P[0], x = P[1], y = P[2], z = P[3];
+    const double R[9] = {1 - 2 * (y * y + z * z), 2 * (x * y - w * z), 2 * (x * z + w * y),
+                         2 * (x * y + w * z), 1 - 2 * (x * x + z * z), 2 * (y * z - w * x),
+                         2 * (x * z - w * y), 2 * (y * z + w * x), 1 - 2 * (x * x + y * y)};
+    const double nq = sqrt(q[0] * q[0] + q[1] * q[1] + q[2] * q[2] + q[3] * q[3]);
+    for (int a = 0; a < 4; ++a) out[a] = q[a] / nq;
+    for (int a = 0; a < 3; ++a) out[4 + a] = P[4 + a] + R[3 * a] * D[4] + R[3 * a + 1] * D[5] + R[3 * a + 2] * D[6];
+}
 
-// One workgroup: the workgroup sums added in order, then the step or the
-// covariance.
-__global__ __launch_bounds__(64) void k_odo_step(OdoStepArgs A) {
+__device__ __forceinline__ uint64_t odo_key(float d2, int32_t j) {   // d2 >= +0: its bits order as the values do
+    return ((uint64_t)__float_as_uint(d2) << 32) | (uint32_t)j;
+}
+template <int ROT>
+__device__ __forceinline__ uint64_t odo_row_min(uint64_t v) {
+    const uint64_t o = ((uint64_t)mp_row_ror<ROT>((uint32_t)(v >> 32)) << 32) | mp_row_ror<ROT>((uint32_t)v);
+    return o < v ? o : v;
+}
+
+__global__ __launch_bounds__(kOThreads) void k_odo_iter(OdoArgs A) {
+    __shared__ double run[kOTerms][kOSum];
     __shared__ double tot[kOTerms];
-    if (threadIdx.x < kOTerms) {
-        double acc = 0.0;
-        for (int g = 0; g < A.nparts; ++g) acc += A.part[(size_t)g * kOTerms + threadIdx.x];
-        tot[threadIdx.x] = acc;
+    __shared__ float pose[8];
+    __shared__ int32_t match[kOSlots * kORounds];
+    __shared__ float tt[kOTerms][kOSlots * kORounds];
+    __shared__ float4 box[2 * kOBlocks];                 // the boxes of the previous scan's index
+    __shared__ float4 super[2 * (kOBlocks / kScanFan)];
+    const int grp = threadIdx.x / kOLanes, gl = threadIdx.x % kOLanes;
+    const int w0 = blockIdx.x * A.rounds * kOSlots;
+    // the boxes are requested with the sums of the launch before and kept
+    // after those have arrived
+    constexpr int kPre = 2 * kOBlocks / kOThreads;
+    float4 pre[kPre], pre_s;
+#pragma unroll
+    for (int u = 0; u < kPre; ++u) pre[u] = A.T.box[min((int)threadIdx.x + u * kOThreads, 2 * A.T.blocks - 1)];
+    pre_s = A.T.super[min((int)threadIdx.x, 2 * A.T.supers - 1)];
+    // the pose of this iteration
+    if (!A.first) odo_total(A.part_in, A.nparts, run, tot);
+#pragma unroll
+    for (int u = 0; u < kPre; ++u)
+        if ((int)threadIdx.x + u * kOThreads < 2 * A.T.blocks) box[threadIdx.x + u * kOThreads] = pre[u];
+    if ((int)threadIdx.x < 2 * A.T.supers) super[threadIdx.x] = pre_s;
+    if (threadIdx.x == 0) {
+        double P[7];
+        if (A.first) {
+            for (int a = 0; a < 7; ++a) P[a] = A.init[a];
+        } else {
+            double in[7];
+            for (int a = 0; a < 7; ++a) in[a] = A.pose_in[a];
+            odo_step(tot, A.lam_rel, A.lam_abs, in, P);
+        }
+        for (int a = 0; a < 7; ++a) pose[a] = (float)P[a];
+        pose[7] = 0.0f;
+        if (blockIdx.x == 0)
+            for (int a = 0; a < 7; ++a) A.pose_out[a] = P[a];
     }
     __syncthreads();
-    if (threadIdx.x != 0) return;
-    const double* H = tot;
-    const double* b = tot + 21;
-    if (!A.final_eval) {
-        double psi[6], kappa = 0.0;
-        if (!chol_solve6<double>(H, b, A.lam_rel, A.lam_abs, psi, kappa))
-            for (int m = 0; m < 6; ++m) psi[m] = 0.0;
-        double D[7];
-        se3_exp_d(psi, D);
-        const double* P = A.pose64;
-        // P exp(psi): Hamilton product and P's rotation applied to D's translation
-        double q[4] = {P[0] * D[0] - P[1] * D[1] - P[2] * D[2] - P[3] * D[3],
-                       P[0] * D[1] + P[1] * D[0] + P[2] * D[3] - P[3] * D[2],
-                       P[0] * D[2] - P[1] * D[3] + P[2] * D[0] + P[3] * D[1],
-                       P[0] * D[3] + P[1] * D[2] - P[2] * D[1] + P[3] * D[0]};
-        const double w = P[0], x = P[1], y = P[2], z = P[3];
-        const double R[9] = {1 - 2 * (y * y + z * z), 2 * (x * y - w * z), 2 * (x * z + w * y),
-                             2 * (x * y + w * z), 1 - 2 * (x * x + z * z), 2 * (y * z - w * x),
-                             2 * (x * z - w * y), 2 * (y * z + w * x), 1 - 2 * (x * x + y * y)};
-        double tn[3];
-        for (int a = 0; a < 3; ++a) tn[a] = P[4 + a] + R[3 * a] * D[4] + R[3 * a + 1] * D[5] + R[3 * a + 2] * D[6];
-        const double nq = sqrt(q[0] * q[0] + q[1] * q[1] + q[2] * q[2] + q[3] * q[3]);
-        for (int a = 0; a < 4; ++a) q[a] /= nq;
-        for (int a = 0; a < 4; ++a) A.pose64[a] = q[a];
-        for (int a = 0; a < 3; ++a) A.pose64[4 + a] = tn[a];
-        for (int a = 0; a < 7; ++a) A.pose32[a] = (float)A.pose64[a];
-        A.pose32[7] = 0.0f;
-        return;
-    }
-    for (int m = 0; m < 27; ++m) A.out[m] = tot[m];
-    A.out[27] = tot[27];
-    A.out[28] = tot[28];
-    // Sigma = scale H^-1: column j solves H x = e_j (the undamped solve with b = -e_j)
-    bool ok = true;
-    for (int jc = 0; jc < 6; ++jc) {
-        double e[6], x[6], kappa = 0.0;
-        for (int m = 0; m < 6; ++m) e[m] = m == jc ? -1.0 : 0.0;
-        if (!chol_solve6<double>(H, e, 0.0, 0.0, x, kappa)) {
-            ok = false;
-            for (int m = 0; m < 6; ++m) x[m] = 0.0;
+    const mpdet::mat3 Rm = mpdet::qmat(mpdet::quat{pose[0], pose[1], pose[2], pose[3]});
+    // matches
+#pragma unroll 1
+    for (int r = 0; r < A.rounds; ++r) {
+        const int w = w0 + r * kOSlots + grp;
+        const bool active = w < A.ns;   // uniform over the point's lanes
+        const float4 sp = A.spts[active ? w : 0];
+        const int k = __float_as_int(sp.w);
+        const float3 p = odo_point(pose, Rm, sp);
+        // below this key a candidate is taken: within d_max, then better than the best so far
+        uint64_t best = odo_key(A.dmax2, 0x7FFFFFFF);
+        const uint64_t none = best;
+        if (!A.first && active) {
+            const int j = A.nn[k];
+            if (j >= 0) {
+                const uint64_t key = odo_key(mp_point_d2(A.trec[3 * j], p), j);
+                best = key < best ? key : best;
+            }
         }
-        for (int m = 0; m < 6; ++m) A.out[29 + 6 * m + jc] = A.cov_scale * x[m];
+        float bound = __uint_as_float((uint32_t)(best >> 32));
+        for (int s0 = 0; s0 < A.T.supers; s0 += kOLanes) {
+            const int sup = s0 + gl;
+            uint32_t sm = mp_row_ballot(active && sup < A.T.supers &&
+                                        mp_box_d2(super + 2 * min(sup, A.T.supers - 1), p) <= bound);
+            while (__any(sm != 0)) {
+                const int su = s0 + (sm ? __builtin_ctz(sm) : 0);
+                const int blk = su * kScanFan + gl;
+                uint32_t bm = mp_row_ballot(sm != 0 && blk < A.T.blocks &&
+                                            mp_box_d2(box + 2 * min(blk, A.T.blocks - 1), p) <= bound);
+                sm &= sm - 1;
+                while (__any(bm != 0)) {
+                    const int q0 = bm ? (su * kScanFan + __builtin_ctz(bm)) * kScanBlock + gl : A.T.n;
+                    bm &= bm - 1;
+                    float4 c[kScanBlock / kOLanes];
+#pragma unroll
+                    for (int u = 0; u < kScanBlock / kOLanes; ++u) c[u] = A.T.pts[min(q0 + kOLanes * u, A.T.n - 1)];
+#pragma unroll
+                    for (int u = 0; u < kScanBlock / kOLanes; ++u) {
+                        const uint64_t key = odo_key(mp_point_d2(c[u], p), __float_as_int(c[u].w));
+                        if (q0 + kOLanes * u < A.T.n && key < best) best = key;
+                    }
+                    best = odo_row_min<8>(best);
+                    best = odo_row_min<4>(best);
+                    best = odo_row_min<2>(best);
+                    best = odo_row_min<1>(best);
+                    bound = __uint_as_float((uint32_t)(best >> 32));
+                }
+            }
+        }
+        if (gl == 0) {
+            const int j = best == none ? -1 : (int)(uint32_t)best;
+            match[r * kOSlots + grp] = active ? j : -1;
+            if (active) A.nn[k] = j;
+        }
     }
-    A.out[65] = ok ? 1.0 : 0.0;
+    __syncthreads();
+    // terms, one lane per point
+    const int np = A.rounds * kOSlots;
+    if ((int)threadIdx.x < np) {
+        float t[kOTerms];
+        for (int m = 0; m < kOTerms; ++m) t[m] = 0.0f;
+        const int j = match[threadIdx.x];
+        if (j >= 0) odo_point_terms(A, pose, Rm, w0 + threadIdx.x, j, t);
+        for (int m = 0; m < kOTerms; ++m) tt[m][threadIdx.x] = t[m];
+    }
+    __syncthreads();
+    if (threadIdx.x < kOTerms * kOSum) {
+        const int m = threadIdx.x / kOSum, c = threadIdx.x % kOSum;
+        double acc = 0.0;
+        for (int i = c; i < np; i += kOSum) acc += (double)tt[m][i];
+        run[m][c] = acc;
+    }
+    __syncthreads();
+    if (threadIdx.x < kOTerms) {
+        double acc = 0.0;
+        for (int c = 0; c < kOSum; ++c) acc += run[threadIdx.x][c];
+        A.part_out[threadIdx.x * kOParts + blockIdx.x] = acc;
+    }
+}
+
+// The final sums and the covariance: out = pose (7, then 0), H 21, b 6, cost,
+// inliers, covariance 36, ok.
+__global__ __launch_bounds__(kOThreads) void k_odo_final(const double* __restrict__ part, int nparts,
+                                                         const double* __restrict__ pose, double cov_scale,
+                                                         double* __restrict__ out) {
+    __shared__ double run[kOTerms][kOSum];
+    __shared__ double tot[kOTerms];
+    odo_total(part, nparts, run, tot);
+    if (threadIdx.x < 8) out[threadIdx.x] = threadIdx.x < 7 ? pose[threadIdx.x] : 0.0;
+    if (threadIdx.x < kOTerms) out[8 + threadIdx.x] = tot[threadIdx.x];
+    // Sigma = scale H^-1: column j solves H x = e_j (the undamped solve with b = -e_j)
+    if (threadIdx.x < 6) {
+        double e[6], x[6];
+        for (int m = 0; m < 6; ++m) e[m] = m == (int)threadIdx.x ? -1.0 : 0.0;
+        const bool ok = odo_solve(tot, e, 0.0, 0.0, x);
+        for (int m = 0; m < 6; ++m) out[8 + 29 + 6 * m + threadIdx.x] = ok ? cov_scale * x[m] : 0.0;
+        if (threadIdx.x == 0) out[8 + 65] = ok ? 1.0 : 0.0;
+    }
 }
 
 }  // namespace
@@ -298,16 +422,15 @@ struct OdoCall {
     char* scratch;   // device address of the fixed work area, or null: the filter's buffers
 };
 
-// Layout of the work area: match keys, matches, workgroup sums, then the
-// pose state.
+// Layout of the work area: matches, workgroup sums of two iterations, the
+// poses of two iterations, the results.
 constexpr size_t kNoAllocScan = 16384;   // largest current scan of mp_odometry_noalloc
-constexpr size_t kStateBytes = sizeof(double) * (8 + 66) + sizeof(float) * 8;
-constexpr size_t kScrNn = sizeof(unsigned long long) * kNoAllocScan;
-constexpr size_t kScrPart = kScrNn + sizeof(int32_t) * kNoAllocScan;
-constexpr size_t kScrState = kScrPart + sizeof(double) * kOTerms * (kNoAllocScan / kTB);
-constexpr size_t kScratchBytes = kScrState + kStateBytes;
-static_assert(kNoAllocScan % kTB == 0, "whole workgroups");
-static_assert(kScrNn % 256 == 0 && kScrPart % 256 == 0 && kScrState % 256 == 0, "aligned sections");
+constexpr size_t kPartBytes = sizeof(double) * kOTerms * kOParts;
+constexpr size_t kOutDoubles = 8 + 66;
+constexpr size_t kWorkBytes = 2 * kPartBytes + sizeof(double) * (16 + kOutDoubles);   // all but the matches
+constexpr size_t kScrWork = sizeof(int32_t) * kNoAllocScan;
+constexpr size_t kScratchBytes = kScrWork + kWorkBytes;
+static_assert(kScrWork % 256 == 0 && kPartBytes % 256 == 0, "aligned sections");
 
 void odometry_impl(void* ctx) {
     OdoCall& c = *static_cast<OdoCall*>(ctx);
@@ -331,79 +454,55 @@ void odometry_impl(void* ctx) {
     }
     hipStream_t s = c.s;
     const int ns = f->scan_n, nt = f->prev_n;
-    const int nparts = (ns + kTB - 1) / kTB;
-    unsigned long long* key = nullptr;
+    // at most kOParts workgroups, each a run of consecutive points of the walk order
+    const int rounds = std::max(1, (ns + kOSlots * kOParts - 1) / (kOSlots * kOParts));
+    const int nparts = (ns + kOSlots * rounds - 1) / (kOSlots * rounds);
     int32_t* nn = nullptr;
-    double* part = nullptr;
-    double* pose64 = nullptr;
+    char* work = nullptr;
     if (c.scratch) {
         // the caller's fixed work area: no allocation
         if ((size_t)ns > kNoAllocScan)
             mp_throw(MP_E_ARG, "mp_odometry_noalloc: current scan of %d points exceeds its limit of %d", ns,
                      (int)kNoAllocScan);
-        key = reinterpret_cast<unsigned long long*>(c.scratch);
-        nn = reinterpret_cast<int32_t*>(c.scratch + kScrNn);
-        part = reinterpret_cast<double*>(c.scratch + kScrPart);
-        pose64 = reinterpret_cast<double*>(c.scratch + kScrState);
+        nn = reinterpret_cast<int32_t*>(c.scratch);
+        work = c.scratch + kScrWork;
     } else {
-        f->odo_key.ensure(sizeof(unsigned long long) * (size_t)ns);
         f->odo_nn.ensure(sizeof(int32_t) * (size_t)ns);
-        f->odo_part.ensure(sizeof(double) * kOTerms * (size_t)nparts);
-        // state: pose64 (8 doubles), out (66 doubles), pose32 (8 floats)
-        f->odo_state.ensure(kStateBytes);
-        key = f->odo_key.as<unsigned long long>();
+        f->odo_work.ensure(kWorkBytes);
         nn = f->odo_nn.as<int32_t>();
-        part = f->odo_part.as<double>();
-        pose64 = f->odo_state.as<double>();
+        work = f->odo_work.as<char>();
     }
-    double* out = pose64 + 8;
-    float* pose32 = reinterpret_cast<float*>(out + 66);
-    double h_state[8 + 66];
-    std::memset(h_state, 0, sizeof(h_state));
-    for (int k = 0; k < 7; ++k) h_state[k] = init[k];
-    float h_pose32[8];
-    for (int k = 0; k < 7; ++k) h_pose32[k] = (float)init[k];
-    h_pose32[7] = 0.0f;
-    MP_HIP(hipMemcpyAsync(pose64, h_state, sizeof(h_state), hipMemcpyHostToDevice, s));
-    MP_HIP(hipMemcpyAsync(pose32, h_pose32, sizeof(h_pose32), hipMemcpyHostToDevice, s));
-    // every key starts unmatched; each terms pass leaves them so again
-    mp_fill_u32(key, 0xFFFFFFFFu, 2 * (size_t)ns, s);
-    OdoNnArgs Q;
-    Q.trec = f->prev_orig.as<float4>();
-    Q.srec = f->scan_orig.as<float4>();
-    Q.pose = pose32;
-    Q.key = key;
-    Q.nt = nt;
-    Q.ns = ns;
-    OdoTermArgs T;
-    T.trec = Q.trec;
-    T.srec = Q.srec;
-    T.pose = pose32;
-    T.key = key;
-    T.nn = nn;
-    T.part = part;
-    T.ns = ns;
-    T.dmax2 = P.d_max * P.d_max;
-    OdoStepArgs U;
-    U.part = part;
-    U.pose64 = pose64;
-    U.pose32 = pose32;
-    U.out = out;
-    U.nparts = nparts;
-    U.lam_rel = P.lambda_rel;
-    U.lam_abs = P.lambda_abs;
-    U.cov_scale = P.cov_scale;
-    const dim3 nn_grid((unsigned)((ns + kNnThreads - 1) / kNnThreads), (unsigned)((nt + kNnTargets - 1) / kNnTargets));
+    double* part[2] = {reinterpret_cast<double*>(work), reinterpret_cast<double*>(work + kPartBytes)};
+    double* pose = reinterpret_cast<double*>(work + 2 * kPartBytes);
+    double* out = pose + 16;
+    const ScanIndex S = mp_scan_index(f->scan_idx, ns);
+    OdoArgs A;
+    A.T = mp_scan_index(f->prev_idx, nt);
+    A.trec = f->prev_orig.as<float4>();
+    A.swalk = f->scan.as<float4>();
+    A.spts = S.pts;
+    A.nn = nn;
+    for (int k = 0; k < 7; ++k) A.init[k] = init[k];
+    A.lam_rel = P.lambda_rel;
+    A.lam_abs = P.lambda_abs;
+    A.ns = ns;
+    A.nparts = nparts;
+    A.rounds = rounds;
+    A.dmax2 = P.d_max * P.d_max;
     for (int it = 0; it <= P.iterations; ++it) {
-        k_odo_nn<<<nn_grid, kNnThreads, 0, s>>>(Q);
-        MP_CHECK_LAUNCH();
-        k_odo_terms<<<(unsigned)nparts, kTB, 0, s>>>(T);
-        MP_CHECK_LAUNCH();
-        U.final_eval = it == P.iterations ? 1 : 0;
-        k_odo_step<<<1, 64, 0, s>>>(U);
+        A.first = it == 0 ? 1 : 0;
+        A.part_in = part[(it + 1) & 1];
+        A.part_out = part[it & 1];
+        A.pose_in = pose + 8 * ((it + 1) & 1);
+        A.pose_out = pose + 8 * (it & 1);
+        k_odo_iter<<<(unsigned)nparts, kOThreads, 0, s>>>(A);
         MP_CHECK_LAUNCH();
     }
-    MP_HIP(hipMemcpyAsync(h_state, pose64, sizeof(h_state), hipMemcpyDeviceToHost, s));
+    k_odo_final<<<1, kOThreads, 0, s>>>(part[P.iterations & 1], nparts, pose + 8 * (P.iterations & 1), P.cov_scale,
+                                        out);
+    MP_CHECK_LAUNCH();
+    double h_state[kOutDoubles];
+    MP_HIP(hipMemcpyAsync(h_state, out, sizeof(h_state), hipMemcpyDeviceToHost, s));
     MP_HIP(hipStreamSynchronize(s));
     const double* ho = h_state + 8;
     for (int k = 0; k < 7; ++k) c.dT_out[k] = (float)h_state[k];
@@ -429,7 +528,7 @@ extern "C" mp_status mp_odometry(mp_filter f, const mp_odometry_params* params, 
     return mp_guarded_call("mp_odometry", odometry_impl, &c);
 }
 
-// Work area of mp_odometry_noalloc (0.21 MB): one copy per device, held until
+// Work area of mp_odometry_noalloc (0.18 MB): one copy per device, held until
 // the process ends.  Host code never uses this name as an address: the device
 // address comes from hipGetSymbolAddress, once per device.
 static __device__ __align__(256) char scratch[kScratchBytes];

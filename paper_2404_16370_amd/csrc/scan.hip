@@ -403,6 +403,7 @@ size_t mp_scan_index_bytes(int32_t n) {
 
 ScanIndex mp_scan_index(const DevMem& mem, int32_t n) {
     ScanIndex X;
+    X.n = n;
     X.blocks = (n + kScanBlock - 1) / kScanBlock;
     X.supers = (n + kIdxThreads - 1) / kIdxThreads;
     X.pts = mem.as<float4>();

@@ -91,3 +91,27 @@ def test_scan_neighbours_of_the_indexed_search(room, O, n, k, kind):
     assert np.array_equal(rec[:, 3:9], cov)
     walk = f.debug_get("scan_walk")
     assert np.array_equal(walk[np.lexsort(walk.T)], rec[np.lexsort(rec.T)])
+
+
+@pytest.mark.parametrize("ns,nt,dmax", [(1, 1, 1.0), (31, 65, 0.5), (33, 64, 3.0), (8193, 1025, 1.0), (2000, 9000, 0.2),
+                                        (9000, 2000, 1e4)])
+def test_odometry_matches_of_the_indexed_search(room, O, ns, nt, dmax):
+    # correspondences bit for bit after several iterations (each starts from
+    # the matches of the one before), H and cost within FP32 of the oracle
+    tgt, src = _cloud(nt, "surface", nt), _cloud(ns, "surface", ns + 1)
+    f = _filter(room, 64, None)
+    recs = []
+    for sc in (tgt, src):
+        f.scan_upload(sc)
+        recs.append((sc, np.ascontiguousarray(f.debug_get("scan")[:, 3:9])))
+    (p0, c0), (p1, c1) = recs
+    for it in (0, 3):
+        res = f.odometry(iterations=it, d_max=dmax)
+        ref = O.gicp_terms(p0, c0, p1, c1, res["dT"], dmax=dmax)
+        nn = f.debug_get("odo_nn")
+        # (the pose is rounded to FP32 between the two: a match may change where two are equally near)
+        assert np.mean(nn != ref["nn"]) <= (0.0 if it == 0 else 1e-3), it
+        if it == 0:
+            assert res["inliers"] == ref["ninl"]
+            assert abs(res["cost"] - ref["cost"]) <= 1e-4 * ref["cost"] + 1e-9
+            assert np.abs(res["H21"] - ref["H21"]).max() <= 1e-4 * np.abs(ref["H21"]).max() + 1e-9
