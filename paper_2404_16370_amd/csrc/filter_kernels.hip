@@ -143,64 +143,57 @@ __device__ inline void jr_inv_t(const float3 om, const float3 rho, float beta, c
 // and, with TRANSPORT, v_ij carried to T_i's tangent by Ad_{T_i^-1 T_j}:
 //   [R v_w; t x (R v_w) + R v_r] with (R, t) = T_i^-1 T_j.
 // T_i <- T_i exp(phi_i) (Jacobi: all j at pre-update poses).
+// v_ij of one neighbour
 template <bool EXACT, bool TRANSPORT>
-__global__ __launch_bounds__(256) void k_svgd(SvgdArgs A) {
-    mp_write_stamp(A.stamp);
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= A.n) return;
-    mpdet::quat qi;
-    float3 ti;
-    load_pose(A.pin, i, qi, ti);
-    float num[6] = {0, 0, 0, 0, 0, 0};
-    float den = 0.0f;
-    for (int a = 0; a < A.K; ++a) {
-        const int j = A.nbr[(size_t)a * A.n + i];
-        if (j < 0 || j >= A.n) continue;
-        const float k = A.kval[(size_t)a * A.n + i];
-        mpdet::quat qj;
-        float3 tj;
-        load_pose(A.pin, j, qj, tj);
-        float3 om, rho, tr;
-        mpdet::quat qr;
-        float beta;
-        mpdet::se3_between_ex(qi, ti, qj, tj, om, rho, qr, tr, beta);
-        const float4 p0 = A.psi[2 * j], p1 = A.psi[2 * j + 1];
-        if (!EXACT && !TRANSPORT) {
-            const float k2r = 2.0f * k * A.sr, k2t = 2.0f * k * A.st;
-            num[0] += k * p0.x - k2r * om.x;
-            num[1] += k * p0.y - k2r * om.y;
-            num[2] += k * p0.z - k2r * om.z;
-            num[3] += k * p0.w - k2t * rho.x;
-            num[4] += k * p1.x - k2t * rho.y;
-            num[5] += k * p1.y - k2t * rho.z;
-        } else {
-            float3 gw = float3{A.sr * om.x, A.sr * om.y, A.sr * om.z};
-            float3 gr = float3{A.st * rho.x, A.st * rho.y, A.st * rho.z};
-            if (EXACT) jr_inv_t(om, rho, beta, gw, gr, gw, gr);
-            const float m2k = -2.0f * k;
-            float3 vw = axpy3(m2k, gw, float3{k * p0.x, k * p0.y, k * p0.z});
-            float3 vr = axpy3(m2k, gr, float3{k * p0.w, k * p1.x, k * p1.y});
-            if (TRANSPORT) {
-                const mpdet::mat3 R = mpdet::qmat(qr);
-                const float3 rw = float3{R.m[0] * vw.x + R.m[1] * vw.y + R.m[2] * vw.z,
-                                         R.m[3] * vw.x + R.m[4] * vw.y + R.m[5] * vw.z,
-                                         R.m[6] * vw.x + R.m[7] * vw.y + R.m[8] * vw.z};
-                const float3 rr = float3{R.m[0] * vr.x + R.m[1] * vr.y + R.m[2] * vr.z,
-                                         R.m[3] * vr.x + R.m[4] * vr.y + R.m[5] * vr.z,
-                                         R.m[6] * vr.x + R.m[7] * vr.y + R.m[8] * vr.z};
-                const float3 tx = cross3(tr, rw);
-                vw = rw;
-                vr = float3{tx.x + rr.x, tx.y + rr.y, tx.z + rr.z};
-            }
-            num[0] += vw.x;
-            num[1] += vw.y;
-            num[2] += vw.z;
-            num[3] += vr.x;
-            num[4] += vr.y;
-            num[5] += vr.z;
+__device__ __forceinline__ void svgd_term(const SvgdArgs& A, const mpdet::quat qi, const float3 ti, int j, float k,
+                                          float v[6]) {
+    mpdet::quat qj;
+    float3 tj;
+    load_pose(A.pin, j, qj, tj);
+    float3 om, rho, tr;
+    mpdet::quat qr;
+    float beta;
+    mpdet::se3_between_ex(qi, ti, qj, tj, om, rho, qr, tr, beta);
+    const float4 p0 = A.psi[2 * j], p1 = A.psi[2 * j + 1];
+    if (!EXACT && !TRANSPORT) {
+        const float k2r = 2.0f * k * A.sr, k2t = 2.0f * k * A.st;
+        v[0] = k * p0.x - k2r * om.x;
+        v[1] = k * p0.y - k2r * om.y;
+        v[2] = k * p0.z - k2r * om.z;
+        v[3] = k * p0.w - k2t * rho.x;
+        v[4] = k * p1.x - k2t * rho.y;
+        v[5] = k * p1.y - k2t * rho.z;
+    } else {
+        float3 gw = float3{A.sr * om.x, A.sr * om.y, A.sr * om.z};
+        float3 gr = float3{A.st * rho.x, A.st * rho.y, A.st * rho.z};
+        if (EXACT) jr_inv_t(om, rho, beta, gw, gr, gw, gr);
+        const float m2k = -2.0f * k;
+        float3 vw = axpy3(m2k, gw, float3{k * p0.x, k * p0.y, k * p0.z});
+        float3 vr = axpy3(m2k, gr, float3{k * p0.w, k * p1.x, k * p1.y});
+        if (TRANSPORT) {
+            const mpdet::mat3 R = mpdet::qmat(qr);
+            const float3 rw = float3{R.m[0] * vw.x + R.m[1] * vw.y + R.m[2] * vw.z,
+                                     R.m[3] * vw.x + R.m[4] * vw.y + R.m[5] * vw.z,
+                                     R.m[6] * vw.x + R.m[7] * vw.y + R.m[8] * vw.z};
+            const float3 rr = float3{R.m[0] * vr.x + R.m[1] * vr.y + R.m[2] * vr.z,
+                                     R.m[3] * vr.x + R.m[4] * vr.y + R.m[5] * vr.z,
+                                     R.m[6] * vr.x + R.m[7] * vr.y + R.m[8] * vr.z};
+            const float3 tx = cross3(tr, rw);
+            vw = rw;
+            vr = float3{tx.x + rr.x, tx.y + rr.y, tx.z + rr.z};
         }
-        den += k;
+        v[0] = vw.x;
+        v[1] = vw.y;
+        v[2] = vw.z;
+        v[3] = vr.x;
+        v[4] = vr.y;
+        v[5] = vr.z;
     }
+}
+
+// T_i exp(num / den)
+__device__ __forceinline__ void svgd_move(const SvgdArgs& A, int i, mpdet::quat qi, float3 ti, const float num[6],
+                                          float den) {
     float phi[6];
     const float inv = den > 0.0f ? 1.0f / den : 0.0f;
     for (int m = 0; m < 6; ++m) phi[m] = num[m] * inv;
@@ -209,6 +202,51 @@ __global__ __launch_bounds__(256) void k_svgd(SvgdArgs A) {
     se3_exp(phi, dq, dt);
     compose(qi, ti, dq, dt);
     store_pose(A.pout, i, qi, ti);
+}
+
+// 16 lanes per particle: lane l forms the terms of neighbours l and l + 16,
+// then lane m < 7 adds component m (the sixth: k) over the list in list order.
+// What bounds it: the gathers of the neighbours' poses and psi; with one lane
+// per particle they follow one another.  One lane / 16 lanes, K = 16: 4096
+// particles 21 / 4.5 us, 65,536 29 / 19 us, 1,048,576 462 / 398 us.
+constexpr int kSvLanes = 16;
+
+template <bool EXACT, bool TRANSPORT>
+__global__ __launch_bounds__(256) void k_svgd(SvgdArgs A) {
+    __shared__ float term[256 / kSvLanes][7][33];
+    __shared__ float sum[256 / kSvLanes][8];
+    mp_write_stamp(A.stamp);
+    const int gl = threadIdx.x % kSvLanes, g = threadIdx.x / kSvLanes;
+    const int i0 = blockIdx.x * (256 / kSvLanes) + g;
+    const int i = min(i0, A.n - 1);
+    mpdet::quat qi;
+    float3 ti;
+    load_pose(A.pin, i, qi, ti);
+    for (int a = gl; a < A.K; a += kSvLanes) {
+        const int j = A.nbr[(size_t)a * A.n + i];
+        float v[6] = {0, 0, 0, 0, 0, 0}, k = 0.0f;   // (no neighbour: adding zero changes no sum)
+        if (j >= 0 && j < A.n) {
+            k = A.kval[(size_t)a * A.n + i];
+            svgd_term<EXACT, TRANSPORT>(A, qi, ti, j, k, v);
+        }
+        for (int m = 0; m < 6; ++m) term[g][m][a] = v[m];
+        term[g][6][a] = k;
+    }
+    __syncthreads();
+    if (gl < 7) {
+        float s = 0.0f;
+        for (int a = 0; a < A.K; ++a) s += term[g][gl][a];
+        sum[g][gl] = s;
+    }
+    __syncthreads();
+    // one lane per particle again
+    if (threadIdx.x >= 256 / kSvLanes) return;
+    const int p = blockIdx.x * (256 / kSvLanes) + threadIdx.x;
+    if (p >= A.n) return;
+    load_pose(A.pin, p, qi, ti);
+    float num[6];
+    for (int m = 0; m < 6; ++m) num[m] = sum[threadIdx.x][m];
+    svgd_move(A, p, qi, ti, num, sum[threadIdx.x][6]);
 }
 
 // ------------------------------------------------------------ prediction
@@ -500,10 +538,11 @@ void mp_launch_svgd(mp_filter f, hipStream_t s) {
     A.stamp = mp_take_stamp(f);
     const bool exact = f->p.svgd_grad == MP_SVGD_GRAD_EXACT;
     const bool transport = f->p.svgd_transport == MP_SVGD_TRANSPORT_ADJOINT;
-    if (exact && transport) k_svgd<true, true><<<nblk(f->n), 256, 0, s>>>(A);
-    else if (exact) k_svgd<true, false><<<nblk(f->n), 256, 0, s>>>(A);
-    else if (transport) k_svgd<false, true><<<nblk(f->n), 256, 0, s>>>(A);
-    else k_svgd<false, false><<<nblk(f->n), 256, 0, s>>>(A);
+    const unsigned grid = nblk(f->n, 256 / kSvLanes);
+    if (exact && transport) k_svgd<true, true><<<grid, 256, 0, s>>>(A);
+    else if (exact) k_svgd<true, false><<<grid, 256, 0, s>>>(A);
+    else if (transport) k_svgd<false, true><<<grid, 256, 0, s>>>(A);
+    else k_svgd<false, false><<<grid, 256, 0, s>>>(A);
     MP_CHECK_LAUNCH();
     f->cur = 1 - f->cur;
 }
