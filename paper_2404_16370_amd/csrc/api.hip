@@ -446,6 +446,7 @@ extern "C" mp_status mp_filter_init(mp_map map, const mp_filter_params* params, 
                             (kStampMarks + 8 + per * (size_t)std::min(params->svgd_iters, 1 << 16)));
             f->stepinfo.alloc(16 * sizeof(double));
             f->red.alloc(sizeof(double) * (N + 3 * ((N + 255) / 256)) + sizeof(int) * ((N + 255) / 256) + 64);
+            mp_fill_u32(mp_radix_wait_flag(f->hist), 0u, 1, s);   // (sorts in one workgroup leave it)
             MP_HIP(hipMemsetAsync(f->flags.p, 0, 64, s));
             MP_HIP(hipMemsetAsync(f->stepinfo.p, 0, 16 * sizeof(double), s));
             MP_HIP(hipMemsetAsync(f->psi.p, 0, 32 * N, s));
@@ -874,6 +875,7 @@ extern "C" mp_status mp_debug_set(mp_filter f, const char* name, const void* src
         if ((size_t)bytes != b.bytes) mp_throw(MP_E_ARG, "'%s' holds %zu bytes, given %lld", name, b.bytes, (long long)bytes);
         MP_HIP(hipMemcpyAsync(b.p, src, b.bytes, hipMemcpyDefault, s));
         MP_HIP(hipStreamSynchronize(s));
+        if (b.p == f->sorted.p) f->rank_set = false;
     });
 }
 

@@ -159,6 +159,7 @@ struct mp_filter_s {
     DevMem codes, sorted, scodes, tmp_keys, tmp_vals, head, end, hist;  // LSH / sort
     DevMem lkeys, lorder;     // the likelihood's walk order: Morton keys, particle per position
     DevMem rank;   // sorted position of each particle (the refresh runs in particle order)
+    bool rank_set = false;   // rank belongs to the current `sorted`
     DevMem nbr, kval, cnt;    // K x N, K x N, N
     DevMem prior, post0, post1;   // N float
     DevMem red;               // reduction scratch
@@ -220,6 +221,13 @@ int mp_radix_passes(int64_t n, int bits);
 // (stamp: stage clock of the first launch, if any)
 void mp_radix_sort_u32_inplace_parity(uint32_t* keys, int32_t* vals, uint32_t* keys_alt, int32_t* vals_alt, int64_t n,
                                       int bits, DevMem& scratch, hipStream_t s, uint64_t* stamp = nullptr);
+// Stable sort of few keys (mp_sort_is_small) by their low `bits` bits in one
+// launch: the sorted keys (kout may be kin), the input index of each, and in
+// head, end and rank (or null) the bucket bounds of every position and the
+// position of every input
+bool mp_sort_is_small(int64_t n);
+void mp_sort_small(const uint32_t* kin, uint32_t* kout, int32_t* vout, int32_t n, int bits,
+                   int32_t* head, int32_t* end, int32_t* rank, hipStream_t s, uint64_t* stamp = nullptr);
 // device word of a 32-bit sort's scratch, zero after a good sort: 1 if a
 // workgroup stopped waiting for its predecessors' counts, 2 if a key's place
 // fell outside the output (its input changed while it ran); neither is

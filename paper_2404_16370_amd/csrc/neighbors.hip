@@ -22,6 +22,7 @@
 
 #include "mp_det.hpp"
 #include "mp_internal.hpp"
+#include "mp_row.hpp"
 
 namespace {
 
@@ -87,14 +88,18 @@ __global__ __launch_bounds__(256) void k_lsh(LshArgs A) {
     A.idx[i] = i;
 }
 
-// Bucket head and end of every sorted position: the run of equal codes around
+// Position of every particle in the sorted order, and bucket head and end of
+// every position: the run of equal codes around
 // s, found by an exponential then binary search on each side (a bucket of m
 // particles costs about 2 log2(m) reads per position).
-__global__ void k_bucket_bounds(const uint32_t* __restrict__ sc, int n, int32_t* __restrict__ head,
-                                int32_t* __restrict__ end, uint64_t* __restrict__ stamp) {
+__global__ void k_bucket_bounds(const uint32_t* __restrict__ sc, const int32_t* __restrict__ sorted, int n,
+                                int32_t* __restrict__ head, int32_t* __restrict__ end, int32_t* __restrict__ rank,
+                                uint64_t* __restrict__ stamp) {
     mp_write_stamp(stamp);
     const int s = blockIdx.x * blockDim.x + threadIdx.x;
     if (s >= n) return;
+    const int i = sorted[s];
+    if (i >= 0 && i < n) rank[i] = s;
     const uint32_t c = sc[s];
     // left: lo is known to hold c, the first position holding c is in (lo - step, lo]
     int lo = s, step = 1;
@@ -137,6 +142,7 @@ struct RefreshArgs {
     int32_t* __restrict__ cnt;    // N
     int32_t n, K, C;
     float sr, st;
+    uint64_t* stamp;              // stage clock, or null
 };
 
 template <int KM>
@@ -175,10 +181,8 @@ struct TopK {
     }
 };
 
-// rank[sorted[s]] = s
-__global__ void k_rank(const int32_t* __restrict__ sorted, int n, int32_t* __restrict__ rank,
-                       uint64_t* __restrict__ stamp) {
-    mp_write_stamp(stamp);
+// rank[sorted[s]] = s, when no sort left it (an order set from outside)
+__global__ void k_rank(const int32_t* __restrict__ sorted, int n, int32_t* __restrict__ rank) {
     const int s = blockIdx.x * blockDim.x + threadIdx.x;
     if (s >= n) return;
     const int i = sorted[s];
@@ -190,6 +194,7 @@ __global__ void k_rank(const int32_t* __restrict__ sorted, int n, int32_t* __res
 // its sorted position (rank) locates its bucket window.
 template <int KM>
 __global__ __launch_bounds__(256) void k_refresh(RefreshArgs A) {
+    mp_write_stamp(A.stamp);
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= A.n) return;
     const int s = A.rank[i];
@@ -291,6 +296,15 @@ void mp_launch_lsh(mp_filter f, uint32_t frame, uint32_t it, hipStream_t s) {
 
 void mp_launch_sort(mp_filter f, hipStream_t s) {
     const int n = f->n;
+    f->rank_set = true;
+    if (mp_sort_is_small(n)) {
+        // the LSH kernel's buffers, see there
+        const bool odd = mp_radix_passes(n, f->p.lsh_bits) % 2 == 1;
+        mp_sort_small(odd ? f->tmp_keys.as<uint32_t>() : f->scodes.as<uint32_t>(),
+                      f->scodes.as<uint32_t>(), f->sorted.as<int32_t>(), n, n > 1 ? f->p.lsh_bits : 0, f->head.as<int32_t>(),
+                      f->end.as<int32_t>(), f->rank.as<int32_t>(), s, mp_take_stamp(f));
+        return;
+    }
     // stable sort of (code, index) from the buffers the LSH kernel filled;
     // the result lands in (scodes, sorted) with no copy
     const bool odd = mp_radix_passes(n, f->p.lsh_bits) % 2 == 1;
@@ -302,15 +316,20 @@ void mp_launch_sort(mp_filter f, hipStream_t s) {
     else
         mp_radix_sort_u32_inplace_parity(f->scodes.as<uint32_t>(), f->sorted.as<int32_t>(), f->tmp_keys.as<uint32_t>(),
                                          f->tmp_vals.as<int32_t>(), n, f->p.lsh_bits, f->hist, s, stamp);
-    k_bucket_bounds<<<nblk(n), 256, 0, s>>>(f->scodes.as<uint32_t>(), n, f->head.as<int32_t>(), f->end.as<int32_t>(),
+    k_bucket_bounds<<<nblk(n), 256, 0, s>>>(f->scodes.as<uint32_t>(), f->sorted.as<int32_t>(), n,
+                                            f->head.as<int32_t>(), f->end.as<int32_t>(), f->rank.as<int32_t>(),
                                             mp_take_stamp(f));
     MP_CHECK_LAUNCH();
 }
 
 void mp_launch_refresh(mp_filter f, hipStream_t s, int window) {
-    k_rank<<<nblk(f->n), 256, 0, s>>>(f->sorted.as<int32_t>(), f->n, f->rank.as<int32_t>(), mp_take_stamp(f));
-    MP_CHECK_LAUNCH();
+    if (!f->rank_set) {
+        k_rank<<<nblk(f->n), 256, 0, s>>>(f->sorted.as<int32_t>(), f->n, f->rank.as<int32_t>());
+        MP_CHECK_LAUNCH();
+        f->rank_set = true;
+    }
     RefreshArgs A;
+    A.stamp = mp_take_stamp(f);
     A.poses = f->poses[f->cur].as<float4>();
     A.sorted = f->sorted.as<int32_t>();
     A.rank = f->rank.as<int32_t>();

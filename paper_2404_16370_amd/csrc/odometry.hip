@@ -253,12 +253,6 @@ __device__ void odo_step(const double* tot, double lam_rel, double lam_abs, cons
 __device__ __forceinline__ uint64_t odo_key(float d2, int32_t j) {   // d2 >= +0: its bits order as the values do
     return ((uint64_t)__float_as_uint(d2) << 32) | (uint32_t)j;
 }
-template <int ROT>
-__device__ __forceinline__ uint64_t odo_row_min(uint64_t v) {
-    const uint64_t o = ((uint64_t)mp_row_ror<ROT>((uint32_t)(v >> 32)) << 32) | mp_row_ror<ROT>((uint32_t)v);
-    return o < v ? o : v;
-}
-
 __global__ __launch_bounds__(kOThreads) void k_odo_iter(OdoArgs A) {
     __shared__ double run[kOTerms][kOSum];
     __shared__ double tot[kOTerms];
@@ -338,10 +332,7 @@ __global__ __launch_bounds__(kOThreads) void k_odo_iter(OdoArgs A) {
                         const uint64_t key = odo_key(mp_point_d2(c[u], p), __float_as_int(c[u].w));
                         if (q0 + kOLanes * u < A.T.n && key < best) best = key;
                     }
-                    best = odo_row_min<8>(best);
-                    best = odo_row_min<4>(best);
-                    best = odo_row_min<2>(best);
-                    best = odo_row_min<1>(best);
+                    best = mp_row_min_u64(best);
                     bound = __uint_as_float((uint32_t)(best >> 32));
                 }
             }

@@ -145,12 +145,6 @@ __device__ __forceinline__ uint64_t knn_key(float d2, int32_t j) {
     return ((uint64_t)__float_as_uint(d2) << 32) | (uint32_t)j;
 }
 
-template <int ROT>
-__device__ __forceinline__ uint64_t row_min_step(uint64_t v) {
-    const uint64_t o = ((uint64_t)mp_row_ror<ROT>((uint32_t)(v >> 32)) << 32) | mp_row_ror<ROT>((uint32_t)v);
-    return o < v ? o : v;
-}
-
 // The loops that are not unrolled keep the code short: a launch over a few
 // hundred points spends its time fetching instructions for the first time.
 template <int KC>
@@ -235,11 +229,7 @@ __global__ __launch_bounds__(kB) void k_scan_knn_cov(const float* __restrict__ x
     for (int a = 0; a < KC; a += kQLanes) {
 #pragma unroll 1
         for (int r = a; r < min(kk, a + kQLanes); ++r) {
-            uint64_t v = best[0];
-            v = row_min_step<8>(v);
-            v = row_min_step<4>(v);
-            v = row_min_step<2>(v);
-            v = row_min_step<1>(v);
+            const uint64_t v = mp_row_min_u64(best[0]);
             if (gl == r - a) mine[a / kQLanes] = (int32_t)(uint32_t)v;
             if (best[0] == v) {   // this lane held the minimum (indices are unique)
 #pragma unroll
@@ -443,5 +433,6 @@ void mp_scan_walk_order(const float* xyz_dev, int32_t n, float cell, const float
     if (n <= 0) return;
     k_morton_keys<<<(n + 255) / 256, 256, 0, s>>>(xyz_dev, n, lo_bad_dev, 1.0f / cell, keys, perm, stamps);
     MP_CHECK_LAUNCH();
-    mp_radix_sort_u32(keys, perm, keys_alt, perm_alt, n, 30, scratch, s);
+    if (mp_sort_is_small(n)) mp_sort_small(keys, keys, perm, n, 30, nullptr, nullptr, nullptr, s);
+    else mp_radix_sort_u32(keys, perm, keys_alt, perm_alt, n, 30, scratch, s);
 }

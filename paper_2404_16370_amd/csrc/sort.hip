@@ -24,6 +24,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "mp_internal.hpp"
 
@@ -482,6 +483,183 @@ __global__ __launch_bounds__(kOsThreads) void k_os_scatter(OsScatterArgs A) {
     }
 }
 
+// inclusive sum over the wave's lanes (all active): within rows of 16, then
+// the rows' totals carried on
+__device__ __forceinline__ uint32_t wave_scan_dpp(uint32_t v) {
+    auto step = [&](auto ctrl, auto rows) {
+        v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, decltype(ctrl)::value, decltype(rows)::value, 0xF, true);
+    };
+    step(std::integral_constant<int, 0x111>{}, std::integral_constant<int, 0xF>{});   // row_shr:1
+    step(std::integral_constant<int, 0x112>{}, std::integral_constant<int, 0xF>{});
+    step(std::integral_constant<int, 0x114>{}, std::integral_constant<int, 0xF>{});
+    step(std::integral_constant<int, 0x118>{}, std::integral_constant<int, 0xF>{});
+    step(std::integral_constant<int, 0x142>{}, std::integral_constant<int, 0xA>{});   // row_bcast:15 into rows 1, 3
+    step(std::integral_constant<int, 0x143>{}, std::integral_constant<int, 0xC>{});   // row_bcast:31 into rows 2, 3
+    return v;
+}
+
+// ------------------------------------------------------------ sort of few keys in one workgroup
+// Up to kSmMax keys stay in the LDS of one workgroup through all passes, 4
+// bits at a time: a thread counts the digits of its ITEMS consecutive keys in
+// counters of its own, one scan over (digit, thread) turns the counts into
+// places, and the thread hands the places out in key order.  For bucket sorts
+// the same launch writes every position's bucket bounds and every value's
+// position.
+//
+// What bounds it: LDS latency and the barriers of a pass, about 2 us each, and
+// one CU's loads and stores.  With bounds and positions, 20-bit keys: 256 keys
+// 11 us, 4096 15 us, 8000 23 us; the one-sweep sort and its bounds kernel, 27
+// to 32 us and five launches whatever the count below 16,384 (where one
+// workgroup took 64 us).
+constexpr int kSmThreads = 1024;
+constexpr int kSmItems = 8;                      // most keys per thread
+constexpr int kSmMax = kSmThreads * kSmItems;
+constexpr int kSmBits = 4;
+constexpr int kSmDigits = 1 << kSmBits;          // one thread scans as many counters
+static_assert(kSmDigits == 16, "a thread's share of the scan is two 16-byte words of 16-bit counters");
+static_assert(4 * kSmItems <= 2 * kSmDigits, "heads and ends fit the counters");
+
+struct SmSortArgs {
+    const uint32_t* kin;
+    uint32_t* kout;       // may be kin
+    int32_t* vout;        // input index of each sorted key
+    int32_t* head;        // bucket bounds per position and position of each value, or null
+    int32_t* end;
+    int32_t* rank;
+    int32_t n, bits;
+    uint64_t* stamp;      // stage clock, or null
+};
+
+template <int ITEMS>
+__global__ __launch_bounds__(kSmThreads) void k_sort_small(SmSortArgs A) {
+    __shared__ __attribute__((aligned(16))) uint32_t sk[kSmThreads * ITEMS];
+    __shared__ __attribute__((aligned(16))) uint16_t sv[kSmThreads * ITEMS];   // index of the key among the inputs
+    __shared__ __attribute__((aligned(16))) uint32_t cnt[kSmDigits * kSmThreads / 2];   // 16-bit counters [digit][thread]
+    __shared__ uint32_t wsum[kSmThreads / 64];
+    mp_write_stamp(A.stamp);
+    const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+    for (int i = t; i < kSmThreads * ITEMS; i += kSmThreads) {
+        sk[i] = i < A.n ? A.kin[i] : 0u;
+        sv[i] = (uint16_t)i;
+    }
+    uint4* scan = reinterpret_cast<uint4*>(cnt) + 2 * t;   // this thread's share of the scan: 16 counters
+    for (int shift = 0; shift < A.bits; shift += kSmBits) {
+        scan[0] = make_uint4(0, 0, 0, 0);
+        scan[1] = make_uint4(0, 0, 0, 0);
+        __syncthreads();
+        uint32_t key[ITEMS];
+        uint16_t val[ITEMS];
+        uint32_t pos[ITEMS];
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r) {
+            key[r] = sk[t * ITEMS + r];
+            val[r] = sv[t * ITEMS + r];
+        }
+        const uint32_t one = 1u << (16 * (t & 1));
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r) {
+            const uint32_t d = (key[r] >> shift) & (kSmDigits - 1);
+            if (t * ITEMS + r < A.n) atomicAdd(&cnt[d * (kSmThreads / 2) + (t >> 1)], one);
+        }
+        __syncthreads();
+        {
+            const uint4 c0 = scan[0], c1 = scan[1];
+            const uint32_t c[8] = {c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w};
+            uint32_t sum = 0;
+#pragma unroll
+            for (int q = 0; q < 8; ++q) sum += (c[q] & 0xFFFFu) + (c[q] >> 16);
+            const uint32_t inc = wave_scan_dpp(sum);
+            if (lane == 63) wsum[w] = inc;
+            __syncthreads();
+            // the waves' totals: lane v of every wave holds the total of waves 0..v
+            const uint32_t tot = wave_scan_dpp(lane < kSmThreads / 64 ? wsum[lane] : 0u);
+            const uint32_t wbase = w == 0 ? 0u : (uint32_t)__builtin_amdgcn_readlane((int)tot, w - 1);
+            uint32_t run = wbase + inc - sum;
+            uint32_t o[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const uint32_t lo = run;
+                run += c[q] & 0xFFFFu;
+                o[q] = lo | (run << 16);
+                run += c[q] >> 16;
+            }
+            scan[0] = make_uint4(o[0], o[1], o[2], o[3]);
+            scan[1] = make_uint4(o[4], o[5], o[6], o[7]);
+        }
+        __syncthreads();
+        // the LDS takes a wave's operations in order: equal digits of a thread
+        // get their places in key order
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r) {
+            const uint32_t d = (key[r] >> shift) & (kSmDigits - 1);
+            pos[r] = 0;
+            if (t * ITEMS + r < A.n)
+                pos[r] = (atomicAdd(&cnt[d * (kSmThreads / 2) + (t >> 1)], one) >> (16 * (t & 1))) & 0xFFFFu;
+        }
+#pragma unroll
+        for (int r = 0; r < ITEMS; ++r)
+            if (t * ITEMS + r < A.n) {   // pos: a permutation of 0..n-1
+                sk[pos[r]] = key[r];
+                sv[pos[r]] = val[r];
+            }
+        __syncthreads();
+    }
+    __syncthreads();
+    for (int i = t; i < A.n; i += kSmThreads) A.kout[i] = sk[i];
+    for (int i = t; i < A.n; i += kSmThreads) A.vout[i] = (int32_t)sv[i];
+    if (!A.head) return;
+    // bucket bounds: the last run start at or before a position, and the first
+    // one after it, carried over the threads' consecutive positions by a scan
+    // in each direction
+    __shared__ int wlast[kSmThreads / 64], wfirst[kSmThreads / 64];
+    uint16_t* sh = reinterpret_cast<uint16_t*>(cnt);   // heads, then (after them) ends: at most 4 kSmThreads ITEMS bytes
+    uint16_t* se = sh + kSmThreads * ITEMS;
+    const int i0 = t * ITEMS;
+    uint32_t starts = 0;   // bit r: position i0 + r starts a run (or is the end)
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+        const int i = i0 + r;
+        const bool st = i == A.n || (i < A.n && (i == 0 || sk[i - 1] != sk[i]));
+        starts |= st ? 1u << r : 0u;
+    }
+    int last = starts ? i0 + 31 - __builtin_clz(starts) : -1;
+    int first = starts ? i0 + __builtin_ctz(starts) : 0x7FFFFFFF;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int u = __shfl_up(last, d, 64), v = __shfl_down(first, d, 64);
+        if (lane >= d) last = max(last, u);
+        if (lane + d < 64) first = min(first, v);
+    }
+    if (lane == 63) wlast[w] = last;
+    if (lane == 0) wfirst[w] = first;
+    __syncthreads();   // (sk is read: it takes the ranks)
+    int before = __shfl_up(last, 1, 64), after = __shfl_down(first, 1, 64);   // of the threads before and after
+    if (lane == 0) before = -1;
+    if (lane == 63) after = A.n;
+#pragma unroll
+    for (int v = 0; v < kSmThreads / 64; ++v) {
+        if (v < w) before = max(before, wlast[v]);
+        if (v > w) after = min(after, wfirst[v]);
+    }
+    after = min(after, A.n);
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+        const int i = i0 + r;
+        if (i < A.n) {
+            const uint32_t lo = starts & (0xFFFFFFFFu >> (31 - r)), hi = starts >> (r + 1) << (r + 1);
+            sh[i] = (uint16_t)(lo ? i0 + 31 - __builtin_clz(lo) : before);
+            se[i] = (uint16_t)(hi ? i0 + __builtin_ctz(hi) : after);
+            sk[sv[i]] = (uint32_t)i;
+        }
+    }
+    __syncthreads();
+    for (int i = t; i < A.n; i += kSmThreads) {
+        A.head[i] = (int32_t)sh[i];
+        A.end[i] = (int32_t)se[i];
+        A.rank[i] = (int32_t)sk[i];
+    }
+}
+
 int64_t os_tiles(int64_t n) { return (n + kOsTile - 1) / kOsTile; }
 
 int os_hist_blocks(int64_t n) {
@@ -570,6 +748,25 @@ int mp_radix_passes(int64_t n, int bits) {
 void mp_radix_sort_u32_inplace_parity(uint32_t* keys, int32_t* vals, uint32_t* keys_alt, int32_t* vals_alt, int64_t n,
                                       int bits, DevMem& scratch, hipStream_t s, uint64_t* stamp) {
     onesweep_sort(keys, vals, keys_alt, vals_alt, n, bits, scratch, s, false, stamp);
+}
+
+bool mp_sort_is_small(int64_t n) { return n <= kSmMax; }
+
+void mp_sort_small(const uint32_t* kin, uint32_t* kout, int32_t* vout, int32_t n, int bits,
+                   int32_t* head, int32_t* end, int32_t* rank, hipStream_t s, uint64_t* stamp) {
+    SmSortArgs A;
+    A.kin = kin;
+    A.kout = kout;
+    A.vout = vout;
+    A.head = head;
+    A.end = end;
+    A.rank = rank;
+    A.n = n;
+    A.bits = bits;
+    A.stamp = stamp;
+    if (n <= kSmThreads * 4) k_sort_small<4><<<1, kSmThreads, 0, s>>>(A);
+    else k_sort_small<kSmItems><<<1, kSmThreads, 0, s>>>(A);
+    MP_CHECK_LAUNCH();
 }
 
 uint32_t* mp_radix_wait_flag(DevMem& scratch) { return scratch.as<uint32_t>() + 4; }

@@ -115,3 +115,26 @@ def test_odometry_matches_of_the_indexed_search(room, O, ns, nt, dmax):
             assert res["inliers"] == ref["ninl"]
             assert abs(res["cost"] - ref["cost"]) <= 1e-4 * ref["cost"] + 1e-9
             assert np.abs(res["H21"] - ref["H21"]).max() <= 1e-4 * np.abs(ref["H21"]).max() + 1e-9
+
+
+@pytest.mark.parametrize("n", [1, 2, 63, 64, 65, 1023, 1024, 1025, 4096, 4097, 8191, 8192, 8193])
+@pytest.mark.parametrize("bits", [0, 3, 8, 20, 30])
+def test_bucket_sort_bounds_and_ranks(room, O, n, bits):
+    # both sides of the one-workgroup sort's limit: order, bounds and (through
+    # the lists) positions as the oracle's stable sort gives them
+    R, t = room["w"]["traj"][0]
+    poses = S.gaussian_particles(n, S.pose8(R, t), 0.3, 1.0, n)
+    f = _filter(room, n, poses, lsh_bits=bits, lsh_alpha=0.5)
+    f.debug_stage(M.MP_STAGE_LSH)
+    f.debug_stage(M.MP_STAGE_SORT)
+    codes = f.debug_get("codes")
+    order = np.argsort(codes, kind="stable").astype(np.int32)
+    assert np.array_equal(f.debug_get("sorted"), order)
+    sc = codes[order]
+    assert np.array_equal(f.debug_get("scodes"), sc)
+    assert np.array_equal(f.debug_get("head"), np.searchsorted(sc, sc, side="left"))
+    assert np.array_equal(f.debug_get("end"), np.searchsorted(sc, sc, side="right"))
+    assert f.debug_get("sort_wait")[0] == 0
+    f.debug_stage(M.MP_STAGE_REFRESH)
+    nbr, q, cnt = O.refresh(f.debug_get("poses"), order, codes, 8, 16, 5.0, 2.5, None)
+    assert np.array_equal(f.debug_get("nbr").T, nbr) and np.array_equal(f.debug_get("cnt"), cnt)
