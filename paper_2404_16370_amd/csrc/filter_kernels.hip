@@ -608,6 +608,63 @@ void mp_copy_poses(mp_filter f, int from, int to, hipStream_t s) {
     MP_CHECK_LAUNCH();
 }
 
+namespace {
+struct QueryArgs {
+    const float4* __restrict__ poses;
+    const float* __restrict__ prior;
+    const double* __restrict__ info;
+    const int32_t* __restrict__ flags;
+    QueryOut* out;     // host memory
+    float* pout;       // N x 7, or null
+    double* wout;      // N, or null
+    int32_t n;
+};
+
+// Packing and the finiteness check of what a query hands out, one thread per
+// four bytes of a pose, so that the stores are whole runs (device memory, or
+// the host's over the link).
+__global__ __launch_bounds__(256) void k_query(QueryArgs A) {
+    const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const float* P = reinterpret_cast<const float*>(A.poses);
+    bool bad = false;
+    if (A.pout && q < 7 * (int64_t)A.n) {
+        const int64_t i = q / 7;
+        const float v = P[8 * i + (q - 7 * i)];
+        bad = !isfinite(v);
+        A.pout[q] = v;
+    }
+    if (A.wout && q < A.n) {
+        const float v = A.prior[q];
+        bad = bad || !isfinite(v);
+        A.wout[q] = (double)v;
+    }
+    if (bad) __hip_atomic_store(&A.out->bad, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (q == 0) {
+        for (int k = 0; k < 8; ++k) A.out->info[k] = A.info[k];
+        int idx = (int)A.info[7];
+        if (idx < 0 || idx >= A.n) idx = 0;
+        for (int k = 0; k < 8; ++k) A.out->pose[k] = P[8 * (int64_t)idx + k];
+        A.out->index = idx;
+        A.out->resolves = A.flags[0];
+    }
+}
+}  // namespace
+
+void mp_launch_query(mp_filter f, QueryOut* out, float* poses, double* weights, hipStream_t s) {
+    QueryArgs A;
+    A.poses = f->poses[f->cur].as<float4>();
+    A.prior = f->prior.as<float>();
+    A.info = f->stepinfo.as<double>();
+    A.flags = f->flags.as<int32_t>();
+    A.out = out;
+    A.pout = poses;
+    A.wout = weights;
+    A.n = f->n;
+    const int64_t items = poses ? 7 * (int64_t)f->n : (weights ? (int64_t)f->n : 1);
+    k_query<<<nblk(items), 256, 0, s>>>(A);
+    MP_CHECK_LAUNCH();
+}
+
 void mp_launch_stamp(uint64_t* p, hipStream_t s) {
     k_stamp<<<1, 64, 0, s>>>(p);
     MP_CHECK_LAUNCH();

@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -45,6 +46,20 @@ struct DevMem {
         std::swap(p, o.p);
         std::swap(bytes, o.bytes);
     }
+};
+
+// Owning allocation of pinned host memory, which kernels write directly.
+struct HostMem {
+    void* p = nullptr;
+    size_t bytes = 0;
+    HostMem() = default;
+    HostMem(const HostMem&) = delete;
+    HostMem& operator=(const HostMem&) = delete;
+    ~HostMem() {
+        if (p) (void)hipHostFree(p);
+    }
+    void ensure(size_t b);   // grow if smaller, contents undefined
+    template <class T> T* as() const { return static_cast<T*>(p); }
 };
 
 // ------------------------------------------------------------ map
@@ -178,6 +193,9 @@ struct mp_filter_s {
     DevMem scan_sort;         // radix-sort scratch of the walk order
     DevMem tlsh;              // 8 float
     DevMem stepinfo;          // posterior summary (doubles)
+    HostMem host;             // what queries read: QueryOut, then packed poses and weights of small filters
+    DevMem pack;              // packed poses and weights of large ones
+    std::mutex query_mu;      // one query at a time uses them
     // stage timers of the last step (mp_stage_begin) and scan upload
     DevMem stamps;            // device clock values: [0] scan start, [1] scan end, then one per mark
     std::vector<StageMark> marks;
@@ -293,6 +311,16 @@ void mp_step_end(mp_filter f, hipStream_t s);
 void mp_launch_svgd(mp_filter f, hipStream_t s);
 void mp_launch_posterior(mp_filter f, hipStream_t s, uint64_t* stamp_end = nullptr);
 void mp_launch_stamp(uint64_t* p, hipStream_t s);
+// The representative state into pinned host memory; poses (N x 7) and weights
+// (N doubles), each or null, packed where the device can write
+struct QueryOut {
+    double info[8];      // posterior summary
+    float pose[8];       // pose of the maximum
+    int32_t index;       // its (clamped) index
+    int32_t resolves;    // FP64 re-solves
+    uint32_t bad;        // set before the launch; 1: a requested pose or weight is not finite
+};
+void mp_launch_query(mp_filter f, QueryOut* out, float* poses, double* weights, hipStream_t s);
 void mp_launch_reset_lists(mp_filter f, hipStream_t s);
 // device fill (graph-safe replacement of hipMemsetAsync)
 void mp_fill_u32(void* p, uint32_t v, size_t n, hipStream_t s);

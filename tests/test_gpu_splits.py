@@ -138,3 +138,37 @@ def test_bucket_sort_bounds_and_ranks(room, O, n, bits):
     f.debug_stage(M.MP_STAGE_REFRESH)
     nbr, q, cnt = O.refresh(f.debug_get("poses"), order, codes, 8, 16, 5.0, 2.5, None)
     assert np.array_equal(f.debug_get("nbr").T, nbr) and np.array_equal(f.debug_get("cnt"), cnt)
+
+
+@pytest.mark.parametrize("n", [1, 37, 255, 29_126, 29_200, 40_000])
+def test_query_outputs_and_their_places(room, n):
+    # both sides of the pinned path's limit; host and device outputs
+    import ctypes as C
+
+    import torch
+    R, t = room["w"]["traj"][0]
+    f = _filter(room, n, S.gaussian_particles(n, S.pose8(R, t), 0.1, 0.3, n), temperature=50.0)
+    f.scan_upload(room["w"]["scans"][0][:200])
+    f.step()
+    P, W = f.debug_get("poses")[:, :7], f.debug_get("prior").astype(np.float64)
+    q = f.posterior_query(poses=True, weights=True)
+    assert np.array_equal(q["poses"], P) and np.array_equal(q["weights"], W)
+    assert np.array_equal(q["map_pose"], P[q["map_index"]])
+    assert np.array_equal(f.posterior_query(poses=True)["poses"], P)
+    assert np.array_equal(f.posterior_query(weights=True)["weights"], W)
+    dp, dw = torch.zeros((n, 7), device="cuda"), torch.zeros(n, dtype=torch.float64, device="cuda")
+    out = M.mp_posterior()
+    M._check(M.lib().mp_posterior_query(f.handle, C.byref(out), C.c_void_p(dp.data_ptr()), C.c_void_p(dw.data_ptr()),
+                                        M._stream(None)))
+    assert np.array_equal(dp.cpu().numpy(), P) and np.array_equal(dw.cpu().numpy(), W)
+    assert out.map_index == q["map_index"] and out.n_eff == q["n_eff"]
+    # a non-finite pose is reported, and the outputs are still written
+    bad = f.debug_get("poses")
+    bad[n - 1, 6] = np.nan
+    f.debug_set("poses", bad)
+    with pytest.raises(M.MegaPFError) as e:
+        f.posterior_query(poses=True)
+    assert e.value.status == M.MP_E_NUMERIC
+    got = np.zeros((n, 7), np.float32)
+    assert M.lib().mp_posterior_query(f.handle, C.byref(out), M._ptr(got), None, M._stream(None)) == M.MP_E_NUMERIC
+    assert np.array_equal(got, bad[:, :7], equal_nan=True)
