@@ -668,7 +668,7 @@ static void lik_prepare_order(mp_filter f, int scorer, hipStream_t s) {
 // workgroup, 4096 particles x 1024 points ran on 16 of the 256 CUs: 266 us a
 // launch, 39 us with 32; 16,384 x 2048 312 -> 125 us, 65,536 x 4096 944 -> 874
 // us (512 of its 1024 workgroups in flight, the last ones alone).
-constexpr int kSplitGroups = 1024;
+constexpr int kSplitGroups = 4096;
 
 static int lik_rounds(int n, int nch) {
     int rounds = kGRounds;
