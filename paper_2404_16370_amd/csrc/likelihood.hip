@@ -105,15 +105,26 @@ __device__ __forceinline__ void add_cost(Acc& S, float y) {
 // 1 - a u^T P u it loses about 10 bits to cancellation when Sigma^S is thin
 // along u, so it is taken as lam_n + a u^T D u with lam_n = 1 - a |n|^2 from
 // the map record (the same quantity for |u| = |n|, both terms non-negative).
-template <bool KAHAN>
-__device__ __forceinline__ void accumulate(Acc& S, const mpdet::mat3& Rm, const float a, const float dmax2,
-                                           const float cmax, const float4 r0, const float4 r1, const float4 r2,
-                                           const float3 p, const bool hit, const float4 gm, const float4 gn) {
+// What one point adds: B = [mu]x Omega, Omega (upper), Omega e, mu (all in the
+// body frame; mu = 0 for an outlier), the inlier flag and the point's cost.
+struct LikTerms {
+    float B[9];
+    float o[6];
+    float w[3];
+    float3 mu;
+    float m, y;
+};
+
+__device__ __forceinline__ LikTerms lik_terms(const mpdet::mat3& Rm, const float a, const float dmax2,
+                                              const float cmax, const float4 r0, const float4 r1, const float4 r2,
+                                              const float3 p, const bool hit, const float4 gm, const float4 gn) {
+    LikTerms T;
     const float ex = gm.x - p.x, ey = gm.y - p.y, ez = gm.z - p.z;
     const float d2 = __builtin_fmaf(ex, ex, __builtin_fmaf(ey, ey, ez * ez));
     const bool inl = hit && (d2 <= dmax2);
-    const float m = inl ? 1.0f : 0.0f;
+    T.m = inl ? 1.0f : 0.0f;
     const float3 mu = make_float3(inl ? r0.x : 0.0f, inl ? r0.y : 0.0f, inl ? r0.z : 0.0f);
+    T.mu = mu;
     const float3 u = mpdet::rot_t(Rm, make_float3(gn.x, gn.y, gn.z));
     const float3 eb = mpdet::rot_t(Rm, make_float3(ex, ey, ez));
     const float p00 = r0.w, p01 = r1.x, p02 = r1.y, p11 = r1.z, p12 = r1.w, p22 = r2.x;
@@ -127,43 +138,54 @@ __device__ __forceinline__ void accumulate(Acc& S, const mpdet::mat3& Rm, const 
     const float o00 = __builtin_fmaf(v0, q0, p00), o01 = __builtin_fmaf(v0, q1, p01);
     const float o02 = __builtin_fmaf(v0, q2, p02), o11 = __builtin_fmaf(v1, q1, p11);
     const float o12 = __builtin_fmaf(v1, q2, p12), o22 = __builtin_fmaf(v2, q2, p22);
-    const float w0 = __builtin_fmaf(o00, eb.x, __builtin_fmaf(o01, eb.y, o02 * eb.z));
-    const float w1 = __builtin_fmaf(o01, eb.x, __builtin_fmaf(o11, eb.y, o12 * eb.z));
-    const float w2 = __builtin_fmaf(o02, eb.x, __builtin_fmaf(o12, eb.y, o22 * eb.z));
-    const float cst = __builtin_fmaf(eb.x, w0, __builtin_fmaf(eb.y, w1, eb.z * w2));
-    add_cost<KAHAN>(S, inl ? fminf(cst, cmax) : 0.0f);
-    S.nin += inl ? 1 : 0;
+    T.o[0] = o00; T.o[1] = o01; T.o[2] = o02; T.o[3] = o11; T.o[4] = o12; T.o[5] = o22;
+    T.w[0] = __builtin_fmaf(o00, eb.x, __builtin_fmaf(o01, eb.y, o02 * eb.z));
+    T.w[1] = __builtin_fmaf(o01, eb.x, __builtin_fmaf(o11, eb.y, o12 * eb.z));
+    T.w[2] = __builtin_fmaf(o02, eb.x, __builtin_fmaf(o12, eb.y, o22 * eb.z));
+    const float cst = __builtin_fmaf(eb.x, T.w[0], __builtin_fmaf(eb.y, T.w[1], eb.z * T.w[2]));
+    T.y = inl ? fminf(cst, cmax) : 0.0f;
+    // B = [mu]x Omega: row0 = -mu_z O_1 + mu_y O_2, row1 = mu_z O_0 - mu_x O_2, row2 = -mu_y O_0 + mu_x O_1
+    T.B[0] = __builtin_fmaf(-mu.z, o01, mu.y * o02);
+    T.B[1] = __builtin_fmaf(-mu.z, o11, mu.y * o12);
+    T.B[2] = __builtin_fmaf(-mu.z, o12, mu.y * o22);
+    T.B[3] = __builtin_fmaf(mu.z, o00, -mu.x * o02);
+    T.B[4] = __builtin_fmaf(mu.z, o01, -mu.x * o12);
+    T.B[5] = __builtin_fmaf(mu.z, o02, -mu.x * o22);
+    T.B[6] = __builtin_fmaf(-mu.y, o00, mu.x * o01);
+    T.B[7] = __builtin_fmaf(-mu.y, o01, mu.x * o11);
+    T.B[8] = __builtin_fmaf(-mu.y, o02, mu.x * o12);
+    return T;
+}
+
+template <bool KAHAN>
+__device__ __forceinline__ void accumulate(Acc& S, const mpdet::mat3& Rm, const float a, const float dmax2,
+                                           const float cmax, const float4 r0, const float4 r1, const float4 r2,
+                                           const float3 p, const bool hit, const float4 gm, const float4 gn) {
+    const LikTerms T = lik_terms(Rm, a, dmax2, cmax, r0, r1, r2, p, hit, gm, gn);
+    const float3 mu = T.mu;
+    const float m = T.m, w0 = T.w[0], w1 = T.w[1], w2 = T.w[2];
+    add_cost<KAHAN>(S, T.y);
+    S.nin += m != 0.0f ? 1 : 0;
     S.oe0 = __builtin_fmaf(m, w0, S.oe0);
     S.oe1 = __builtin_fmaf(m, w1, S.oe1);
     S.oe2 = __builtin_fmaf(m, w2, S.oe2);
     S.bw0 = __builtin_fmaf(w1, mu.z, __builtin_fmaf(-w2, mu.y, S.bw0));
     S.bw1 = __builtin_fmaf(w2, mu.x, __builtin_fmaf(-w0, mu.z, S.bw1));
     S.bw2 = __builtin_fmaf(w0, mu.y, __builtin_fmaf(-w1, mu.x, S.bw2));
-    // B = [mu]x Omega: row0 = -mu_z O_1 + mu_y O_2, row1 = mu_z O_0 - mu_x O_2, row2 = -mu_y O_0 + mu_x O_1
-    const float B00 = __builtin_fmaf(-mu.z, o01, mu.y * o02);
-    const float B01 = __builtin_fmaf(-mu.z, o11, mu.y * o12);
-    const float B02 = __builtin_fmaf(-mu.z, o12, mu.y * o22);
-    const float B10 = __builtin_fmaf(mu.z, o00, -mu.x * o02);
-    const float B11 = __builtin_fmaf(mu.z, o01, -mu.x * o12);
-    const float B12 = __builtin_fmaf(mu.z, o02, -mu.x * o22);
-    const float B20 = __builtin_fmaf(-mu.y, o00, mu.x * o01);
-    const float B21 = __builtin_fmaf(-mu.y, o01, mu.x * o11);
-    const float B22 = __builtin_fmaf(-mu.y, o02, mu.x * o12);
     // H_ww = -B [mu]x
-    S.h[0] = __builtin_fmaf(-B01, mu.z, __builtin_fmaf(B02, mu.y, S.h[0]));
-    S.h[1] = __builtin_fmaf(-B02, mu.x, __builtin_fmaf(B00, mu.z, S.h[1]));
-    S.h[2] = __builtin_fmaf(-B00, mu.y, __builtin_fmaf(B01, mu.x, S.h[2]));
-    S.h[6] = __builtin_fmaf(-B12, mu.x, __builtin_fmaf(B10, mu.z, S.h[6]));
-    S.h[7] = __builtin_fmaf(-B10, mu.y, __builtin_fmaf(B11, mu.x, S.h[7]));
-    S.h[11] = __builtin_fmaf(-B20, mu.y, __builtin_fmaf(B21, mu.x, S.h[11]));
+    S.h[0] = __builtin_fmaf(-T.B[1], mu.z, __builtin_fmaf(T.B[2], mu.y, S.h[0]));
+    S.h[1] = __builtin_fmaf(-T.B[2], mu.x, __builtin_fmaf(T.B[0], mu.z, S.h[1]));
+    S.h[2] = __builtin_fmaf(-T.B[0], mu.y, __builtin_fmaf(T.B[1], mu.x, S.h[2]));
+    S.h[6] = __builtin_fmaf(-T.B[5], mu.x, __builtin_fmaf(T.B[3], mu.z, S.h[6]));
+    S.h[7] = __builtin_fmaf(-T.B[3], mu.y, __builtin_fmaf(T.B[4], mu.x, S.h[7]));
+    S.h[11] = __builtin_fmaf(-T.B[6], mu.y, __builtin_fmaf(T.B[7], mu.x, S.h[11]));
     // H_wv = B (zero for outliers: mu was replaced by 0)
-    S.h[3] += B00; S.h[4] += B01; S.h[5] += B02;
-    S.h[8] += B10; S.h[9] += B11; S.h[10] += B12;
-    S.h[12] += B20; S.h[13] += B21; S.h[14] += B22;
+    S.h[3] += T.B[0]; S.h[4] += T.B[1]; S.h[5] += T.B[2];
+    S.h[8] += T.B[3]; S.h[9] += T.B[4]; S.h[10] += T.B[5];
+    S.h[12] += T.B[6]; S.h[13] += T.B[7]; S.h[14] += T.B[8];
     // H_vv = Omega (inliers)
-    S.h[15] = __builtin_fmaf(m, o00, S.h[15]); S.h[16] = __builtin_fmaf(m, o01, S.h[16]);
-    S.h[17] = __builtin_fmaf(m, o02, S.h[17]); S.h[18] = __builtin_fmaf(m, o11, S.h[18]);
-    S.h[19] = __builtin_fmaf(m, o12, S.h[19]); S.h[20] = __builtin_fmaf(m, o22, S.h[20]);
+#pragma unroll
+    for (int q = 0; q < 6; ++q) S.h[15 + q] = __builtin_fmaf(m, T.o[q], S.h[15 + q]);
 }
 
 // P = (Sigma^S + I)^-1 of a raw scan record r0 = (mu, S00), r1 = (S01, S02,
@@ -356,6 +378,129 @@ __global__ __launch_bounds__(kLanes) void k_lik(LikArgs A) {
     out[26 * st] = -S.oe2;
     out[27 * st] = S.cost - S.comp;
     out[28 * st] = (float)(k1 - k0 - S.nin);   // outliers of this chunk
+}
+
+// The PARTICLE layout's sums with a lane per (particle, point), for passes too
+// small to fill the chip with a lane per particle.  A workgroup takes P
+// particles against one chunk, 256 / P points at a time: its threads form the
+// terms of a point each, then one wave adds the cross products with mu, one or
+// two the plain sums and one the cost and the inliers, all in point order and
+// with the multiply-adds of a lane per particle: the sums are the same bit for
+// bit.
+//
+// What bounds it: small passes, two rounds of a gather and of up to 64 points
+// added one after another (256 x 300 69 -> 10.3 us, of which 3 are the launch);
+// larger ones, the vector units (8000 x 500 117 -> 48 us, 12 ns per evaluation
+// of a CU).
+constexpr int kFewThreads = 256;
+constexpr int kFewRows = 7;   // rows of a point: -Omega e | m, B0 | 1, B1 | 1, B2 | 1, Omega[0..2] | m, Omega[3..5] | m, mu | cost
+
+template <int BACKEND, int P>
+__global__ __launch_bounds__(kFewThreads) void k_lik_few(LikArgs A) {
+    constexpr int Q = kFewThreads / P;
+    __shared__ float4 rows[P][Q * kFewRows + 1];
+    mp_write_stamp(A.stamp);
+    const int chunk = blockIdx.x / A.nbx, pblk = blockIdx.x - chunk * A.nbx;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int g1 = threadIdx.x / Q, q = threadIdx.x % Q;
+    const auto particle = [&](int g) {
+        const int s = pblk * P + g;
+        const int i = g < P && s < A.n ? (A.order ? A.order[s] : s) : -1;
+        return i < A.n ? i : -1;
+    };
+    const int i1 = max(particle(g1), 0);
+    const float4 q4 = A.poses[2 * i1];
+    const float4 t4 = A.poses[2 * i1 + 1];
+    // what this thread adds: row r2 of particle g2
+    const int a2 = wave == 3 ? lane + 64 : lane;
+    const int g2 = wave == 0 ? lane >> 2 : (wave == 2 ? lane : a2 >> 3);
+    const int r2 = wave == 0 ? lane & 3 : (wave == 2 ? kFewRows - 1 : a2 & 7);
+    const int i2 = particle(g2);
+    const bool adds = g2 < P && r2 < kFewRows - (wave == 2 ? 0 : 1);
+    const mpdet::mat3 Rm = mpdet::qmat(mpdet::quat{q4.x, q4.y, q4.z, q4.w});
+    const float3 t = make_float3(t4.x, t4.y, t4.z);
+    float s0 = 0.0f, s1 = 0.0f, s2 = 0.0f;
+    const int k0 = chunk * A.chunk_len;
+    const int k1 = min(A.ns, k0 + A.chunk_len);
+    for (int kb = k0; kb < k1; kb += Q) {
+        if (kb != k0) __syncthreads();
+        if (kb + q < k1) {
+            float4 r0 = A.scan[(size_t)(kb + q) * 3], r1 = A.scan[(size_t)(kb + q) * 3 + 1];
+            float4 r2 = A.scan[(size_t)(kb + q) * 3 + 2];
+            const float3 p = mpdet::xform(Rm.m, t, make_float3(r0.x, r0.y, r0.z));
+            const int32_t c = lik_cell<BACKEND>(A.map, p);
+            float4 gm, gn;
+            lik_record<BACKEND>(A.map, c, gm, gn);
+            stage_inverse(r0, r1, r2);
+            const LikTerms T = lik_terms(Rm, A.map.gicp_a, A.dmax2, A.cmax, r0, r1, r2, p, lik_hit<BACKEND>(c), gm, gn);
+            float4* o = rows[g1] + q * kFewRows;
+            o[0] = make_float4(-T.w[0], -T.w[1], -T.w[2], T.m);
+            o[1] = make_float4(T.B[0], T.B[1], T.B[2], 1.0f);
+            o[2] = make_float4(T.B[3], T.B[4], T.B[5], 1.0f);
+            o[3] = make_float4(T.B[6], T.B[7], T.B[8], 1.0f);
+            o[4] = make_float4(T.o[0], T.o[1], T.o[2], T.m);
+            o[5] = make_float4(T.o[3], T.o[4], T.o[5], T.m);
+            o[6] = make_float4(T.mu.x, T.mu.y, T.mu.z, T.y);
+        }
+        __syncthreads();
+        if (adds) {
+            const float4* v = rows[g2];
+            const int np = min(Q, k1 - kb);
+            if (wave == 0) {   // - row x mu
+#pragma unroll 4
+                for (int k = 0; k < np; ++k, v += kFewRows) {
+                    const float4 r = v[r2], mu = v[kFewRows - 1];
+                    s0 = __builtin_fmaf(-r.y, mu.z, __builtin_fmaf(r.z, mu.y, s0));
+                    s1 = __builtin_fmaf(-r.z, mu.x, __builtin_fmaf(r.x, mu.z, s1));
+                    s2 = __builtin_fmaf(-r.x, mu.y, __builtin_fmaf(r.y, mu.x, s2));
+                }
+            } else if (wave == 2) {   // cost (compensated: s1) and inliers
+#pragma unroll 4
+                for (int k = 0; k < np; ++k, v += kFewRows) {
+                    const float yy = v[kFewRows - 1].w - s1;
+                    const float tt = s0 + yy;
+                    s1 = (tt - s0) - yy;
+                    s0 = tt;
+                    s2 += v[0].w;
+                }
+            } else {
+#pragma unroll 4
+                for (int k = 0; k < np; ++k, v += kFewRows) {
+                    const float4 r = v[r2];
+                    s0 = __builtin_fmaf(r.w, r.x, s0);
+                    s1 = __builtin_fmaf(r.w, r.y, s1);
+                    s2 = __builtin_fmaf(r.w, r.z, s2);
+                }
+            }
+        }
+    }
+    if (!adds || i2 < 0) return;
+    float* o = A.partial + (size_t)chunk * kNumPartial * A.n + i2;
+    const size_t n = (size_t)A.n;
+    if (wave == 0) {   // the rows' columns from the diagonal on
+        if (r2 == 0) {
+            o[21 * n] = s0;
+            o[22 * n] = s1;
+            o[23 * n] = s2;
+        } else if (r2 == 1) {
+            o[0] = s0;
+            o[n] = s1;
+            o[2 * n] = s2;
+        } else if (r2 == 2) {
+            o[6 * n] = s1;
+            o[7 * n] = s2;
+        } else {
+            o[11 * n] = s2;
+        }
+    } else if (wave == 2) {
+        o[27 * n] = s0 - s1;
+        o[28 * n] = (float)(k1 - k0) - s2;
+    } else {
+        const int to = r2 == 0 ? 24 : (r2 == 3 ? 12 : (r2 < 3 ? 5 * r2 - 2 : 3 * r2 + 3));   // 24, 3, 8, 12, 15, 18
+        o[to * n] = s0;
+        o[(to + 1) * n] = s1;
+        o[(to + 2) * n] = s2;
+    }
 }
 
 // Grouped layout: 16 lanes per particle.  A workgroup (8 waves) keeps a
@@ -666,8 +811,8 @@ static void lik_prepare_order(mp_filter f, int scorer, hipStream_t s) {
 // workgroups gives each fewer particles (no sum depends on it; the price is
 // staging a chunk for fewer particles).  With 256 particles in every
 // workgroup, 4096 particles x 1024 points ran on 16 of the 256 CUs: 266 us a
-// launch, 39 us with 32; 16,384 x 2048 312 -> 125 us, 65,536 x 4096 944 -> 874
-// us (512 of its 1024 workgroups in flight, the last ones alone).
+// launch, 39 us with 32; 16,384 x 2048 312 -> 122 us, 65,536 x 4096 944 -> 845
+// us (of its 1024 workgroups the last ran alone).
 constexpr int kSplitGroups = 4096;
 
 static int lik_rounds(int n, int nch) {
@@ -771,6 +916,29 @@ void lik_solve(mp_filter f, bool grouped, int nch, const int32_t* order, hipStre
 }
 }  // namespace
 
+// Lanes of k_lik (particles times chunks) up to which the PARTICLE layout takes
+// a lane per evaluation instead, unless the caller chose a gather batch: below
+// three waves a CU, k_lik waits for one point after another.  With chunks of 250
+// points, 16,000 lanes 117 -> 48 us, 40,000 127 -> 107 us.  Chunks of fewer than
+// 16 points leave a round part empty (40,000 particles, 16 points 20 -> 17 us,
+// 8 points 16 -> 17 us).
+constexpr int64_t kFewLanes = 40960;
+constexpr int kFewMinLen = 16;
+// Workgroups of 4 particles (64 points a round) until 3 a CU are there, then of
+// 8, then of 16: 256 x 300 10.3 us with 4 and 16.4 with 16, 2000 x 1000 30 us
+// with 8 and 45 with 4, 8000 x 500 48 us with 16 and 60 with 8.
+constexpr int kFewGroups = 768;
+
+template <int BACKEND>
+void launch_lik_few(LikArgs A, int nch, hipStream_t s) {
+    const auto groups = [&](int p) { return (A.n + p - 1) / p * nch; };
+    const int p = groups(4) <= kFewGroups ? 4 : (groups(8) <= kFewGroups ? 8 : 16);
+    A.nbx = (A.n + p - 1) / p;
+    if (p == 4) k_lik_few<BACKEND, 4><<<groups(4), kFewThreads, 0, s>>>(A);
+    else if (p == 8) k_lik_few<BACKEND, 8><<<groups(8), kFewThreads, 0, s>>>(A);
+    else k_lik_few<BACKEND, 16><<<groups(16), kFewThreads, 0, s>>>(A);
+}
+
 void mp_launch_likelihood(mp_filter f, hipStream_t s) {
     LikPlan P = lik_plan(f);
     lik_prepare_order(f, P.scorer, s);
@@ -810,6 +978,10 @@ void mp_launch_likelihood(mp_filter f, hipStream_t s) {
             k_lik<MP_NNF_DENSE, 4, MP_SCORER_SCOREFIELD><<<nbx * nch, kLanes, 0, s>>>(A);
         else
             k_lik<MP_NNF_HASH, 4, MP_SCORER_SCOREFIELD><<<nbx * nch, kLanes, 0, s>>>(A);
+        MP_CHECK_LAUNCH();
+    } else if (ns > 0 && f->p.lik_batch == 0 && (int64_t)n * nch <= kFewLanes && A.chunk_len >= kFewMinLen) {
+        if (A.map.backend == MP_NNF_DENSE) launch_lik_few<MP_NNF_DENSE>(A, nch, s);
+        else launch_lik_few<MP_NNF_HASH>(A, nch, s);
         MP_CHECK_LAUNCH();
     } else if (ns > 0) {
         if (A.map.backend == MP_NNF_DENSE) launch_lik_batch<MP_NNF_DENSE>(f->p.lik_batch, nbx * nch, s, A);

@@ -172,3 +172,26 @@ def test_query_outputs_and_their_places(room, n):
     got = np.zeros((n, 7), np.float32)
     assert M.lib().mp_posterior_query(f.handle, C.byref(out), M._ptr(got), None, M._stream(None)) == M.MP_E_NUMERIC
     assert np.array_equal(got, bad[:, :7], equal_nan=True)
+
+
+@pytest.mark.parametrize("backend", [M.MP_NNF_DENSE, M.MP_NNF_HASH])
+@pytest.mark.parametrize("n,ns", [(1, 1), (7, 31), (8, 32), (9, 33), (300, 256), (257, 257), (100, 1100), (2000, 40), (2500, 400),
+                                  (20000, 500), (5, 15)])
+def test_lane_per_evaluation_sums(room, n, ns, backend):
+    # lik_batch = 0 takes a lane per evaluation in small PARTICLE passes, 4 a
+    # lane per particle: the same sums
+    m = M.Map(room["w"]["map_xyz"], voxel=0.5, backend=backend)
+    R, t = room["w"]["traj"][0]
+    poses = S.gaussian_particles(n, S.pose8(R, t), 0.1, 0.3, 3)
+    got = []
+    for batch in (0, 4):
+        p = M.mp_filter_default_params(n_particles=n, k=8, lsh_bits=16, svgd_iters=1, d_max=1.0, lik_batch=batch,
+                                       lik_layout=M.MP_LIK_LAYOUT_PARTICLE)
+        f = M.Filter(m, p, poses=poses)
+        f.scan_upload(room["w"]["scans"][0][:ns])
+        f.debug_set("capture_hb", 1)
+        f.debug_stage(M.MP_STAGE_LIK)
+        got.append((f.debug_get("hb"), f.debug_get("psi")))
+        f.close()
+    assert np.array_equal(got[0][0], got[1][0]) and np.array_equal(got[0][1], got[1][1])
+    assert got[0][1][:, 7].max() > 0
