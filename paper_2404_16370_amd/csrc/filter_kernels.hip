@@ -315,7 +315,11 @@ __global__ __launch_bounds__(256) void k_init_uniform(InitArgs A) {
 }
 
 // ------------------------------------------------------------ posterior
-// Deterministic two-level reductions: per-block partials, then one block.
+// Deterministic two-level reductions: per-block partials, then one block.  What
+// bounds it is the launches, 3 to 5 us each: up to kRB partials are reduced by
+// every block of the next kernel (one load a thread), the last round leaves the
+// partials of its sums, and small filters take k_post_small.  Ten rounds, 65,536
+// particles x 16 99 -> 73 us, 20,011 x 16 90 -> 62 us, 4097 x 8 71 -> 49 us.
 constexpr int kRB = 256;
 
 __device__ inline double block_max(double v) {
@@ -405,7 +409,8 @@ __global__ __launch_bounds__(kRB) void k_post_logits(PostArgs A) {
     }
 }
 
-__global__ __launch_bounds__(kRB) void k_post_max_final(PostArgs A) {
+// the partials' results, from every block of a launch (block 0 keeps them)
+__device__ inline double post_max(const PostArgs& A) {
     double m = -INFINITY, mll = -INFINITY;
     for (int b = threadIdx.x; b < A.nb; b += kRB) {
         m = fmax(m, A.part[b]);
@@ -413,73 +418,26 @@ __global__ __launch_bounds__(kRB) void k_post_max_final(PostArgs A) {
     }
     m = block_max(m);
     mll = block_max(mll);
-    if (threadIdx.x == 0) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
         A.info[0] = m;
         A.info[6] = mll;
     }
+    return m;
 }
 
-__global__ __launch_bounds__(kRB) void k_post_expsum(PostArgs A) {
-    const int i = blockIdx.x * kRB + threadIdx.x;
-    const double m = A.info[0];
-    const double e = (i < A.n) ? exp(A.l[i] - m) : 0.0;
-    const double s = block_sum(e);
-    if (threadIdx.x == 0) A.part[blockIdx.x] = s;
-}
-
-__global__ __launch_bounds__(kRB) void k_post_sum_final(PostArgs A) {
+__device__ inline double post_sum(const PostArgs& A) {
     double s = 0.0;
-    for (int b = threadIdx.x; b < A.nb; b += kRB) s += A.part[b];
+    for (int b = threadIdx.x; b < A.nb; b += kRB) s += A.part[2 * A.nb + b];
     s = block_sum(s);
-    if (threadIdx.x == 0) {
+    const double ev = A.info[0] + log(s);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
         A.info[1] = s;
-        A.info[2] = A.info[0] + log(s);
+        A.info[2] = ev;
     }
+    return ev;
 }
 
-__global__ __launch_bounds__(kRB) void k_post_normalise(PostArgs A) {
-    const int i = blockIdx.x * kRB + threadIdx.x;
-    if (i >= A.n) return;
-    A.p0[i] = (float)exp(A.l[i] - A.info[2]);
-}
-
-// one Jacobi round of Eq. 11: p'_i = sum_j k_ij p_j / sum_j k_ij
-__global__ __launch_bounds__(kRB) void k_post_round(const float* __restrict__ pin, float* __restrict__ pout,
-                                                    const int32_t* __restrict__ nbr, const float* __restrict__ kval,
-                                                    int n, int K) {
-    const int i = blockIdx.x * kRB + threadIdx.x;
-    if (i >= n) return;
-    float num = 0.0f, den = 0.0f;
-    for (int a = 0; a < K; ++a) {
-        const int j = nbr[(size_t)a * n + i];
-        if (j < 0 || j >= n) continue;
-        const float k = kval[(size_t)a * n + i];
-        num += k * pin[j];
-        den += k;
-    }
-    pout[i] = den > 0.0f ? num / den : pin[i];
-}
-
-__global__ __launch_bounds__(kRB) void k_post_z(PostArgs A, const float* __restrict__ p) {
-    const int i = blockIdx.x * kRB + threadIdx.x;
-    double v = -INFINITY;
-    int idx = 0x7FFFFFFF;
-    double s = 0.0;
-    if (i < A.n) {
-        v = (double)p[i];
-        idx = i;
-        s = v;
-    }
-    s = block_sum(s);
-    block_argmax(v, idx);
-    if (threadIdx.x == 0) {
-        A.part[blockIdx.x] = s;
-        A.part[A.nb + blockIdx.x] = v;
-        A.ipart[blockIdx.x] = idx;
-    }
-}
-
-__global__ __launch_bounds__(kRB) void k_post_z_final(PostArgs A) {
+__device__ inline double post_z(const PostArgs& A) {
     double s = 0.0, v = -INFINITY;
     int idx = 0x7FFFFFFF;
     for (int b = threadIdx.x; b < A.nb; b += kRB) {
@@ -493,18 +451,106 @@ __global__ __launch_bounds__(kRB) void k_post_z_final(PostArgs A) {
     }
     s = block_sum(s);
     block_argmax(v, idx);
-    if (threadIdx.x == 0) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
         A.info[3] = s;
         A.info[4] = v / s;
         A.info[7] = (double)idx;
     }
+    return s;
 }
 
+__global__ __launch_bounds__(kRB) void k_post_max_final(PostArgs A) { post_max(A); }
+__global__ __launch_bounds__(kRB) void k_post_sum_final(PostArgs A) { post_sum(A); }
+__global__ __launch_bounds__(kRB) void k_post_z_final(PostArgs A) { post_z(A); }
+
+// WIDE: more partials than one block reads at once; a launch of its own reduced them
+template <bool WIDE>
+__global__ __launch_bounds__(kRB) void k_post_expsum(PostArgs A) {
+    const int i = blockIdx.x * kRB + threadIdx.x;
+    const double m = WIDE ? A.info[0] : post_max(A);
+    const double e = (i < A.n) ? exp(A.l[i] - m) : 0.0;
+    const double s = block_sum(e);
+    if (threadIdx.x == 0) A.part[2 * A.nb + blockIdx.x] = s;   // the maxima are still being read
+}
+
+template <bool WIDE>
+__global__ __launch_bounds__(kRB) void k_post_normalise(PostArgs A) {
+    const int i = blockIdx.x * kRB + threadIdx.x;
+    const double ev = WIDE ? A.info[2] : post_sum(A);
+    if (i >= A.n) return;
+    A.p0[i] = (float)exp(A.l[i] - ev);
+}
+
+// one Jacobi round of Eq. 11: p'_i = sum_j k_ij p_j / sum_j k_ij.  Eight
+// neighbours' loads are in flight before the first is added.
+__device__ inline float post_average(const PostArgs& A, const float* __restrict__ pin, int i) {
+    constexpr int kU = 8;
+    const size_t n = (size_t)A.n;
+    float num = 0.0f, den = 0.0f;
+    const float own = pin[i];
+    for (int a0 = 0; a0 < A.K; a0 += kU) {
+        int32_t j[kU];
+        float k[kU], p[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            const size_t at = (size_t)min(a0 + u, A.K - 1) * n + i;
+            j[u] = A.nbr[at];
+            k[u] = A.kval[at];
+        }
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            if (a0 + u >= A.K || j[u] >= A.n) j[u] = -1;
+            p[u] = pin[max(j[u], 0)];
+        }
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            num = j[u] >= 0 ? num + k[u] * p[u] : num;
+            den = j[u] >= 0 ? den + k[u] : den;
+        }
+    }
+    return den > 0.0f ? num / den : own;
+}
+
+// sum and largest of the weights: this block's partials
+__device__ inline void post_z_part(const PostArgs& A, float p, int i) {
+    double v = -INFINITY;
+    int idx = 0x7FFFFFFF;
+    double s = 0.0;
+    if (i < A.n) {
+        v = (double)p;
+        idx = i;
+        s = v;
+    }
+    s = block_sum(s);
+    block_argmax(v, idx);
+    if (threadIdx.x == 0) {
+        A.part[blockIdx.x] = s;
+        A.part[A.nb + blockIdx.x] = v;
+        A.ipart[blockIdx.x] = idx;
+    }
+}
+
+template <bool LAST>
+__global__ __launch_bounds__(kRB) void k_post_round(PostArgs A, const float* __restrict__ pin,
+                                                    float* __restrict__ pout) {
+    const int i = blockIdx.x * kRB + threadIdx.x;
+    float p = 0.0f;
+    if (i < A.n) pout[i] = p = post_average(A, pin, i);
+    if (LAST) post_z_part(A, p, i);
+}
+
+__global__ __launch_bounds__(kRB) void k_post_z(PostArgs A, const float* __restrict__ p) {   // without a round
+    const int i = blockIdx.x * kRB + threadIdx.x;
+    post_z_part(A, i < A.n ? p[i] : 0.0f, i);
+}
+
+template <bool WIDE>
 __global__ __launch_bounds__(kRB) void k_post_store(PostArgs A, const float* __restrict__ p) {
     const int i = blockIdx.x * kRB + threadIdx.x;
+    const double z = WIDE ? A.info[3] : post_z(A);
     double q = 0.0;
     if (i < A.n) {
-        q = (double)p[i] / A.info[3];
+        q = (double)p[i] / z;
         A.prior_out[i] = (float)q;
     }
     const double s = block_sum(q * q);
@@ -516,6 +562,192 @@ __global__ __launch_bounds__(kRB) void k_post_neff_final(PostArgs A) {
     for (int b = threadIdx.x; b < A.nb; b += kRB) s += A.part[2 * A.nb + b];
     s = block_sum(s);
     if (threadIdx.x == 0) A.info[5] = 1.0 / s;
+    mp_write_stamp(A.stamp_end);
+}
+
+// The whole posterior in one workgroup, for filters whose lists fit its
+// registers: 1024 threads, particle r * 1024 + thread its r-th, kPostSlots /
+// R list slots each.  Wave w reduces particles [256 w, 256 (w + 1)) and the
+// results are reduced as above, in the same trees, so it gives the same bits.
+// What bounds it: one CU's LDS gathers and FP64 exp and log.  Ten rounds, 256
+// particles x 8 54 -> 19 us, 1000 x 16 80 -> 23 us, 4096 x 8 71 -> 37 us (49 in
+// the launches above).  Lists kept in more registers would spill.
+constexpr int kPT = 1024;
+constexpr int kPostSlots = 32;
+
+// wave w's tree over its 256 values of v (4 a lane) as block_sum adds them
+__device__ inline double wave_sum(const double* v, int lane) {
+    double x = (v[lane] + v[lane + 128]) + (v[lane + 64] + v[lane + 192]);
+    for (int s = 32; s > 0; s >>= 1) x = x + __shfl_down(x, s);
+    return __shfl(x, 0);
+}
+
+// sum over the blocks' partials
+__device__ inline double parts_sum(const double* part, int nb, int lane) {
+    double x = lane < nb ? part[lane] : 0.0;
+    for (int s = kPT / kRB / 2 * 4; s > 0; s >>= 1) x = x + __shfl_down(x, s);
+    return __shfl(x, 0);
+}
+
+__device__ inline void pick(double& v, int& idx, double b, int ib) {
+    if (b > v || (b == v && ib < idx)) {
+        v = b;
+        idx = ib;
+    }
+}
+
+template <int R>
+__global__ __launch_bounds__(kPT) void k_post_small(PostArgs A, int rounds) {
+    constexpr int N = R * kPT, KC = kPostSlots / R, W = kPT / 64;
+    __shared__ double sh[N];
+    __shared__ float pb[2][N + 1];   // and a zero
+    __shared__ double part[3][W];
+    __shared__ int ipart[W];
+    mp_write_stamp(A.stamp);
+    if (threadIdx.x < 2) pb[threadIdx.x][N] = 0.0f;
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int n = A.n;
+    int32_t j[R][KC];
+    float kv[R][KC];
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int a = 0; a < KC; ++a) {
+            const int i = r * kPT + tid;
+            const bool in = a < A.K && i < n;
+            const size_t at = in ? (size_t)a * n + i : 0;
+            const int32_t x = A.nbr[at];
+            const float k = A.kval[at];
+            const bool valid = in && x >= 0 && x < n;
+            kv[r][a] = valid ? k : 0.0f;   // an empty slot adds 0 * 0
+            j[r][a] = valid ? x : N;
+        }
+    // logits and their maximum
+    double m = -INFINITY, mll = -INFINITY;
+#pragma unroll 1
+    for (int i = tid; i < n; i += kPT) {
+        const double pr = fmax((double)A.prior[i], A.floor_p);
+        const double ll = (double)A.psi[2 * i + 1].z;
+        const double l = log(pr) + ll * A.inv_tau;
+        sh[i] = l;
+        m = fmax(m, l);
+        mll = fmax(mll, ll);
+    }
+    for (int s = 32; s > 0; s >>= 1) {
+        m = fmax(m, __shfl_xor(m, s));
+        mll = fmax(mll, __shfl_xor(mll, s));
+    }
+    if (lane == 0) {
+        part[0][wave] = m;
+        part[1][wave] = mll;
+    }
+    __syncthreads();
+    m = lane < W ? part[0][lane] : -INFINITY;
+    mll = lane < W ? part[1][lane] : -INFINITY;
+    for (int s = 32; s > 0; s >>= 1) {
+        m = fmax(m, __shfl_xor(m, s));
+        mll = fmax(mll, __shfl_xor(mll, s));
+    }
+    // evidence
+    double l[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) l[r] = sh[r * kPT + tid];   // own values: of no thread beyond n
+    for (int r = 0; r < R; ++r) {
+        const int i = r * kPT + tid;
+        sh[i] = i < n ? exp(sh[i] - m) : 0.0;
+    }
+    __syncthreads();
+    if (wave < A.nb) {
+        const double s = wave_sum(sh + wave * kRB, lane);
+        if (lane == 0) part[2][wave] = s;
+    }
+    __syncthreads();
+    const double sum = parts_sum(part[2], A.nb, lane);
+    const double ev = m + log(sum);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int i = r * kPT + tid;
+        pb[0][i] = i < n ? (float)exp(l[r] - ev) : 0.0f;
+        pb[1][i] = 0.0f;
+    }
+    // rounds
+    int cur = 0;
+    for (int it = 0; it < rounds; ++it, cur ^= 1) {
+        __syncthreads();
+        const float* pin = pb[cur];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int i = r * kPT + tid;
+            float num = 0.0f, den = 0.0f;
+#pragma unroll
+            for (int a = 0; a < KC; ++a) {
+                if (a < A.K) {
+                    num = num + kv[r][a] * pin[j[r][a]];
+                    den = den + kv[r][a];
+                }
+            }
+            pb[cur ^ 1][i] = den > 0.0f ? num / den : pin[i];
+        }
+    }
+    // sum and largest weight
+    __syncthreads();
+    const float* pf = pb[cur];
+    if (wave < A.nb) {
+        const int at = wave * kRB + lane;
+        double x[4];
+        for (int q = 0; q < 4; ++q) x[q] = at + 64 * q < n ? (double)pf[at + 64 * q] : 0.0;
+        double s = (x[0] + x[2]) + (x[1] + x[3]);
+        for (int q = 0; q < 4; ++q) x[q] = at + 64 * q < n ? x[q] : -INFINITY;
+        int idx = at < n ? at : 0x7FFFFFFF, idx1 = at + 64 < n ? at + 64 : 0x7FFFFFFF;
+        double v = x[0], v1 = x[1];
+        pick(v, idx, x[2], at + 128 < n ? at + 128 : 0x7FFFFFFF);
+        pick(v1, idx1, x[3], at + 192 < n ? at + 192 : 0x7FFFFFFF);
+        pick(v, idx, v1, idx1);
+        for (int d = 32; d > 0; d >>= 1) {
+            s = s + __shfl_down(s, d);
+            pick(v, idx, __shfl_down(v, d), __shfl_down(idx, d));
+        }
+        if (lane == 0) {
+            part[0][wave] = s;
+            part[1][wave] = v;
+            ipart[wave] = idx;
+        }
+    }
+    __syncthreads();
+    const double z = parts_sum(part[0], A.nb, lane);
+    double v = -INFINITY;
+    int idx = 0x7FFFFFFF;
+    if (lane < A.nb) pick(v, idx, part[1][lane], ipart[lane]);
+    for (int d = 32; d > 0; d >>= 1) pick(v, idx, __shfl_down(v, d), __shfl_down(idx, d));
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int i = r * kPT + tid;
+        double q = 0.0;
+        if (i < n) {
+            q = (double)pf[i] / z;
+            A.prior_out[i] = (float)q;
+            A.p0[i] = pb[0][i];
+            A.p1[i] = pb[1][i];
+        }
+        sh[i] = q * q;
+    }
+    __syncthreads();
+    if (wave < A.nb) {
+        const double s = wave_sum(sh + wave * kRB, lane);
+        if (lane == 0) part[2][wave] = s;
+    }
+    __syncthreads();
+    const double q2 = parts_sum(part[2], A.nb, lane);
+    if (tid == 0) {
+        A.info[0] = m;
+        A.info[1] = sum;
+        A.info[2] = ev;
+        A.info[3] = z;
+        A.info[4] = v / z;
+        A.info[5] = 1.0 / q2;
+        A.info[6] = mll;
+        A.info[7] = (double)idx;
+    }
     mp_write_stamp(A.stamp_end);
 }
 
@@ -693,24 +925,44 @@ void mp_launch_posterior(mp_filter f, hipStream_t s, uint64_t* stamp_end) {
     A.floor_p = (double)f->p.prior_floor;
     A.stamp = mp_take_stamp(f);
     A.stamp_end = stamp_end;
-    k_post_logits<<<nb, kRB, 0, s>>>(A);
-    k_post_max_final<<<1, kRB, 0, s>>>(A);
-    k_post_expsum<<<nb, kRB, 0, s>>>(A);
-    k_post_sum_final<<<1, kRB, 0, s>>>(A);
-    k_post_normalise<<<nb, kRB, 0, s>>>(A);
-    MP_CHECK_LAUNCH();
-    float* a = A.p0;
-    float* b = A.p1;
-    for (int r = 0; r < f->p.post_iters; ++r) {
-        k_post_round<<<nb, kRB, 0, s>>>(a, b, A.nbr, A.kval, n, f->K);
-        float* t = a;
-        a = b;
-        b = t;
+    const int rounds = f->p.post_iters;
+    // one workgroup while a lane's list slots fit its registers
+    const int slots = f->K * ((n + kPT - 1) / kPT);
+    if (n <= kPT && slots <= kPostSlots) {
+        k_post_small<1><<<1, kPT, 0, s>>>(A, rounds);
+    } else if (n <= 2 * kPT && slots <= kPostSlots) {
+        k_post_small<2><<<1, kPT, 0, s>>>(A, rounds);
+    } else if (n <= 4 * kPT && 4 * f->K <= kPostSlots) {
+        k_post_small<4><<<1, kPT, 0, s>>>(A, rounds);
+    } else {
+        const bool wide = nb > kRB;
+        k_post_logits<<<nb, kRB, 0, s>>>(A);
+        if (wide) {
+            k_post_max_final<<<1, kRB, 0, s>>>(A);
+            k_post_expsum<true><<<nb, kRB, 0, s>>>(A);
+            k_post_sum_final<<<1, kRB, 0, s>>>(A);
+            k_post_normalise<true><<<nb, kRB, 0, s>>>(A);
+        } else {
+            k_post_expsum<false><<<nb, kRB, 0, s>>>(A);
+            k_post_normalise<false><<<nb, kRB, 0, s>>>(A);
+        }
+        float* a = A.p0;
+        float* b = A.p1;
+        for (int r = 0; r < rounds; ++r) {
+            if (r + 1 < rounds) k_post_round<false><<<nb, kRB, 0, s>>>(A, a, b);
+            else k_post_round<true><<<nb, kRB, 0, s>>>(A, a, b);
+            float* t = a;
+            a = b;
+            b = t;
+        }
+        if (rounds <= 0) k_post_z<<<nb, kRB, 0, s>>>(A, a);
+        if (wide) {
+            k_post_z_final<<<1, kRB, 0, s>>>(A);
+            k_post_store<true><<<nb, kRB, 0, s>>>(A, a);
+        } else {
+            k_post_store<false><<<nb, kRB, 0, s>>>(A, a);
+        }
+        k_post_neff_final<<<1, kRB, 0, s>>>(A);
     }
-    MP_CHECK_LAUNCH();
-    k_post_z<<<nb, kRB, 0, s>>>(A, a);
-    k_post_z_final<<<1, kRB, 0, s>>>(A);
-    k_post_store<<<nb, kRB, 0, s>>>(A, a);
-    k_post_neff_final<<<1, kRB, 0, s>>>(A);
     MP_CHECK_LAUNCH();
 }

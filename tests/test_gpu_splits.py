@@ -195,3 +195,26 @@ def test_lane_per_evaluation_sums(room, n, ns, backend):
         f.close()
     assert np.array_equal(got[0][0], got[1][0]) and np.array_equal(got[0][1], got[1][1])
     assert got[0][1][:, 7].max() > 0
+
+
+@pytest.mark.parametrize("n,k,rounds", [
+    (1, 1, 10), (3, 8, 3), (256, 8, 10), (257, 8, 9), (1000, 32, 10), (1025, 16, 10), (1025, 17, 10), (2049, 8, 10),
+    (4096, 8, 0), (4096, 8, 1), (4096, 9, 10), (4097, 8, 10), (65_536, 16, 2), (65_537, 9, 2), (70_000, 4, 0)])
+def test_posterior_over_its_kernels(room, O, n, k, rounds):
+    # one workgroup up to 4096 particles and 32 list slots a lane; beyond, the
+    # partials are reduced by every block up to 65,536 particles
+    R, t = room["w"]["traj"][0]
+    f = _filter(room, n, S.gaussian_particles(n, S.pose8(R, t), 0.03, 0.1, 3), k=k, window_c=k, post_iters=rounds)
+    f.scan_upload(room["w"]["scans"][0][:40])
+    f.step()
+    nbr, kv = f.debug_get("nbr").T, f.debug_get("kval").T.astype(np.float64)   # the oracle's are n x K
+    ref = O.posterior(np.full(n, 1.0 / n), f.debug_get("psi")[:, 6].astype(np.float64), nbr,
+                      np.where(nbr >= 0, kv, 0.0), rounds=rounds)
+    q = f.posterior_query(weights=True)
+    # the weights are held in 32 bits between the rounds: k products, k sums, a
+    # division and a rounding each, on both sides of the division
+    tol = ((2 * k + 4) * rounds + 3) * 2.0 ** -24
+    assert np.all(np.abs(q["weights"] - ref["post"]) <= tol * ref["post"] + 1e-38)
+    assert abs(q["n_eff"] - ref["n_eff"]) <= 3 * tol * ref["n_eff"]
+    assert abs(q["map_weight"] - ref["post"].max()) <= tol * ref["post"].max()
+    f.close()
