@@ -25,3 +25,10 @@ __device__ __forceinline__ float mp_box_d2(const float4* __restrict__ b, const f
     const float dz = fmaxf(fmaxf(lo.z - p.z, p.z - hi.z), 0.0f);
     return __builtin_fmaf(dx, dx, __builtin_fmaf(dy, dy, dz * dz));
 }
+
+// A box's order among the 16 of a row: its distance (rounded down by up to 15
+// units in the last place, so that it bounds the points in it as before) and
+// the lane; ~0 for none.
+__device__ __forceinline__ uint32_t mp_box_key(bool in, const float4* b, const float3 p, int lane) {
+    return in ? (__float_as_uint(mp_box_d2(b, p)) & ~15u) | (uint32_t)lane : ~0u;
+}

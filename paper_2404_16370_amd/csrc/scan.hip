@@ -127,15 +127,18 @@ __global__ __launch_bounds__(kIdxThreads) void k_scan_index(const float* __restr
 // k nearest other scan points of each point, 16 lanes per point.  The lanes
 // test the boxes of the index 16 at a time, first those of 1024 points, then
 // the 16 blocks of each that may hold a neighbour; of a block that passes,
-// every lane takes four points.  Lane l keeps its KC best (d2, j) that do not
-// exceed a bound on the group's k-th distance; the 16 sorted lists are then
-// merged by rounds of a (d2, j) minimum across the group.  Then the FP64
-// Gaussian of the point and its neighbours.
+// every lane takes four points.  The row's list is sorted across its lanes
+// (lane l keeps the l-th and, for k > 16, the (16 + l)-th smallest (d2, j)): a
+// candidate within the k-th distance is handed to all lanes, each of which
+// keeps its own entry, the candidate or the entry of the lane before.  Then the
+// FP64 Gaussian of the point and its neighbours, a lane per sum, and the
+// eigen-solves of the workgroup's 16 points side by side in one wave.
 //
-// What bounds it: latency of the list upkeep, the merge and the FP64
-// eigen-solve, a few thousand instructions a point at two to four waves per
-// SIMD.  8192 points take 66 us and 65,536 224 us; a search through all n
-// points, staged in LDS, took 290 us and 4.6 ms.
+// What bounds it: latency of the insertions and of the eigen-solve (some 30
+// dependent FP64 divisions and roots).  300 points take 21 us, 8192 32 us and
+// 65,536 110 us; with a list per lane, a merge, the boxes in index order and an
+// eigen-solve per wave of four points it took 30, 54 and 220 us, and a search
+// through all n points, staged in LDS, 290 us for 8192 and 4.6 ms for 65,536.
 constexpr int kQLanes = 16;
 static_assert(kScanFan == kQLanes, "one lane per block of a box of 1024 points");
 
@@ -147,28 +150,31 @@ __device__ __forceinline__ uint64_t knn_key(float d2, int32_t j) {
 
 // The loops that are not unrolled keep the code short: a launch over a few
 // hundred points spends its time fetching instructions for the first time.
-template <int KC>
+template <int H>   // list entries per lane
 __global__ __launch_bounds__(kB) void k_scan_knn_cov(const float* __restrict__ xyz, ScanIndex X, int n, int k,
                                                      float eps, float4* __restrict__ rec, float4* __restrict__ walk,
                                                      uint64_t* __restrict__ stamp_end) {
-    __shared__ float nbr[kB / kQLanes][KC][3];
+    constexpr int kPer = kB / kQLanes;
+    __shared__ float nbr[kPer][H * kQLanes][3];
+    __shared__ double cov[kPer][7];   // 6 and a pad
     const int grp = threadIdx.x / kQLanes, gl = threadIdx.x % kQLanes;
-    const int w = blockIdx.x * (kB / kQLanes) + grp;
+    const int w = blockIdx.x * kPer + grp;
     const bool active = w < n;   // uniform over the point's lanes
     const float4 p4 = X.pts[active ? w : 0];
     const float3 pi = make_float3(p4.x, p4.y, p4.z);
-    const int i = __float_as_int(p4.w);
     const int kk = min(k, n - 1);
-    uint64_t best[KC];
+    uint64_t best[H];
 #pragma unroll
-    for (int m = 0; m < KC; ++m) best[m] = knn_key(__builtin_inff(), 0x7FFFFFFF);
-    // lists needed per lane to bound the group's kk-th distance (kk <= KC)
+    for (int m = 0; m < H; ++m) best[m] = knn_key(__builtin_inff(), 0x7FFFFFFF);
+    // lists needed per lane for the seed below to bound the kk-th distance
     const int mb = kk > kQLanes ? 1 : 0;
     float bound = __builtin_inff();
     // Seed the bound from the (up to 64) points nearest to this one in walk
     // order: every lane measures up to four of them with the arithmetic of the
-    // search, and the largest of the lanes' best (second best for mb = 1)
-    // bounds the kk-th distance, as in the search below.
+    // search: 16 (mb + 1) >= kk of them lie at or below the largest of the lanes'
+    // best (second best for mb = 1), and so do the kk nearest.  Candidates (and
+    // boxes) above the bound are never needed.  (Without a seed 8192 points take
+    // 60 us: the first candidates all go through the list.)
     const int nseed = min(4, (n - 1) / kQLanes);
     if (nseed > mb) {
         const int start = max(0, min(w - kQLanes * nseed / 2, n - 1 - kQLanes * nseed));
@@ -182,20 +188,27 @@ __global__ __launch_bounds__(kB) void k_scan_knn_cov(const float* __restrict__ x
         }
         bound = mp_row_max(mb >= 1 ? s1 : s0);
     }
-    // the boxes, walked by the whole wave: a group without work idles along
-    for (int s0 = 0; s0 < X.supers; s0 += kQLanes) {
-        const int sup = s0 + gl;
-        uint32_t sm = mp_row_ballot(active && sup < X.supers &&
-                                    mp_box_d2(X.super + 2 * min(sup, X.supers - 1), pi) <= bound);
-        while (__any(sm != 0)) {
-            const int su = s0 + (sm ? __builtin_ctz(sm) : 0);
-            const int blk = su * kScanFan + gl;
-            uint32_t bm = mp_row_ballot(sm != 0 && blk < X.blocks &&
-                                        mp_box_d2(X.box + 2 * min(blk, X.blocks - 1), pi) <= bound);
-            sm &= sm - 1;
-            while (__any(bm != 0)) {
-                const int q0 = bm ? (su * kScanFan + __builtin_ctz(bm)) * kScanBlock + gl : n;
-                bm &= bm - 1;
+    // the boxes, nearest first and walked by the whole wave: a group without
+    // work idles along
+    const int batches = (X.supers + kQLanes - 1) / kQLanes;
+    int batch = w / (kIdxThreads * kQLanes);   // its own first
+    for (int t = 0; t < batches; ++t, batch = batch + 1 < batches ? batch + 1 : 0) {
+        const int sup = batch * kQLanes + gl;
+        uint32_t sk = mp_box_key(active && sup < X.supers, X.super + 2 * min(sup, X.supers - 1), pi, gl);
+        for (;;) {
+            const uint32_t su = mp_row_min_u32(sk);
+            const bool go = su != ~0u && __uint_as_float(su & ~15u) <= bound;
+            if (!__any(go)) break;
+            if ((su & 15u) == (uint32_t)gl) sk = ~0u;
+            const int blk0 = (batch * kQLanes + (int)(su & 15u)) * kScanFan;
+            const int blk = blk0 + gl;
+            uint32_t bk = mp_box_key(go && blk < X.blocks, X.box + 2 * min(blk, X.blocks - 1), pi, gl);
+            for (;;) {
+                const uint32_t bl = mp_row_min_u32(bk);
+                const bool gob = bl != ~0u && __uint_as_float(bl & ~15u) <= bound;
+                if (!__any(gob)) break;
+                if ((bl & 15u) == (uint32_t)gl) bk = ~0u;
+                const int q0 = gob ? (blk0 + (int)(bl & 15u)) * kScanBlock + gl : n;
                 float4 next = X.pts[min(q0, n - 1)];
 #pragma unroll 1
                 for (int r = 0; r < kScanBlock / kQLanes; ++r) {
@@ -204,74 +217,68 @@ __global__ __launch_bounds__(kB) void k_scan_knn_cov(const float* __restrict__ x
                     next = X.pts[min(q + kQLanes, n - 1)];
                     const float d2 = mp_point_d2(c, pi);
                     const uint64_t key = knn_key(d2, __float_as_int(c.w));
-                    if (q < n && q != w && d2 <= bound && key < best[KC - 1]) {
-#pragma unroll
-                        for (int m = KC - 1; m >= 0; --m) {
-                            const bool up = m > 0 && key < best[m > 0 ? m - 1 : 0];
-                            best[m] = up ? best[m > 0 ? m - 1 : 0] : (key < best[m] ? key : best[m]);
+                    uint32_t hits = mp_row_ballot(q < n && q != w && d2 <= bound);
+                    if (!__any(hits != 0)) continue;
+                    do {
+                        const uint64_t got = __shfl((unsigned long long)key, hits ? __builtin_ctz(hits) : 0, kQLanes);
+                        const uint64_t in = hits ? got : ~0ull;
+                        hits &= hits - 1;
+                        const uint64_t before = mp_row_shr(best[0], 0);
+                        if (H > 1) {   // the upper 16 first: their first lane follows the lower ones' last
+                            const uint64_t last = __shfl((unsigned long long)best[0], kQLanes - 1, kQLanes);
+                            const uint64_t b1 = mp_row_shr(best[H - 1], last);
+                            best[H - 1] = in < b1 ? b1 : (in < best[H - 1] ? in : best[H - 1]);
                         }
-                    }
+                        best[0] = in < before ? before : (in < best[0] ? in : best[0]);
+                    } while (__any(hits != 0));
+                    float far = gl < kk ? __uint_as_float((uint32_t)(best[0] >> 32)) : 0.0f;
+                    if (H > 1) far = fmaxf(far, kQLanes + gl < kk ? __uint_as_float((uint32_t)(best[H - 1] >> 32)) : 0.0f);
+                    bound = fminf(bound, mp_row_max(far));
                 }
-                // Group bound: every lane holds at least mb + 1 distinct candidates
-                // at or below its best[mb], so 16 (mb + 1) >= kk candidates lie at or
-                // below the maximum over the group, and so does every one of the
-                // final kk.  Candidates (and boxes) above it are never needed.
-                bound = fminf(bound, mp_row_max(__uint_as_float((uint32_t)((mb >= 1 ? best[1] : best[0]) >> 32))));
             }
         }
     }
-    // merge: round r takes the smallest head of the group's lists and pops it;
-    // lane r % 16 fetches that neighbour
-    int mine[KC / kQLanes > 0 ? KC / kQLanes : 1];
 #pragma unroll
-    for (int a = 0; a < KC; a += kQLanes) mine[a / kQLanes] = 0;
-#pragma unroll
-    for (int a = 0; a < KC; a += kQLanes) {
-#pragma unroll 1
-        for (int r = a; r < min(kk, a + kQLanes); ++r) {
-            const uint64_t v = mp_row_min_u64(best[0]);
-            if (gl == r - a) mine[a / kQLanes] = (int32_t)(uint32_t)v;
-            if (best[0] == v) {   // this lane held the minimum (indices are unique)
-#pragma unroll
-                for (int m = 0; m + 1 < KC; ++m) best[m] = best[m + 1];
-                best[KC - 1] = knn_key(__builtin_inff(), 0x7FFFFFFF);
-            }
-        }
-        const int j = mine[a / kQLanes];
-        if (active && a + gl < kk) {
-            nbr[grp][a + gl][0] = xyz[3 * j];
-            nbr[grp][a + gl][1] = xyz[3 * j + 1];
-            nbr[grp][a + gl][2] = xyz[3 * j + 2];
+    for (int m = 0; m < H; ++m) {
+        const int a = m * kQLanes + gl;
+        if (active && a < kk) {
+            const int j = (int32_t)(uint32_t)best[m];
+            nbr[grp][a][0] = xyz[3 * j];
+            nbr[grp][a][1] = xyz[3 * j + 1];
+            nbr[grp][a][2] = xyz[3 * j + 2];
         }
     }
     __syncthreads();
-    if (active && gl == 0) {
-        double c6[6];
-        if (kk + 1 < 5) {
-            c6[0] = 1; c6[1] = 0; c6[2] = 0; c6[3] = 1; c6[4] = 0; c6[5] = 1;
-        } else {
-            // sums in list order, the point itself first
-            double sm[3] = {(double)pi.x, (double)pi.y, (double)pi.z};
-#pragma unroll 1
-            for (int a = 0; a < kk; ++a) {
-                sm[0] = sm[0] + (double)nbr[grp][a][0];
-                sm[1] = sm[1] + (double)nbr[grp][a][1];
-                sm[2] = sm[2] + (double)nbr[grp][a][2];
-            }
-            const double dn = (double)(kk + 1);
-            const double mu[3] = {sm[0] / dn, sm[1] / dn, sm[2] / dn};
-            double S[6] = {0, 0, 0, 0, 0, 0};
-            double d0 = (double)pi.x - mu[0], d1 = (double)pi.y - mu[1], d2 = (double)pi.z - mu[2];
-#pragma unroll 1
-            for (int a = 0;; ++a) {
-                S[0] += d0 * d0; S[1] += d0 * d1; S[2] += d0 * d2;
-                S[3] += d1 * d1; S[4] += d1 * d2; S[5] += d2 * d2;
-                if (a == kk) break;
-                d0 = (double)nbr[grp][a][0] - mu[0];
-                d1 = (double)nbr[grp][a][1] - mu[1];
-                d2 = (double)nbr[grp][a][2] - mu[2];
-            }
-            for (int a = 0; a < 6; ++a) S[a] /= dn;
+    const bool given = kk + 1 >= 5;   // fewer points give the identity
+    const double dn = (double)(kk + 1);
+    if (given) {
+        // sums in list order, the point itself first
+        const auto axis = [](const float3& v, int a) { return a == 0 ? v.x : (a == 1 ? v.y : v.z); };
+        const int x = min(gl, 2);
+        double sm = (double)axis(pi, x);
+#pragma unroll 2
+        for (int a = 0; a < kk; ++a) sm = sm + (double)nbr[grp][a][x];
+        sm = sm / dn;
+        const double mu[3] = {__shfl(sm, 0, kQLanes), __shfl(sm, 1, kQLanes), __shfl(sm, 2, kQLanes)};
+        const int r = gl < 3 ? 0 : (gl < 5 ? 1 : 2), c = gl < 3 ? gl : (gl < 5 ? gl - 2 : 2);
+        const double mr = r == 0 ? mu[0] : (r == 1 ? mu[1] : mu[2]), mc = c == 0 ? mu[0] : (c == 1 ? mu[1] : mu[2]);
+        double S = 0.0;
+        double d0 = (double)axis(pi, r) - mr, d1 = (double)axis(pi, c) - mc;
+        S += d0 * d1;
+#pragma unroll 2
+        for (int a = 0; a < kk; ++a) {
+            d0 = (double)nbr[grp][a][r] - mr;
+            d1 = (double)nbr[grp][a][c] - mc;
+            S += d0 * d1;
+        }
+        if (gl < 6) cov[grp][gl] = S / dn;
+    }
+    __syncthreads();
+    const int wl = blockIdx.x * kPer + threadIdx.x;
+    if (threadIdx.x < kPer && wl < n) {
+        double c6[6] = {1, 0, 0, 1, 0, 1};
+        if (given) {
+            const double* S = cov[threadIdx.x];
             double A[9] = {S[0], S[1], S[2], S[1], S[3], S[4], S[2], S[4], S[5]};
             double nv[3];
             jacobi_min_vec(A, nv);
@@ -283,15 +290,17 @@ __global__ __launch_bounds__(kB) void k_scan_knn_cov(const float* __restrict__ x
             c6[4] = -a * nv[1] * nv[2];
             c6[5] = 1.0 - a * nv[2] * nv[2];
         }
-        const float4 r0 = make_float4(pi.x, pi.y, pi.z, (float)c6[0]);
+        const float4 p = X.pts[wl];
+        const int i = __float_as_int(p.w);
+        const float4 r0 = make_float4(p.x, p.y, p.z, (float)c6[0]);
         const float4 r1 = make_float4((float)c6[1], (float)c6[2], (float)c6[3], (float)c6[4]);
         const float4 r2 = make_float4((float)c6[5], 0.0f, 0.0f, 0.0f);
         rec[3 * i] = r0;
         rec[3 * i + 1] = r1;
         rec[3 * i + 2] = r2;
-        walk[3 * w] = r0;
-        walk[3 * w + 1] = r1;
-        walk[3 * w + 2] = r2;
+        walk[3 * wl] = r0;
+        walk[3 * wl + 1] = r1;
+        walk[3 * wl + 2] = r2;
     }
     stamp_last(stamp_end);
 }
@@ -415,9 +424,8 @@ void mp_scan_records(const float* xyz, const float* cov6, const int32_t* perm, i
     } else {
         constexpr int per = kB / kQLanes;
         const unsigned grid = (unsigned)((n + per - 1) / per);
-        if (k <= 8) k_scan_knn_cov<8><<<grid, kB, 0, s>>>(xyz, X, n, k, eps, r4, w4, stamp_end);
-        else if (k <= 16) k_scan_knn_cov<16><<<grid, kB, 0, s>>>(xyz, X, n, k, eps, r4, w4, stamp_end);
-        else k_scan_knn_cov<32><<<grid, kB, 0, s>>>(xyz, X, n, k, eps, r4, w4, stamp_end);
+        if (k <= kQLanes) k_scan_knn_cov<1><<<grid, kB, 0, s>>>(xyz, X, n, k, eps, r4, w4, stamp_end);
+        else k_scan_knn_cov<2><<<grid, kB, 0, s>>>(xyz, X, n, k, eps, r4, w4, stamp_end);
     }
     MP_CHECK_LAUNCH();
 }

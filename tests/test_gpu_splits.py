@@ -218,3 +218,11 @@ def test_posterior_over_its_kernels(room, O, n, k, rounds):
     assert abs(q["n_eff"] - ref["n_eff"]) <= 3 * tol * ref["n_eff"]
     assert abs(q["map_weight"] - ref["post"].max()) <= tol * ref["post"].max()
     f.close()
+
+
+@pytest.mark.parametrize("n,kind", [(16_385, "surface"), (20_000, "cell")])
+def test_searches_over_several_rows_of_boxes(room, O, n, kind):
+    # an index of more than 16 boxes of 1024 points is walked 16 at a time,
+    # from the point's own on
+    test_scan_neighbours_of_the_indexed_search(room, O, n, 10, kind)
+    test_odometry_matches_of_the_indexed_search(room, O, 300, n, 1.0)
