@@ -29,9 +29,12 @@
 //
 // What bounds it: latency (the sums and the step's FP64 chain, about 3 us,
 // then the dependent loads of the search).  An iteration takes 16 us on
-// 8192-point scans and 51 us on 65,536-point ones (130 us for the first,
-// which has no matches to start from); searching all targets for every point,
-// with the step and the terms in launches of their own, took 36 and 820 us.
+// 8192-point scans and 51 us on 65,536-point ones; searching all targets for
+// every point, with the step and the terms in launches of their own, took 36
+// and 820 us.  The first two iterations, whose matches of the iteration before
+// are missing or far off, take the boxes nearest first (65,536 points: 131 and
+// 81 -> 59 and 60 us); for the later ones finding the nearest box costs more
+// than the few others that are still below the bound (51 -> 57 us).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -253,6 +256,8 @@ __device__ void odo_step(const double* tot, double lam_rel, double lam_abs, cons
 __device__ __forceinline__ uint64_t odo_key(float d2, int32_t j) {   // d2 >= +0: its bits order as the values do
     return ((uint64_t)__float_as_uint(d2) << 32) | (uint32_t)j;
 }
+
+template <bool NEAREST>   // boxes nearest first, or in index order
 __global__ __launch_bounds__(kOThreads) void k_odo_iter(OdoArgs A) {
     __shared__ double run[kOTerms][kOSum];
     __shared__ double tot[kOTerms];
@@ -311,29 +316,58 @@ __global__ __launch_bounds__(kOThreads) void k_odo_iter(OdoArgs A) {
             }
         }
         float bound = __uint_as_float((uint32_t)(best >> 32));
-        for (int s0 = 0; s0 < A.T.supers; s0 += kOLanes) {
-            const int sup = s0 + gl;
-            uint32_t sm = mp_row_ballot(active && sup < A.T.supers &&
-                                        mp_box_d2(super + 2 * min(sup, A.T.supers - 1), p) <= bound);
-            while (__any(sm != 0)) {
-                const int su = s0 + (sm ? __builtin_ctz(sm) : 0);
-                const int blk = su * kScanFan + gl;
-                uint32_t bm = mp_row_ballot(sm != 0 && blk < A.T.blocks &&
-                                            mp_box_d2(box + 2 * min(blk, A.T.blocks - 1), p) <= bound);
-                sm &= sm - 1;
-                while (__any(bm != 0)) {
-                    const int q0 = bm ? (su * kScanFan + __builtin_ctz(bm)) * kScanBlock + gl : A.T.n;
-                    bm &= bm - 1;
-                    float4 c[kScanBlock / kOLanes];
+        // a block of a row's choice (if any) against its point
+        const auto visit = [&](bool go, int blk) {
+            const int q0 = go ? blk * kScanBlock + gl : A.T.n;
+            float4 c[kScanBlock / kOLanes];
 #pragma unroll
-                    for (int u = 0; u < kScanBlock / kOLanes; ++u) c[u] = A.T.pts[min(q0 + kOLanes * u, A.T.n - 1)];
+            for (int u = 0; u < kScanBlock / kOLanes; ++u) c[u] = A.T.pts[min(q0 + kOLanes * u, A.T.n - 1)];
 #pragma unroll
-                    for (int u = 0; u < kScanBlock / kOLanes; ++u) {
-                        const uint64_t key = odo_key(mp_point_d2(c[u], p), __float_as_int(c[u].w));
-                        if (q0 + kOLanes * u < A.T.n && key < best) best = key;
+            for (int u = 0; u < kScanBlock / kOLanes; ++u) {
+                const uint64_t key = odo_key(mp_point_d2(c[u], p), __float_as_int(c[u].w));
+                if (q0 + kOLanes * u < A.T.n && key < best) best = key;
+            }
+            best = mp_row_min_u64(best);
+            bound = __uint_as_float((uint32_t)(best >> 32));
+        };
+        const int batches = (A.T.supers + kOLanes - 1) / kOLanes;
+        if (NEAREST) {
+            int batch = min(w / (kScanBlock * kScanFan * kOLanes), batches - 1);   // where its match likely is
+            for (int b = 0; b < batches; ++b, batch = batch + 1 < batches ? batch + 1 : 0) {
+                const int sup = batch * kOLanes + gl;
+                uint32_t sk = mp_box_key(active && sup < A.T.supers, super + 2 * min(sup, A.T.supers - 1), p, gl);
+                for (;;) {
+                    const uint32_t su = mp_row_min_u32(sk);
+                    const bool go = su != ~0u && __uint_as_float(su & ~15u) <= bound;
+                    if (!__any(go)) break;
+                    if ((su & 15u) == (uint32_t)gl) sk = ~0u;
+                    const int blk0 = (batch * kOLanes + (int)(su & 15u)) * kScanFan;
+                    const int blk = blk0 + gl;
+                    uint32_t bk = mp_box_key(go && blk < A.T.blocks, box + 2 * min(blk, A.T.blocks - 1), p, gl);
+                    for (;;) {
+                        const uint32_t bl = mp_row_min_u32(bk);
+                        const bool gob = bl != ~0u && __uint_as_float(bl & ~15u) <= bound;
+                        if (!__any(gob)) break;
+                        if ((bl & 15u) == (uint32_t)gl) bk = ~0u;
+                        visit(gob, blk0 + (int)(bl & 15u));
                     }
-                    best = mp_row_min_u64(best);
-                    bound = __uint_as_float((uint32_t)(best >> 32));
+                }
+            }
+        } else {
+            for (int s0 = 0; s0 < A.T.supers; s0 += kOLanes) {
+                const int sup = s0 + gl;
+                uint32_t sm = mp_row_ballot(active && sup < A.T.supers &&
+                                            mp_box_d2(super + 2 * min(sup, A.T.supers - 1), p) <= bound);
+                while (__any(sm != 0)) {
+                    const int su = s0 + (sm ? __builtin_ctz(sm) : 0);
+                    const int blk = su * kScanFan + gl;
+                    uint32_t bm = mp_row_ballot(sm != 0 && blk < A.T.blocks &&
+                                                mp_box_d2(box + 2 * min(blk, A.T.blocks - 1), p) <= bound);
+                    sm &= sm - 1;
+                    while (__any(bm != 0)) {
+                        visit(bm != 0, su * kScanFan + (bm ? __builtin_ctz(bm) : 0));
+                        bm &= bm - 1;
+                    }
                 }
             }
         }
@@ -486,7 +520,8 @@ void odometry_impl(void* ctx) {
         A.part_out = part[it & 1];
         A.pose_in = pose + 8 * ((it + 1) & 1);
         A.pose_out = pose + 8 * (it & 1);
-        k_odo_iter<<<(unsigned)nparts, kOThreads, 0, s>>>(A);
+        if (it < 2) k_odo_iter<true><<<(unsigned)nparts, kOThreads, 0, s>>>(A);
+        else k_odo_iter<false><<<(unsigned)nparts, kOThreads, 0, s>>>(A);
         MP_CHECK_LAUNCH();
     }
     k_odo_final<<<1, kOThreads, 0, s>>>(part[P.iterations & 1], nparts, pose + 8 * (P.iterations & 1), P.cov_scale,
