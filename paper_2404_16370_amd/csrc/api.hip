@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <chrono>
 #include <cmath>
 #include <cstdarg>
 #include <numeric>
@@ -496,6 +497,22 @@ extern "C" mp_status mp_filter_destroy(mp_filter f) {
     });
 }
 
+// The verdict of a scan's check, 15 us after the call on an idle stream: polled
+// for a while, as waiting for the stream costs as much again and would wait for
+// the sort as well.  (An upload of 300 points returned after 42 us and was done
+// after 85 with the verdict copied back before the sort; 22 and 60 us now.)
+static bool scan_is_bad(const ScanPrep& P, hipStream_t s) {
+    const auto read = [&]() { return __atomic_load_n(P.verdict, __ATOMIC_ACQUIRE); };
+    const auto t0 = std::chrono::steady_clock::now();
+    while (read() >> 1 != P.seq)
+        if (std::chrono::steady_clock::now() - t0 > std::chrono::microseconds(200)) {   // behind other work
+            MP_HIP(hipStreamSynchronize(s));
+            if (read() >> 1 != P.seq) mp_throw(MP_E_HIP, "no verdict on the scan");
+            break;
+        }
+    return (read() & 1u) != 0;
+}
+
 extern "C" mp_status mp_scan_upload(mp_filter f, const float* xyz, const float* cov6, int32_t n, void* stream) {
     return guarded("mp_scan_upload", [&]() {
         if (!f || n < 0 || (n > 0 && !xyz)) mp_throw(MP_E_ARG, "null argument or n < 0");
@@ -505,7 +522,11 @@ extern "C" mp_status mp_scan_upload(mp_filter f, const float* xyz, const float* 
             f->scan_xyz.ensure(sizeof(float) * 3 * (size_t)n);
             f->scan.ensure(sizeof(float) * 12 * (size_t)n);
             f->scan_perm.ensure(sizeof(int32_t) * (size_t)n);
-            f->scan_work.ensure(sizeof(uint32_t) * (4 * (size_t)n + 4));
+            f->scan_work.ensure(sizeof(float4) * (kPrepParts + 1) + sizeof(uint32_t) * 3 * (size_t)n);
+            if (!f->scan_verdict.p) {
+                f->scan_verdict.ensure(64);
+                *f->scan_verdict.as<uint32_t>() = 0;   // the number of no scan
+            }
             f->scan_sort.ensure(mp_radix_scratch_bytes(n));
             // caller data (host or device) into the filter's staging buffers
             MP_HIP(hipMemcpyAsync(f->scan_xyz.p, xyz, sizeof(float) * 3 * (size_t)n, hipMemcpyDefault, s));
@@ -515,14 +536,24 @@ extern "C" mp_status mp_scan_upload(mp_filter f, const float* xyz, const float* 
                 MP_HIP(hipMemcpyAsync(f->scan_cov.p, cov6, sizeof(float) * 6 * (size_t)n, hipMemcpyDefault, s));
                 dcov = f->scan_cov.as<float>();
             }
-            uint32_t* work = f->scan_work.as<uint32_t>();
-            float* lo_bad = reinterpret_cast<float*>(work + 4 * (size_t)n);
-            // validation on the device; only its 4-byte verdict comes back
-            mp_scan_check(f->scan_xyz.as<float>(), dcov, n, lo_bad, s);
-            float bad = 0.0f;
-            MP_HIP(hipMemcpyAsync(&bad, lo_bad + 3, sizeof(float), hipMemcpyDeviceToHost, s));
-            MP_HIP(hipStreamSynchronize(s));
-            if (bad != 0.0f) mp_throw(MP_E_ARG, cov6 ? "non-finite scan point or covariance" : "non-finite scan point");
+            // Walk order for the likelihood: Morton order of the points on a grid of half the
+            // map voxel, so that consecutive points of one particle land in the same or
+            // neighbouring voxels (the sum over points does not depend on the order).
+            // Only the verdict of the check comes back: the sort, which touches nothing that
+            // a refused scan must leave alone, runs while the host waits for it.
+            ScanPrep P;
+            P.part = f->scan_work.as<float4>();
+            P.start = reinterpret_cast<uint64_t*>(P.part + kPrepParts);
+            P.key = reinterpret_cast<uint32_t*>(P.part + kPrepParts + 1);
+            P.idx = f->scan_perm.as<int32_t>();
+            P.xyz = f->scan_xyz.as<float>();
+            P.cov = dcov;
+            P.verdict = f->scan_verdict.as<uint32_t>();
+            P.seq = f->scan_seq = f->scan_seq % 0x7FFFFFFFu + 1;
+            P.n = n;
+            mp_scan_walk_order(P, 0.5f * f->map->params.voxel, P.key + n, reinterpret_cast<int32_t*>(P.key + 2 * (size_t)n),
+                               f->scan_sort, s);
+            if (scan_is_bad(P, s)) mp_throw(MP_E_ARG, cov6 ? "non-finite scan point or covariance" : "non-finite scan point");
             // the current records become the previous scan's (odometry)
             if (f->orig_n > 0) {
                 f->scan_orig.swap(f->prev_orig);
@@ -532,16 +563,8 @@ extern "C" mp_status mp_scan_upload(mp_filter f, const float* xyz, const float* 
             f->scan_orig.ensure(sizeof(float) * 12 * (size_t)n);
             f->scan_idx.ensure(mp_scan_index_bytes(n));
             f->orig_n = n;
-            uint64_t* stamps = f->stamps.as<uint64_t>();
-            // Walk order for the likelihood: Morton order of the points on a grid of half the
-            // map voxel, so that consecutive points of one particle land in the same or
-            // neighbouring voxels (the sum over points does not depend on the order).
-            mp_scan_walk_order(f->scan_xyz.as<float>(), n, 0.5f * f->map->params.voxel, lo_bad, work, work + n,
-                               f->scan_perm.as<int32_t>(), reinterpret_cast<int32_t*>(work + 2 * (size_t)n),
-                               f->scan_sort, stamps, s);
-            mp_scan_records(f->scan_xyz.as<float>(), dcov, f->scan_perm.as<int32_t>(), n, f->p.scan_k, f->p.cov_eps,
-                            mp_scan_index(f->scan_idx, n), f->scan_orig.as<float>(), f->scan.as<float>(), stamps + 1,
-                            s);
+            mp_scan_records(P.xyz, dcov, P.idx, n, f->p.scan_k, f->p.cov_eps, mp_scan_index(f->scan_idx, n),
+                            f->scan_orig.as<float>(), f->scan.as<float>(), P.start, f->stamps.as<uint64_t>(), s);
             f->scan_timed = true;
         }
         f->scan_n = n;

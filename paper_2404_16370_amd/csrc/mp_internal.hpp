@@ -189,7 +189,9 @@ struct mp_filter_s {
     int32_t orig_n = 0;       // points of the records in scan_orig (the last non-empty scan)
     DevMem odo_nn, odo_work;  // odometry work arrays
     DevMem scan_cov;          // n x 6 float staging of caller covariances
-    DevMem scan_work;         // walk-order keys and work arrays (4n words) + lo/bad (4 floats)
+    DevMem scan_work;         // parts and clock of ScanPrep, walk-order keys and work arrays (3n words)
+    HostMem scan_verdict;     // verdict of the last uploaded scan's check, and its number
+    uint32_t scan_seq = 0;
     DevMem scan_sort;         // radix-sort scratch of the walk order
     DevMem tlsh;              // 8 float
     DevMem stepinfo;          // posterior summary (doubles)
@@ -268,18 +270,29 @@ struct ScanIndex {
 };
 size_t mp_scan_index_bytes(int32_t n);
 ScanIndex mp_scan_index(const DevMem& mem, int32_t n);
-// the index, then every point's record in the caller's order and in walk order
-// (stamp_end: raised to the device clock at which the last workgroup ends)
+// the index, then every point's record in the caller's order and in walk order;
+// stamps: [0] set to *start, [1] to the device clock at which the last workgroup ends
 void mp_scan_records(const float* xyz_dev, const float* cov6_dev, const int32_t* perm, int32_t n, int32_t k, float eps,
-                     const ScanIndex& X, float* rec_dev, float* walk_dev, uint64_t* stamp_end, hipStream_t s);
-// lo_bad_dev (4 floats): bounding-box minimum corner of the points, then 1 if any
-// point or covariance entry is not finite (else 0)
-void mp_scan_check(const float* xyz_dev, const float* cov6_dev, int32_t n, float* lo_bad_dev, hipStream_t s);
-// (stamps: [0] set to the device clock, [1] zeroed)
-// walk order of the likelihood: stable sort of the points by the Morton key of
-// their cell (edge `cell`); keys/keys_alt/perm_alt are n-entry work arrays
-void mp_scan_walk_order(const float* xyz_dev, int32_t n, float cell, const float* lo_bad_dev, uint32_t* keys,
-                        uint32_t* keys_alt, int32_t* perm, int32_t* perm_alt, DevMem& scratch, uint64_t* stamps,
+                     const ScanIndex& X, float* rec_dev, float* walk_dev, const uint64_t* start, uint64_t* stamps,
+                     hipStream_t s);
+// walk order of the likelihood: stable sort of the n > 0 points by the Morton
+// key of their cell (edge `cell`); idx holds the result, key, keys_alt and
+// perm_alt are n-entry work arrays
+constexpr int kPrepOne = 8192;   // points of a scan that one workgroup prepares
+constexpr int kPrepParts = 64;   // workgroups that check a larger one (of 65,536 at most)
+struct ScanPrep {
+    const float* xyz;    // n x 3
+    const float* cov;    // n x 6, or null
+    float4* part;        // kPrepParts
+    uint32_t* key;
+    int32_t* idx;
+    uint64_t* start;     // device clock at which the keys were begun
+    uint32_t* verdict;   // host memory: 2 seq, plus 1 if an input is not finite
+    uint32_t seq;
+    int32_t n;
+    float inv_cell;
+};
+void mp_scan_walk_order(ScanPrep A, float cell, uint32_t* keys_alt, int32_t* perm_alt, DevMem& scratch,
                         hipStream_t s);
 
 // filter stages

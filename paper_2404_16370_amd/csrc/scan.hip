@@ -89,8 +89,14 @@ __device__ __forceinline__ float wave_min(float v) {
 }
 
 __global__ __launch_bounds__(kIdxThreads) void k_scan_index(const float* __restrict__ xyz,
-                                                            const int32_t* __restrict__ perm, int n, ScanIndex X) {
+                                                            const int32_t* __restrict__ perm, int n, ScanIndex X,
+                                                            const uint64_t* __restrict__ start,
+                                                            uint64_t* __restrict__ stamps) {
     __shared__ float box[kScanFan][6];
+    if (blockIdx.x == 0 && threadIdx.x == 0) {   // the upload stands: its clock values
+        stamps[0] = *start;
+        stamps[1] = 0;
+    }
     const int w = blockIdx.x * kIdxThreads + threadIdx.x;
     float b[6];   // lower corner, negated upper corner: both are minima
 #pragma unroll
@@ -324,46 +330,6 @@ __global__ void k_scan_given_cov(const float* __restrict__ cov, ScanIndex X, int
     stamp_last(stamp_end);
 }
 
-// Finiteness of the points (and covariances) and the minimum corner of the
-// points' bounding box: one workgroup (n <= 65536), deterministic (min and or).
-constexpr int kChk = 1024;
-__global__ __launch_bounds__(kChk) void k_scan_check(const float* __restrict__ xyz, const float* __restrict__ cov,
-                                                     int n, float* __restrict__ lo_bad) {
-    __shared__ float red[3][kChk];
-    __shared__ int rbad[kChk];
-    float lo[3] = {__builtin_inff(), __builtin_inff(), __builtin_inff()};
-    int bad = 0;
-    for (int i = threadIdx.x; i < n; i += kChk) {
-#pragma unroll
-        for (int a = 0; a < 3; ++a) {
-            const float v = xyz[3 * i + a];
-            bad |= !__builtin_isfinite(v);
-            lo[a] = fminf(lo[a], v);
-        }
-        if (cov)
-#pragma unroll
-            for (int a = 0; a < 6; ++a) bad |= !__builtin_isfinite(cov[6 * i + a]);
-    }
-#pragma unroll
-    for (int a = 0; a < 3; ++a) red[a][threadIdx.x] = lo[a];
-    rbad[threadIdx.x] = bad;
-    __syncthreads();
-    for (int h = kChk / 2; h >= 1; h >>= 1) {
-        if ((int)threadIdx.x < h) {
-#pragma unroll
-            for (int a = 0; a < 3; ++a) red[a][threadIdx.x] = fminf(red[a][threadIdx.x], red[a][threadIdx.x + h]);
-            rbad[threadIdx.x] |= rbad[threadIdx.x + h];
-        }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        lo_bad[0] = red[0][0];
-        lo_bad[1] = red[1][0];
-        lo_bad[2] = red[2][0];
-        lo_bad[3] = rbad[0] ? 1.0f : 0.0f;
-    }
-}
-
 __device__ inline uint32_t spread10(uint32_t v) {
     v &= 0x3FFu;
     v = (v | (v << 16)) & 0x030000FFu;
@@ -373,24 +339,87 @@ __device__ inline uint32_t spread10(uint32_t v) {
     return v;
 }
 
-// 30-bit Morton (Z-order) key of each point's cell (edge `cell`, 1024 cells
-// per axis from the box corner, clamped) and the identity permutation
-__global__ void k_morton_keys(const float* __restrict__ xyz, int n, const float* __restrict__ lo_bad, float inv_cell,
-                              uint32_t* __restrict__ key, int32_t* __restrict__ idx, uint64_t* __restrict__ stamps) {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i == 0) {
-        stamps[0] = (uint64_t)wall_clock64();
-        stamps[1] = 0;
+// Check, walk keys and verdict of an uploaded scan.  What bounds it: launches
+// and the host's wait.  The verdict (2 seq, plus 1 if any point or covariance
+// entry is not finite) goes straight to pinned host memory, so that the host
+// can go on while the device sorts.
+constexpr int kChk = 1024;
+
+struct ScanMin {
+    float lo[3];   // minimum corner of the points
+    bool bad;
+};
+
+// of the points [from, to), by a workgroup of kChk
+__device__ __forceinline__ ScanMin scan_min(const ScanPrep& A, int from, int to) {
+    __shared__ float red[4][kChk / 64];
+    ScanMin M{{__builtin_inff(), __builtin_inff(), __builtin_inff()}, false};
+    for (int i = from + threadIdx.x; i < to; i += kChk) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            const float v = A.xyz[3 * i + a];
+            M.bad |= !__builtin_isfinite(v);
+            M.lo[a] = fminf(M.lo[a], v);
+        }
+        if (A.cov)
+#pragma unroll
+            for (int a = 0; a < 6; ++a) M.bad |= !__builtin_isfinite(A.cov[6 * (size_t)i + a]);
     }
-    if (i >= n) return;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) M.lo[a] = wave_min(M.lo[a]);
+    const bool any = __any(M.bad);
+    if (lane == 0) {
+        for (int a = 0; a < 3; ++a) red[a][wave] = M.lo[a];
+        red[3][wave] = any ? 1.0f : 0.0f;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int a = 0; a < 3; ++a) M.lo[a] = wave_min(red[a][lane % (kChk / 64)]);
+    M.bad = __any(red[3][lane % (kChk / 64)] != 0.0f);
+    return M;
+}
+
+// 30-bit Morton (Z-order) key of the point's cell (1024 cells per axis from
+// the box corner, clamped) and the identity permutation
+__device__ __forceinline__ void scan_key(const ScanPrep& A, const float lo[3], int i) {
     uint32_t c[3];
 #pragma unroll
     for (int a = 0; a < 3; ++a) {
-        const float q = floorf((xyz[3 * i + a] - lo_bad[a]) * inv_cell);
+        const float q = floorf((A.xyz[3 * i + a] - lo[a]) * A.inv_cell);
         c[a] = (uint32_t)fminf(fmaxf(q, 0.0f), 1023.0f);
     }
-    key[i] = spread10(c[0]) | (spread10(c[1]) << 1) | (spread10(c[2]) << 2);
-    idx[i] = i;
+    A.key[i] = spread10(c[0]) | (spread10(c[1]) << 1) | (spread10(c[2]) << 2);
+    A.idx[i] = i;
+}
+
+__device__ __forceinline__ void scan_verdict(const ScanPrep& A, bool bad) {
+    *A.start = (uint64_t)wall_clock64();
+    __hip_atomic_store(A.verdict, 2 * A.seq + (bad ? 1u : 0u), __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// scans of up to kPrepOne points, in one workgroup
+__global__ __launch_bounds__(kChk) void k_scan_prep(ScanPrep A) {
+    const ScanMin M = scan_min(A, 0, A.n);
+    if (threadIdx.x == 0) scan_verdict(A, M.bad);
+    for (int i = threadIdx.x; i < A.n; i += kChk) scan_key(A, M.lo, i);
+}
+
+// larger ones: a workgroup per kChk points, whose results every workgroup of
+// the keys reduces (up to 64 of them, one a lane)
+__global__ __launch_bounds__(kChk) void k_scan_check(ScanPrep A) {
+    const ScanMin M = scan_min(A, blockIdx.x * kChk, min(A.n, ((int)blockIdx.x + 1) * kChk));
+    if (threadIdx.x == 0) A.part[blockIdx.x] = make_float4(M.lo[0], M.lo[1], M.lo[2], M.bad ? 1.0f : 0.0f);
+}
+
+__global__ __launch_bounds__(256) void k_scan_keys(ScanPrep A) {
+    const int nb = (A.n + kChk - 1) / kChk;
+    const float4 p = A.part[min((int)(threadIdx.x & 63), nb - 1)];
+    const float lo[3] = {wave_min(p.x), wave_min(p.y), wave_min(p.z)};
+    const bool bad = __any(p.w != 0.0f);
+    if (blockIdx.x == 0 && threadIdx.x == 0) scan_verdict(A, bad);
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < A.n) scan_key(A, lo, i);
 }
 
 }  // namespace
@@ -412,35 +441,35 @@ ScanIndex mp_scan_index(const DevMem& mem, int32_t n) {
 }
 
 void mp_scan_records(const float* xyz, const float* cov6, const int32_t* perm, int32_t n, int32_t k, float eps,
-                     const ScanIndex& X, float* rec, float* walk, uint64_t* stamp_end, hipStream_t s) {
+                     const ScanIndex& X, float* rec, float* walk, const uint64_t* start, uint64_t* stamps,
+                     hipStream_t s) {
     if (n <= 0) return;
     if (k > kKMax) mp_throw(MP_E_UNSUPPORTED, "scan_k above %d", kKMax);
-    k_scan_index<<<X.supers, kIdxThreads, 0, s>>>(xyz, perm, n, X);
+    k_scan_index<<<X.supers, kIdxThreads, 0, s>>>(xyz, perm, n, X, start, stamps);
     MP_CHECK_LAUNCH();
     float4* r4 = reinterpret_cast<float4*>(rec);
     float4* w4 = reinterpret_cast<float4*>(walk);
     if (cov6) {
-        k_scan_given_cov<<<(n + 255) / 256, 256, 0, s>>>(cov6, X, n, r4, w4, stamp_end);
+        k_scan_given_cov<<<(n + 255) / 256, 256, 0, s>>>(cov6, X, n, r4, w4, stamps + 1);
     } else {
         constexpr int per = kB / kQLanes;
         const unsigned grid = (unsigned)((n + per - 1) / per);
-        if (k <= kQLanes) k_scan_knn_cov<1><<<grid, kB, 0, s>>>(xyz, X, n, k, eps, r4, w4, stamp_end);
-        else k_scan_knn_cov<2><<<grid, kB, 0, s>>>(xyz, X, n, k, eps, r4, w4, stamp_end);
+        if (k <= kQLanes) k_scan_knn_cov<1><<<grid, kB, 0, s>>>(xyz, X, n, k, eps, r4, w4, stamps + 1);
+        else k_scan_knn_cov<2><<<grid, kB, 0, s>>>(xyz, X, n, k, eps, r4, w4, stamps + 1);
     }
     MP_CHECK_LAUNCH();
 }
 
-void mp_scan_check(const float* xyz_dev, const float* cov6_dev, int32_t n, float* lo_bad_dev, hipStream_t s) {
-    k_scan_check<<<1, kChk, 0, s>>>(xyz_dev, cov6_dev, n, lo_bad_dev);
-    MP_CHECK_LAUNCH();
-}
-
-void mp_scan_walk_order(const float* xyz_dev, int32_t n, float cell, const float* lo_bad_dev, uint32_t* keys,
-                        uint32_t* keys_alt, int32_t* perm, int32_t* perm_alt, DevMem& scratch, uint64_t* stamps,
+void mp_scan_walk_order(ScanPrep A, float cell, uint32_t* keys_alt, int32_t* perm_alt, DevMem& scratch,
                         hipStream_t s) {
-    if (n <= 0) return;
-    k_morton_keys<<<(n + 255) / 256, 256, 0, s>>>(xyz_dev, n, lo_bad_dev, 1.0f / cell, keys, perm, stamps);
+    A.inv_cell = 1.0f / cell;
+    if (A.n <= kPrepOne) {
+        k_scan_prep<<<1, kChk, 0, s>>>(A);
+    } else {
+        k_scan_check<<<(A.n + kChk - 1) / kChk, kChk, 0, s>>>(A);
+        k_scan_keys<<<(A.n + 255) / 256, 256, 0, s>>>(A);
+    }
     MP_CHECK_LAUNCH();
-    if (mp_sort_is_small(n)) mp_sort_small(keys, keys, perm, n, 30, nullptr, nullptr, nullptr, s);
-    else mp_radix_sort_u32(keys, perm, keys_alt, perm_alt, n, 30, scratch, s);
+    if (mp_sort_is_small(A.n)) mp_sort_small(A.key, A.key, A.idx, A.n, 30, nullptr, nullptr, nullptr, s);
+    else mp_radix_sort_u32(A.key, A.idx, keys_alt, perm_alt, A.n, 30, scratch, s);
 }

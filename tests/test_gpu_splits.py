@@ -226,3 +226,28 @@ def test_searches_over_several_rows_of_boxes(room, O, n, kind):
     # from the point's own on
     test_scan_neighbours_of_the_indexed_search(room, O, n, 10, kind)
     test_odometry_matches_of_the_indexed_search(room, O, 300, n, 1.0)
+
+
+@pytest.mark.parametrize("n", [1, 1023, 1024, 1025, 8192, 8193, 65_536])
+def test_refused_scan_leaves_the_last_one(room, n):
+    # both ways of preparing a scan: a non-finite entry anywhere is refused and
+    # the records, the clock and the next odometry stay those of the scan before
+    poses = S.gaussian_particles(8, S.pose8(*room["w"]["traj"][0]), 0.1, 0.3, 3)
+    f = _filter(room, 8, poses)
+    good = _cloud(n, "surface", n)
+    cov = np.tile(np.float32([1, 0, 0, 1, 0, 1]), (n, 1))
+    f.scan_upload(good, cov6=cov)
+    keep = [f.debug_get(b) for b in ("scan", "scan_walk")]
+    time = f.stage_times()
+    for where, value in ((0, np.nan), (n // 2, np.inf), (n - 1, -np.inf)):
+        bad, bad_cov = good.copy(), cov.copy()
+        bad[where, 1] = value
+        bad_cov[where, 5] = value
+        for args in ((bad, None), (good, bad_cov)):
+            with pytest.raises(M.MegaPFError):
+                f.scan_upload(args[0], cov6=args[1])
+            assert all(np.array_equal(f.debug_get(b), k) for b, k in zip(("scan", "scan_walk"), keep))
+    assert f.stage_times() == time
+    f.scan_upload(good, cov6=cov)
+    assert np.array_equal(f.debug_get("scan"), keep[0]) and np.array_equal(f.debug_get("scan_walk"), keep[1])
+    f.close()
