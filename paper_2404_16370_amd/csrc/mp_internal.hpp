@@ -30,21 +30,25 @@ struct MpError {
 #define MP_CHECK_LAUNCH() MP_HIP(hipGetLastError())
 
 // ------------------------------------------------------------ device memory
-// Owning device allocation; freed in the destructor.
+// Owning device allocation; freed in the destructor.  Or a part of another
+// one (part_of), which has to live as long.
 struct DevMem {
     void* p = nullptr;
     size_t bytes = 0;
+    bool part = false;
     DevMem() = default;
     DevMem(const DevMem&) = delete;
     DevMem& operator=(const DevMem&) = delete;
     ~DevMem() { release(); }
     void alloc(size_t b);          // exact size, contents undefined
-    void ensure(size_t b);         // grow if smaller
+    void ensure(size_t b);         // grow if smaller (a part becomes an allocation of its own)
+    void part_of(const DevMem& whole, size_t offset, size_t b);
     void release();
     template <class T> T* as() const { return static_cast<T*>(p); }
     void swap(DevMem& o) {
         std::swap(p, o.p);
         std::swap(bytes, o.bytes);
+        std::swap(part, o.part);
     }
 };
 
@@ -166,6 +170,7 @@ struct mp_filter_s {
     int32_t lik_chunks = 1, lik_chunk_len = 0;
     float lsh_lo[3], lsh_hi[3];
     // state
+    DevMem arena;             // the buffers whose sizes are fixed at creation are parts of it
     DevMem poses[2];          // N x 8 float
     DevMem psi;               // N x 8 float: psi[6], loglik, inliers
     DevMem hb;                // N x 28 float (debug)
