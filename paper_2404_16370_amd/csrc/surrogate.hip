@@ -139,20 +139,20 @@ __device__ __forceinline__ void mlp32(const char* __restrict__ img, const float 
     const float* b3 = reinterpret_cast<const float*>(img + kImgB3);
     const float* fq = reinterpret_cast<const float*>(img + kImgFQ);
 
-    f32x16 acc[4];
+    const auto bias = [&](const float* src, f32x16 (&v)[4]) {
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
+        for (int r = 0; r < 4; ++r)
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const float4 bb = *reinterpret_cast<const float4*>(b1 + 32 * r + 8 * q + 4 * h);
-            acc[r][4 * q] = bb.x;
-            acc[r][4 * q + 1] = bb.y;
-            acc[r][4 * q + 2] = bb.z;
-            acc[r][4 * q + 3] = bb.w;
-        }
+            for (int q = 0; q < 4; ++q) {
+                const float4 bb = *reinterpret_cast<const float4*>(src + 32 * r + 8 * q + 4 * h);
+                v[r][4 * q] = bb.x;
+                v[r][4 * q + 1] = bb.y;
+                v[r][4 * q + 2] = bb.z;
+                v[r][4 * q + 3] = bb.w;
+            }
+    };
     // layer 1: k-step s covers axis s/4, frequencies 8 (s%4) + 4 h + 0..3 (sin, cos each)
-#pragma unroll
-    for (int s = 0; s < 12; ++s) {
+    const auto features = [&](int s) {
         const float4 fr = *reinterpret_cast<const float4*>(fq + 8 * (s & 3) + 4 * h);
         const float xs = x[s >> 2];
         __bf16 v0, v1, v2, v3, v4, v5, v6, v7;
@@ -160,41 +160,54 @@ __device__ __forceinline__ void mlp32(const char* __restrict__ img, const float 
         feature_pair(fr.y, xs, v2, v3);
         feature_pair(fr.z, xs, v4, v5);
         feature_pair(fr.w, xs, v6, v7);
-        const bf16x8 bx = bf16x8{v0, v1, v2, v3, v4, v5, v6, v7};
+        return bf16x8{v0, v1, v2, v3, v4, v5, v6, v7};
+    };
+    // a k-step's B operand of the next layer from its 8 accumulators
+    const auto hidden = [&](const f32x16 (&v)[4], int s2) {
+        bf16x8 b;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) acc[r] = mfma32(f1[(r * 12 + s) * 64 + lane], bx, acc[r]);
+        for (int j = 0; j < 8; ++j) b[j] = (__bf16)silu_f(v[s2 >> 1][8 * (s2 & 1) + j]);
+        return b;
+    };
+    f32x16 acc[4], acc2[4];
+    bias(b1, acc);
+    bf16x8 bx = features(0), w[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) w[r] = f1[(r * 12) * 64 + lane];
+#pragma unroll
+    for (int s = 0; s < 12; ++s) {
+        bf16x8 wn[4], bn = bx;   // the next step's
+#pragma unroll
+        for (int r = 0; r < 4; ++r) wn[r] = s < 11 ? f1[(r * 12 + s + 1) * 64 + lane] : f2[(r * 8) * 64 + lane];
+        if (s < 11) bn = features(s + 1);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[r] = mfma32(w[r], bx, acc[r]);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) w[r] = wn[r];
+        bx = bn;
     }
-    bf16x8 hb[8];
-#pragma unroll
-    for (int s2 = 0; s2 < 8; ++s2)
-#pragma unroll
-        for (int j = 0; j < 8; ++j) hb[s2][j] = (__bf16)silu_f(acc[s2 >> 1][8 * (s2 & 1) + j]);
     // layer 2
+    bias(b2, acc2);
+    bx = hidden(acc, 0);
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
+    for (int s2 = 0; s2 < 8; ++s2) {
+        bf16x8 wn[4], bn = bx;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const float4 bb = *reinterpret_cast<const float4*>(b2 + 32 * r + 8 * q + 4 * h);
-            acc[r][4 * q] = bb.x;
-            acc[r][4 * q + 1] = bb.y;
-            acc[r][4 * q + 2] = bb.z;
-            acc[r][4 * q + 3] = bb.w;
-        }
+        for (int r = 0; r < 4; ++r) wn[r] = s2 < 7 ? f2[(r * 8 + s2 + 1) * 64 + lane] : w[r];
+        if (s2 < 7) bn = hidden(acc, s2 + 1);
 #pragma unroll
-    for (int s2 = 0; s2 < 8; ++s2)
+        for (int r = 0; r < 4; ++r) acc2[r] = mfma32(w[r], bx, acc2[r]);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) acc[r] = mfma32(f2[(r * 8 + s2) * 64 + lane], hb[s2], acc[r]);
-#pragma unroll
-    for (int s2 = 0; s2 < 8; ++s2)
-#pragma unroll
-        for (int j = 0; j < 8; ++j) hb[s2][j] = (__bf16)silu_f(acc[s2 >> 1][8 * (s2 & 1) + j]);
+        for (int r = 0; r < 4; ++r) w[r] = wn[r];
+        bx = bn;
+    }
     // layer 3: outputs in rows 4 tt .. 4 tt + 3 (other A rows zero)
     f32x16 o = {};
     const bf16x8 zero = {};
     const int o3 = m - 4 * tt;
     const bool row = o3 >= 0 && o3 < 4;
 #pragma unroll
-    for (int s2 = 0; s2 < 8; ++s2) o = mfma32(row ? f3[(s2 * 4 + o3) * 2 + h] : zero, hb[s2], o);
+    for (int s2 = 0; s2 < 8; ++s2) o = mfma32(row ? f3[(s2 * 4 + o3) * 2 + h] : zero, hidden(acc2, s2), o);
     if (h == tt) {
         y[0] = o[0] + b3[0];
         y[1] = o[1] + b3[1];
