@@ -65,3 +65,36 @@ __device__ __forceinline__ void mp_dense_record(const MapView& v, uint32_t c, fl
     m = *reinterpret_cast<const float4*>(b);
     n = *reinterpret_cast<const float4*>(b + 16);
 }
+
+// The hash lookup in two halves: the first slot of a point's probe sequence,
+// and the id found there or further on (-1: none).  As
+// mp_nnf_lookup<MP_NNF_HASH>; `valid` false finds nothing.
+struct HashProbe {
+    uint32_t key, h;   // key 0: outside the grid's box
+    uint2 s0;
+};
+
+__device__ __forceinline__ HashProbe mp_hash_probe(const MapView& v, float px, float py, float pz, bool valid) {
+    const uint32_t x = (uint32_t)floor_cell(px * v.inv_r) - (uint32_t)v.org[0];
+    const uint32_t y = (uint32_t)floor_cell(py * v.inv_r) - (uint32_t)v.org[1];
+    const uint32_t z = (uint32_t)floor_cell(pz * v.inv_r) - (uint32_t)v.org[2];
+    const bool in = valid & (x < (uint32_t)v.dim[0]) & (y < (uint32_t)v.dim[1]) & (z < (uint32_t)v.dim[2]);
+    HashProbe p;
+    p.key = in ? (z * (uint32_t)v.dim[1] + y) * (uint32_t)v.dim[0] + x + 1u : 0u;
+    p.h = in ? mp_grid_hash((int32_t)x, (int32_t)y, (int32_t)z) & v.mask : 0u;
+    p.s0 = v.table[p.h];
+    return p;
+}
+
+__device__ __forceinline__ int32_t mp_hash_find(const MapView& v, const HashProbe& p) {
+    int32_t g = p.s0.x == p.key && p.key != 0u ? (int32_t)p.s0.y : -1;
+    bool more = p.key != 0u && p.s0.x != p.key && p.s0.x != 0u;
+    uint32_t h = p.h;
+    while (more) {
+        h = (h + 1u) & v.mask;
+        const uint2 s = v.table[h];
+        if (s.x == p.key) g = (int32_t)s.y;
+        more = s.x != p.key && s.x != 0u;
+    }
+    return g;
+}

@@ -251,3 +251,26 @@ def test_refused_scan_leaves_the_last_one(room, n):
     f.scan_upload(good, cov6=cov)
     assert np.array_equal(f.debug_get("scan"), keep[0]) and np.array_equal(f.debug_get("scan_walk"), keep[1])
     f.close()
+
+
+@pytest.mark.parametrize("ns,batch", [(512, 2), (1023, 2), (1100, 4), (1100, 8)])
+def test_hash_lookups_of_a_batch(room, ns, batch):
+    # the hash map's probes are requested a batch at a time: the dense map's sums
+    R, t = room["w"]["traj"][0]
+    poses = S.gaussian_particles(2100, S.pose8(R, t), 0.3, 3.0, 3)   # some points leave the band's box
+    got = []
+    for backend in (M.MP_NNF_DENSE, M.MP_NNF_HASH):
+        m = M.Map(room["w"]["map_xyz"], voxel=0.5, backend=backend)
+        p = M.mp_filter_default_params(n_particles=len(poses), k=8, lsh_bits=16, svgd_iters=1, d_max=1.0,
+                                       lik_batch=batch, lik_layout=M.MP_LIK_LAYOUT_GROUPED)
+        f = M.Filter(m, p, poses=poses)
+        f.scan_upload(room["w"]["scans"][0][:ns])
+        f.debug_set("capture_hb", 1)
+        f.debug_stage(M.MP_STAGE_LSH)
+        f.debug_stage(M.MP_STAGE_SORT)
+        f.debug_stage(M.MP_STAGE_LIK)
+        got.append((f.debug_get("hb"), f.debug_get("psi")))
+        f.close()
+    assert np.array_equal(got[0][0], got[1][0]) and np.array_equal(got[0][1], got[1][1])
+    inliers = got[0][1][:, 7]
+    assert inliers.max() > 0 and inliers.min() < ns   # (some particles lie off the map)
