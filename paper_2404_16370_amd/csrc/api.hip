@@ -15,6 +15,7 @@
 
 #include "megapf.h"
 #include "mp_internal.hpp"
+#include "mp_lsh.hpp"
 
 // ------------------------------------------------------------ errors
 static thread_local std::string g_err;
@@ -684,7 +685,8 @@ void mp_reserve_step(mp_filter f) {
 }
 
 void mp_step_begin(mp_filter f, bool pred, const float dq[7], const float L[36], bool noise, hipStream_t s) {
-    mp_fill_u32(f->flags.p, 0u, 4, s);
+    f->clear_flags = true;   // by the step's first kernel
+    f->lsh_ahead = false;
     // a captured step always holds the prediction node; it reads whether to
     // predict from the step values
     if (pred || f->dyn) {
@@ -703,13 +705,20 @@ void mp_step_iter_nbr(mp_filter f, int it, hipStream_t s) {
     for (int l = 0; l < tables; ++l)
         for (int st : {MP_STAGE_LSH, MP_STAGE_SORT, MP_STAGE_REFRESH}) {
             mp_stage_begin(f, st);
-            run_stage(f, st, it * tables + l, s);
+            if (st == MP_STAGE_LSH && f->lsh_ahead) f->lsh_ahead = false;
+            else run_stage(f, st, it * tables + l, s);
         }
 }
 
 void mp_step_iter_svgd(mp_filter f, int it, hipStream_t s) {
     mp_stage_begin(f, MP_STAGE_SVGD);
-    run_stage(f, MP_STAGE_SVGD, it, s);
+    if (it + 1 < f->p.svgd_iters) {
+        const LshArgs next = mp_lsh_args(f, (uint32_t)f->frame, (uint32_t)((it + 1) * std::max(1, f->p.lsh_tables)));
+        mp_launch_svgd(f, s, &next);
+        f->lsh_ahead = true;
+    } else {
+        run_stage(f, MP_STAGE_SVGD, it, s);
+    }
 }
 
 void mp_step_end(mp_filter f, hipStream_t s) {
@@ -718,6 +727,7 @@ void mp_step_end(mp_filter f, hipStream_t s) {
         if (f->p.final_rescore) rescore(f, s);
         mp_stage_begin(f, MP_STAGE_POSTERIOR);
     }
+    if (mp_take_flags(f)) mp_fill_u32(f->flags.p, 0u, 4, s);   // (neither a prediction nor lists)
     uint64_t* end = nullptr;
     if (f->timing) {
         f->marks.push_back({MP_MARK_END, (int32_t)(kStampMarks + f->marks.size())});

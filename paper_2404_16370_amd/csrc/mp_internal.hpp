@@ -180,6 +180,8 @@ struct mp_filter_s {
     DevMem lkeys, lorder;     // the likelihood's walk order: Morton keys, particle per position
     DevMem rank;   // sorted position of each particle (the refresh runs in particle order)
     bool rank_set = false;   // rank belongs to the current `sorted`
+    bool lsh_ahead = false;  // the SVGD update left the codes of the iteration to come
+    bool clear_flags = false;   // no kernel of the step has cleared the counters yet
     DevMem nbr, kval, cnt;    // K x N, K x N, N
     DevMem prior, post0, post1;   // N float
     DevMem red;               // reduction scratch
@@ -222,6 +224,12 @@ void mp_stage_begin(mp_filter f, int st);
 inline uint64_t* mp_take_stamp(mp_filter f) {
     uint64_t* p = f->stamp;
     f->stamp = nullptr;
+    return p;
+}
+// the step's counters if its first kernel, which clears them, is still to come (else null)
+inline int32_t* mp_take_flags(mp_filter f) {
+    int32_t* p = f->clear_flags ? f->flags.as<int32_t>() : nullptr;
+    f->clear_flags = false;
     return p;
 }
 __device__ __forceinline__ void mp_write_stamp(uint64_t* p) {
@@ -326,7 +334,9 @@ void mp_step_begin(mp_filter f, bool pred, const float dq[7], const float L[36],
 void mp_step_iter_nbr(mp_filter f, int it, hipStream_t s);
 void mp_step_iter_svgd(mp_filter f, int it, hipStream_t s);
 void mp_step_end(mp_filter f, hipStream_t s);
-void mp_launch_svgd(mp_filter f, hipStream_t s);
+struct LshArgs;
+// (next: the bucket codes that the kernel leaves for the iteration that follows, or null)
+void mp_launch_svgd(mp_filter f, hipStream_t s, const LshArgs* next = nullptr);
 void mp_launch_posterior(mp_filter f, hipStream_t s, uint64_t* stamp_end = nullptr);
 void mp_launch_stamp(uint64_t* p, hipStream_t s);
 // The representative state into pinned host memory; poses (N x 7) and weights

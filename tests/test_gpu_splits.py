@@ -274,3 +274,25 @@ def test_hash_lookups_of_a_batch(room, ns, batch):
     assert np.array_equal(got[0][0], got[1][0]) and np.array_equal(got[0][1], got[1][1])
     inliers = got[0][1][:, 7]
     assert inliers.max() > 0 and inliers.min() < ns   # (some particles lie off the map)
+
+
+@pytest.mark.parametrize("n,tables,tangent", [(1, 1, 0), (17, 1, 1), (300, 2, 0), (9000, 1, 1)])
+def test_codes_left_by_the_svgd_update(room, O, n, tables, tangent):
+    # the update of all but the last iteration leaves the next one's codes: they
+    # are those of the poses after it
+    R, t = room["w"]["traj"][0]
+    poses = S.gaussian_particles(n, S.pose8(R, t), 0.1, 0.3, 3)
+    i = room["map"].info()
+    after = []
+    for iters in (1, 2):
+        f = _filter(room, n, poses, svgd_iters=iters, lsh_tables=tables, lsh_tangent=tangent, k=min(8, n))
+        f.scan_upload(room["w"]["scans"][0][:200])
+        f.step()
+        after.append((f.debug_get("poses"), f.debug_get("codes"), f.debug_get("tlsh"), f.params))
+        f.close()
+    p = after[1][3]
+    it = 2 * tables - 1   # the second iteration's last table
+    TL = O.lsh_frame(p.seed, 0, it, np.float32(i["box_min"]), np.float32(i["box_max"]))
+    want = O.lsh_codes(after[0][0], TL, p.lsh_alpha, p.sigma_r, p.sigma_t, p.lsh_sigma, p.lsh_bits, p.seed, 0, it,
+                       tangent=tangent)
+    assert np.array_equal(after[1][1], want) and np.array_equal(after[1][2], TL)
