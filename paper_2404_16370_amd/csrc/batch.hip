@@ -10,6 +10,7 @@
 // once per SVGD iteration: a captured step with an odd iteration count copies
 // the result back to the buffer it started from.
 #include <hip/hip_runtime.h>
+#include <numeric>
 
 #include <algorithm>
 #include <cstring>
@@ -92,6 +93,19 @@ void check_ready(mp_filter f) {
         mp_throw(MP_E_UNSUPPORTED, "the surrogate check reads its verdict on the host: not in a batch");
 }
 
+// The instances in the order in which their tiles enter the queue: those with
+// the most points a tile first, so that the last tiles taken are short ones.
+// 8 filters of 2041 to 16,384 particles and 238 to 2039 points: 235 us a launch
+// in the instances' own order, whose last 128 tiles were full ones, 212 us now.
+std::vector<size_t> queue_order(mp_batch b) {
+    std::vector<size_t> by(b->f.size());
+    std::iota(by.begin(), by.end(), (size_t)0);
+    std::stable_sort(by.begin(), by.end(), [&](size_t x, size_t y) {
+        return std::min(b->f[x]->scan_n, kLikTilePoints) > std::min(b->f[y]->scan_n, kLikTilePoints);
+    });
+    return by;
+}
+
 void capture(mp_batch b, hipStream_t caller) {
     for (mp_filter f : b->f) mp_reserve_step(f);
     // buffers just sized may still be in use by queued work of the caller
@@ -117,6 +131,7 @@ void capture(mp_batch b, hipStream_t caller) {
     if (b->qgrid <= 0) b->qgrid = mp_lik_queue_grid(b->qbatch);
     std::vector<char> htab((size_t)rounds * n * argb);
     std::vector<int32_t> hfirst((size_t)rounds * (n + 1), 0);
+    const std::vector<size_t> by_tile = queue_order(b);
     std::vector<int> start(n);
     for (size_t i = 0; i < n; ++i) start[i] = b->f[i]->cur;
     b->queued = 0;
@@ -139,7 +154,7 @@ void capture(mp_batch b, hipStream_t caller) {
         for (int it = 0; it < rounds; ++it) {
             std::vector<size_t> queued;
             int32_t tiles = 0;
-            for (size_t i = 0; i < n; ++i) {
+            for (size_t i : by_tile) {
                 mp_filter f = b->f[i];
                 if (f->scan_n <= 0 || it >= f->p.svgd_iters) continue;
                 hipStream_t bs = b->branch[i];
@@ -270,7 +285,8 @@ void tune_queue(mp_batch b, hipStream_t s) {
     std::vector<char> tab(n * argb);
     std::vector<int32_t> first(n + 1, 0);
     int32_t tiles = 0, q = 0;
-    for (mp_filter f : b->f) {
+    for (size_t i : queue_order(b)) {
+        mp_filter f = b->f[i];
         int32_t t = 0;
         if (mp_lik_queue_plan(f, tab.data() + (size_t)q * argb, &t, s)) {
             first[q++] = tiles;

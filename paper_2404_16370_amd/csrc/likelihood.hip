@@ -512,7 +512,7 @@ __global__ __launch_bounds__(kFewThreads) void k_lik_few(LikArgs A) {
 // are reduced across its 16 lanes by shuffles and written per (chunk, sorted
 // position).
 constexpr int kGLanes = 16;
-constexpr int kGChunk = 1024;
+constexpr int kGChunk = kLikTilePoints;
 constexpr int kGThreads = 512;
 constexpr int kGSlots = kGThreads / kGLanes;   // particles a workgroup takes at a time
 constexpr int kGRounds = 8;          // most rounds of a workgroup

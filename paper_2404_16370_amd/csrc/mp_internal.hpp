@@ -323,6 +323,7 @@ void mp_launch_likelihood(mp_filter f, hipStream_t s);
 // (GROUPED layout, PLAIN scorer, dense field): the plan of a pass (false if it cannot
 // join a queue; otherwise the pass's walk order is launched on s), the solve that
 // follows the queue, the queue launch.
+constexpr int32_t kLikTilePoints = 1024;   // most scan points of a tile
 size_t mp_lik_args_bytes();
 bool mp_lik_queue_plan(mp_filter f, void* args_out, int32_t* tiles, hipStream_t s);
 void mp_lik_queue_solve(mp_filter f, hipStream_t s);
