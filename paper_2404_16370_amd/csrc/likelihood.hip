@@ -520,13 +520,14 @@ constexpr int kGRounds = 8;          // most rounds of a workgroup
 // One tile of the grouped layout: scan chunk `chunk` (kGChunk points)
 // against the A.rounds * kGSlots particles of sorted block `pblk`; the whole
 // workgroup takes part (it stages the chunk in `tile`).
-template <int BACKEND, int BATCH, int SC>
+template <int BACKEND, int BATCH, int SC, int THREADS = kGThreads>
 __device__ __forceinline__ void grp_tile(const LikArgs& A, const int chunk, const int pblk, float4* tile) {
+    constexpr int kSlots = THREADS / kGLanes;   // particles taken at a time
     const int k0 = chunk * kGChunk;
     const int cnt = min(kGChunk, A.ns - k0);
     // the whole chunk is staged; records past the scan's end are zero (a
     // finite point at the origin that the walk below marks invalid)
-    for (int j = threadIdx.x; j < kGChunk; j += kGThreads) {
+    for (int j = threadIdx.x; j < kGChunk; j += THREADS) {
         float4 r0 = make_float4(0.0f, 0.0f, 0.0f, 0.0f), r1 = r0, r2 = r0;
         if (j < cnt) {
             r0 = A.scan[(size_t)(k0 + j) * 3];
@@ -544,7 +545,7 @@ __device__ __forceinline__ void grp_tile(const LikArgs& A, const int chunk, cons
     const float a = A.map.gicp_a;
     static_assert(kGChunk % (kGLanes * BATCH) == 0, "a batch never runs past the staged chunk");
     for (int round = 0; round < A.rounds; ++round) {
-        const int sp = (pblk * A.rounds + round) * kGSlots + grp;   // sorted position
+        const int sp = (pblk * A.rounds + round) * kSlots + grp;   // sorted position
         if (sp - grp >= A.n) break;                                 // (uniform) no particle left
         int i = sp < A.n ? (A.order ? A.order[sp] : sp) : 0;
         const bool active = sp < A.n && i >= 0 && i < A.n;
@@ -624,14 +625,14 @@ __device__ __forceinline__ void grp_tile(const LikArgs& A, const int chunk, cons
     }
 }
 
-template <int BACKEND, int BATCH, int SC>
-__global__ __launch_bounds__(kGThreads) void k_lik_grp(LikArgs A) {
+template <int BACKEND, int BATCH, int SC, int THREADS = kGThreads>
+__global__ __launch_bounds__(THREADS) void k_lik_grp(LikArgs A) {
     __shared__ float4 tile[kGChunk * 3];
     mp_write_stamp(A.stamp);
     const int nb = A.nbx * A.nchunks;
     const int logical = remap_xcd(blockIdx.x, nb);
     const int chunk = logical / A.nbx;
-    grp_tile<BACKEND, BATCH, SC>(A, chunk, logical - chunk * A.nbx, tile);
+    grp_tile<BACKEND, BATCH, SC, THREADS>(A, chunk, logical - chunk * A.nbx, tile);
 }
 
 // Persistent likelihood over the tiles of several filters (one pass each,
@@ -953,6 +954,16 @@ void launch_lik_few(LikArgs A, int nch, hipStream_t s) {
     else k_lik_few<BACKEND, 16><<<groups(16), kFewThreads, 0, s>>>(A);
 }
 
+// Grouped passes of up to a workgroup a CU wait for gathers, two waves or fewer
+// to a SIMD: eight points' gathers at a time (8192 x 1024 40.3 -> 38.9 us; from
+// 512 workgroups on two are faster, 67 -> 72 us at 8192 x 2048).  Passes of up
+// to half as many workgroups take workgroups of half the size, so that all CUs
+// have one (4096 x 1024 36.7 -> 28.9 us, 2048 x 512 20.1 -> 15.8; 6000 x 1024
+// 36.7 -> 37.3).  lik_rounds gives such passes one round.
+constexpr unsigned kGFewGroups = 256;
+constexpr unsigned kGHalfGroups = 128;
+static_assert(kGFewGroups < kSplitGroups, "one round");
+
 void mp_launch_likelihood(mp_filter f, hipStream_t s) {
     LikPlan P = lik_plan(f);
     lik_prepare_order(f, P.scorer, s);
@@ -982,6 +993,15 @@ void mp_launch_likelihood(mp_filter f, hipStream_t s) {
         } else if (f->p.lik_batch == 4) {
             if (dense) k_lik_grp<MP_NNF_DENSE, 4, MP_SCORER_PLAIN><<<grid, kGThreads, 0, s>>>(A);
             else k_lik_grp<MP_NNF_HASH, 4, MP_SCORER_PLAIN><<<grid, kGThreads, 0, s>>>(A);
+        } else if (f->p.lik_batch == 0 && dense && grid <= kGFewGroups) {
+            if (grid <= kGHalfGroups) {
+                LikArgs F = A;
+                F.nbx = (n + kGSlots / 2 - 1) / (kGSlots / 2);
+                k_lik_grp<MP_NNF_DENSE, 8, MP_SCORER_PLAIN, kGThreads / 2>
+                    <<<(unsigned)(F.nbx * nch), kGThreads / 2, 0, s>>>(F);
+            } else {
+                k_lik_grp<MP_NNF_DENSE, 8, MP_SCORER_PLAIN><<<grid, kGThreads, 0, s>>>(A);
+            }
         } else {   // 2, and the default: two records in flight keep the kernel at 94 VGPRs
             if (dense) k_lik_grp<MP_NNF_DENSE, 2, MP_SCORER_PLAIN><<<grid, kGThreads, 0, s>>>(A);
             else k_lik_grp<MP_NNF_HASH, 2, MP_SCORER_PLAIN><<<grid, kGThreads, 0, s>>>(A);

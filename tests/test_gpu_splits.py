@@ -296,3 +296,22 @@ def test_codes_left_by_the_svgd_update(room, O, n, tables, tangent):
     want = O.lsh_codes(after[0][0], TL, p.lsh_alpha, p.sigma_r, p.sigma_t, p.lsh_sigma, p.lsh_bits, p.seed, 0, it,
                        tangent=tangent)
     assert np.array_equal(after[1][1], want) and np.array_equal(after[1][2], TL)
+
+
+@pytest.mark.parametrize("n,ns", [(2048, 512), (2049, 1023), (4096, 1024), (4097, 1024), (4096, 1025), (8192, 600), (8193, 600)])
+def test_small_grouped_passes(room, n, ns):
+    # lik_batch = 0 takes smaller workgroups and more gathers at a time up to 128
+    # and 256 workgroups, 2 never: the same sums
+    R, t = room["w"]["traj"][0]
+    poses = S.gaussian_particles(n, S.pose8(R, t), 0.1, 0.3, 3)
+    got = []
+    for batch in (0, 2):
+        f = _filter(room, n, poses, lik_batch=batch, lik_layout=M.MP_LIK_LAYOUT_GROUPED)
+        f.scan_upload(room["w"]["scans"][0][:ns])
+        f.debug_set("capture_hb", 1)
+        for stage in (M.MP_STAGE_LSH, M.MP_STAGE_SORT, M.MP_STAGE_LIK):
+            f.debug_stage(stage)
+        got.append((f.debug_get("hb"), f.debug_get("psi")))
+        f.close()
+    assert np.array_equal(got[0][0], got[1][0]) and np.array_equal(got[0][1], got[1][1])
+    assert got[0][1][:, 7].max() > 0
