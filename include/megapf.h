@@ -383,7 +383,7 @@ MP_API mp_status mp_debug_map_point_knn(const float* xyz, int64_t n, const mp_ma
 
 /* Test access to the stable radix sort that distributes particles into LSH
  * buckets (Alg. 1, distribute loop): sorts keys[0..n), each below 2^bits
- * (bits 1..32; the sort makes one pass per 8 bits), equal keys keeping their
+ * (bits 1..32; the sort makes one pass per 8 to 10 bits), equal keys keeping their
  * input order, and writes the sorted keys to keys_out and, for each sorted
  * position, the input index of its key to order_out.  keys (n uint32), keys_out (n uint32) and
  * order_out (n int32) are host or device pointers; synchronises.  Errors:

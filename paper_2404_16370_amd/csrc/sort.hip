@@ -234,9 +234,9 @@ constexpr int kOsThreads = 512;
 constexpr int kOsWaves = kOsThreads / 64;
 constexpr int kOsItems = 8;                      // keys per thread: a wave ranks 8 rounds of 64
 constexpr int kOsTile = kOsThreads * kOsItems;   // 4096 keys per tile
-static_assert(kOsThreads == 512, "two threads per digit sum the histogram blocks");
 constexpr int kOsWaveKeys = kOsTile / kOsWaves;  // 512 consecutive keys per wave
 constexpr int kOsMaxPasses = 4;
+constexpr int kOsMaxCounts = 2 * 1024;           // passes times digits, at most (see os_plan)
 constexpr int kOsHistThreads = 1024;
 constexpr int kOsHistKeys = 16;                  // consecutive keys per histogram thread and round
 constexpr int kOsMaxHistBlocks = 64;
@@ -248,7 +248,7 @@ constexpr uint32_t kStInc = 2u << 30;            // the count of all keys up to 
 constexpr uint32_t kStVal = (1u << 30) - 1u;
 // scratch words: [0, 4) tile counters of the passes, [4] wait flag, then the
 // published words [pass][tile][digit], then the histogram blocks' counts
-// [block][pass][digit]
+// [block][pass][digit] in kOsMaxCounts words each
 constexpr int kOsHead = 16;
 
 __device__ inline uint32_t os_load(const uint32_t* p) {
@@ -261,9 +261,9 @@ __device__ inline void os_store(uint32_t* p, uint32_t v) {
 struct OsHistArgs {
     const uint32_t* __restrict__ keys;
     int64_t n;
-    int32_t passes;
+    int32_t passes, bits;            // bits per pass
     int32_t vec;                     // keys 16-byte aligned: read four at a time
-    uint32_t* __restrict__ part;     // [gridDim.x][kOsMaxPasses][256]
+    uint32_t* __restrict__ part;     // [gridDim.x][kOsMaxCounts]
     uint32_t* __restrict__ clear;    // counters, flag and published words: zeroed
     int64_t clear_words;
     uint64_t* stamp;                 // stage clock, or null
@@ -273,11 +273,13 @@ struct OsHistArgs {
 // keys and adds runs of equal digits with one LDS atomic per run (keys of a
 // converged filter share codes over long runs).
 __global__ __launch_bounds__(kOsHistThreads) void k_os_hist(OsHistArgs A) {
-    __shared__ uint32_t h[kOsMaxPasses * 256];
+    __shared__ uint32_t h[kOsMaxCounts];
     mp_write_stamp(A.stamp);
+    const int counts = A.passes << A.bits;
+    const uint32_t mask = (1u << A.bits) - 1u;
     const int64_t gt = (int64_t)blockIdx.x * kOsHistThreads + threadIdx.x;
     const int64_t gstride = (int64_t)gridDim.x * kOsHistThreads;
-    for (int j = threadIdx.x; j < kOsMaxPasses * 256; j += kOsHistThreads) h[j] = 0;
+    for (int j = threadIdx.x; j < counts; j += kOsHistThreads) h[j] = 0;
     for (int64_t j = gt; j < A.clear_words; j += gstride) A.clear[j] = 0;
     __syncthreads();
     for (int64_t i0 = gt * kOsHistKeys; i0 < A.n; i0 += gstride * kOsHistKeys) {
@@ -298,24 +300,23 @@ __global__ __launch_bounds__(kOsHistThreads) void k_os_hist(OsHistArgs A) {
         }
         const int cnt = (int)min<int64_t>(kOsHistKeys, A.n - i0);
         for (int p = 0; p < A.passes; ++p) {
-            uint32_t cur = (k[0] >> (8 * p)) & 255u, run = 1;
+            uint32_t cur = (k[0] >> (A.bits * p)) & mask, run = 1;
 #pragma unroll
             for (int c = 1; c < kOsHistKeys; ++c) {
-                const uint32_t d = (k[c] >> (8 * p)) & 255u;
+                const uint32_t d = (k[c] >> (A.bits * p)) & mask;
                 if (c < cnt && d == cur) {
                     ++run;
                 } else if (c < cnt) {
-                    atomicAdd(&h[p * 256 + cur], run);
+                    atomicAdd(&h[(p << A.bits) + cur], run);
                     cur = d;
                     run = 1;
                 }
             }
-            atomicAdd(&h[p * 256 + cur], run);
+            atomicAdd(&h[(p << A.bits) + cur], run);
         }
     }
     __syncthreads();
-    for (int j = threadIdx.x; j < kOsMaxPasses * 256; j += kOsHistThreads)
-        A.part[(size_t)blockIdx.x * kOsMaxPasses * 256 + j] = h[j];
+    for (int j = threadIdx.x; j < counts; j += kOsHistThreads) A.part[(size_t)blockIdx.x * kOsMaxCounts + j] = h[j];
 }
 
 struct OsScatterArgs {
@@ -325,25 +326,30 @@ struct OsScatterArgs {
     int32_t* __restrict__ vout;
     int64_t n;
     int32_t shift, pass, nhist;
-    const uint32_t* __restrict__ part;   // [nhist][kOsMaxPasses][256]
-    uint32_t* status;                    // this pass: [tiles][256], zero at launch
+    const uint32_t* __restrict__ part;   // [nhist][kOsMaxCounts]
+    uint32_t* status;                    // this pass: [tiles][digits], zero at launch
     uint32_t* ticket;                    // this pass's tile counter, zero at launch
     uint32_t* wait_flag;                 // 1: a look-back gave up; 2: a key fell outside the output
 };
 
-// One pass: the grid has exactly one workgroup per tile.
+// One pass over BITS-bit digits: the grid has exactly one workgroup per tile.
+template <int BITS>
 __global__ __launch_bounds__(kOsThreads) void k_os_scatter(OsScatterArgs A) {
-    __shared__ uint32_t wc[kOsWaves][256];   // per-wave digit counts, then the waves' exclusive offsets
+    constexpr int D = 1 << BITS;
+    constexpr int kPer = D > kOsThreads ? D / kOsThreads : 1;   // consecutive digits of a thread
+    constexpr int kOwners = D / kPer;                           // threads that hold digits
+    constexpr int kParts = D >= kOsThreads ? 1 : kOsThreads / D;   // threads that sum a digit's histogram blocks
+    __shared__ uint32_t wc[kOsWaves][D];     // per-wave digit counts, then the waves' exclusive offsets
     __shared__ uint32_t sk[kOsTile];
     __shared__ int32_t sv[kOsTile];
-    __shared__ uint32_t tstart[256];         // first local position of each digit in the tile
-    __shared__ uint32_t gbase[256];          // global position of a digit's keys minus tstart
-    __shared__ uint32_t htot[2][256];        // digit totals summed by the two halves of the workgroup
-    __shared__ uint32_t wsc[4], wsg[4];
+    __shared__ uint32_t tstart[D];           // first local position of each digit in the tile
+    __shared__ uint32_t gbase[D];            // global position of a digit's keys minus tstart
+    __shared__ uint32_t htot[kParts][D];     // digit totals summed by the parts of the workgroup
+    __shared__ uint32_t wsc[kOsWaves], wsg[kOsWaves];
     __shared__ uint32_t s_tile;
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
     if (t == 0) s_tile = atomicAdd(A.ticket, 1u);
-    for (int j = t; j < kOsWaves * 256; j += kOsThreads) (&wc[0][0])[j] = 0;
+    for (int j = t; j < kOsWaves * D; j += kOsThreads) (&wc[0][0])[j] = 0;
     __syncthreads();
     const uint32_t tile = s_tile;
     const int64_t tbase = (int64_t)tile * kOsTile;
@@ -356,32 +362,37 @@ __global__ __launch_bounds__(kOsThreads) void k_os_scatter(OsScatterArgs A) {
         key[r] = i < A.n ? A.kin[i] : 0u;
         val[r] = i < A.n ? A.vin[i] : 0;
     }
-    // digit totals of this pass over all keys, from the histogram blocks:
-    // each half of the workgroup sums every other block (loads in flight together)
+    // digit totals of this pass over all keys, from the histogram blocks: each
+    // part of the workgroup sums its share of them (loads in flight together)
     {
-        const int d = t & 255, hb = t >> 8;
-        uint32_t pv[kOsMaxHistBlocks / 2];
+        constexpr int kShare = kOsMaxHistBlocks / 2;
+        const int part = kParts > 1 ? t / D : 0;
+        for (int d = t % D; d < D; d += kOsThreads) {
+            uint32_t sum = 0;
+            for (int b0 = 0; b0 < A.nhist; b0 += kShare * kParts) {
+                uint32_t pv[kShare];
 #pragma unroll
-        for (int b = 0; b < kOsMaxHistBlocks / 2; ++b) {
-            const int blk = 2 * b + hb;
-            pv[b] = blk < A.nhist ? A.part[((size_t)blk * kOsMaxPasses + A.pass) * 256 + d] : 0u;
+                for (int b = 0; b < kShare; ++b) {
+                    const int blk = b0 + kParts * b + part;
+                    pv[b] = blk < A.nhist ? A.part[(size_t)blk * kOsMaxCounts + (A.pass << BITS) + d] : 0u;
+                }
+#pragma unroll
+                for (int b = 0; b < kShare; ++b) sum += pv[b];
+            }
+            htot[part][d] = sum;
         }
-        uint32_t sum = 0;
-#pragma unroll
-        for (int b = 0; b < kOsMaxHistBlocks / 2; ++b) sum += pv[b];
-        htot[hb][d] = sum;
     }
     // rank of each key among the keys of its wave with the same digit, in
-    // key order: the lanes of a round sharing the digit (eight ballots), plus
+    // key order: the lanes of a round sharing the digit (a ballot per bit), plus
     // the wave's running count of that digit from earlier rounds
     const uint64_t below = lane == 0 ? 0ull : (~0ull >> (64 - lane));
 #pragma unroll
     for (int r = 0; r < kOsItems; ++r) {
         const bool valid = wbase + r * 64 + lane < A.n;
-        const uint32_t d = (key[r] >> A.shift) & 255u;
+        const uint32_t d = (key[r] >> A.shift) & (D - 1u);
         uint64_t peers = __ballot(valid);
 #pragma unroll
-        for (int b = 0; b < 8; ++b) {
+        for (int b = 0; b < BITS; ++b) {
             const bool bit = (d >> b) & 1u;
             const uint64_t bb = __ballot(bit);
             peers &= bit ? bb : ~bb;
@@ -392,71 +403,87 @@ __global__ __launch_bounds__(kOsThreads) void k_os_scatter(OsScatterArgs A) {
         lr[r] = b0 + rk;
     }
     __syncthreads();
-    uint32_t cnt = 0, incc = 0, incg = 0, tot = 0;
-    if (t < 256) {
-        tot = htot[0][t] + htot[1][t];
-        for (int v = 0; v < kOsWaves; ++v) {
-            const uint32_t c = wc[v][t];
-            wc[v][t] = cnt;
-            cnt += c;
+    uint32_t cnt[kPer], tot[kPer], incc = 0, incg = 0;
+    if (t < kOwners) {
+        uint32_t sumc = 0, sumg = 0;
+#pragma unroll
+        for (int j = 0; j < kPer; ++j) {
+            const int d = t * kPer + j;
+            tot[j] = 0;
+            for (int part = 0; part < kParts; ++part) tot[j] += htot[part][d];
+            cnt[j] = 0;
+            for (int v = 0; v < kOsWaves; ++v) {
+                const uint32_t c = wc[v][d];
+                wc[v][d] = cnt[j];
+                cnt[j] += c;
+            }
+            os_store(A.status + (size_t)tile * D + d, (tile == 0 ? kStInc : kStAgg) | cnt[j]);
+            sumc += cnt[j];
+            sumg += tot[j];
         }
-        os_store(A.status + (size_t)tile * 256 + t, (tile == 0 ? kStInc : kStAgg) | cnt);
-        incc = wave_incl_scan(cnt, lane);
-        incg = wave_incl_scan(tot, lane);
+        incc = wave_incl_scan(sumc, lane);
+        incg = wave_incl_scan(sumg, lane);
         if (lane == 63) {
             wsc[w] = incc;
             wsg[w] = incg;
         }
+        incc -= sumc;   // exclusive
+        incg -= sumg;
     }
     __syncthreads();
-    if (t < 256) {
-        uint32_t bc = 0, bg = 0;
+    if (t < kOwners) {
         for (int v = 0; v < w; ++v) {
-            bc += wsc[v];
-            bg += wsg[v];
+            incc += wsc[v];
+            incg += wsg[v];
         }
-        const uint32_t ts = bc + incc - cnt;   // tile-local start of digit t
-        const uint32_t gs = bg + incg - tot;   // global start of digit t
-        // keys of digit t in the tiles before this one
-        uint32_t excl = 0;
-        int64_t tp = (int64_t)tile - 1;
-        uint32_t idle = 0;
-        while (tp >= 0) {
-            uint32_t st[kOsWindow];
 #pragma unroll
-            for (int k = 0; k < kOsWindow; ++k)
-                st[k] = tp - k >= 0 ? os_load(A.status + (size_t)(tp - k) * 256 + t) : kStInc;
-            int used = 0;
-            bool done = false;
+        for (int j = 0; j < kPer; ++j) {
+            const int d = t * kPer + j;
+            const uint32_t ts = incc;   // tile-local start of digit d
+            const uint32_t gs = incg;   // global start of digit d
+            incc += cnt[j];
+            incg += tot[j];
+            // keys of digit d in the tiles before this one
+            uint32_t excl = 0;
+            int64_t tp = (int64_t)tile - 1;
+            uint32_t idle = 0;
+            while (tp >= 0) {
+                uint32_t st[kOsWindow];
 #pragma unroll
-            for (int k = 0; k < kOsWindow; ++k) {
-                if (done || used < k) continue;              // stopped earlier in the window
-                const uint32_t sw = st[k];
-                if ((sw & ~kStVal) == 0u) continue;          // not published yet: read again from here
-                excl += sw & kStVal;
-                used = k + 1;
-                done = (sw & kStInc) != 0u;
-            }
-            if (done) break;
-            tp -= used;
-            if (used == 0) {
-                if (++idle > kOsSpinLimit) {
-                    os_store(A.wait_flag, 1u);
-                    break;
+                for (int k = 0; k < kOsWindow; ++k)
+                    st[k] = tp - k >= 0 ? os_load(A.status + (size_t)(tp - k) * D + d) : kStInc;
+                int used = 0;
+                bool done = false;
+#pragma unroll
+                for (int k = 0; k < kOsWindow; ++k) {
+                    if (done || used < k) continue;              // stopped earlier in the window
+                    const uint32_t sw = st[k];
+                    if ((sw & ~kStVal) == 0u) continue;          // not published yet: read again from here
+                    excl += sw & kStVal;
+                    used = k + 1;
+                    done = (sw & kStInc) != 0u;
                 }
-                __builtin_amdgcn_s_sleep(1);
+                if (done) break;
+                tp -= used;
+                if (used == 0) {
+                    if (++idle > kOsSpinLimit) {
+                        os_store(A.wait_flag, 1u);
+                        break;
+                    }
+                    __builtin_amdgcn_s_sleep(1);
+                }
             }
+            if (tile > 0) os_store(A.status + (size_t)tile * D + d, kStInc | (excl + cnt[j]));
+            tstart[d] = ts;
+            gbase[d] = gs + excl - ts;
         }
-        if (tile > 0) os_store(A.status + (size_t)tile * 256 + t, kStInc | (excl + cnt));
-        tstart[t] = ts;
-        gbase[t] = gs + excl - ts;
     }
     __syncthreads();
     // keys to their sorted places in the tile
 #pragma unroll
     for (int r = 0; r < kOsItems; ++r) {
         if (wbase + r * 64 + lane < A.n) {
-            const uint32_t d = (key[r] >> A.shift) & 255u;
+            const uint32_t d = (key[r] >> A.shift) & (D - 1u);
             const uint32_t lp = tstart[d] + wc[w][d] + lr[r];
             sk[lp] = key[r];
             sv[lp] = val[r];
@@ -469,7 +496,7 @@ __global__ __launch_bounds__(kOsThreads) void k_os_scatter(OsScatterArgs A) {
         const int j = r * kOsThreads + t;
         if (j < tn) {
             const uint32_t kk = sk[j];
-            const uint32_t pos = gbase[(kk >> A.shift) & 255u] + (uint32_t)j;
+            const uint32_t pos = gbase[(kk >> A.shift) & (D - 1u)] + (uint32_t)j;
             // a pass whose input is not a permutation of the counted keys (the
             // keys changed under the sort) could place a key past the end:
             // such keys are dropped and the sort flagged
@@ -667,33 +694,51 @@ int os_hist_blocks(int64_t n) {
     return (int)std::max<int64_t>(1, std::min<int64_t>(kOsMaxHistBlocks, (n + per - 1) / per));
 }
 
+// Bits per pass and passes.  Wider digits where they save a pass: of 9 bits at
+// any size (18-bit keys, hist and passes: 16,384 35 -> 24 us, 1,048,576 68 -> 51;
+// 27 bits 43 -> 33 and 87 -> 75), of 10 only for up to two passes over few keys
+// (20 bits: 16,384 34 -> 29 us, 65,536 35 -> 34, 262,144 46 -> 46, 1,048,576
+// 68 -> 80; three such passes, 30 bits: 16,384 42 -> 42, 65,536 46 -> 49).
+constexpr int64_t kOsWideMax = 32768;
+struct OsPlan {
+    int bits, passes;
+};
+
+OsPlan os_plan(int64_t n, int bits) {
+    const auto passes = [&](int b) { return (bits + b - 1) / b; };
+    if (passes(9) < passes(8)) return {9, passes(9)};
+    if (passes(10) < passes(8) && passes(10) <= 2 && n <= kOsWideMax) return {10, passes(10)};
+    return {8, std::min(kOsMaxPasses, passes(8))};
+}
+
 size_t os_scratch_words(int64_t n) {
-    return (size_t)kOsHead + (size_t)kOsMaxPasses * (size_t)os_tiles(n) * 256 +
-           (size_t)kOsMaxHistBlocks * kOsMaxPasses * 256;
+    return (size_t)kOsHead + (size_t)os_tiles(n) * kOsMaxCounts + (size_t)kOsMaxHistBlocks * kOsMaxCounts;
 }
 
 // Stable sort of 32-bit keys by their low `bits` bits (one launch for the
-// digit counts, one per 8-bit pass), ping-ponging with the alt arrays; the
+// digit counts, one per pass), ping-ponging with the alt arrays; the
 // result lands as in radix_sort.
 void onesweep_sort(uint32_t* keys, int32_t* vals, uint32_t* keys_alt, int32_t* vals_alt, int64_t n, int bits,
                    DevMem& scratch, hipStream_t s, bool copy_back, uint64_t* stamp = nullptr) {
     if (n <= 1 || bits <= 0) return;
     if (n > (int64_t)kStVal) mp_throw(MP_E_UNSUPPORTED, "radix sort of more than 2^30 - 1 keys");
-    const int passes = std::min(kOsMaxPasses, (bits + 7) / 8);
+    const OsPlan plan = os_plan(n, bits);
+    const int passes = plan.passes, digits = 1 << plan.bits;
     const int64_t tiles = os_tiles(n);
     const int nhist = os_hist_blocks(n);
     scratch.ensure(sizeof(uint32_t) * os_scratch_words(n));
     uint32_t* base = scratch.as<uint32_t>();
     uint32_t* status = base + kOsHead;
-    uint32_t* part = status + (size_t)kOsMaxPasses * (size_t)tiles * 256;
+    uint32_t* part = status + (size_t)tiles * kOsMaxCounts;
     OsHistArgs H;
     H.keys = keys;
     H.n = n;
     H.passes = passes;
+    H.bits = plan.bits;
     H.vec = ((uintptr_t)keys & 15u) == 0 ? 1 : 0;
     H.part = part;
     H.clear = base;
-    H.clear_words = kOsHead + (int64_t)passes * tiles * 256;
+    H.clear_words = kOsHead + (int64_t)passes * tiles * digits;
     H.stamp = stamp;
     k_os_hist<<<nhist, kOsHistThreads, 0, s>>>(H);
     MP_CHECK_LAUNCH();
@@ -708,14 +753,16 @@ void onesweep_sort(uint32_t* keys, int32_t* vals, uint32_t* keys_alt, int32_t* v
         A.kout = kb;
         A.vout = vb;
         A.n = n;
-        A.shift = 8 * p;
+        A.shift = plan.bits * p;
         A.pass = p;
         A.nhist = nhist;
         A.part = part;
-        A.status = status + (size_t)p * (size_t)tiles * 256;
+        A.status = status + (size_t)p * (size_t)tiles * digits;
         A.ticket = base + p;
         A.wait_flag = base + 4;
-        k_os_scatter<<<(unsigned)tiles, kOsThreads, 0, s>>>(A);
+        if (plan.bits == 8) k_os_scatter<8><<<(unsigned)tiles, kOsThreads, 0, s>>>(A);
+        else if (plan.bits == 9) k_os_scatter<9><<<(unsigned)tiles, kOsThreads, 0, s>>>(A);
+        else k_os_scatter<10><<<(unsigned)tiles, kOsThreads, 0, s>>>(A);
         MP_CHECK_LAUNCH();
         std::swap(ka, kb);
         std::swap(va, vb);
@@ -742,7 +789,7 @@ void mp_radix_sort_u32(uint32_t* keys, int32_t* vals, uint32_t* keys_alt, int32_
 }
 
 int mp_radix_passes(int64_t n, int bits) {
-    return (n <= 1 || bits <= 0) ? 0 : std::min(kOsMaxPasses, (bits + 7) / 8);
+    return (n <= 1 || bits <= 0) ? 0 : os_plan(n, bits).passes;
 }
 
 void mp_radix_sort_u32_inplace_parity(uint32_t* keys, int32_t* vals, uint32_t* keys_alt, int32_t* vals_alt, int64_t n,

@@ -315,3 +315,16 @@ def test_small_grouped_passes(room, n, ns):
         f.close()
     assert np.array_equal(got[0][0], got[1][0]) and np.array_equal(got[0][1], got[1][1])
     assert got[0][1][:, 7].max() > 0
+
+
+@pytest.mark.parametrize("n", [2, 4097, 32_768, 32_769, 300_001])
+@pytest.mark.parametrize("bits", [9, 10, 17, 18, 19, 20, 25, 27, 28])
+def test_sort_passes_of_wider_digits(n, bits):
+    # 9 bits a pass where that saves one, 10 up to 32,768 keys
+    rng = np.random.default_rng(n + bits)
+    random = rng.integers(0, 1 << bits, n, dtype=np.uint64).astype(np.uint32)
+    runs = np.repeat(rng.integers(0, 1 << bits, n // 700 + 1, dtype=np.uint64), 700)[:n].astype(np.uint32)
+    for keys in (random, runs, np.full(n, (1 << bits) - 1, np.uint32)):
+        out, order = M.debug_sort_u32(keys, bits)
+        ref = np.argsort(keys, kind="stable")
+        assert np.array_equal(order, ref.astype(np.int32)) and np.array_equal(out, keys[ref])
