@@ -755,8 +755,9 @@ __global__ __launch_bounds__(256) void k_solve(SolveArgs A) {
 }
 
 
-// Morton key (8 bits per axis over the map box, z y x interleaved from the
-// top bit) of each particle's translation, and the particle's index
+// Morton key (6 bits per axis over the map box, z y x interleaved from the
+// top bit: two passes of the sort; with 8 bits and three passes the likelihood
+// is no faster) of each particle's translation, and the particle's index
 __global__ void k_walk_keys(const float4* __restrict__ poses, int n, float lo0, float lo1, float lo2, float s0,
                             float s1, float s2, uint32_t* __restrict__ keys, int32_t* __restrict__ idx,
                             uint64_t* __restrict__ stamp) {
@@ -764,13 +765,13 @@ __global__ void k_walk_keys(const float4* __restrict__ poses, int n, float lo0, 
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const float4 t = poses[2 * i + 1];
-    const float c0 = fminf(fmaxf((t.x - lo0) * s0, 0.0f), 255.0f);
-    const float c1 = fminf(fmaxf((t.y - lo1) * s1, 0.0f), 255.0f);
-    const float c2 = fminf(fmaxf((t.z - lo2) * s2, 0.0f), 255.0f);
+    const float c0 = fminf(fmaxf((t.x - lo0) * s0, 0.0f), 63.0f);
+    const float c1 = fminf(fmaxf((t.y - lo1) * s1, 0.0f), 63.0f);
+    const float c2 = fminf(fmaxf((t.z - lo2) * s2, 0.0f), 63.0f);
     const uint32_t x = (uint32_t)c0, y = (uint32_t)c1, z = (uint32_t)c2;   // NaN -> 0
     uint32_t key = 0;
 #pragma unroll
-    for (int b = 7; b >= 0; --b) key = (key << 3) | (((z >> b) & 1u) << 2) | (((y >> b) & 1u) << 1) | ((x >> b) & 1u);
+    for (int b = 5; b >= 0; --b) key = (key << 3) | (((z >> b) & 1u) << 2) | (((y >> b) & 1u) << 1) | ((x >> b) & 1u);
     keys[i] = key;
     idx[i] = i;
 }
@@ -789,8 +790,12 @@ static bool lik_grouped(mp_filter f) {
 // them) gather records of one part of the map: 26.6 -> 24.6 ms per launch at
 // 1M x 8192 against the LSH order, whose adjacent codes are not neighbours in
 // space while the particles are spread.  The order changes no particle's sums.
+// Below 2^30 evaluations its sort (about 35 us) costs what it gives or more:
+// spread particles, sort and pass, 131,072 x 4096 1.84 ms in Morton and 1.86 in
+// LSH order, 65,536 x 4096 940 and 927 us, 32,768 x 4096 491 and 470 us, and
+// converged ones 65,536 x 4096 895 and 871 us.
 static bool lik_spatial(mp_filter f, int scorer) {
-    return scorer != MP_SCORER_SURROGATE && lik_grouped(f) && (int64_t)f->n * (int64_t)f->scan_n >= (1LL << 27);
+    return scorer != MP_SCORER_SURROGATE && lik_grouped(f) && (int64_t)f->n * (int64_t)f->scan_n >= (1LL << 30);
 }
 
 static const int32_t* lik_order(mp_filter f, int scorer) {
@@ -798,7 +803,7 @@ static const int32_t* lik_order(mp_filter f, int scorer) {
 }
 
 // the spatial walk order of the current poses into lorder (a stable sort of
-// the 24-bit keys: ties keep ascending particle index); the LSH sort's
+// the 18-bit keys: ties keep ascending particle index); the LSH sort's
 // ping-pong buffers and scratch are free while the likelihood runs
 static void lik_prepare_order(mp_filter f, int scorer, hipStream_t s) {
     if (!lik_spatial(f, scorer)) return;
@@ -806,9 +811,9 @@ static void lik_prepare_order(mp_filter f, int scorer, hipStream_t s) {
     float lo[3], sc[3];
     for (int a = 0; a < 3; ++a) {
         lo[a] = f->lsh_lo[a];
-        sc[a] = 256.0f / std::max(1e-3f, f->lsh_hi[a] - f->lsh_lo[a]);
+        sc[a] = 64.0f / std::max(1e-3f, f->lsh_hi[a] - f->lsh_lo[a]);
     }
-    constexpr int kBits = 24;
+    constexpr int kBits = 18;
     // start on the side that makes the last pass land in (lkeys, lorder)
     const bool odd = mp_radix_passes(n, kBits) % 2 == 1;
     uint32_t* k0 = odd ? f->tmp_keys.as<uint32_t>() : f->lkeys.as<uint32_t>();
