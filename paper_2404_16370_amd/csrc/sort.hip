@@ -535,7 +535,7 @@ __device__ __forceinline__ uint32_t wave_scan_dpp(uint32_t v) {
 //
 // What bounds it: LDS latency and the barriers of a pass, about 2 us each, and
 // one CU's loads and stores.  With bounds and positions, 20-bit keys: 256 keys
-// 11 us, 4096 15 us, 8000 23 us; the one-sweep sort and its bounds kernel, 27
+// 7 us, 4096 15 us, 8000 23 us; the one-sweep sort and its bounds kernel, 27
 // to 32 us and five launches whatever the count below 16,384 (where one
 // workgroup took 64 us).
 constexpr int kSmThreads = 1024;
@@ -557,15 +557,15 @@ struct SmSortArgs {
     uint64_t* stamp;      // stage clock, or null
 };
 
-template <int ITEMS>
-__global__ __launch_bounds__(kSmThreads) void k_sort_small(SmSortArgs A) {
-    __shared__ __attribute__((aligned(16))) uint32_t sk[kSmThreads * ITEMS];
-    __shared__ __attribute__((aligned(16))) uint16_t sv[kSmThreads * ITEMS];   // index of the key among the inputs
-    __shared__ __attribute__((aligned(16))) uint32_t cnt[kSmDigits * kSmThreads / 2];   // 16-bit counters [digit][thread]
-    __shared__ uint32_t wsum[kSmThreads / 64];
+template <int ITEMS, int T = kSmThreads>   // keys per thread, threads
+__global__ __launch_bounds__(T) void k_sort_small(SmSortArgs A) {
+    __shared__ __attribute__((aligned(16))) uint32_t sk[T * ITEMS];
+    __shared__ __attribute__((aligned(16))) uint16_t sv[T * ITEMS];   // index of the key among the inputs
+    __shared__ __attribute__((aligned(16))) uint32_t cnt[kSmDigits * T / 2];   // 16-bit counters [digit][thread]
+    __shared__ uint32_t wsum[T / 64];
     mp_write_stamp(A.stamp);
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-    for (int i = t; i < kSmThreads * ITEMS; i += kSmThreads) {
+    for (int i = t; i < T * ITEMS; i += T) {
         sk[i] = i < A.n ? A.kin[i] : 0u;
         sv[i] = (uint16_t)i;
     }
@@ -586,7 +586,7 @@ __global__ __launch_bounds__(kSmThreads) void k_sort_small(SmSortArgs A) {
 #pragma unroll
         for (int r = 0; r < ITEMS; ++r) {
             const uint32_t d = (key[r] >> shift) & (kSmDigits - 1);
-            if (t * ITEMS + r < A.n) atomicAdd(&cnt[d * (kSmThreads / 2) + (t >> 1)], one);
+            if (t * ITEMS + r < A.n) atomicAdd(&cnt[d * (T / 2) + (t >> 1)], one);
         }
         __syncthreads();
         {
@@ -599,7 +599,7 @@ __global__ __launch_bounds__(kSmThreads) void k_sort_small(SmSortArgs A) {
             if (lane == 63) wsum[w] = inc;
             __syncthreads();
             // the waves' totals: lane v of every wave holds the total of waves 0..v
-            const uint32_t tot = wave_scan_dpp(lane < kSmThreads / 64 ? wsum[lane] : 0u);
+            const uint32_t tot = wave_scan_dpp(lane < T / 64 ? wsum[lane] : 0u);
             const uint32_t wbase = w == 0 ? 0u : (uint32_t)__builtin_amdgcn_readlane((int)tot, w - 1);
             uint32_t run = wbase + inc - sum;
             uint32_t o[8];
@@ -621,7 +621,7 @@ __global__ __launch_bounds__(kSmThreads) void k_sort_small(SmSortArgs A) {
             const uint32_t d = (key[r] >> shift) & (kSmDigits - 1);
             pos[r] = 0;
             if (t * ITEMS + r < A.n)
-                pos[r] = (atomicAdd(&cnt[d * (kSmThreads / 2) + (t >> 1)], one) >> (16 * (t & 1))) & 0xFFFFu;
+                pos[r] = (atomicAdd(&cnt[d * (T / 2) + (t >> 1)], one) >> (16 * (t & 1))) & 0xFFFFu;
         }
 #pragma unroll
         for (int r = 0; r < ITEMS; ++r)
@@ -632,15 +632,15 @@ __global__ __launch_bounds__(kSmThreads) void k_sort_small(SmSortArgs A) {
         __syncthreads();
     }
     __syncthreads();
-    for (int i = t; i < A.n; i += kSmThreads) A.kout[i] = sk[i];
-    for (int i = t; i < A.n; i += kSmThreads) A.vout[i] = (int32_t)sv[i];
+    for (int i = t; i < A.n; i += T) A.kout[i] = sk[i];
+    for (int i = t; i < A.n; i += T) A.vout[i] = (int32_t)sv[i];
     if (!A.head) return;
     // bucket bounds: the last run start at or before a position, and the first
     // one after it, carried over the threads' consecutive positions by a scan
     // in each direction
-    __shared__ int wlast[kSmThreads / 64], wfirst[kSmThreads / 64];
-    uint16_t* sh = reinterpret_cast<uint16_t*>(cnt);   // heads, then (after them) ends: at most 4 kSmThreads ITEMS bytes
-    uint16_t* se = sh + kSmThreads * ITEMS;
+    __shared__ int wlast[T / 64], wfirst[T / 64];
+    uint16_t* sh = reinterpret_cast<uint16_t*>(cnt);   // heads, then (after them) ends: at most 4 T ITEMS bytes
+    uint16_t* se = sh + T * ITEMS;
     const int i0 = t * ITEMS;
     uint32_t starts = 0;   // bit r: position i0 + r starts a run (or is the end)
 #pragma unroll
@@ -664,7 +664,7 @@ __global__ __launch_bounds__(kSmThreads) void k_sort_small(SmSortArgs A) {
     if (lane == 0) before = -1;
     if (lane == 63) after = A.n;
 #pragma unroll
-    for (int v = 0; v < kSmThreads / 64; ++v) {
+    for (int v = 0; v < T / 64; ++v) {
         if (v < w) before = max(before, wlast[v]);
         if (v > w) after = min(after, wfirst[v]);
     }
@@ -680,7 +680,7 @@ __global__ __launch_bounds__(kSmThreads) void k_sort_small(SmSortArgs A) {
         }
     }
     __syncthreads();
-    for (int i = t; i < A.n; i += kSmThreads) {
+    for (int i = t; i < A.n; i += T) {
         A.head[i] = (int32_t)sh[i];
         A.end[i] = (int32_t)se[i];
         A.rank[i] = (int32_t)sk[i];
@@ -811,7 +811,13 @@ void mp_sort_small(const uint32_t* kin, uint32_t* kout, int32_t* vout, int32_t n
     A.n = n;
     A.bits = bits;
     A.stamp = stamp;
-    if (n <= kSmThreads * 4) k_sort_small<4><<<1, kSmThreads, 0, s>>>(A);
+    // fewer waves wait less at the barriers: 16-bit keys, 1000 of them 10.1 us
+    // with 1024 threads and 7.5 with 512, 2000 10.9 and 9.4, 4000 (8 a thread)
+    // 12.9 and 14.1
+    constexpr int kHalf = kSmThreads / 2;
+    if (n <= 2 * kHalf) k_sort_small<2, kHalf><<<1, kHalf, 0, s>>>(A);
+    else if (n <= 4 * kHalf) k_sort_small<4, kHalf><<<1, kHalf, 0, s>>>(A);
+    else if (n <= kSmThreads * 4) k_sort_small<4><<<1, kSmThreads, 0, s>>>(A);
     else k_sort_small<kSmItems><<<1, kSmThreads, 0, s>>>(A);
     MP_CHECK_LAUNCH();
 }

@@ -328,3 +328,10 @@ def test_sort_passes_of_wider_digits(n, bits):
         out, order = M.debug_sort_u32(keys, bits)
         ref = np.argsort(keys, kind="stable")
         assert np.array_equal(order, ref.astype(np.int32)) and np.array_equal(out, keys[ref])
+
+
+@pytest.mark.parametrize("n", [511, 512, 513, 2047, 2048, 2049])
+@pytest.mark.parametrize("bits", [4, 16, 24])
+def test_bucket_sort_of_half_a_workgroup(room, O, n, bits):
+    # up to 2048 keys 512 threads sort, 2 keys or 4 a thread
+    test_bucket_sort_bounds_and_ranks(room, O, n, bits)
