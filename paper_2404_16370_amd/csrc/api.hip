@@ -78,6 +78,14 @@ void DevMem::release() {
     part = false;
 }
 
+const void* ManyTab::put(const void* data, size_t n) {
+    const size_t at = (host.size() + 15) / 16 * 16;
+    if (at + n > dev.bytes) mp_throw(MP_E_STATE, "launch tables of %zu bytes are full", dev.bytes);
+    host.resize(at + n);
+    std::memcpy(host.data() + at, data, n);
+    return dev.as<char>() + at;
+}
+
 constexpr size_t kStampMarks = 2;   // clock values of a scan upload before those of a step
 
 constexpr size_t kPinnedQuery = 1 << 20;   // bytes of poses and weights that a query packs into pinned host memory

@@ -48,6 +48,8 @@ struct mp_batch_s {
     std::vector<hipEvent_t> pre;        // per instance: its lists are ready
     hipEvent_t lik_done = nullptr;
     DevMem qtab, qfirst, qcount;        // [round][instance] args, [round][instance + 1] first tiles, [round] counters
+    ManyTab many;                       // tables of the launches over several instances
+    hipEvent_t moved = nullptr;         // the update of those instances' particles is done
     int32_t qbatch = 2, qgrid = 0;      // gather batch and workgroups of the queue kernel
     int32_t queued = 0;                 // instances in the queue of the first round
     int64_t queue_tiles = 0;            // tiles per step through the queues
@@ -63,6 +65,7 @@ void release(mp_batch b) {
     for (hipEvent_t e : b->join) (void)hipEventDestroy(e);
     for (hipEvent_t e : b->pre) (void)hipEventDestroy(e);
     if (b->lik_done) (void)hipEventDestroy(b->lik_done);
+    if (b->moved) (void)hipEventDestroy(b->moved);
     if (b->fork) (void)hipEventDestroy(b->fork);
     if (b->uploaded) (void)hipEventDestroy(b->uploaded);
     if (b->host_dyn) (void)hipHostFree(b->host_dyn);
@@ -132,12 +135,23 @@ void capture(mp_batch b, hipStream_t caller) {
     std::vector<char> htab((size_t)rounds * n * argb);
     std::vector<int32_t> hfirst((size_t)rounds * (n + 1), 0);
     const std::vector<size_t> by_tile = queue_order(b);
+    // Instances whose likelihood is queued share the launches around it, as each
+    // waits for the queue in any case: some 30 kernels of a few us on the branches
+    // of a graph, at most four at a time, took 150 us an iteration beside the 212
+    // of the queue, four shared ones and the larger sorts 120 (8 instances of 2041
+    // to 16,384 particles: a step of ten iterations 3.8 -> 3.4 ms).  With one
+    // hash table a list; an instance with several keeps its branch.
+    std::vector<char> shared(n, 0);
+    for (size_t i = 0; i < n; ++i) shared[i] = mp_lik_queueable(b->f[i]) && b->f[i]->p.lsh_tables <= 1;
+    b->many.host.clear();
+    b->many.dev.ensure(std::max<size_t>(16, kManyBytes * (size_t)rounds * n));
     std::vector<int> start(n);
     for (size_t i = 0; i < n; ++i) start[i] = b->f[i]->cur;
     b->queued = 0;
     b->queue_tiles = 0;
     MP_HIP(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
     try {
+        if (rounds > 0) mp_fill_u32(b->qcount.p, 0u, (size_t)rounds, s);   // the queues' counters
         MP_HIP(hipEventRecord(b->fork, s));
         for (size_t i = 0; i < n; ++i) {
             mp_filter f = b->f[i];
@@ -152,43 +166,71 @@ void capture(mp_batch b, hipStream_t caller) {
         // one persistent launch over the tiles of all queued likelihood passes,
         // then each instance's solve and SVGD update
         for (int it = 0; it < rounds; ++it) {
+            std::vector<mp_filter> together, small;   // the instances that share launches, and those with a small sort
+            std::vector<size_t> large;
+            for (size_t i = 0; i < n; ++i) {
+                mp_filter f = b->f[i];
+                if (!shared[i] || it >= f->p.svgd_iters) continue;
+                const bool is_small = mp_sort_is_small(f->n);
+                together.push_back(f);
+                if (it == 0) mp_launch_lsh(f, (uint32_t)f->frame, 0, b->branch[i]);
+                f->lsh_ahead = false;
+                if (is_small) {
+                    small.push_back(f);
+                } else {
+                    large.push_back(i);
+                    if (it > 0) MP_HIP(hipStreamWaitEvent(b->branch[i], b->moved, 0));
+                    mp_launch_sort(f, b->branch[i]);
+                }
+                if (it == 0 || !is_small) MP_HIP(hipEventRecord(b->pre[i], b->branch[i]));
+                if (it == 0 && is_small) MP_HIP(hipStreamWaitEvent(s, b->pre[i], 0));
+            }
+            mp_many_sort(small, b->many, s);   // beside the larger ones
+            for (size_t i : large) MP_HIP(hipStreamWaitEvent(s, b->pre[i], 0));
+            mp_many_refresh(together, b->many, s);
             std::vector<size_t> queued;
             int32_t tiles = 0;
             for (size_t i : by_tile) {
                 mp_filter f = b->f[i];
                 if (f->scan_n <= 0 || it >= f->p.svgd_iters) continue;
-                hipStream_t bs = b->branch[i];
-                mp_step_iter_nbr(f, it, bs);
+                hipStream_t bs = shared[i] ? s : b->branch[i];
+                if (!shared[i]) mp_step_iter_nbr(f, it, bs);
                 int32_t t = 0;
                 char* slot = htab.data() + ((size_t)it * n + queued.size()) * argb;
                 if (mp_lik_queue_plan(f, slot, &t, bs)) {
                     hfirst[(size_t)it * (n + 1) + queued.size()] = tiles;
                     tiles += t;
                     queued.push_back(i);
-                    MP_HIP(hipEventRecord(b->pre[i], bs));
-                    MP_HIP(hipStreamWaitEvent(s, b->pre[i], 0));
+                    if (!shared[i]) {
+                        MP_HIP(hipEventRecord(b->pre[i], bs));
+                        MP_HIP(hipStreamWaitEvent(s, b->pre[i], 0));
+                    }
                 } else {
                     mp_launch_likelihood(f, bs);
                 }
             }
             if (!queued.empty()) {
                 int32_t* counter = b->qcount.as<int32_t>() + it;
-                mp_fill_u32(counter, 0u, 1, s);
                 mp_launch_lik_queue(b->qtab.as<char>() + (size_t)it * n * argb,
                                     b->qfirst.as<int32_t>() + (size_t)it * (n + 1), counter, (int)queued.size(),
                                     tiles, b->qbatch, b->qgrid, s);
                 MP_HIP(hipEventRecord(b->lik_done, s));
                 for (size_t i : queued) {
+                    if (shared[i]) continue;
                     MP_HIP(hipStreamWaitEvent(b->branch[i], b->lik_done, 0));
                     mp_lik_queue_solve(b->f[i], b->branch[i]);
                 }
                 if (it == 0) b->queued = (int32_t)queued.size();
                 b->queue_tiles += tiles;
             }
+            mp_many_solve(together, b->many, s);
+            mp_many_svgd(together, it, b->many, s);
+            MP_HIP(hipEventRecord(b->moved, s));
             for (size_t i = 0; i < n; ++i) {
                 mp_filter f = b->f[i];
                 if (f->scan_n <= 0 || it >= f->p.svgd_iters) continue;
-                mp_step_iter_svgd(f, it, b->branch[i]);
+                if (!shared[i]) mp_step_iter_svgd(f, it, b->branch[i]);
+                else if (it + 1 == f->p.svgd_iters) MP_HIP(hipStreamWaitEvent(b->branch[i], b->moved, 0));
             }
         }
         for (size_t i = 0; i < n; ++i) {
@@ -221,6 +263,9 @@ void capture(mp_batch b, hipStream_t caller) {
     // the queue tables hold pointers and sizes that stay fixed while the graph does
     if (rounds > 0) {
         MP_HIP(hipMemcpyAsync(b->qtab.p, htab.data(), htab.size(), hipMemcpyHostToDevice, caller));
+        if (!b->many.host.empty())
+            MP_HIP(hipMemcpyAsync(b->many.dev.p, b->many.host.data(), b->many.host.size(), hipMemcpyHostToDevice,
+                                  caller));
         MP_HIP(hipMemcpyAsync(b->qfirst.p, hfirst.data(), sizeof(int32_t) * hfirst.size(), hipMemcpyHostToDevice,
                               caller));
         MP_HIP(hipStreamSynchronize(caller));
@@ -369,6 +414,7 @@ void create_impl(void* p) {
         MP_HIP(hipEventCreateWithFlags(&b->fork, hipEventDisableTiming));
         MP_HIP(hipEventCreateWithFlags(&b->uploaded, hipEventDisableTiming));
         MP_HIP(hipEventCreateWithFlags(&b->lik_done, hipEventDisableTiming));
+        MP_HIP(hipEventCreateWithFlags(&b->moved, hipEventDisableTiming));
         MP_HIP(hipHostMalloc(reinterpret_cast<void**>(&b->host_dyn), sizeof(StepDyn) * (size_t)c.n,
                              hipHostMallocDefault));
         b->dyn.alloc(sizeof(StepDyn) * (size_t)c.n);

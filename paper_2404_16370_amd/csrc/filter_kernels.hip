@@ -7,6 +7,7 @@
 #include "mp_det.hpp"
 #include "mp_internal.hpp"
 #include "mp_lsh.hpp"
+#include "mp_many.hpp"
 
 namespace {
 
@@ -215,15 +216,14 @@ constexpr int kSvLanes = 16;
 // L.codes: leave the codes of the next iteration's buckets as well (a launch
 // less for each: ten iterations of 4096 particles 821 -> 794 us a frame)
 template <bool EXACT, bool TRANSPORT>
-__global__ __launch_bounds__(256) void k_svgd(SvgdArgs A, LshArgs L) {
+__device__ __forceinline__ void svgd_rows(const SvgdArgs& A, LshArgs L, int block) {
     __shared__ float term[256 / kSvLanes][7][33];
     __shared__ float sum[256 / kSvLanes][8];
     __shared__ float sL[8];
-    mp_write_stamp(A.stamp);
     if (L.dyn) L.frame = L.dyn->frame;
-    if (L.codes && threadIdx.x == 255) lsh_draw(L, sL);
+    if (L.codes && threadIdx.x == 255) lsh_draw(L, sL, block == 0);
     const int gl = threadIdx.x % kSvLanes, g = threadIdx.x / kSvLanes;
-    const int i0 = blockIdx.x * (256 / kSvLanes) + g;
+    const int i0 = block * (256 / kSvLanes) + g;
     const int i = min(i0, A.n - 1);
     mpdet::quat qi;
     float3 ti;
@@ -247,7 +247,7 @@ __global__ __launch_bounds__(256) void k_svgd(SvgdArgs A, LshArgs L) {
     __syncthreads();
     // one lane per particle again
     if (threadIdx.x >= 256 / kSvLanes) return;
-    const int p = blockIdx.x * (256 / kSvLanes) + threadIdx.x;
+    const int p = block * (256 / kSvLanes) + threadIdx.x;
     if (p >= A.n) return;
     load_pose(A.pin, p, qi, ti);
     float num[6];
@@ -255,6 +255,24 @@ __global__ __launch_bounds__(256) void k_svgd(SvgdArgs A, LshArgs L) {
     svgd_move(A, p, qi, ti, num, sum[threadIdx.x][6]);
     if (L.codes)
         lsh_code(L, sL, p, make_float4(qi.w, qi.x, qi.y, qi.z), make_float4(ti.x, ti.y, ti.z, 0.0f));
+}
+
+template <bool EXACT, bool TRANSPORT>
+__global__ __launch_bounds__(256) void k_svgd(SvgdArgs A, LshArgs L) {
+    mp_write_stamp(A.stamp);
+    svgd_rows<EXACT, TRANSPORT>(A, L, blockIdx.x);
+}
+
+struct SvgdLsh {
+    SvgdArgs A;
+    LshArgs L;
+};
+
+template <bool EXACT, bool TRANSPORT>
+__global__ __launch_bounds__(256) void k_svgd_many(Many<SvgdLsh> M) {
+    int block;
+    const SvgdLsh q = many_args(M, block);
+    svgd_rows<EXACT, TRANSPORT>(q.A, q.L, block);
 }
 
 // ------------------------------------------------------------ prediction
@@ -766,8 +784,10 @@ __global__ void k_stamp(uint64_t* p) { mp_write_stamp(p); }
 
 }  // namespace
 
-void mp_launch_svgd(mp_filter f, hipStream_t s, const LshArgs* next) {
-    SvgdArgs A;
+// (leaves the update's poses current)
+static SvgdLsh svgd_args(mp_filter f, const LshArgs* next) {
+    SvgdLsh q;
+    SvgdArgs& A = q.A;
     A.pin = f->poses[f->cur].as<float4>();
     A.pout = f->poses[1 - f->cur].as<float4>();
     A.psi = f->psi.as<float4>();
@@ -777,20 +797,57 @@ void mp_launch_svgd(mp_filter f, hipStream_t s, const LshArgs* next) {
     A.K = f->K;
     A.sr = f->p.sigma_r;
     A.st = f->p.sigma_t;
-    A.stamp = mp_take_stamp(f);
-    const bool exact = f->p.svgd_grad == MP_SVGD_GRAD_EXACT;
-    const bool transport = f->p.svgd_transport == MP_SVGD_TRANSPORT_ADJOINT;
-    const unsigned grid = nblk(f->n, 256 / kSvLanes);
-    LshArgs L;
-    L.codes = nullptr;
-    L.dyn = nullptr;
-    if (next) L = *next;
-    if (exact && transport) k_svgd<true, true><<<grid, 256, 0, s>>>(A, L);
-    else if (exact) k_svgd<true, false><<<grid, 256, 0, s>>>(A, L);
-    else if (transport) k_svgd<false, true><<<grid, 256, 0, s>>>(A, L);
-    else k_svgd<false, false><<<grid, 256, 0, s>>>(A, L);
-    MP_CHECK_LAUNCH();
+    A.stamp = nullptr;
+    if (next) {
+        q.L = *next;
+    } else {
+        q.L.codes = nullptr;
+        q.L.dyn = nullptr;
+    }
     f->cur = 1 - f->cur;
+    return q;
+}
+
+static int svgd_kind(mp_filter f) {
+    return (f->p.svgd_grad == MP_SVGD_GRAD_EXACT ? 2 : 0) + (f->p.svgd_transport == MP_SVGD_TRANSPORT_ADJOINT ? 1 : 0);
+}
+
+void mp_launch_svgd(mp_filter f, hipStream_t s, const LshArgs* next) {
+    SvgdLsh q = svgd_args(f, next);
+    q.A.stamp = mp_take_stamp(f);
+    const unsigned grid = nblk(f->n, 256 / kSvLanes);
+    switch (svgd_kind(f)) {
+        case 3: k_svgd<true, true><<<grid, 256, 0, s>>>(q.A, q.L); break;
+        case 2: k_svgd<true, false><<<grid, 256, 0, s>>>(q.A, q.L); break;
+        case 1: k_svgd<false, true><<<grid, 256, 0, s>>>(q.A, q.L); break;
+        default: k_svgd<false, false><<<grid, 256, 0, s>>>(q.A, q.L);
+    }
+    MP_CHECK_LAUNCH();
+}
+
+void mp_many_svgd(const std::vector<mp_filter>& fs, int it, ManyTab& T, hipStream_t s) {
+    for (int kind = 0; kind < 4; ++kind) {
+        std::vector<SvgdLsh> a;
+        std::vector<int32_t> blocks;
+        for (mp_filter f : fs) {
+            if (svgd_kind(f) != kind) continue;
+            const bool more = it + 1 < f->p.svgd_iters;
+            const LshArgs next = mp_lsh_args(f, (uint32_t)f->frame, (uint32_t)((it + 1) * std::max(1, f->p.lsh_tables)));
+            a.push_back(svgd_args(f, more ? &next : nullptr));
+            f->lsh_ahead = more;
+            blocks.push_back((int32_t)nblk(f->n, 256 / kSvLanes));
+        }
+        if (a.empty()) continue;
+        unsigned grid;
+        const Many<SvgdLsh> M = many_table(T, a, blocks, grid);
+        switch (kind) {
+            case 3: k_svgd_many<true, true><<<grid, 256, 0, s>>>(M); break;
+            case 2: k_svgd_many<true, false><<<grid, 256, 0, s>>>(M); break;
+            case 1: k_svgd_many<false, true><<<grid, 256, 0, s>>>(M); break;
+            default: k_svgd_many<false, false><<<grid, 256, 0, s>>>(M);
+        }
+        MP_CHECK_LAUNCH();
+    }
 }
 
 void mp_launch_predict(mp_filter f, const float dT[7], const float L[36], bool noise, hipStream_t s,

@@ -33,6 +33,7 @@
 #include "mp_det.hpp"
 #include "mp_internal.hpp"
 #include "mp_lookup.hpp"
+#include "mp_many.hpp"
 #include "mp_solve.hpp"
 
 namespace {
@@ -705,9 +706,8 @@ struct SolveArgs {
     uint64_t* stamp;             // stage clock, or null
 };
 
-__global__ __launch_bounds__(256) void k_solve(SolveArgs A) {
-    mp_write_stamp(A.stamp);
-    const int col = blockIdx.x * blockDim.x + threadIdx.x;   // partial column
+__device__ __forceinline__ void solve_column(const SolveArgs& A, int block) {
+    const int col = block * blockDim.x + threadIdx.x;   // partial column
     if (col >= A.n) return;
     const int i = A.order ? A.order[col] : col;
     if (i < 0 || i >= A.n) return;
@@ -754,6 +754,16 @@ __global__ __launch_bounds__(256) void k_solve(SolveArgs A) {
     }
 }
 
+__global__ __launch_bounds__(256) void k_solve(SolveArgs A) {
+    mp_write_stamp(A.stamp);
+    solve_column(A, blockIdx.x);
+}
+
+__global__ __launch_bounds__(256) void k_solve_many(Many<SolveArgs> M) {
+    int block;
+    const SolveArgs A = many_args(M, block);
+    solve_column(A, block);
+}
 
 // Morton key (6 bits per axis over the map box, z y x interleaved from the
 // top bit: two passes of the sort; with 8 bits and three passes the likelihood
@@ -914,7 +924,7 @@ LikPlan lik_plan(mp_filter f) {
 
 // psi, log-likelihood and inliers from the pass's chunk partials (GROUPED:
 // indexed by position in the pass's walk order)
-void lik_solve(mp_filter f, bool grouped, int nch, const int32_t* order, hipStream_t s) {
+SolveArgs solve_args(mp_filter f, bool grouped, int nch, const int32_t* order) {
     const int n = f->n;
     const int ns = f->scan_n;
     SolveArgs S;
@@ -930,8 +940,14 @@ void lik_solve(mp_filter f, bool grouped, int nch, const int32_t* order, hipStre
     S.cmax = f->p.c_max;
     S.lam_rel = f->p.lambda_rel;
     S.lam_abs = f->p.lambda_abs;
+    S.stamp = nullptr;
+    return S;
+}
+
+void lik_solve(mp_filter f, bool grouped, int nch, const int32_t* order, hipStream_t s) {
+    SolveArgs S = solve_args(f, grouped, nch, order);
     S.stamp = mp_take_stamp(f);
-    k_solve<<<(n + 255) / 256, 256, 0, s>>>(S);
+    k_solve<<<(S.n + 255) / 256, 256, 0, s>>>(S);
     MP_CHECK_LAUNCH();
 }
 }  // namespace
@@ -1037,10 +1053,29 @@ void mp_launch_likelihood(mp_filter f, hipStream_t s) {
 // ------------------------------------------------------------ tile queue
 size_t mp_lik_args_bytes() { return sizeof(LikArgs); }
 
+bool mp_lik_queueable(mp_filter f) {
+    return f->scan_n > 0 && lik_grouped(f) && lik_plan(f).scorer == MP_SCORER_PLAIN &&
+           f->map->view.backend == MP_NNF_DENSE;
+}
+
+void mp_many_solve(const std::vector<mp_filter>& fs, ManyTab& T, hipStream_t s) {
+    std::vector<SolveArgs> a;
+    std::vector<int32_t> blocks;
+    for (mp_filter f : fs) {
+        const LikPlan P = lik_plan(f);
+        a.push_back(solve_args(f, P.grouped, P.nch, P.A.order));
+        blocks.push_back((f->n + 255) / 256);
+    }
+    if (a.empty()) return;
+    unsigned grid;
+    const Many<SolveArgs> M = many_table(T, a, blocks, grid);
+    k_solve_many<<<grid, 256, 0, s>>>(M);
+    MP_CHECK_LAUNCH();
+}
+
 bool mp_lik_queue_plan(mp_filter f, void* args_out, int32_t* tiles, hipStream_t s) {
-    if (f->scan_n <= 0) return false;
+    if (!mp_lik_queueable(f)) return false;
     const LikPlan P = lik_plan(f);
-    if (!P.grouped || P.scorer != MP_SCORER_PLAIN || P.A.map.backend != MP_NNF_DENSE) return false;
     lik_prepare_order(f, P.scorer, s);
     std::memcpy(args_out, &P.A, sizeof(LikArgs));
     *tiles = P.A.nbx * P.nch;

@@ -52,6 +52,14 @@ struct DevMem {
     }
 };
 
+// Tables of a captured graph's launches: filled on the host while the graph is
+// captured, in device memory (of fixed size) before it runs.
+struct ManyTab {
+    DevMem dev;
+    std::vector<char> host;
+    const void* put(const void* data, size_t bytes);   // device address of a copy
+};
+
 // Owning allocation of pinned host memory, which kernels write directly.
 struct HostMem {
     void* p = nullptr;
@@ -258,9 +266,20 @@ void mp_radix_sort_u32_inplace_parity(uint32_t* keys, int32_t* vals, uint32_t* k
 // launch: the sorted keys (kout may be kin), the input index of each, and in
 // head, end and rank (or null) the bucket bounds of every position and the
 // position of every input
+// arguments of a sort of few keys in one workgroup
+struct SmSortArgs {
+    const uint32_t* kin;
+    uint32_t* kout;       // may be kin
+    int32_t* vout;        // input index of each sorted key
+    int32_t* head;        // bucket bounds per position and position of each value, or null
+    int32_t* end;
+    int32_t* rank;
+    int32_t n, bits;
+    uint64_t* stamp;      // stage clock, or null
+};
 bool mp_sort_is_small(int64_t n);
-void mp_sort_small(const uint32_t* kin, uint32_t* kout, int32_t* vout, int32_t n, int bits,
-                   int32_t* head, int32_t* end, int32_t* rank, hipStream_t s, uint64_t* stamp = nullptr);
+void mp_sort_small(const SmSortArgs& A, hipStream_t s);
+void mp_sort_small_many(const std::vector<SmSortArgs>& a, ManyTab& T, hipStream_t s);
 // device word of a 32-bit sort's scratch, zero after a good sort: 1 if a
 // workgroup stopped waiting for its predecessors' counts, 2 if a key's place
 // fell outside the output (its input changed while it ran); neither is
@@ -330,6 +349,15 @@ void mp_lik_queue_solve(mp_filter f, hipStream_t s);
 int mp_lik_queue_grid(int batch);
 void mp_launch_lik_queue(const void* tab_dev, const int32_t* first_dev, int32_t* counter_dev, int n_inst, int tiles,
                          int batch, int grid, hipStream_t s);
+// One launch over several filters for each stage of an iteration around a
+// queued likelihood pass (results as by the filters' own launches): bucket sorts
+// of filters that take a small one, refreshes, solves, SVGD updates of iteration it
+constexpr size_t kManyBytes = 1024;   // most table bytes of a filter in the four
+void mp_many_sort(const std::vector<mp_filter>& fs, ManyTab& T, hipStream_t s);
+void mp_many_refresh(const std::vector<mp_filter>& fs, ManyTab& T, hipStream_t s);
+void mp_many_solve(const std::vector<mp_filter>& fs, ManyTab& T, hipStream_t s);
+void mp_many_svgd(const std::vector<mp_filter>& fs, int it, ManyTab& T, hipStream_t s);
+bool mp_lik_queueable(mp_filter f);   // mp_lik_queue_plan would say true
 // the phases of mp_step_launches (a batch interleaves them across filters)
 void mp_step_begin(mp_filter f, bool pred, const float dq[7], const float L[36], bool noise, hipStream_t s);
 void mp_step_iter_nbr(mp_filter f, int it, hipStream_t s);

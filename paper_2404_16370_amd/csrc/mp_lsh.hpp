@@ -25,14 +25,14 @@ struct LshArgs {
 };
 LshArgs mp_lsh_args(mp_filter f, uint32_t frame, uint32_t it);
 
-// T^LSH is the same for every particle: one lane of a workgroup draws it
-__device__ __forceinline__ void lsh_draw(const LshArgs& A, float* sL) {
+// T^LSH is the same for every particle: one lane of a workgroup draws it (and one records it)
+__device__ __forceinline__ void lsh_draw(const LshArgs& A, float* sL, bool record) {
     mpdet::quat q0;
     float3 t0;
     mpdet::random_pose(A.seed, 0u, A.frame, A.it, mpdet::PURPOSE_TLSH, A.lo, A.hi, q0, t0);
     sL[0] = q0.w; sL[1] = q0.x; sL[2] = q0.y; sL[3] = q0.z;
     sL[4] = t0.x; sL[5] = t0.y; sL[6] = t0.z; sL[7] = 0.0f;
-    if (blockIdx.x == 0)
+    if (record)
         for (int k = 0; k < 8; ++k) A.tlsh[k] = sL[k];
 }
 

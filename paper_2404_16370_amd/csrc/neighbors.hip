@@ -23,6 +23,7 @@
 #include "mp_det.hpp"
 #include "mp_internal.hpp"
 #include "mp_lsh.hpp"
+#include "mp_many.hpp"
 #include "mp_row.hpp"
 
 namespace {
@@ -33,7 +34,7 @@ __global__ __launch_bounds__(256) void k_lsh(LshArgs A) {
     if (A.dyn) A.frame = A.dyn->frame;
     if (A.flags && i < 4) A.flags[i] = 0;
     __shared__ float sL[8];
-    if (threadIdx.x == 0) lsh_draw(A, sL);
+    if (threadIdx.x == 0) lsh_draw(A, sL, blockIdx.x == 0);
     __syncthreads();
     if (i < A.n) lsh_code(A, sL, i, A.poses[2 * i], A.poses[2 * i + 1]);
 }
@@ -202,10 +203,9 @@ constexpr int kRfLanes = 16;
 constexpr int kRfMax = 98304;   // most particles
 
 template <int R>
-__global__ __launch_bounds__(256) void k_refresh_row(RefreshArgs A) {
-    mp_write_stamp(A.stamp);
+__device__ __forceinline__ void refresh_row(const RefreshArgs& A, int block) {
     const int gl = threadIdx.x % kRfLanes;
-    const int i0 = blockIdx.x * (256 / kRfLanes) + threadIdx.x / kRfLanes;
+    const int i0 = block * (256 / kRfLanes) + threadIdx.x / kRfLanes;
     const int i = min(i0, A.n - 1);
     const int s = A.rank[i];
     const bool active = i0 < A.n && s >= 0 && s < A.n && A.sorted[max(0, min(s, A.n - 1))] == i;   // uniform over the row
@@ -303,6 +303,19 @@ __global__ void k_reset_lists(int32_t* __restrict__ nbr, float* __restrict__ kva
     prior[i] = 1.0f / (float)n;
 }
 
+template <int R>
+__global__ __launch_bounds__(256) void k_refresh_row(RefreshArgs A) {
+    mp_write_stamp(A.stamp);
+    refresh_row<R>(A, blockIdx.x);
+}
+
+template <int R>
+__global__ __launch_bounds__(256) void k_refresh_row_many(Many<RefreshArgs> M) {
+    int block;
+    const RefreshArgs A = many_args(M, block);
+    refresh_row<R>(A, block);
+}
+
 inline unsigned nblk(int64_t n, int b = 256) { return (unsigned)((n + b - 1) / b); }
 
 }  // namespace
@@ -344,15 +357,21 @@ void mp_launch_lsh(mp_filter f, uint32_t frame, uint32_t it, hipStream_t s) {
     MP_CHECK_LAUNCH();
 }
 
+static SmSortArgs small_sort_args(mp_filter f) {
+    // the LSH kernel's buffers, see there
+    const bool odd = mp_radix_passes(f->n, f->p.lsh_bits) % 2 == 1;
+    return SmSortArgs{odd ? f->tmp_keys.as<uint32_t>() : f->scodes.as<uint32_t>(), f->scodes.as<uint32_t>(),
+                      f->sorted.as<int32_t>(), f->head.as<int32_t>(), f->end.as<int32_t>(), f->rank.as<int32_t>(),
+                      f->n, f->n > 1 ? f->p.lsh_bits : 0, nullptr};
+}
+
 void mp_launch_sort(mp_filter f, hipStream_t s) {
     const int n = f->n;
     f->rank_set = true;
     if (mp_sort_is_small(n)) {
-        // the LSH kernel's buffers, see there
-        const bool odd = mp_radix_passes(n, f->p.lsh_bits) % 2 == 1;
-        mp_sort_small(odd ? f->tmp_keys.as<uint32_t>() : f->scodes.as<uint32_t>(),
-                      f->scodes.as<uint32_t>(), f->sorted.as<int32_t>(), n, n > 1 ? f->p.lsh_bits : 0, f->head.as<int32_t>(),
-                      f->end.as<int32_t>(), f->rank.as<int32_t>(), s, mp_take_stamp(f));
+        SmSortArgs A = small_sort_args(f);
+        A.stamp = mp_take_stamp(f);
+        mp_sort_small(A, s);
         return;
     }
     // stable sort of (code, index) from the buffers the LSH kernel filled;
@@ -372,14 +391,9 @@ void mp_launch_sort(mp_filter f, hipStream_t s) {
     MP_CHECK_LAUNCH();
 }
 
-void mp_launch_refresh(mp_filter f, hipStream_t s, int window) {
-    if (!f->rank_set) {
-        k_rank<<<nblk(f->n), 256, 0, s>>>(f->sorted.as<int32_t>(), f->n, f->rank.as<int32_t>());
-        MP_CHECK_LAUNCH();
-        f->rank_set = true;
-    }
+static RefreshArgs refresh_args(mp_filter f, int window) {
     RefreshArgs A;
-    A.stamp = mp_take_stamp(f);
+    A.stamp = nullptr;
     A.poses = f->poses[f->cur].as<float4>();
     A.sorted = f->sorted.as<int32_t>();
     A.rank = f->rank.as<int32_t>();
@@ -393,20 +407,68 @@ void mp_launch_refresh(mp_filter f, hipStream_t s, int window) {
     A.C = window < 0 ? f->p.window_c : window;
     A.sr = f->p.sigma_r;
     A.st = f->p.sigma_t;
+    return A;
+}
+
+// candidates per lane of the row kernel, or 0: one lane per particle
+static int refresh_rows(mp_filter f, int C) {
     // 16 lanes per particle while one lane each would leave most of the chip
     // waiting for its loads, and for windows whose candidates fit five a lane.
     // K = 16, window 32, one lane / 16 lanes: 4096 particles 47 / 8.6 us,
     // 65,536 58 / 39 us, 131,072 70 / 70 us, 262,144 94 / 132 us.
-    const int64_t cands = (int64_t)A.C + f->K - 1;
-    if (f->n <= kRfMax && cands <= 5 * kRfLanes) {
+    const int64_t cands = (int64_t)C + f->K - 1;
+    if (f->n > kRfMax || cands > 5 * kRfLanes) return 0;
+    return cands <= 2 * kRfLanes ? 2 : (cands <= 3 * kRfLanes ? 3 : 5);
+}
+
+void mp_launch_refresh(mp_filter f, hipStream_t s, int window) {
+    if (!f->rank_set) {
+        k_rank<<<nblk(f->n), 256, 0, s>>>(f->sorted.as<int32_t>(), f->n, f->rank.as<int32_t>());
+        MP_CHECK_LAUNCH();
+        f->rank_set = true;
+    }
+    RefreshArgs A = refresh_args(f, window);
+    A.stamp = mp_take_stamp(f);
+    const int R = refresh_rows(f, A.C);
+    if (R) {
         const unsigned grid = nblk(f->n, 256 / kRfLanes);
-        if (cands <= 2 * kRfLanes) k_refresh_row<2><<<grid, 256, 0, s>>>(A);
-        else if (cands <= 3 * kRfLanes) k_refresh_row<3><<<grid, 256, 0, s>>>(A);
+        if (R == 2) k_refresh_row<2><<<grid, 256, 0, s>>>(A);
+        else if (R == 3) k_refresh_row<3><<<grid, 256, 0, s>>>(A);
         else k_refresh_row<5><<<grid, 256, 0, s>>>(A);
     } else if (f->K <= 8) k_refresh<8><<<nblk(f->n), 256, 0, s>>>(A);
     else if (f->K <= 16) k_refresh<16><<<nblk(f->n), 256, 0, s>>>(A);
     else k_refresh<32><<<nblk(f->n), 256, 0, s>>>(A);
     MP_CHECK_LAUNCH();
+}
+
+void mp_many_sort(const std::vector<mp_filter>& fs, ManyTab& T, hipStream_t s) {
+    std::vector<SmSortArgs> a;
+    for (mp_filter f : fs) {
+        f->rank_set = true;
+        a.push_back(small_sort_args(f));
+    }
+    if (!a.empty()) mp_sort_small_many(a, T, s);
+}
+
+void mp_many_refresh(const std::vector<mp_filter>& fs, ManyTab& T, hipStream_t s) {
+    for (int R : {2, 3, 5}) {
+        std::vector<RefreshArgs> a;
+        std::vector<int32_t> blocks;
+        for (mp_filter f : fs)
+            if (refresh_rows(f, f->p.window_c) == R) {
+                a.push_back(refresh_args(f, -1));
+                blocks.push_back((int32_t)nblk(f->n, 256 / kRfLanes));
+            }
+        if (a.empty()) continue;
+        unsigned grid;
+        const Many<RefreshArgs> M = many_table(T, a, blocks, grid);
+        if (R == 2) k_refresh_row_many<2><<<grid, 256, 0, s>>>(M);
+        else if (R == 3) k_refresh_row_many<3><<<grid, 256, 0, s>>>(M);
+        else k_refresh_row_many<5><<<grid, 256, 0, s>>>(M);
+        MP_CHECK_LAUNCH();
+    }
+    for (mp_filter f : fs)
+        if (!refresh_rows(f, f->p.window_c)) mp_launch_refresh(f, s);
 }
 
 void mp_launch_reset_lists(mp_filter f, hipStream_t s) {

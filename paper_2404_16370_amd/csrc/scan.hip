@@ -470,6 +470,6 @@ void mp_scan_walk_order(ScanPrep A, float cell, uint32_t* keys_alt, int32_t* per
         k_scan_keys<<<(A.n + 255) / 256, 256, 0, s>>>(A);
     }
     MP_CHECK_LAUNCH();
-    if (mp_sort_is_small(A.n)) mp_sort_small(A.key, A.key, A.idx, A.n, 30, nullptr, nullptr, nullptr, s);
+    if (mp_sort_is_small(A.n)) mp_sort_small(SmSortArgs{A.key, A.key, A.idx, nullptr, nullptr, nullptr, A.n, 30, nullptr}, s);
     else mp_radix_sort_u32(A.key, A.idx, keys_alt, perm_alt, A.n, 30, scratch, s);
 }

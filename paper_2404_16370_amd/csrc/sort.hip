@@ -27,6 +27,7 @@
 #include <type_traits>
 
 #include "mp_internal.hpp"
+#include "mp_many.hpp"
 
 namespace {
 
@@ -546,24 +547,12 @@ constexpr int kSmDigits = 1 << kSmBits;          // one thread scans as many cou
 static_assert(kSmDigits == 16, "a thread's share of the scan is two 16-byte words of 16-bit counters");
 static_assert(4 * kSmItems <= 2 * kSmDigits, "heads and ends fit the counters");
 
-struct SmSortArgs {
-    const uint32_t* kin;
-    uint32_t* kout;       // may be kin
-    int32_t* vout;        // input index of each sorted key
-    int32_t* head;        // bucket bounds per position and position of each value, or null
-    int32_t* end;
-    int32_t* rank;
-    int32_t n, bits;
-    uint64_t* stamp;      // stage clock, or null
-};
-
 template <int ITEMS, int T = kSmThreads>   // keys per thread, threads
-__global__ __launch_bounds__(T) void k_sort_small(SmSortArgs A) {
+__device__ __forceinline__ void sort_small(const SmSortArgs& A) {
     __shared__ __attribute__((aligned(16))) uint32_t sk[T * ITEMS];
     __shared__ __attribute__((aligned(16))) uint16_t sv[T * ITEMS];   // index of the key among the inputs
     __shared__ __attribute__((aligned(16))) uint32_t cnt[kSmDigits * T / 2];   // 16-bit counters [digit][thread]
     __shared__ uint32_t wsum[T / 64];
-    mp_write_stamp(A.stamp);
     const int t = threadIdx.x, lane = t & 63, w = t >> 6;
     for (int i = t; i < T * ITEMS; i += T) {
         sk[i] = i < A.n ? A.kin[i] : 0u;
@@ -687,6 +676,19 @@ __global__ __launch_bounds__(T) void k_sort_small(SmSortArgs A) {
     }
 }
 
+template <int ITEMS, int T = kSmThreads>
+__global__ __launch_bounds__(T) void k_sort_small(SmSortArgs A) {
+    mp_write_stamp(A.stamp);
+    sort_small<ITEMS, T>(A);
+}
+
+template <int ITEMS, int T = kSmThreads>
+__global__ __launch_bounds__(T) void k_sort_small_many(Many<SmSortArgs> M) {
+    int block;
+    const SmSortArgs A = many_args(M, block);
+    sort_small<ITEMS, T>(A);
+}
+
 int64_t os_tiles(int64_t n) { return (n + kOsTile - 1) / kOsTile; }
 
 int os_hist_blocks(int64_t n) {
@@ -799,26 +801,29 @@ void mp_radix_sort_u32_inplace_parity(uint32_t* keys, int32_t* vals, uint32_t* k
 
 bool mp_sort_is_small(int64_t n) { return n <= kSmMax; }
 
-void mp_sort_small(const uint32_t* kin, uint32_t* kout, int32_t* vout, int32_t n, int bits,
-                   int32_t* head, int32_t* end, int32_t* rank, hipStream_t s, uint64_t* stamp) {
-    SmSortArgs A;
-    A.kin = kin;
-    A.kout = kout;
-    A.vout = vout;
-    A.head = head;
-    A.end = end;
-    A.rank = rank;
-    A.n = n;
-    A.bits = bits;
-    A.stamp = stamp;
+void mp_sort_small(const SmSortArgs& A, hipStream_t s) {
     // fewer waves wait less at the barriers: 16-bit keys, 1000 of them 10.1 us
     // with 1024 threads and 7.5 with 512, 2000 10.9 and 9.4, 4000 (8 a thread)
     // 12.9 and 14.1
     constexpr int kHalf = kSmThreads / 2;
-    if (n <= 2 * kHalf) k_sort_small<2, kHalf><<<1, kHalf, 0, s>>>(A);
-    else if (n <= 4 * kHalf) k_sort_small<4, kHalf><<<1, kHalf, 0, s>>>(A);
-    else if (n <= kSmThreads * 4) k_sort_small<4><<<1, kSmThreads, 0, s>>>(A);
+    if (A.n <= 2 * kHalf) k_sort_small<2, kHalf><<<1, kHalf, 0, s>>>(A);
+    else if (A.n <= 4 * kHalf) k_sort_small<4, kHalf><<<1, kHalf, 0, s>>>(A);
+    else if (A.n <= kSmThreads * 4) k_sort_small<4><<<1, kSmThreads, 0, s>>>(A);
     else k_sort_small<kSmItems><<<1, kSmThreads, 0, s>>>(A);
+    MP_CHECK_LAUNCH();
+}
+
+// (all with the layout of the largest)
+void mp_sort_small_many(const std::vector<SmSortArgs>& a, ManyTab& T, hipStream_t s) {
+    int n = 0;
+    for (const SmSortArgs& A : a) n = std::max(n, A.n);
+    constexpr int kHalf = kSmThreads / 2;
+    unsigned grid;
+    const Many<SmSortArgs> M = many_table(T, a, std::vector<int32_t>(a.size(), 1), grid);
+    if (n <= 2 * kHalf) k_sort_small_many<2, kHalf><<<grid, kHalf, 0, s>>>(M);
+    else if (n <= 4 * kHalf) k_sort_small_many<4, kHalf><<<grid, kHalf, 0, s>>>(M);
+    else if (n <= kSmThreads * 4) k_sort_small_many<4><<<grid, kSmThreads, 0, s>>>(M);
+    else k_sort_small_many<kSmItems><<<grid, kSmThreads, 0, s>>>(M);
     MP_CHECK_LAUNCH();
 }
 

@@ -335,3 +335,40 @@ def test_sort_passes_of_wider_digits(n, bits):
 def test_bucket_sort_of_half_a_workgroup(room, O, n, bits):
     # up to 2048 keys 512 threads sort, 2 keys or 4 a thread
     test_bucket_sort_bounds_and_ranks(room, O, n, bits)
+
+
+def test_batch_of_unlike_instances(room):
+    # the launches that instances share: sorts on both sides of the small sort's
+    # limit, three widths of the row refresh and the lane-per-particle one, every
+    # SVGD variant, unequal iteration counts, and instances that share none
+    # (several tables, hash map), each against a filter stepped alone
+    R, t = room["w"]["traj"][0]
+    hashed = M.Map(room["w"]["map_xyz"], voxel=0.5, backend=M.MP_NNF_HASH)
+    kinds = [dict(n=1, k=1, window_c=1), dict(n=2050, svgd_iters=3), dict(n=8193, k=16, window_c=32),
+             dict(n=9000, k=20, window_c=40, svgd_grad=M.MP_SVGD_GRAD_EXACT), dict(n=700, k=32, window_c=64),
+             dict(n=3000, svgd_transport=M.MP_SVGD_TRANSPORT_ADJOINT), dict(n=40, lsh_bits=0, svgd_iters=1),
+             dict(n=600, svgd_grad=M.MP_SVGD_GRAD_EXACT, svgd_transport=M.MP_SVGD_TRANSPORT_ADJOINT),
+             dict(n=2500, lsh_tables=2), dict(n=2100, m=hashed), dict(n=2300, final_rescore=1, ns=0)]
+    pairs = []
+    for q, kind in enumerate(kinds):
+        kw = dict(k=8, svgd_iters=2, window_c=16, lsh_bits=16, d_max=1.0, seed=5 + q)
+        kw.update(kind)
+        n, m, ns = kw.pop("n"), kw.pop("m", room["map"]), kw.pop("ns", 200 + 97 * q)
+        both = []
+        for _ in range(2):
+            p = M.mp_filter_default_params(n_particles=n, lik_layout=M.MP_LIK_LAYOUT_GROUPED, **kw)
+            f = M.Filter(m, p, poses=S.gaussian_particles(n, S.pose8(R, t), 0.1, 0.3, q))
+            f.scan_upload(room["w"]["scans"][0][:ns])
+            both.append(f)
+        pairs.append(both)
+    b = M.Batch([x[0] for x in pairs], autotune=False)
+    dT = np.array([1, 0, 0, 0, 0.01, 0, 0], np.float32)
+    cov = np.eye(6, dtype=np.float32) * 1e-6
+    for _ in range(3):   # one capture, replayed
+        b.step(np.tile(dT, (len(pairs), 1)), np.tile(cov.reshape(1, 36), (len(pairs), 1)))
+        for q, (x, y) in enumerate(pairs):
+            y.step(dT, cov)
+            for name in ("poses", "psi", "nbr", "kval", "codes", "prior"):
+                assert np.array_equal(x.debug_get(name), y.debug_get(name), equal_nan=True), (q, name)
+    assert b.info()["captures"] == 1
+    b.close()
