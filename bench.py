@@ -185,7 +185,7 @@ def odometry_leg(M, m, w, scans, cpu):
                           k=k))
     f.close()
     ns = len(recs[-1])
-    evals = 21.0 * ns * len(recs[-2])       # distance evaluations of 21 correspondence searches
+    evals = 21.0 * ns * len(recs[-2])       # pairs of 21 correspondence searches (the index skips most of them)
     t_med = float(np.median(times))
     out = {"ms_per_call": 1e3 * t_med, "scan_points": ns, "iterations": 20, "pairs": len(pairs),
            "error_m_deg": {"prior": [q["prior"] for q in pairs], "refined_from_prior": [q["refined"] for q in pairs],
@@ -193,7 +193,8 @@ def odometry_leg(M, m, w, scans, cpu):
            "motion_deg": [q["motion_deg"] for q in pairs], "inliers": [q["inliers"] for q in pairs],
            "roofline": {"bound": "alu", "achieved": evals * 8 / t_med / 1e12, "peak": PEAK_FP32 / 1e12,
                         "unit": "TFLOP/s", "frac": evals * 8 / t_med / PEAK_FP32, "traffic": None,
-                        "kernel": "k_odo_nn + k_odo_terms + k_odo_step, 21 evaluations (8 flops per distance)"}}
+                        "kernel": "k_odo_iter x 21 + k_odo_final (8 flops per pair; latency-bound, most pairs are "
+                                  "skipped by the scan's index)"}}
     if cpu:
         import oracle as O
         dt, worst = [], 0.0
@@ -801,22 +802,24 @@ def stage_roofline(stages, wl, lik_flops_launch, t_step):
     """Each stage of one filter step against the resource that bounds it.
     `frac` takes the algorithmic bytes per particle: what the method must
     move, neighbour gathers included (prediction 56 B per
-    frame; LSH 36 B; sort 16 B per 8-bit pass + 12 B of bucket bounds;
+    frame; LSH 36 B in the first iteration, later ones' codes are left by the
+    SVGD update, 12 B; sort 16 B per 8-bit pass + 12 B of bucket bounds;
     refresh 28 + 4K + 32C + 32K + 8K; SVGD 28 + 8K + 56K; posterior 20 + R
     (12K + 4)).  A fraction above 1 means the caches serve the gathers.
     `frac_compulsory` takes the bytes each launch must move once, gathers
-    counted once.  The likelihood and the scan k-NN are set against the FP32
-    peak.  `step` sums the stages' roofline times over the measured step time."""
+    counted once.  The likelihood and the scan k-NN (all pairs, most of which
+    its index skips) are set against the FP32 peak.  `step` sums the stages' roofline times over the measured step time."""
     n, it, K, C, R = wl["particles"], wl["svgd_iters"], wl["k"], wl["window_c"], wl["post_iters"]
     ns, passes = wl["scan_points"], (wl["lsh_bits"] + 7) // 8
     svgd_c, refresh_c = svgd_refresh_bytes(K)
     work = {
         "predict": ("hbm", 56.0 * n, 64.0 * n),
-        "lsh": ("hbm", 36.0 * n * it, 44.0 * n * it),
+        "lsh": ("hbm", 36.0 * n, 44.0 * n),
         "sort": ("hbm", (16.0 * passes + 12.0) * n * it, (16.0 * passes + 12.0) * n * it),
         "refresh": ("hbm", (28.0 + 4 * K + 32.0 * C + 32.0 * K + 8 * K) * n * it, refresh_c * n * it),
         "likelihood": ("alu", lik_flops_launch * it, lik_flops_launch * it),
-        "svgd": ("hbm", (28.0 + 8 * K + 56.0 * K + 28.0) * n * it, svgd_c * n * it),
+        "svgd": ("hbm", (28.0 + 8 * K + 56.0 * K + 28.0) * n * it + 12.0 * n * (it - 1),
+                 svgd_c * n * it + 12.0 * n * (it - 1)),
         "posterior": ("hbm", (20.0 + R * (12.0 * K + 4)) * n, (36.0 + R * (8.0 * K + 8)) * n),
         "scan": ("alu", 8.0 * ns * (ns - 1), 8.0 * ns * (ns - 1)),
     }
