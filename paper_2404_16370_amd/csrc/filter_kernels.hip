@@ -209,9 +209,13 @@ __device__ __forceinline__ void svgd_move(const SvgdArgs& A, int i, mpdet::quat&
 // 16 lanes per particle: lane l forms the terms of neighbours l and l + 16,
 // then lane m < 7 adds component m (the sixth: k) over the list in list order.
 // What bounds it: the gathers of the neighbours' poses and psi; with one lane
-// per particle they follow one another.  One lane / 16 lanes, K = 16: 4096
-// particles 21 / 4.5 us, 65,536 29 / 19 us, 1,048,576 462 / 398 us.
+// per particle they follow one another.  From kSvMax particles on one lane each
+// fills the chip, and leaves out the lists' empty places.  One lane / 16 lanes,
+// K = 16, converged and spread (whose lists are nearly empty): 32,768 particles
+// 27 / 11 us and 11 / 7, 65,536 29 / 20 and 12 / 12, 131,072 42 / 41 and 14 / 22,
+// 1,048,576 506 / 455 and 60 / 146.
 constexpr int kSvLanes = 16;
+constexpr int kSvMax = 98304;
 
 // L.codes: leave the codes of the next iteration's buckets as well (a launch
 // less for each: ten iterations of 4096 particles 821 -> 794 us a frame)
@@ -257,10 +261,41 @@ __device__ __forceinline__ void svgd_rows(const SvgdArgs& A, LshArgs L, int bloc
         lsh_code(L, sL, p, make_float4(qi.w, qi.x, qi.y, qi.z), make_float4(ti.x, ti.y, ti.z, 0.0f));
 }
 
+// one lane per particle
 template <bool EXACT, bool TRANSPORT>
+__device__ __forceinline__ void svgd_lanes(const SvgdArgs& A, LshArgs L, int block) {
+    __shared__ float sL[8];
+    if (L.dyn) L.frame = L.dyn->frame;
+    if (L.codes && threadIdx.x == 255) lsh_draw(L, sL, block == 0);
+    const int i = block * 256 + threadIdx.x;
+    mpdet::quat qi;
+    float3 ti;
+    if (i < A.n) {
+        load_pose(A.pin, i, qi, ti);
+        float num[6] = {0, 0, 0, 0, 0, 0};
+        float den = 0.0f;
+        for (int a = 0; a < A.K; ++a) {
+            const int j = A.nbr[(size_t)a * A.n + i];
+            if (j < 0 || j >= A.n) continue;
+            const float k = A.kval[(size_t)a * A.n + i];
+            float v[6];
+            svgd_term<EXACT, TRANSPORT>(A, qi, ti, j, k, v);
+            for (int m = 0; m < 6; ++m) num[m] += v[m];
+            den += k;
+        }
+        svgd_move(A, i, qi, ti, num, den);
+    }
+    if (!L.codes) return;   // (uniform)
+    __syncthreads();
+    if (i < A.n)
+        lsh_code(L, sL, i, make_float4(qi.w, qi.x, qi.y, qi.z), make_float4(ti.x, ti.y, ti.z, 0.0f));
+}
+
+template <bool EXACT, bool TRANSPORT, bool ROWS>
 __global__ __launch_bounds__(256) void k_svgd(SvgdArgs A, LshArgs L) {
     mp_write_stamp(A.stamp);
-    svgd_rows<EXACT, TRANSPORT>(A, L, blockIdx.x);
+    if (ROWS) svgd_rows<EXACT, TRANSPORT>(A, L, blockIdx.x);
+    else svgd_lanes<EXACT, TRANSPORT>(A, L, blockIdx.x);
 }
 
 struct SvgdLsh {
@@ -268,11 +303,12 @@ struct SvgdLsh {
     LshArgs L;
 };
 
-template <bool EXACT, bool TRANSPORT>
+template <bool EXACT, bool TRANSPORT, bool ROWS>
 __global__ __launch_bounds__(256) void k_svgd_many(Many<SvgdLsh> M) {
     int block;
     const SvgdLsh q = many_args(M, block);
-    svgd_rows<EXACT, TRANSPORT>(q.A, q.L, block);
+    if (ROWS) svgd_rows<EXACT, TRANSPORT>(q.A, q.L, block);
+    else svgd_lanes<EXACT, TRANSPORT>(q.A, q.L, block);
 }
 
 // ------------------------------------------------------------ prediction
@@ -347,7 +383,8 @@ __global__ __launch_bounds__(256) void k_init_uniform(InitArgs A) {
 // bounds it is the launches, 3 to 5 us each: up to kRB partials are reduced by
 // every block of the next kernel (one load a thread), the last round leaves the
 // partials of its sums, and small filters take k_post_small.  Ten rounds, 65,536
-// particles x 16 99 -> 73 us, 20,011 x 16 90 -> 62 us, 4097 x 8 71 -> 49 us.
+// particles x 16 99 -> 71 us, 20,011 x 16 90 -> 63 us, 4097 x 8 71 -> 51 us;
+// 1,048,576 x 16 961 -> 934 us converged, 292 -> 259 spread.
 constexpr int kRB = 256;
 
 __device__ inline double block_max(double v) {
@@ -521,14 +558,17 @@ __device__ inline float post_average(const PostArgs& A, const float* __restrict_
         float k[kU], p[kU];
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
-            const size_t at = (size_t)min(a0 + u, A.K - 1) * n + i;
-            j[u] = A.nbr[at];
-            k[u] = A.kval[at];
+            j[u] = A.nbr[(size_t)min(a0 + u, A.K - 1) * n + i];
+            if (a0 + u >= A.K || j[u] >= A.n) j[u] = -1;
         }
 #pragma unroll
-        for (int u = 0; u < kU; ++u) {
-            if (a0 + u >= A.K || j[u] >= A.n) j[u] = -1;
-            p[u] = pin[max(j[u], 0)];
+        for (int u = 0; u < kU; ++u) {   // (an empty place costs no load)
+            k[u] = 0.0f;
+            p[u] = 0.0f;
+            if (j[u] >= 0) {
+                k[u] = A.kval[(size_t)(a0 + u) * n + i];
+                p[u] = pin[j[u]];
+            }
         }
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
@@ -808,25 +848,33 @@ static SvgdLsh svgd_args(mp_filter f, const LshArgs* next) {
     return q;
 }
 
+// variant: gradient, transport, lanes per particle
 static int svgd_kind(mp_filter f) {
-    return (f->p.svgd_grad == MP_SVGD_GRAD_EXACT ? 2 : 0) + (f->p.svgd_transport == MP_SVGD_TRANSPORT_ADJOINT ? 1 : 0);
+    return (f->p.svgd_grad == MP_SVGD_GRAD_EXACT ? 4 : 0) + (f->p.svgd_transport == MP_SVGD_TRANSPORT_ADJOINT ? 2 : 0) +
+           (f->n <= kSvMax ? 1 : 0);
 }
+
+static unsigned svgd_blocks(mp_filter f) { return nblk(f->n, f->n <= kSvMax ? 256 / kSvLanes : 256); }
 
 void mp_launch_svgd(mp_filter f, hipStream_t s, const LshArgs* next) {
     SvgdLsh q = svgd_args(f, next);
     q.A.stamp = mp_take_stamp(f);
-    const unsigned grid = nblk(f->n, 256 / kSvLanes);
+    const unsigned grid = svgd_blocks(f);
     switch (svgd_kind(f)) {
-        case 3: k_svgd<true, true><<<grid, 256, 0, s>>>(q.A, q.L); break;
-        case 2: k_svgd<true, false><<<grid, 256, 0, s>>>(q.A, q.L); break;
-        case 1: k_svgd<false, true><<<grid, 256, 0, s>>>(q.A, q.L); break;
-        default: k_svgd<false, false><<<grid, 256, 0, s>>>(q.A, q.L);
+        case 7: k_svgd<true, true, true><<<grid, 256, 0, s>>>(q.A, q.L); break;
+        case 6: k_svgd<true, true, false><<<grid, 256, 0, s>>>(q.A, q.L); break;
+        case 5: k_svgd<true, false, true><<<grid, 256, 0, s>>>(q.A, q.L); break;
+        case 4: k_svgd<true, false, false><<<grid, 256, 0, s>>>(q.A, q.L); break;
+        case 3: k_svgd<false, true, true><<<grid, 256, 0, s>>>(q.A, q.L); break;
+        case 2: k_svgd<false, true, false><<<grid, 256, 0, s>>>(q.A, q.L); break;
+        case 1: k_svgd<false, false, true><<<grid, 256, 0, s>>>(q.A, q.L); break;
+        default: k_svgd<false, false, false><<<grid, 256, 0, s>>>(q.A, q.L);
     }
     MP_CHECK_LAUNCH();
 }
 
 void mp_many_svgd(const std::vector<mp_filter>& fs, int it, ManyTab& T, hipStream_t s) {
-    for (int kind = 0; kind < 4; ++kind) {
+    for (int kind = 0; kind < 8; ++kind) {
         std::vector<SvgdLsh> a;
         std::vector<int32_t> blocks;
         for (mp_filter f : fs) {
@@ -835,16 +883,20 @@ void mp_many_svgd(const std::vector<mp_filter>& fs, int it, ManyTab& T, hipStrea
             const LshArgs next = mp_lsh_args(f, (uint32_t)f->frame, (uint32_t)((it + 1) * std::max(1, f->p.lsh_tables)));
             a.push_back(svgd_args(f, more ? &next : nullptr));
             f->lsh_ahead = more;
-            blocks.push_back((int32_t)nblk(f->n, 256 / kSvLanes));
+            blocks.push_back((int32_t)svgd_blocks(f));
         }
         if (a.empty()) continue;
         unsigned grid;
         const Many<SvgdLsh> M = many_table(T, a, blocks, grid);
         switch (kind) {
-            case 3: k_svgd_many<true, true><<<grid, 256, 0, s>>>(M); break;
-            case 2: k_svgd_many<true, false><<<grid, 256, 0, s>>>(M); break;
-            case 1: k_svgd_many<false, true><<<grid, 256, 0, s>>>(M); break;
-            default: k_svgd_many<false, false><<<grid, 256, 0, s>>>(M);
+            case 7: k_svgd_many<true, true, true><<<grid, 256, 0, s>>>(M); break;
+            case 6: k_svgd_many<true, true, false><<<grid, 256, 0, s>>>(M); break;
+            case 5: k_svgd_many<true, false, true><<<grid, 256, 0, s>>>(M); break;
+            case 4: k_svgd_many<true, false, false><<<grid, 256, 0, s>>>(M); break;
+            case 3: k_svgd_many<false, true, true><<<grid, 256, 0, s>>>(M); break;
+            case 2: k_svgd_many<false, true, false><<<grid, 256, 0, s>>>(M); break;
+            case 1: k_svgd_many<false, false, true><<<grid, 256, 0, s>>>(M); break;
+            default: k_svgd_many<false, false, false><<<grid, 256, 0, s>>>(M);
         }
         MP_CHECK_LAUNCH();
     }

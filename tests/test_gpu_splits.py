@@ -372,3 +372,9 @@ def test_batch_of_unlike_instances(room):
                 assert np.array_equal(x.debug_get(name), y.debug_get(name), equal_nan=True), (q, name)
     assert b.info()["captures"] == 1
     b.close()
+
+
+@pytest.mark.parametrize("n", [98_304, 98_305, 131_072])
+def test_codes_left_by_either_svgd_kernel(room, O, n):
+    # 16 lanes per particle up to 98,304 particles, one beyond
+    test_codes_left_by_the_svgd_update(room, O, n, 1, 0)
