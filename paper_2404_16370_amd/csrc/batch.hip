@@ -139,8 +139,10 @@ void capture(mp_batch b, hipStream_t caller) {
     // waits for the queue in any case: some 30 kernels of a few us on the branches
     // of a graph, at most four at a time, took 150 us an iteration beside the 212
     // of the queue, four shared ones and the larger sorts 120 (8 instances of 2041
-    // to 16,384 particles: a step of ten iterations 3.8 -> 3.4 ms).  With one
-    // hash table a list; an instance with several keeps its branch.
+    // to 16,384 particles: a step of ten iterations 3.8 -> 3.4 ms).  The larger
+    // instances' sorts, one-lane refreshes and walk orders stay on their branches
+    // (32 instances of 4096 to 262,144 particles: 431 ms a step, 442 with those in
+    // line, 432 with nothing shared), as does an instance with several hash tables.
     std::vector<char> shared(n, 0);
     for (size_t i = 0; i < n; ++i) shared[i] = mp_lik_queueable(b->f[i]) && b->f[i]->p.lsh_tables <= 1;
     b->many.host.clear();
@@ -181,23 +183,35 @@ void capture(mp_batch b, hipStream_t caller) {
                     large.push_back(i);
                     if (it > 0) MP_HIP(hipStreamWaitEvent(b->branch[i], b->moved, 0));
                     mp_launch_sort(f, b->branch[i]);
+                    if (!mp_refresh_is_rows(f)) mp_launch_refresh(f, b->branch[i]);
+                    mp_lik_queue_order(f, b->branch[i]);
                 }
                 if (it == 0 || !is_small) MP_HIP(hipEventRecord(b->pre[i], b->branch[i]));
                 if (it == 0 && is_small) MP_HIP(hipStreamWaitEvent(s, b->pre[i], 0));
             }
             mp_many_sort(small, b->many, s);   // beside the larger ones
+            for (mp_filter f : small) {
+                if (!mp_refresh_is_rows(f)) mp_launch_refresh(f, s);
+                mp_lik_queue_order(f, s);
+            }
             for (size_t i : large) MP_HIP(hipStreamWaitEvent(s, b->pre[i], 0));
             mp_many_refresh(together, b->many, s);
             std::vector<size_t> queued;
             int32_t tiles = 0;
+            int64_t groups = 0;
+            for (mp_filter f : b->f)
+                if (it < f->p.svgd_iters) groups += mp_lik_queue_groups(f);
             for (size_t i : by_tile) {
                 mp_filter f = b->f[i];
                 if (f->scan_n <= 0 || it >= f->p.svgd_iters) continue;
                 hipStream_t bs = shared[i] ? s : b->branch[i];
-                if (!shared[i]) mp_step_iter_nbr(f, it, bs);
+                if (!shared[i]) {
+                    mp_step_iter_nbr(f, it, bs);
+                    mp_lik_queue_order(f, bs);
+                }
                 int32_t t = 0;
                 char* slot = htab.data() + ((size_t)it * n + queued.size()) * argb;
-                if (mp_lik_queue_plan(f, slot, &t, bs)) {
+                if (mp_lik_queue_plan(f, slot, &t, groups)) {
                     hfirst[(size_t)it * (n + 1) + queued.size()] = tiles;
                     tiles += t;
                     queued.push_back(i);
@@ -330,10 +344,13 @@ void tune_queue(mp_batch b, hipStream_t s) {
     std::vector<char> tab(n * argb);
     std::vector<int32_t> first(n + 1, 0);
     int32_t tiles = 0, q = 0;
+    int64_t groups = 0;
+    for (mp_filter f : b->f) groups += mp_lik_queue_groups(f);
     for (size_t i : queue_order(b)) {
         mp_filter f = b->f[i];
         int32_t t = 0;
-        if (mp_lik_queue_plan(f, tab.data() + (size_t)q * argb, &t, s)) {
+        mp_lik_queue_order(f, s);
+        if (mp_lik_queue_plan(f, tab.data() + (size_t)q * argb, &t, groups)) {
             first[q++] = tiles;
             tiles += t;
         }

@@ -804,8 +804,11 @@ static bool lik_grouped(mp_filter f) {
 // spread particles, sort and pass, 131,072 x 4096 1.84 ms in Morton and 1.86 in
 // LSH order, 65,536 x 4096 940 and 927 us, 32,768 x 4096 491 and 470 us, and
 // converged ones 65,536 x 4096 895 and 871 us.
+// In a batch the sorts of several filters run side by side, and the order is
+// taken from 2^27.
 static bool lik_spatial(mp_filter f, int scorer) {
-    return scorer != MP_SCORER_SURROGATE && lik_grouped(f) && (int64_t)f->n * (int64_t)f->scan_n >= (1LL << 30);
+    const int64_t from = f->capturing ? 1LL << 27 : 1LL << 30;
+    return scorer != MP_SCORER_SURROGATE && lik_grouped(f) && (int64_t)f->n * (int64_t)f->scan_n >= from;
 }
 
 static const int32_t* lik_order(mp_filter f, int scorer) {
@@ -845,11 +848,14 @@ static void lik_prepare_order(mp_filter f, int scorer, hipStream_t s) {
 // us (of its 1024 workgroups the last ran alone).
 constexpr int kSplitGroups = 4096;
 
-static int lik_rounds(int n, int nch) {
+// groups: workgroups of 32 particles of the launch
+static int lik_rounds(int64_t groups) {
     int rounds = kGRounds;
-    while (rounds > 1 && (int64_t)((n + kGSlots * rounds - 1) / (kGSlots * rounds)) * nch < kSplitGroups) rounds /= 2;
+    while (rounds > 1 && groups / rounds < kSplitGroups) rounds /= 2;
     return rounds;
 }
+
+static int64_t lik_groups(int n, int nch) { return (int64_t)((n + kGSlots - 1) / kGSlots) * nch; }
 
 // scan-point chunks per particle tile and the chunk length
 static int lik_chunks(mp_filter f, int& clen) {
@@ -895,7 +901,7 @@ LikPlan lik_plan(mp_filter f) {
     P.grouped = lik_grouped(f) && P.scorer != MP_SCORER_SURROGATE;
     int clen = 0;
     P.nch = lik_chunks(f, clen);
-    const int rounds = lik_rounds(n, P.nch);
+    const int rounds = lik_rounds(lik_groups(n, P.nch));
     const int nbx = P.grouped ? (n + kGSlots * rounds - 1) / (kGSlots * rounds) : (n + kLanes - 1) / kLanes;
     f->lik_chunks = P.nch;
     f->lik_chunk_len = clen;
@@ -1073,10 +1079,21 @@ void mp_many_solve(const std::vector<mp_filter>& fs, ManyTab& T, hipStream_t s) 
     MP_CHECK_LAUNCH();
 }
 
-bool mp_lik_queue_plan(mp_filter f, void* args_out, int32_t* tiles, hipStream_t s) {
+int64_t mp_lik_queue_groups(mp_filter f) {
+    int clen = 0;
+    return mp_lik_queueable(f) ? lik_groups(f->n, lik_chunks(f, clen)) : 0;
+}
+
+void mp_lik_queue_order(mp_filter f, hipStream_t s) {
+    if (mp_lik_queueable(f)) lik_prepare_order(f, MP_SCORER_PLAIN, s);
+}
+
+bool mp_lik_queue_plan(mp_filter f, void* args_out, int32_t* tiles, int64_t groups) {
     if (!mp_lik_queueable(f)) return false;
-    const LikPlan P = lik_plan(f);
-    lik_prepare_order(f, P.scorer, s);
+    LikPlan P = lik_plan(f);
+    // the whole queue decides how many particles a tile takes
+    P.A.rounds = lik_rounds(groups);
+    P.A.nbx = (f->n + kGSlots * P.A.rounds - 1) / (kGSlots * P.A.rounds);
     std::memcpy(args_out, &P.A, sizeof(LikArgs));
     *tiles = P.A.nbx * P.nch;
     return true;

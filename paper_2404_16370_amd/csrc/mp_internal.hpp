@@ -344,7 +344,9 @@ void mp_launch_likelihood(mp_filter f, hipStream_t s);
 // follows the queue, the queue launch.
 constexpr int32_t kLikTilePoints = 1024;   // most scan points of a tile
 size_t mp_lik_args_bytes();
-bool mp_lik_queue_plan(mp_filter f, void* args_out, int32_t* tiles, hipStream_t s);
+void mp_lik_queue_order(mp_filter f, hipStream_t s);   // the pass's walk order
+bool mp_lik_queue_plan(mp_filter f, void* args_out, int32_t* tiles, int64_t groups);
+int64_t mp_lik_queue_groups(mp_filter f);   // this pass's share of the queue's `groups`
 void mp_lik_queue_solve(mp_filter f, hipStream_t s);
 int mp_lik_queue_grid(int batch);
 void mp_launch_lik_queue(const void* tab_dev, const int32_t* first_dev, int32_t* counter_dev, int n_inst, int tiles,
@@ -354,6 +356,7 @@ void mp_launch_lik_queue(const void* tab_dev, const int32_t* first_dev, int32_t*
 // of filters that take a small one, refreshes, solves, SVGD updates of iteration it
 constexpr size_t kManyBytes = 1024;   // most table bytes of a filter in the four
 void mp_many_sort(const std::vector<mp_filter>& fs, ManyTab& T, hipStream_t s);
+bool mp_refresh_is_rows(mp_filter f);   // else mp_many_refresh leaves the filter out
 void mp_many_refresh(const std::vector<mp_filter>& fs, ManyTab& T, hipStream_t s);
 void mp_many_solve(const std::vector<mp_filter>& fs, ManyTab& T, hipStream_t s);
 void mp_many_svgd(const std::vector<mp_filter>& fs, int it, ManyTab& T, hipStream_t s);

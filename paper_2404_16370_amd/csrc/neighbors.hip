@@ -468,9 +468,9 @@ void mp_many_refresh(const std::vector<mp_filter>& fs, ManyTab& T, hipStream_t s
         else k_refresh_row_many<5><<<grid, 256, 0, s>>>(M);
         MP_CHECK_LAUNCH();
     }
-    for (mp_filter f : fs)
-        if (!refresh_rows(f, f->p.window_c)) mp_launch_refresh(f, s);
 }
+
+bool mp_refresh_is_rows(mp_filter f) { return refresh_rows(f, f->p.window_c) != 0; }
 
 void mp_launch_reset_lists(mp_filter f, hipStream_t s) {
     k_reset_lists<<<nblk(f->n), 256, 0, s>>>(f->nbr.as<int32_t>(), f->kval.as<float>(), f->cnt.as<int32_t>(),
