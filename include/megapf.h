@@ -328,7 +328,9 @@ enum {
  * mp_scan_upload), milliseconds, summed over the step's iterations, from the
  * device clock: a stage runs from the start of its first kernel to the start
  * of the next stage's (the last one to the step's end); synchronises the
- * device.  ms_out has MP_NUM_STAGES entries; stages not run read 0.
+ * device.  The SVGD update leaves the first table's codes of the iteration that
+ * follows, so the LSH spans there count but take no time of their own.  ms_out
+ * has MP_NUM_STAGES entries; stages not run read 0.
  * counts_out (nullable, MP_NUM_STAGES) receives the number of timed spans. */
 MP_API mp_status mp_stage_times(mp_filter f, float* ms_out, int32_t* counts_out);
 
