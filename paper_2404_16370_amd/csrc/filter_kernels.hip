@@ -634,12 +634,13 @@ __global__ __launch_bounds__(kRB) void k_post_neff_final(PostArgs A) {
 }
 
 // The whole posterior in one workgroup, for filters whose lists fit its
-// registers: 1024 threads, particle r * 1024 + thread its r-th, kPostSlots /
+// registers: T threads, particle r * T + thread its r-th, kPostSlots /
 // R list slots each.  Wave w reduces particles [256 w, 256 (w + 1)) and the
 // results are reduced as above, in the same trees, so it gives the same bits.
 // What bounds it: one CU's LDS gathers and FP64 exp and log.  Ten rounds, 256
-// particles x 8 54 -> 19 us, 1000 x 16 80 -> 23 us, 4096 x 8 71 -> 37 us (49 in
-// the launches above).  Lists kept in more registers would spill.
+// particles x 8 54 -> 14 us (19 with 1024 threads, which wait longer at the
+// barriers), 1000 x 16 80 -> 23 us, 4096 x 8 71 -> 37 us (49 in the launches
+// above).  Lists kept in more registers would spill.
 constexpr int kPT = 1024;
 constexpr int kPostSlots = 32;
 
@@ -664,9 +665,9 @@ __device__ inline void pick(double& v, int& idx, double b, int ib) {
     }
 }
 
-template <int R>
-__global__ __launch_bounds__(kPT) void k_post_small(PostArgs A, int rounds) {
-    constexpr int N = R * kPT, KC = kPostSlots / R, W = kPT / 64;
+template <int R, int T = kPT>
+__global__ __launch_bounds__(T) void k_post_small(PostArgs A, int rounds) {
+    constexpr int N = R * T, KC = kPostSlots / R, W = T / 64;
     __shared__ double sh[N];
     __shared__ float pb[2][N + 1];   // and a zero
     __shared__ double part[3][W];
@@ -681,7 +682,7 @@ __global__ __launch_bounds__(kPT) void k_post_small(PostArgs A, int rounds) {
     for (int r = 0; r < R; ++r)
 #pragma unroll
         for (int a = 0; a < KC; ++a) {
-            const int i = r * kPT + tid;
+            const int i = r * T + tid;
             const bool in = a < A.K && i < n;
             const size_t at = in ? (size_t)a * n + i : 0;
             const int32_t x = A.nbr[at];
@@ -693,7 +694,7 @@ __global__ __launch_bounds__(kPT) void k_post_small(PostArgs A, int rounds) {
     // logits and their maximum
     double m = -INFINITY, mll = -INFINITY;
 #pragma unroll 1
-    for (int i = tid; i < n; i += kPT) {
+    for (int i = tid; i < n; i += T) {
         const double pr = fmax((double)A.prior[i], A.floor_p);
         const double ll = (double)A.psi[2 * i + 1].z;
         const double l = log(pr) + ll * A.inv_tau;
@@ -719,9 +720,9 @@ __global__ __launch_bounds__(kPT) void k_post_small(PostArgs A, int rounds) {
     // evidence
     double l[R];
 #pragma unroll
-    for (int r = 0; r < R; ++r) l[r] = sh[r * kPT + tid];   // own values: of no thread beyond n
+    for (int r = 0; r < R; ++r) l[r] = sh[r * T + tid];   // own values: of no thread beyond n
     for (int r = 0; r < R; ++r) {
-        const int i = r * kPT + tid;
+        const int i = r * T + tid;
         sh[i] = i < n ? exp(sh[i] - m) : 0.0;
     }
     __syncthreads();
@@ -734,7 +735,7 @@ __global__ __launch_bounds__(kPT) void k_post_small(PostArgs A, int rounds) {
     const double ev = m + log(sum);
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        const int i = r * kPT + tid;
+        const int i = r * T + tid;
         pb[0][i] = i < n ? (float)exp(l[r] - ev) : 0.0f;
         pb[1][i] = 0.0f;
     }
@@ -745,7 +746,7 @@ __global__ __launch_bounds__(kPT) void k_post_small(PostArgs A, int rounds) {
         const float* pin = pb[cur];
 #pragma unroll
         for (int r = 0; r < R; ++r) {
-            const int i = r * kPT + tid;
+            const int i = r * T + tid;
             float num = 0.0f, den = 0.0f;
 #pragma unroll
             for (int a = 0; a < KC; ++a) {
@@ -789,7 +790,7 @@ __global__ __launch_bounds__(kPT) void k_post_small(PostArgs A, int rounds) {
     for (int d = 32; d > 0; d >>= 1) pick(v, idx, __shfl_down(v, d), __shfl_down(idx, d));
 #pragma unroll
     for (int r = 0; r < R; ++r) {
-        const int i = r * kPT + tid;
+        const int i = r * T + tid;
         double q = 0.0;
         if (i < n) {
             q = (double)pf[i] / z;
@@ -1052,7 +1053,9 @@ void mp_launch_posterior(mp_filter f, hipStream_t s, uint64_t* stamp_end) {
     const int rounds = f->p.post_iters;
     // one workgroup while a lane's list slots fit its registers
     const int slots = f->K * ((n + kPT - 1) / kPT);
-    if (n <= kPT && slots <= kPostSlots) {
+    if (n <= kPT / 4 && slots <= kPostSlots) {
+        k_post_small<1, kPT / 4><<<1, kPT / 4, 0, s>>>(A, rounds);
+    } else if (n <= kPT && slots <= kPostSlots) {
         k_post_small<1><<<1, kPT, 0, s>>>(A, rounds);
     } else if (n <= 2 * kPT && slots <= kPostSlots) {
         k_post_small<2><<<1, kPT, 0, s>>>(A, rounds);
