@@ -553,7 +553,6 @@ extern "C" mp_status mp_scan_upload(mp_filter f, const float* xyz, const float* 
         hipStream_t s = as_stream(stream);
         if (n > 0) {
             f->scan_xyz.ensure(sizeof(float) * 3 * (size_t)n);
-            f->scan.ensure(sizeof(float) * 12 * (size_t)n);
             f->scan_perm.ensure(sizeof(int32_t) * (size_t)n);
             f->scan_work.ensure(sizeof(float4) * (kPrepParts + 1) + sizeof(uint32_t) * 3 * (size_t)n);
             if (!f->scan_verdict.p) {
@@ -587,14 +586,27 @@ extern "C" mp_status mp_scan_upload(mp_filter f, const float* xyz, const float* 
             mp_scan_walk_order(P, 0.5f * f->map->params.voxel, P.key + n, reinterpret_cast<int32_t*>(P.key + 2 * (size_t)n),
                                f->scan_sort, s);
             if (scan_is_bad(P, s)) mp_throw(MP_E_ARG, cov6 ? "non-finite scan point or covariance" : "non-finite scan point");
-            // the current records become the previous scan's (odometry)
-            if (f->orig_n > 0) {
+            // The current records become the previous scan's (odometry), whose places take the
+            // new ones.  Larger places are all there before an old one is given up, so that a
+            // failed allocation leaves the last two scans as a refusal does.
+            const bool follows = f->orig_n > 0;
+            DevMem& orig = follows ? f->prev_orig : f->scan_orig;
+            DevMem& idx = follows ? f->prev_idx : f->scan_idx;
+            const size_t rec_bytes = sizeof(float) * 12 * (size_t)n, idx_bytes = mp_scan_index_bytes(n);
+            {
+                DevMem walk_new, orig_new, idx_new;
+                if (f->scan.bytes < rec_bytes) walk_new.alloc(rec_bytes);
+                if (orig.bytes < rec_bytes) orig_new.alloc(rec_bytes);
+                if (idx.bytes < idx_bytes) idx_new.alloc(idx_bytes);
+                if (walk_new.p) f->scan.swap(walk_new);
+                if (orig_new.p) orig.swap(orig_new);
+                if (idx_new.p) idx.swap(idx_new);
+            }
+            if (follows) {
                 f->scan_orig.swap(f->prev_orig);
                 f->scan_idx.swap(f->prev_idx);
                 f->prev_n = f->orig_n;
             }
-            f->scan_orig.ensure(sizeof(float) * 12 * (size_t)n);
-            f->scan_idx.ensure(mp_scan_index_bytes(n));
             f->orig_n = n;
             mp_scan_records(P.xyz, dcov, P.idx, n, f->p.scan_k, f->p.cov_eps, mp_scan_index(f->scan_idx, n),
                             f->scan_orig.as<float>(), f->scan.as<float>(), P.start, f->stamps.as<uint64_t>(), s);
