@@ -585,7 +585,11 @@ extern "C" mp_status mp_scan_upload(mp_filter f, const float* xyz, const float* 
             P.n = n;
             mp_scan_walk_order(P, 0.5f * f->map->params.voxel, P.key + n, reinterpret_cast<int32_t*>(P.key + 2 * (size_t)n),
                                f->scan_sort, s);
-            if (scan_is_bad(P, s)) mp_throw(MP_E_ARG, cov6 ? "non-finite scan point or covariance" : "non-finite scan point");
+            if (scan_is_bad(P, s)) {
+                // (the sort: an upload that answers the refusal may come on another stream)
+                MP_HIP(hipStreamSynchronize(s));
+                mp_throw(MP_E_ARG, cov6 ? "non-finite scan point or covariance" : "non-finite scan point");
+            }
             // The current records become the previous scan's (odometry), whose places take the
             // new ones.  Larger places are all there before an old one is given up, so that a
             // failed allocation leaves the last two scans as a refusal does.

@@ -57,3 +57,30 @@ def test_larger_refused_scan_leaves_the_last_ones(room, n, uploads):
     assert np.array_equal(x.debug_get("psi"), y.debug_get("psi"))
     for f in both:
         f.close()
+
+
+@pytest.mark.parametrize("n", [300, 8193, 65_536])
+def test_refused_upload_leaves_no_work_behind(room, n):
+    # the upload that answers a refusal may come on another stream: nothing of
+    # the refused one is still running on its own
+    import torch
+    f = _filter(room)
+    good = np.random.default_rng(n).uniform(-5, 5, (n, 3)).astype(np.float32)
+    bad = good.copy()
+    bad[n - 1, 2] = np.inf
+    one, other = torch.cuda.Stream(), torch.cuda.Stream()
+    src = torch.from_numpy(bad).cuda()
+    torch.cuda.synchronize()
+    for _ in range(5):
+        with pytest.raises(M.MegaPFError):
+            f.scan_upload(src, stream=one.cuda_stream)
+        assert one.query()
+        f.scan_upload(good, stream=other.cuda_stream)
+        other.synchronize()
+    torch.cuda.synchronize()
+    ref = _filter(room)
+    ref.scan_upload(good)
+    for name in ("scan", "scan_walk"):
+        assert np.array_equal(f.debug_get(name), ref.debug_get(name)), name
+    f.close()
+    ref.close()
