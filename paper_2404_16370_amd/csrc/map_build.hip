@@ -552,7 +552,13 @@ void mp_build_map(mp_map m, const float* xyz, int64_t n, hipStream_t s) {
     mp_map_info& info = m->info;
     std::memset(&info, 0, sizeof(info));
 
+    // no Gaussian: a dense field without cells, so that every lookup gives its miss record
     auto finish_empty = [&]() {
+        m->drec.alloc(sizeof(float4) * 2);
+        k_dense_records<<<1, kBlock, 0, s>>>(nullptr, 0, nullptr, m->drec.as<float4>());
+        MP_CHECK_LAUNCH();
+        view.drec = m->drec.as<float4>();
+        info.device_bytes = (int64_t)m->drec.bytes;
         view.backend = MP_NNF_DENSE;
         view.dim[0] = view.dim[1] = view.dim[2] = 0;
         info.backend = MP_NNF_DENSE;
