@@ -16,6 +16,7 @@
 #include "megapf.h"
 #include "mp_internal.hpp"
 #include "mp_lsh.hpp"
+#include "mp_place.hpp"
 
 // ------------------------------------------------------------ errors
 static thread_local std::string g_err;
@@ -106,15 +107,17 @@ void HostMem::ensure(size_t b) {
 
 static inline hipStream_t as_stream(void* s) { return static_cast<hipStream_t>(s); }
 
-static bool is_device_ptr(const void* p) {
-    hipPointerAttribute_t a;
+// false: memory that the runtime does not know (ordinary host memory)
+static bool pointer_attr(const void* p, hipPointerAttribute_t& a) {
     std::memset(&a, 0, sizeof(a));
     const hipError_t e = hipPointerGetAttributes(&a, p);
-    if (e != hipSuccess) {
-        (void)hipGetLastError();
-        return false;
-    }
-    return a.type == hipMemoryTypeDevice || a.type == hipMemoryTypeManaged;
+    if (e != hipSuccess) (void)hipGetLastError();
+    return e == hipSuccess;
+}
+
+static bool is_device_ptr(const void* p) {
+    hipPointerAttribute_t a;
+    return pointer_attr(p, a) && (a.type == hipMemoryTypeDevice || a.type == hipMemoryTypeManaged);
 }
 
 // bring `bytes` of caller data into device memory (no copy for device pointers)
@@ -439,6 +442,7 @@ extern "C" mp_status mp_filter_init(mp_map map, const mp_filter_params* params, 
         }
         mp_filter f = new mp_filter_s();
         try {
+            MP_HIP(hipGetDevice(&f->device));
             f->map = map;
             map->users++;
             f->p = *params;
@@ -829,11 +833,15 @@ extern "C" mp_status mp_posterior_query(mp_filter f, mp_posterior* out, float* p
         // Poses and weights are packed and checked on the device.  Small
         // filters' go straight to pinned host memory and from there to the
         // caller, larger ones to a device buffer and from there in one copy
-        // each; device outputs are written in place.  (Both copied whole and
-        // converted on the host, 1,048,576 particles took 20.3 ms, 2.8 now;
-        // 4096 particles 130 us, 45 now, most of it the wait for the stream.)
+        // each; outputs on the filter's device are written in place.  (Both copied
+        // whole and converted on the host, 1,048,576 particles took 20.3 ms, 2.8
+        // now; 4096 particles 130 us, 45 now, most of it the wait for the stream.)
         std::lock_guard<std::mutex> lock(f->query_mu);
-        const bool p_dev = poses_out && is_device_ptr(poses_out), w_dev = weights_out && is_device_ptr(weights_out);
+        const auto in_place = [&](const void* p) {
+            hipPointerAttribute_t a;
+            return p && pointer_attr(p, a) && mp_in_place(a, f->device);
+        };
+        const bool p_dev = in_place(poses_out), w_dev = in_place(weights_out);
         const bool staged = (poses_out && !p_dev) || (weights_out && !w_dev);
         const size_t head = 256, wbytes = sizeof(double) * N, pbytes = sizeof(float) * 7 * N;
         const bool pinned = staged && wbytes + pbytes <= kPinnedQuery;
@@ -846,11 +854,14 @@ extern "C" mp_status mp_posterior_query(mp_filter f, mp_posterior* out, float* p
         static_assert(sizeof(QueryOut) <= 256, "before the packed outputs");
         q->bad = 0;
         mp_launch_query(f, q, pp, wp, s);
-        if (!pinned && pp && !p_dev) MP_HIP(hipMemcpyAsync(poses_out, pp, pbytes, hipMemcpyDeviceToHost, s));
-        if (!pinned && wp && !w_dev) MP_HIP(hipMemcpyAsync(weights_out, wp, wbytes, hipMemcpyDeviceToHost, s));
+        // from pinned memory to the host once it is there, else (another device's memory too) in stream order
+        const bool p_late = pinned && pp && !p_dev && !is_device_ptr(poses_out);
+        const bool w_late = pinned && wp && !w_dev && !is_device_ptr(weights_out);
+        if (pp && !p_dev && !p_late) MP_HIP(hipMemcpyAsync(poses_out, pp, pbytes, hipMemcpyDefault, s));
+        if (wp && !w_dev && !w_late) MP_HIP(hipMemcpyAsync(weights_out, wp, wbytes, hipMemcpyDefault, s));
         MP_HIP(hipStreamSynchronize(s));
-        if (pinned && pp && !p_dev) std::memcpy(poses_out, pp, pbytes);
-        if (pinned && wp && !w_dev) std::memcpy(weights_out, wp, wbytes);
+        if (p_late) std::memcpy(poses_out, pp, pbytes);
+        if (w_late) std::memcpy(weights_out, wp, wbytes);
         std::memset(out, 0, sizeof(*out));
         for (int k = 0; k < 7; ++k) out->map_pose[k] = q->pose[k];
         out->map_index = q->index;

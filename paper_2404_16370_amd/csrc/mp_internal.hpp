@@ -169,6 +169,7 @@ struct mp_filter_s {
     int batch_users = 0;          // batches holding this filter
     mp_filter_params p{};
     hipStream_t last_stream = nullptr;
+    int device = 0;           // its buffers' device
     int32_t n = 0, K = 0;
     int32_t frame = 0;
     int32_t lsh_counter = 0;  // frame value used by the LSH counter of the next pass
