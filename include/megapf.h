@@ -361,6 +361,8 @@ MP_API mp_status mp_stage_times(mp_filter f, float* ms_out, int32_t* counts_out)
  *             outside the output (keys changed during the sort); then that
  *             sort's order is wrong
  *   "capture_hb"  int32 (set only)
+ *   "query_stage" int32 (set only): most bytes of pinned host memory that
+ *             mp_posterior_query packs poses and weights into at a time
  * bytes must equal the named buffer's size.  mp_debug_stage runs one stage
  * on the current state (iteration selects the LSH frame counter; dT/cov_dT as
  * in mp_filter_step, used by MP_STAGE_PREDICT only); MP_DEBUG_RESCORE runs

@@ -89,8 +89,6 @@ const void* ManyTab::put(const void* data, size_t n) {
 
 constexpr size_t kStampMarks = 2;   // clock values of a scan upload before those of a step
 
-constexpr size_t kPinnedQuery = 1 << 20;   // bytes of poses and weights that a query packs into pinned host memory
-
 void HostMem::ensure(size_t b) {
     if (bytes >= b) return;
     if (p) (void)hipHostFree(p);
@@ -830,38 +828,40 @@ extern "C" mp_status mp_posterior_query(mp_filter f, mp_posterior* out, float* p
         if (!f || !out) mp_throw(MP_E_ARG, "null argument");
         hipStream_t s = as_stream(stream);
         const size_t N = (size_t)f->n;
-        // Poses and weights are packed and checked on the device.  Small
-        // filters' go straight to pinned host memory and from there to the
-        // caller, larger ones to a device buffer and from there in one copy
-        // each; outputs on the filter's device are written in place.  (Both copied
-        // whole and converted on the host, 1,048,576 particles took 20.3 ms, 2.8
-        // now; 4096 particles 130 us, 45 now, most of it the wait for the stream.)
+        // Poses and weights are packed and checked on the device; outputs on the
+        // filter's device are written in place, others go through pinned host
+        // memory, query_stage bytes at a time.  (Both copied whole and converted on
+        // the host, 1,048,576 particles took 20.3 ms; packed in 36 MiB of device memory
+        // and copied from there 2.7 ms, now 2.5, with stages of 0.5 MiB 2.9, of 1 to
+        // 16 MiB 2.5 to 2.6; weights alone 0.61 and 0.56, with 1 MiB 0.63.  4096
+        // particles 130 us, 28 now, most of it the wait for the stream.)
         std::lock_guard<std::mutex> lock(f->query_mu);
         const auto in_place = [&](const void* p) {
             hipPointerAttribute_t a;
             return p && pointer_attr(p, a) && mp_in_place(a, f->device);
         };
-        const bool p_dev = in_place(poses_out), w_dev = in_place(weights_out);
-        const bool staged = (poses_out && !p_dev) || (weights_out && !w_dev);
-        const size_t head = 256, wbytes = sizeof(double) * N, pbytes = sizeof(float) * 7 * N;
-        const bool pinned = staged && wbytes + pbytes <= kPinnedQuery;
-        f->host.ensure(head + (pinned ? wbytes + pbytes : 0));
-        if (staged && !pinned) f->pack.ensure(wbytes + pbytes);
-        char* stage = pinned ? f->host.as<char>() + head : f->pack.as<char>();
-        double* wp = weights_out ? (w_dev ? weights_out : reinterpret_cast<double*>(stage)) : nullptr;
-        float* pp = poses_out ? (p_dev ? poses_out : reinterpret_cast<float*>(stage + wbytes)) : nullptr;
+        const bool p_staged = poses_out && !in_place(poses_out), w_staged = weights_out && !in_place(weights_out);
+        const bool p_host = p_staged && !is_device_ptr(poses_out), w_host = w_staged && !is_device_ptr(weights_out);
+        const size_t per = (p_staged ? sizeof(float) * 7 : 0) + (w_staged ? sizeof(double) : 0);   // bytes of a particle
+        const size_t head = 256, room = std::min(per * N, std::max(per, f->query_stage));
+        f->host.ensure(head + room);
+        char* stage = f->host.as<char>() + head;
         QueryOut* q = f->host.as<QueryOut>();
         static_assert(sizeof(QueryOut) <= 256, "before the packed outputs");
         q->bad = 0;
-        mp_launch_query(f, q, pp, wp, s);
-        // from pinned memory to the host once it is there, else (another device's memory too) in stream order
-        const bool p_late = pinned && pp && !p_dev && !is_device_ptr(poses_out);
-        const bool w_late = pinned && wp && !w_dev && !is_device_ptr(weights_out);
-        if (pp && !p_dev && !p_late) MP_HIP(hipMemcpyAsync(poses_out, pp, pbytes, hipMemcpyDefault, s));
-        if (wp && !w_dev && !w_late) MP_HIP(hipMemcpyAsync(weights_out, wp, wbytes, hipMemcpyDefault, s));
-        MP_HIP(hipStreamSynchronize(s));
-        if (p_late) std::memcpy(poses_out, pp, pbytes);
-        if (w_late) std::memcpy(weights_out, wp, wbytes);
+        const size_t most = per ? room / per : N;   // particles at a time
+        for (size_t i0 = 0; i0 < N; i0 += most) {
+            const size_t m = std::min(most, N - i0), wbytes = sizeof(double) * m, pbytes = sizeof(float) * 7 * m;
+            double* wp = w_staged ? reinterpret_cast<double*>(stage) : (weights_out ? weights_out + i0 : nullptr);
+            float* pp = p_staged ? reinterpret_cast<float*>(stage + (w_staged ? wbytes : 0))
+                                 : (poses_out ? poses_out + 7 * i0 : nullptr);
+            mp_launch_query(f, q, pp, wp, (int32_t)i0, (int32_t)m, s);
+            if (p_staged && !p_host) MP_HIP(hipMemcpyAsync(poses_out + 7 * i0, pp, pbytes, hipMemcpyDefault, s));
+            if (w_staged && !w_host) MP_HIP(hipMemcpyAsync(weights_out + i0, wp, wbytes, hipMemcpyDefault, s));
+            MP_HIP(hipStreamSynchronize(s));
+            if (p_host) std::memcpy(poses_out + 7 * i0, pp, pbytes);
+            if (w_host) std::memcpy(weights_out + i0, wp, wbytes);
+        }
         std::memset(out, 0, sizeof(*out));
         for (int k = 0; k < 7; ++k) out->map_pose[k] = q->pose[k];
         out->map_index = q->index;
@@ -972,6 +972,14 @@ extern "C" mp_status mp_debug_set(mp_filter f, const char* name, const void* src
             f->capture_hb = v ? 1 : 0;
             if (f->capture_hb) f->hb.ensure(28 * 4 * (size_t)f->n);
             if (f->capture_hb) f->solve_how.ensure(4 * (size_t)f->n);
+            return;
+        }
+        if (std::string(name ? name : "") == "query_stage") {
+            if (bytes != 4) mp_throw(MP_E_ARG, "query_stage takes one int32");
+            int32_t v = 0;
+            fetch_host(src, 4, &v, s);
+            if (v < 0) mp_throw(MP_E_ARG, "query_stage must not be negative");
+            f->query_stage = (size_t)v;
             return;
         }
         const NamedBuf b = lookup_buf(f, name);

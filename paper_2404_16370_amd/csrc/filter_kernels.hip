@@ -972,9 +972,10 @@ struct QueryArgs {
     const double* __restrict__ info;
     const int32_t* __restrict__ flags;
     QueryOut* out;     // host memory
-    float* pout;       // N x 7, or null
-    double* wout;      // N, or null
+    float* pout;       // m x 7, or null
+    double* wout;      // m, or null
     int32_t n;
+    int32_t i0, m;     // the particles that are handed out
 };
 
 // Packing and the finiteness check of what a query hands out, one thread per
@@ -984,19 +985,19 @@ __global__ __launch_bounds__(256) void k_query(QueryArgs A) {
     const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
     const float* P = reinterpret_cast<const float*>(A.poses);
     bool bad = false;
-    if (A.pout && q < 7 * (int64_t)A.n) {
+    if (A.pout && q < 7 * (int64_t)A.m) {
         const int64_t i = q / 7;
-        const float v = P[8 * i + (q - 7 * i)];
+        const float v = P[8 * (A.i0 + i) + (q - 7 * i)];
         bad = !isfinite(v);
         A.pout[q] = v;
     }
-    if (A.wout && q < A.n) {
-        const float v = A.prior[q];
+    if (A.wout && q < A.m) {
+        const float v = A.prior[A.i0 + q];
         bad = bad || !isfinite(v);
         A.wout[q] = (double)v;
     }
     if (bad) __hip_atomic_store(&A.out->bad, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-    if (q == 0) {
+    if (q == 0 && A.i0 == 0) {
         for (int k = 0; k < 8; ++k) A.out->info[k] = A.info[k];
         int idx = (int)A.info[7];
         if (idx < 0 || idx >= A.n) idx = 0;
@@ -1007,7 +1008,8 @@ __global__ __launch_bounds__(256) void k_query(QueryArgs A) {
 }
 }  // namespace
 
-void mp_launch_query(mp_filter f, QueryOut* out, float* poses, double* weights, hipStream_t s) {
+void mp_launch_query(mp_filter f, QueryOut* out, float* poses, double* weights, int32_t i0, int32_t m,
+                     hipStream_t s) {
     QueryArgs A;
     A.poses = f->poses[f->cur].as<float4>();
     A.prior = f->prior.as<float>();
@@ -1017,7 +1019,9 @@ void mp_launch_query(mp_filter f, QueryOut* out, float* poses, double* weights, 
     A.pout = poses;
     A.wout = weights;
     A.n = f->n;
-    const int64_t items = poses ? 7 * (int64_t)f->n : (weights ? (int64_t)f->n : 1);
+    A.i0 = i0;
+    A.m = m;
+    const int64_t items = poses ? 7 * (int64_t)m : (weights ? (int64_t)m : 1);
     k_query<<<nblk(items), 256, 0, s>>>(A);
     MP_CHECK_LAUNCH();
 }

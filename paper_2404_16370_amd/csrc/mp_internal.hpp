@@ -211,9 +211,9 @@ struct mp_filter_s {
     DevMem scan_sort;         // radix-sort scratch of the walk order
     DevMem tlsh;              // 8 float
     DevMem stepinfo;          // posterior summary (doubles)
-    HostMem host;             // what queries read: QueryOut, then packed poses and weights of small filters
-    DevMem pack;              // packed poses and weights of large ones
-    std::mutex query_mu;      // one query at a time uses them
+    HostMem host;             // what queries read: QueryOut, then packed poses and weights
+    size_t query_stage = 2 << 20;   // most bytes of the latter
+    std::mutex query_mu;      // one query at a time uses it
     // stage timers of the last step (mp_stage_begin) and scan upload
     DevMem stamps;            // device clock values: [0] scan start, [1] scan end, then one per mark
     std::vector<StageMark> marks;
@@ -381,7 +381,8 @@ struct QueryOut {
     int32_t resolves;    // FP64 re-solves
     uint32_t bad;        // set before the launch; 1: a requested pose or weight is not finite
 };
-void mp_launch_query(mp_filter f, QueryOut* out, float* poses, double* weights, hipStream_t s);
+// (of the m particles from i0 on; the summary with the first)
+void mp_launch_query(mp_filter f, QueryOut* out, float* poses, double* weights, int32_t i0, int32_t m, hipStream_t s);
 void mp_launch_reset_lists(mp_filter f, hipStream_t s);
 // device fill (graph-safe replacement of hipMemsetAsync)
 void mp_fill_u32(void* p, uint32_t v, size_t n, hipStream_t s);

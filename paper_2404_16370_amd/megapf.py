@@ -471,9 +471,9 @@ class Filter:
         return out
 
     def debug_set(self, name, value, stream=None):
-        if name == "capture_hb":
+        if name in ("capture_hb", "query_stage"):
             v = np.array([int(value)], np.int32)
-            _check(lib().mp_debug_set(self.handle, b"capture_hb", _ptr(v), 4, _stream(stream)))
+            _check(lib().mp_debug_set(self.handle, name.encode(), _ptr(v), 4, _stream(stream)))
             return
         dt, shp = _DEBUG_LAYOUT[name]
         arr = np.ascontiguousarray(value, dt).reshape(shp(self.n, self.K, self.scan_n))
