@@ -536,16 +536,16 @@ extern "C" mp_status mp_filter_destroy(mp_filter f) {
 // for a while, as waiting for the stream costs as much again and would wait for
 // the sort as well.  (An upload of 300 points returned after 42 us and was done
 // after 85 with the verdict copied back before the sort; 22 and 60 us now.)
-static bool scan_is_bad(const ScanPrep& P, hipStream_t s) {
+static uint32_t scan_verdict(const ScanPrep& P, hipStream_t s) {
     const auto read = [&]() { return __atomic_load_n(P.verdict, __ATOMIC_ACQUIRE); };
     const auto t0 = std::chrono::steady_clock::now();
-    while (read() >> 1 != P.seq)
+    while (read() >> 2 != P.seq)
         if (std::chrono::steady_clock::now() - t0 > std::chrono::microseconds(200)) {   // behind other work
             MP_HIP(hipStreamSynchronize(s));
-            if (read() >> 1 != P.seq) mp_throw(MP_E_HIP, "no verdict on the scan");
+            if (read() >> 2 != P.seq) mp_throw(MP_E_HIP, "no verdict on the scan");
             break;
         }
-    return (read() & 1u) != 0;
+    return read() & 3u;
 }
 
 extern "C" mp_status mp_scan_upload(mp_filter f, const float* xyz, const float* cov6, int32_t n, void* stream) {
@@ -556,7 +556,7 @@ extern "C" mp_status mp_scan_upload(mp_filter f, const float* xyz, const float* 
         if (n > 0) {
             f->scan_xyz.ensure(sizeof(float) * 3 * (size_t)n);
             f->scan_perm.ensure(sizeof(int32_t) * (size_t)n);
-            f->scan_work.ensure(sizeof(float4) * (kPrepParts + 1) + sizeof(uint32_t) * 3 * (size_t)n);
+            f->scan_work.ensure(sizeof(float4) * (2 * kPrepParts + 1) + sizeof(uint32_t) * 5 * (size_t)n);
             if (!f->scan_verdict.p) {
                 f->scan_verdict.ensure(64);
                 *f->scan_verdict.as<uint32_t>() = 0;   // the number of no scan
@@ -577,17 +577,20 @@ extern "C" mp_status mp_scan_upload(mp_filter f, const float* xyz, const float* 
             // a refused scan must leave alone, runs while the host waits for it.
             ScanPrep P;
             P.part = f->scan_work.as<float4>();
-            P.start = reinterpret_cast<uint64_t*>(P.part + kPrepParts);
-            P.key = reinterpret_cast<uint32_t*>(P.part + kPrepParts + 1);
+            P.start = reinterpret_cast<uint64_t*>(P.part + 2 * kPrepParts);
+            P.key = reinterpret_cast<uint32_t*>(P.part + 2 * kPrepParts + 1);
             P.idx = f->scan_perm.as<int32_t>();
             P.xyz = f->scan_xyz.as<float>();
             P.cov = dcov;
             P.verdict = f->scan_verdict.as<uint32_t>();
-            P.seq = f->scan_seq = f->scan_seq % 0x7FFFFFFFu + 1;
+            P.seq = f->scan_seq = f->scan_seq % 0x3FFFFFFFu + 1;
             P.n = n;
-            mp_scan_walk_order(P, 0.5f * f->map->params.voxel, P.key + n, reinterpret_cast<int32_t*>(P.key + 2 * (size_t)n),
-                               f->scan_sort, s);
-            if (scan_is_bad(P, s)) {
+            uint32_t* key_alt = P.key + n;
+            int32_t* work[3];   // an order's second buffer, the index's order, places in the walk order
+            for (size_t k = 0; k < 3; ++k) work[k] = reinterpret_cast<int32_t*>(P.key + (2 + k) * (size_t)n);
+            mp_scan_walk_order(P, 0.5f * f->map->params.voxel, key_alt, work[0], f->scan_sort, s);
+            const uint32_t verdict = scan_verdict(P, s);
+            if (verdict & 1u) {
                 // (the sort: an upload that answers the refusal may come on another stream)
                 MP_HIP(hipStreamSynchronize(s));
                 mp_throw(MP_E_ARG, cov6 ? "non-finite scan point or covariance" : "non-finite scan point");
@@ -600,13 +603,15 @@ extern "C" mp_status mp_scan_upload(mp_filter f, const float* xyz, const float* 
             DevMem& idx = follows ? f->prev_idx : f->scan_idx;
             const size_t rec_bytes = sizeof(float) * 12 * (size_t)n, idx_bytes = mp_scan_index_bytes(n);
             {
-                DevMem walk_new, orig_new, idx_new;
+                DevMem walk_new, orig_new, idx_new, own_new;
                 if (f->scan.bytes < rec_bytes) walk_new.alloc(rec_bytes);
                 if (orig.bytes < rec_bytes) orig_new.alloc(rec_bytes);
                 if (idx.bytes < idx_bytes) idx_new.alloc(idx_bytes);
+                if ((verdict & 2u) && f->scan_own.bytes < rec_bytes) own_new.alloc(rec_bytes);
                 if (walk_new.p) f->scan.swap(walk_new);
                 if (orig_new.p) orig.swap(orig_new);
                 if (idx_new.p) idx.swap(idx_new);
+                if (own_new.p) f->scan_own.swap(own_new);
             }
             if (follows) {
                 f->scan_orig.swap(f->prev_orig);
@@ -614,8 +619,18 @@ extern "C" mp_status mp_scan_upload(mp_filter f, const float* xyz, const float* 
                 f->prev_n = f->orig_n;
             }
             f->orig_n = n;
-            mp_scan_records(P.xyz, dcov, P.idx, n, f->p.scan_k, f->p.cov_eps, mp_scan_index(f->scan_idx, n),
-                            f->scan_orig.as<float>(), f->scan.as<float>(), P.start, f->stamps.as<uint64_t>(), s);
+            f->idx_own = (verdict & 2u) != 0;
+            const int32_t* perm = P.idx;
+            ScanRecords R{f->scan_orig.as<float4>(), f->scan.as<float4>(), nullptr, nullptr};
+            if (f->idx_own) {
+                mp_scan_index_order(P, key_alt, work[1], work[0], work[2], f->scan_sort, s);
+                perm = work[1];
+                R.index = f->scan_own.as<float4>();
+                R.walk = f->scan.as<float4>();
+                R.wpos = work[2];
+            }
+            mp_scan_records(P.xyz, dcov, perm, n, f->p.scan_k, f->p.cov_eps, mp_scan_index(f->scan_idx, n), R, P.start,
+                            f->stamps.as<uint64_t>(), s);
             f->scan_timed = true;
         }
         f->scan_n = n;

@@ -205,7 +205,9 @@ struct mp_filter_s {
     int32_t orig_n = 0;       // points of the records in scan_orig (the last non-empty scan)
     DevMem odo_nn, odo_work;  // odometry work arrays
     DevMem scan_cov;          // n x 6 float staging of caller covariances
-    DevMem scan_work;         // parts and clock of ScanPrep, walk-order keys and work arrays (3n words)
+    DevMem scan_work;         // parts and clock of ScanPrep, keys and work arrays of its orders (5n words)
+    bool idx_own = false;     // the current scan's index has an order of its own:
+    DevMem scan_own;          // n x 12 float records in that order
     HostMem scan_verdict;     // verdict of the last uploaded scan's check, and its number
     uint32_t scan_seq = 0;
     DevMem scan_sort;         // radix-sort scratch of the walk order
@@ -292,8 +294,9 @@ void mp_build_map(mp_map m, const float* xyz_dev, int64_t n, hipStream_t s);
 void mp_map_lookup_launch(const MapView& v, const float* xyz_dev, int64_t n, int32_t* gid_dev, hipStream_t s);
 
 // scan covariances (scan.hip)
-// spatial index of a scan for neighbour searches: its points in walk order,
-// the boxes (2 float4) of every 64 of them and of every 16 blocks
+// spatial index of a scan for neighbour searches: its points in an order that
+// keeps neighbours together (the walk order, or mp_scan_index_order's), the
+// boxes (2 float4) of every 64 of them and of every 16 blocks
 constexpr int kScanBlock = 64, kScanFan = 16;
 struct ScanIndex {
     float4* pts;     // n: x, y, z, caller index (bits)
@@ -303,11 +306,18 @@ struct ScanIndex {
 };
 size_t mp_scan_index_bytes(int32_t n);
 ScanIndex mp_scan_index(const DevMem& mem, int32_t n);
-// the index, then every point's record in the caller's order and in walk order;
+// where a scan's records (3 float4 each) go: in the caller's order, in the index's
+// order, and in walk order, where that is another one than the index's
+struct ScanRecords {
+    float4* caller;
+    float4* index;
+    float4* walk;          // or null
+    const int32_t* wpos;   // a point's place in the walk order, by caller index
+};
+// the index of the points in the order of `perm` (caller indices), then every point's record;
 // stamps: [0] set to *start, [1] to the device clock at which the last workgroup ends
 void mp_scan_records(const float* xyz_dev, const float* cov6_dev, const int32_t* perm, int32_t n, int32_t k, float eps,
-                     const ScanIndex& X, float* rec_dev, float* walk_dev, const uint64_t* start, uint64_t* stamps,
-                     hipStream_t s);
+                     const ScanIndex& X, const ScanRecords& R, const uint64_t* start, uint64_t* stamps, hipStream_t s);
 // walk order of the likelihood: stable sort of the n > 0 points by the Morton
 // key of their cell (edge `cell`); idx holds the result, key, keys_alt and
 // perm_alt are n-entry work arrays
@@ -316,17 +326,22 @@ constexpr int kPrepParts = 64;   // workgroups that check a larger one (of 65,53
 struct ScanPrep {
     const float* xyz;    // n x 3
     const float* cov;    // n x 6, or null
-    float4* part;        // kPrepParts
+    float4* part;        // 2 kPrepParts
     uint32_t* key;
     int32_t* idx;
     uint64_t* start;     // device clock at which the keys were begun
-    uint32_t* verdict;   // host memory: 2 seq, plus 1 if an input is not finite
+    uint32_t* verdict;   // host memory: 4 seq, plus 1 if an input is not finite, plus 2 if the walk
+                         // order's cells do not tell neighbours apart (mp_scan_index_order)
     uint32_t seq;
     int32_t n;
     float inv_cell;
 };
 void mp_scan_walk_order(ScanPrep A, float cell, uint32_t* keys_alt, int32_t* perm_alt, DevMem& scratch,
                         hipStream_t s);
+// an order of the index for scans whose extent the walk order's cells do not fit:
+// perm (caller indices), and wpos: every point's place in the walk order
+void mp_scan_index_order(const ScanPrep& A, uint32_t* keys_alt, int32_t* perm, int32_t* perm_alt, int32_t* wpos,
+                         DevMem& scratch, hipStream_t s);
 
 // filter stages
 void mp_launch_init_uniform(mp_filter f, const float lo[3], const float hi[3], hipStream_t s);

@@ -67,7 +67,7 @@ __device__ __forceinline__ float3 odo_point(const float* pose, const mpdet::mat3
 struct OdoArgs {
     ScanIndex T;                       // the previous scan's index
     const float4* __restrict__ trec;   // its records, caller order (3 float4 per point)
-    const float4* __restrict__ swalk;  // the current scan's records in walk order
+    const float4* __restrict__ swalk;  // the current scan's records in its index's order
     const float4* __restrict__ spts;   // and its points with their caller index
     int32_t* nn;                       // ns, caller order: target index or -1 (read and rewritten by each iteration)
     const double* __restrict__ part_in;   // the iteration before: [kOTerms][kOParts] workgroup sums
@@ -504,7 +504,7 @@ void odometry_impl(void* ctx) {
     OdoArgs A;
     A.T = mp_scan_index(f->prev_idx, nt);
     A.trec = f->prev_orig.as<float4>();
-    A.swalk = f->scan.as<float4>();
+    A.swalk = (f->idx_own ? f->scan_own : f->scan).as<float4>();
     A.spts = S.pts;
     A.nn = nn;
     for (int k = 0; k < 7; ++k) A.init[k] = init[k];

@@ -75,11 +75,12 @@ __device__ __forceinline__ void stamp_last(uint64_t* p) {
 }
 
 // ------------------------------------------------------------ spatial index of a scan
-// The scan in the likelihood's walk order (Morton order of its cells), as
-// (x, y, z, caller index) per point, with the bounding boxes of every block
-// of 64 consecutive points and of every 16 blocks: the neighbour searches
-// (here and in the odometry) skip a box when it lies farther away than what
-// they already hold.  One workgroup per 1024 points, one wave per block.
+// The scan in the likelihood's walk order (Morton order of its cells) or one of
+// its own (k_index_keys below), as (x, y, z, caller index) per point, with the
+// bounding boxes of every block of 64 consecutive points and of every 16 blocks:
+// the neighbour searches (here and in the odometry) skip a box when it lies
+// farther away than what they already hold.  One workgroup per 1024 points, one
+// wave per block.
 constexpr int kIdxThreads = kScanBlock * kScanFan;
 
 __device__ __forceinline__ float wave_min(float v) {
@@ -154,12 +155,24 @@ __device__ __forceinline__ uint64_t knn_key(float d2, int32_t j) {
     return ((uint64_t)__float_as_uint(d2) << 32) | (uint32_t)j;
 }
 
+// the record of caller index i, at place w of the index
+__device__ __forceinline__ void store_record(const ScanRecords& R, int i, int w, const float4 r0, const float4 r1,
+                                             const float4 r2) {
+    const auto put = [&](float4* __restrict__ to, int at) {
+        to[3 * at] = r0;
+        to[3 * at + 1] = r1;
+        to[3 * at + 2] = r2;
+    };
+    put(R.caller, i);
+    put(R.index, w);
+    if (R.walk) put(R.walk, R.wpos[i]);
+}
+
 // The loops that are not unrolled keep the code short: a launch over a few
 // hundred points spends its time fetching instructions for the first time.
 template <int H>   // list entries per lane
 __global__ __launch_bounds__(kB) void k_scan_knn_cov(const float* __restrict__ xyz, ScanIndex X, int n, int k,
-                                                     float eps, float4* __restrict__ rec, float4* __restrict__ walk,
-                                                     uint64_t* __restrict__ stamp_end) {
+                                                     float eps, ScanRecords R, uint64_t* __restrict__ stamp_end) {
     constexpr int kPer = kB / kQLanes;
     __shared__ float nbr[kPer][H * kQLanes][3];
     __shared__ double cov[kPer][7];   // 6 and a pad
@@ -301,18 +314,13 @@ __global__ __launch_bounds__(kB) void k_scan_knn_cov(const float* __restrict__ x
         const float4 r0 = make_float4(p.x, p.y, p.z, (float)c6[0]);
         const float4 r1 = make_float4((float)c6[1], (float)c6[2], (float)c6[3], (float)c6[4]);
         const float4 r2 = make_float4((float)c6[5], 0.0f, 0.0f, 0.0f);
-        rec[3 * i] = r0;
-        rec[3 * i + 1] = r1;
-        rec[3 * i + 2] = r2;
-        walk[3 * wl] = r0;
-        walk[3 * wl + 1] = r1;
-        walk[3 * wl + 2] = r2;
+        store_record(R, i, wl, r0, r1, r2);
     }
     stamp_last(stamp_end);
 }
 
-__global__ void k_scan_given_cov(const float* __restrict__ cov, ScanIndex X, int n, float4* __restrict__ rec,
-                                 float4* __restrict__ walk, uint64_t* __restrict__ stamp_end) {
+__global__ void k_scan_given_cov(const float* __restrict__ cov, ScanIndex X, int n, ScanRecords R,
+                                 uint64_t* __restrict__ stamp_end) {
     const int w = blockIdx.x * blockDim.x + threadIdx.x;
     if (w < n) {
         const float4 p = X.pts[w];
@@ -320,12 +328,7 @@ __global__ void k_scan_given_cov(const float* __restrict__ cov, ScanIndex X, int
         const float* c = cov + 6 * (size_t)i;
         const float4 r0 = make_float4(p.x, p.y, p.z, c[0]), r1 = make_float4(c[1], c[2], c[3], c[4]);
         const float4 r2 = make_float4(c[5], 0.0f, 0.0f, 0.0f);
-        rec[3 * i] = r0;
-        rec[3 * i + 1] = r1;
-        rec[3 * i + 2] = r2;
-        walk[3 * w] = r0;
-        walk[3 * w + 1] = r1;
-        walk[3 * w + 2] = r2;
+        store_record(R, i, w, r0, r1, r2);
     }
     stamp_last(stamp_end);
 }
@@ -340,26 +343,30 @@ __device__ inline uint32_t spread10(uint32_t v) {
 }
 
 // Check, walk keys and verdict of an uploaded scan.  What bounds it: launches
-// and the host's wait.  The verdict (2 seq, plus 1 if any point or covariance
-// entry is not finite) goes straight to pinned host memory, so that the host
-// can go on while the device sorts.
+// and the host's wait.  The verdict goes straight to pinned host memory, so that
+// the host can go on while the device sorts.
 constexpr int kChk = 1024;
 
+constexpr int kOwnOrderMin = 3072;   // points, see scan_unfit
+
 struct ScanMin {
-    float lo[3];   // minimum corner of the points
+    float lo[6];   // minimum corner of the points, negated maximum corner
     bool bad;
 };
 
 // of the points [from, to), by a workgroup of kChk
 __device__ __forceinline__ ScanMin scan_min(const ScanPrep& A, int from, int to) {
-    __shared__ float red[4][kChk / 64];
-    ScanMin M{{__builtin_inff(), __builtin_inff(), __builtin_inff()}, false};
+    __shared__ float red[7][kChk / 64];
+    constexpr float kInf = __builtin_inff();
+    ScanMin M{{kInf, kInf, kInf, kInf, kInf, kInf}, false};
+    const int corners = A.n < kOwnOrderMin ? 3 : 6;   // (scan_unfit asks for the maximum)
     for (int i = from + threadIdx.x; i < to; i += kChk) {
 #pragma unroll
         for (int a = 0; a < 3; ++a) {
             const float v = A.xyz[3 * i + a];
             M.bad |= !__builtin_isfinite(v);
             M.lo[a] = fminf(M.lo[a], v);
+            if (corners == 6) M.lo[3 + a] = fminf(M.lo[3 + a], -v);
         }
         if (A.cov)
 #pragma unroll
@@ -367,16 +374,18 @@ __device__ __forceinline__ ScanMin scan_min(const ScanPrep& A, int from, int to)
     }
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
 #pragma unroll
-    for (int a = 0; a < 3; ++a) M.lo[a] = wave_min(M.lo[a]);
+    for (int a = 0; a < 6; ++a)
+        if (a < corners) M.lo[a] = wave_min(M.lo[a]);
     const bool any = __any(M.bad);
     if (lane == 0) {
-        for (int a = 0; a < 3; ++a) red[a][wave] = M.lo[a];
-        red[3][wave] = any ? 1.0f : 0.0f;
+        for (int a = 0; a < 6; ++a) red[a][wave] = M.lo[a];
+        red[6][wave] = any ? 1.0f : 0.0f;
     }
     __syncthreads();
 #pragma unroll
-    for (int a = 0; a < 3; ++a) M.lo[a] = wave_min(red[a][lane % (kChk / 64)]);
-    M.bad = __any(red[3][lane % (kChk / 64)] != 0.0f);
+    for (int a = 0; a < 6; ++a)
+        if (a < corners) M.lo[a] = wave_min(red[a][lane % (kChk / 64)]);
+    M.bad = __any(red[6][lane % (kChk / 64)] != 0.0f);
     return M;
 }
 
@@ -393,15 +402,36 @@ __device__ __forceinline__ void scan_key(const ScanPrep& A, const float lo[3], i
     A.idx[i] = i;
 }
 
-__device__ __forceinline__ void scan_verdict(const ScanPrep& A, bool bad) {
+// Whether the cells of the walk order, which the index takes over, do not tell
+// neighbours apart: the scan reaches beyond the 1024 cells of an axis (what lies
+// there is clamped into the last one), or has more than a block of points to a
+// cell even if it fills its box.  Small scans keep the walk order: their index has
+// few boxes in any case (microseconds of an upload and of ten iterations of
+// odometry, points in random order and one 8 km off, walk order / own order: 2000
+// points 83 and 284 / 101 and 202; in the order of a turning sensor 69 and 187 /
+// 102 and 204; 4000 points 117 and 409 / 123 and 236, and 100 and 261 / 128 and 226).
+__device__ __forceinline__ bool scan_unfit(const ScanPrep& A, const float lo[6]) {
+    if (A.n < kOwnOrderMin) return false;
+    float cells = 1.0f, most = 0.0f;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const float c = floorf((-lo[3 + a] - lo[a]) * A.inv_cell) + 1.0f;
+        cells *= c;
+        most = fmaxf(most, c);
+    }
+    return most > 1024.0f || cells * (float)kScanBlock < (float)A.n;
+}
+
+__device__ __forceinline__ void scan_verdict(const ScanPrep& A, const float lo[6], bool bad) {
     *A.start = (uint64_t)wall_clock64();
-    __hip_atomic_store(A.verdict, 2 * A.seq + (bad ? 1u : 0u), __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    const uint32_t word = 4 * A.seq + (scan_unfit(A, lo) ? 2u : 0u) + (bad ? 1u : 0u);
+    __hip_atomic_store(A.verdict, word, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // scans of up to kPrepOne points, in one workgroup
 __global__ __launch_bounds__(kChk) void k_scan_prep(ScanPrep A) {
     const ScanMin M = scan_min(A, 0, A.n);
-    if (threadIdx.x == 0) scan_verdict(A, M.bad);
+    if (threadIdx.x == 0) scan_verdict(A, M.lo, M.bad);
     for (int i = threadIdx.x; i < A.n; i += kChk) scan_key(A, M.lo, i);
 }
 
@@ -409,17 +439,76 @@ __global__ __launch_bounds__(kChk) void k_scan_prep(ScanPrep A) {
 // the keys reduces (up to 64 of them, one a lane)
 __global__ __launch_bounds__(kChk) void k_scan_check(ScanPrep A) {
     const ScanMin M = scan_min(A, blockIdx.x * kChk, min(A.n, ((int)blockIdx.x + 1) * kChk));
-    if (threadIdx.x == 0) A.part[blockIdx.x] = make_float4(M.lo[0], M.lo[1], M.lo[2], M.bad ? 1.0f : 0.0f);
+    if (threadIdx.x == 0) {
+        A.part[2 * blockIdx.x] = make_float4(M.lo[0], M.lo[1], M.lo[2], M.bad ? 1.0f : 0.0f);
+        A.part[2 * blockIdx.x + 1] = make_float4(M.lo[3], M.lo[4], M.lo[5], 0.0f);
+    }
 }
 
 __global__ __launch_bounds__(256) void k_scan_keys(ScanPrep A) {
     const int nb = (A.n + kChk - 1) / kChk;
-    const float4 p = A.part[min((int)(threadIdx.x & 63), nb - 1)];
-    const float lo[3] = {wave_min(p.x), wave_min(p.y), wave_min(p.z)};
+    const int b = min((int)(threadIdx.x & 63), nb - 1);
+    const float4 p = A.part[2 * b];
+    float lo[6] = {wave_min(p.x), wave_min(p.y), wave_min(p.z)};
     const bool bad = __any(p.w != 0.0f);
-    if (blockIdx.x == 0 && threadIdx.x == 0) scan_verdict(A, bad);
+    if (blockIdx.x == 0) {
+        const float4 u = A.part[2 * b + 1];
+        lo[3] = wave_min(u.x);
+        lo[4] = wave_min(u.y);
+        lo[5] = wave_min(u.z);
+        if (threadIdx.x == 0) scan_verdict(A, lo, bad);
+    }
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i < A.n) scan_key(A, lo, i);
+}
+
+// ------------------------------------------------------------ an index's own order
+// Morton keys on cells that grow with the distance from the scan's middle, for
+// scans that do not fit the walk order's cells whatever its points' spread: per
+// axis the middle is the median of 64 points taken evenly, the unit s the largest
+// axis's median distance from it, and a cell log2(1 + 16 |d| / s) / 21 wide, 1024
+// of them, up to 10^6 s away.  No result depends on the order but that of the
+// odometry's sums over the current scan.
+//
+// What bounds it: a sort and a launch more in the upload.  Milliseconds of an
+// upload and of ten iterations of odometry, 65,536 points in random order, all
+// points against all, walk order, own order: one of them 8 km off 4.5 and 8.4,
+// 3.1 and 26.8, 0.32 and 0.85; 1000 m wide 4.5 and 8.4, 2.6 and 9.7, 0.33 and
+// 0.79; 5 m wide under 5 m cells 4.5 and 8.4, 2.6 and 23.8, 0.30 and 0.77.  8192
+// points, one off, 0.39 and 0.42, 0.19 and 0.71, 0.16 and 0.26.
+__device__ __forceinline__ float wave_median(float v) {   // of a wave's 64 values
+    const int lane = threadIdx.x & 63;
+    int below = 0;
+    for (int j = 0; j < 64; ++j) {
+        const float o = __shfl(v, j);
+        below += o < v || (o == v && j < lane) ? 1 : 0;
+    }
+    const uint64_t at = __ballot(below == 32);   // one lane
+    return __shfl(v, at ? __builtin_ctzll(at) : 0);
+}
+
+__global__ __launch_bounds__(256) void k_index_keys(ScanPrep A, uint32_t* __restrict__ key, int32_t* __restrict__ perm,
+                                                    int32_t* __restrict__ wpos) {
+    const int64_t j = (int64_t)(threadIdx.x & 63) * A.n / 64;
+    float mid[3], s = 0.0f;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const float v = A.xyz[3 * j + a];
+        mid[a] = wave_median(v);
+        s = fmaxf(s, wave_median(fabsf(v - mid[a])));
+    }
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i >= A.n) return;
+    uint32_t c[3];
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const float d = A.xyz[3 * i + a] - mid[a];
+        const float q = 512.0f + copysignf(21.0f * __log2f(1.0f + 16.0f * fabsf(d) / s), d);
+        c[a] = (uint32_t)fminf(fmaxf(q, 0.0f), 1023.0f);   // (s = 0: the axis in two halves; NaN: 0)
+    }
+    key[i] = spread10(c[0]) | (spread10(c[1]) << 1) | (spread10(c[2]) << 2);
+    perm[i] = i;
+    wpos[A.idx[i]] = i;   // (A.idx: the walk order, sorted)
 }
 
 }  // namespace
@@ -441,21 +530,18 @@ ScanIndex mp_scan_index(const DevMem& mem, int32_t n) {
 }
 
 void mp_scan_records(const float* xyz, const float* cov6, const int32_t* perm, int32_t n, int32_t k, float eps,
-                     const ScanIndex& X, float* rec, float* walk, const uint64_t* start, uint64_t* stamps,
-                     hipStream_t s) {
+                     const ScanIndex& X, const ScanRecords& R, const uint64_t* start, uint64_t* stamps, hipStream_t s) {
     if (n <= 0) return;
     if (k > kKMax) mp_throw(MP_E_UNSUPPORTED, "scan_k above %d", kKMax);
     k_scan_index<<<X.supers, kIdxThreads, 0, s>>>(xyz, perm, n, X, start, stamps);
     MP_CHECK_LAUNCH();
-    float4* r4 = reinterpret_cast<float4*>(rec);
-    float4* w4 = reinterpret_cast<float4*>(walk);
     if (cov6) {
-        k_scan_given_cov<<<(n + 255) / 256, 256, 0, s>>>(cov6, X, n, r4, w4, stamps + 1);
+        k_scan_given_cov<<<(n + 255) / 256, 256, 0, s>>>(cov6, X, n, R, stamps + 1);
     } else {
         constexpr int per = kB / kQLanes;
         const unsigned grid = (unsigned)((n + per - 1) / per);
-        if (k <= kQLanes) k_scan_knn_cov<1><<<grid, kB, 0, s>>>(xyz, X, n, k, eps, r4, w4, stamps + 1);
-        else k_scan_knn_cov<2><<<grid, kB, 0, s>>>(xyz, X, n, k, eps, r4, w4, stamps + 1);
+        if (k <= kQLanes) k_scan_knn_cov<1><<<grid, kB, 0, s>>>(xyz, X, n, k, eps, R, stamps + 1);
+        else k_scan_knn_cov<2><<<grid, kB, 0, s>>>(xyz, X, n, k, eps, R, stamps + 1);
     }
     MP_CHECK_LAUNCH();
 }
@@ -472,4 +558,12 @@ void mp_scan_walk_order(ScanPrep A, float cell, uint32_t* keys_alt, int32_t* per
     MP_CHECK_LAUNCH();
     if (mp_sort_is_small(A.n)) mp_sort_small(SmSortArgs{A.key, A.key, A.idx, nullptr, nullptr, nullptr, A.n, 30, nullptr}, s);
     else mp_radix_sort_u32(A.key, A.idx, keys_alt, perm_alt, A.n, 30, scratch, s);
+}
+
+void mp_scan_index_order(const ScanPrep& A, uint32_t* keys_alt, int32_t* perm, int32_t* perm_alt, int32_t* wpos,
+                         DevMem& scratch, hipStream_t s) {
+    k_index_keys<<<(A.n + 255) / 256, 256, 0, s>>>(A, A.key, perm, wpos);
+    MP_CHECK_LAUNCH();
+    if (mp_sort_is_small(A.n)) mp_sort_small(SmSortArgs{A.key, A.key, perm, nullptr, nullptr, nullptr, A.n, 30, nullptr}, s);
+    else mp_radix_sort_u32(A.key, perm, keys_alt, perm_alt, A.n, 30, scratch, s);
 }
