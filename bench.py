@@ -935,7 +935,8 @@ def main():
         e1.record()
         f.step(dT, cov)
         e2.record()
-        st = f.stage_times()   # synchronises the device
+        e2.synchronize()
+        st = f.stage_times()
         lik_ms.append(st["likelihood_core"][0])
         lik_n.append(st["likelihood_core"][1])
         up_ms.append(e0.elapsed_time(e1))

@@ -327,8 +327,9 @@ enum {
 /* Per-stage device time of the last mp_filter_step (scan stage: of the last
  * mp_scan_upload), milliseconds, summed over the step's iterations, from the
  * device clock: a stage runs from the start of its first kernel to the start
- * of the next stage's (the last one to the step's end); synchronises the
- * device.  The SVGD update leaves the first table's codes of the iteration that
+ * of the next stage's (the last one to the step's end); waits for that step and
+ * that upload (a filter's first call: for the device; from then on its steps and
+ * uploads record an event each).  The SVGD update leaves the first table's codes of the iteration that
  * follows, so the LSH spans there count but take no time of their own.  ms_out
  * has MP_NUM_STAGES entries; stages not run read 0.
  * counts_out (nullable, MP_NUM_STAGES) receives the number of timed spans. */

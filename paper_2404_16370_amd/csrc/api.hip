@@ -397,6 +397,8 @@ static void destroy_filter(mp_filter f) {
     if (!f) return;
     if (f->map) f->map->users--;
     if (f->sur) f->sur->users--;
+    if (f->step_ev) (void)hipEventDestroy(f->step_ev);
+    if (f->scan_ev) (void)hipEventDestroy(f->scan_ev);
     delete f;
 }
 
@@ -548,6 +550,19 @@ static uint32_t scan_verdict(const ScanPrep& P, hipStream_t s) {
     return read() & 3u;
 }
 
+// The clock values [from, from + count) to the host and an event behind them, for a
+// filter whose stage times are asked for: mp_stage_times then waits for that
+// event, and not for other work on the device.  (Not for every filter: the events
+// alone, one with each upload and step, took a frame of 256 particles from 153 to
+// 160 us.)
+static bool leave_times(mp_filter f, hipEvent_t ev, size_t from, size_t count, hipStream_t s) {
+    if (!ev || sizeof(uint64_t) * (from + count) > f->stamps.bytes) return false;
+    MP_HIP(hipMemcpyAsync(f->times.as<uint64_t>() + from, f->stamps.as<uint64_t>() + from, sizeof(uint64_t) * count,
+                          hipMemcpyDeviceToHost, s));
+    MP_HIP(hipEventRecord(ev, s));
+    return true;
+}
+
 extern "C" mp_status mp_scan_upload(mp_filter f, const float* xyz, const float* cov6, int32_t n, void* stream) {
     return guarded("mp_scan_upload", [&]() {
         if (!f || n < 0 || (n > 0 && !xyz)) mp_throw(MP_E_ARG, "null argument or n < 0");
@@ -632,6 +647,7 @@ extern "C" mp_status mp_scan_upload(mp_filter f, const float* xyz, const float* 
             mp_scan_records(P.xyz, dcov, perm, n, f->p.scan_k, f->p.cov_eps, mp_scan_index(f->scan_idx, n), R, P.start,
                             f->stamps.as<uint64_t>(), s);
             f->scan_timed = true;
+            f->scan_rec = leave_times(f, f->scan_ev, 0, kStampMarks, s);
         }
         f->scan_n = n;
         f->last_stream = s;
@@ -831,6 +847,7 @@ extern "C" mp_status mp_filter_step(mp_filter f, const float dT[7], const float 
         }
         f->timing = false;
         f->stamp = nullptr;
+        f->step_rec = leave_times(f, f->step_ev, kStampMarks, f->marks.size(), s);
         f->sur_fallback = false;
         f->frame++;
         f->last_stream = s;
@@ -900,9 +917,18 @@ extern "C" mp_status mp_stage_times(mp_filter f, float* ms_out, int32_t* counts_
         int32_t counts[MP_NUM_STAGES] = {};
         double ticks[MP_NUM_STAGES] = {};
         if (f->scan_timed || !f->marks.empty()) {
-            std::vector<uint64_t> t(f->stamps.bytes / sizeof(uint64_t));
-            MP_HIP(hipDeviceSynchronize());
-            MP_HIP(hipMemcpy(t.data(), f->stamps.p, sizeof(uint64_t) * t.size(), hipMemcpyDeviceToHost));
+            if ((!f->marks.empty() && !f->step_rec) || (f->scan_timed && !f->scan_rec)) {   // not asked for before
+                f->times.ensure(f->stamps.bytes);
+                if (!f->step_ev) MP_HIP(hipEventCreateWithFlags(&f->step_ev, hipEventDisableTiming));
+                if (!f->scan_ev) MP_HIP(hipEventCreateWithFlags(&f->scan_ev, hipEventDisableTiming));
+                MP_HIP(hipDeviceSynchronize());
+                MP_HIP(hipMemcpy(f->times.p, f->stamps.p, f->stamps.bytes, hipMemcpyDeviceToHost));
+                f->step_rec = f->scan_rec = true;   // (an event that was never recorded is over)
+            } else {
+                if (!f->marks.empty()) MP_HIP(hipEventSynchronize(f->step_ev));
+                if (f->scan_timed) MP_HIP(hipEventSynchronize(f->scan_ev));
+            }
+            const uint64_t* t = f->times.as<uint64_t>();
             auto add = [&](int st, uint64_t from, uint64_t to, bool count) {
                 ticks[st] += to > from ? (double)(to - from) : 0.0;
                 counts[st] += count ? 1 : 0;

@@ -222,6 +222,11 @@ struct mp_filter_s {
     bool timing = false;      // a step is being launched eagerly: its stages are marked
     uint64_t* stamp = nullptr;   // where the next kernel that starts a stage writes its clock
     bool scan_timed = false;
+    // For filters whose stage times are asked for (from the first mp_stage_times on): steps and
+    // uploads leave their clock values in `times` and record an event.
+    HostMem times;
+    hipEvent_t step_ev = nullptr, scan_ev = nullptr;
+    bool step_rec = false, scan_rec = false;   // `times` holds the last one's, once its event is over
 };
 
 // Stage times.  The first kernel of a stage writes the device clock to the
