@@ -197,7 +197,9 @@ __global__ __launch_bounds__(256) void k_refresh(RefreshArgs A) {
 // 16, ... (at most R of them: the window, then the old list), all their loads
 // in flight together, and the K - 1 smallest (q, j) are then taken one by one
 // as the minimum over the lanes.  A candidate found twice has one key and is
-// taken once.  With one lane per particle the candidates' loads follow one
+// taken once; a round of candidates that no lane of the wave has costs nothing
+// (the nearly empty lists of spread particles: 98,304 35 -> 21 us, converged ones
+// 50 -> 39).  With one lane per particle the candidates' loads follow one
 // another, some 1 us each while few waves run.
 constexpr int kRfLanes = 16;
 constexpr int kRfMax = 98304;   // most particles
@@ -236,19 +238,27 @@ __device__ __forceinline__ void refresh_row(const RefreshArgs& A, int block) {
     }
     uint64_t key[R];
     float4 qj[R], tj[R];
+    bool ok[R], any[R];   // (any: uniform over the wave)
 #pragma unroll
     for (int u = 0; u < R; ++u) {
-        const int j = max(0, min(jc[u], A.n - 1));
+        ok[u] = jc[u] >= 0 && jc[u] < A.n && jc[u] != i;
+        any[u] = __any(ok[u]);
+    }
+#pragma unroll
+    for (int u = 0; u < R; ++u) {
+        if (!any[u]) continue;
+        const int j = ok[u] ? jc[u] : i;
         qj[u] = A.poses[2 * j];
         tj[u] = A.poses[2 * j + 1];
     }
 #pragma unroll
     for (int u = 0; u < R; ++u) {
+        key[u] = none;
+        if (!any[u]) continue;
         // q >= +0: its bits order as its values do
         const float qv = mpdet::qdist(qi, ti, mpdet::quat{qj[u].x, qj[u].y, qj[u].z, qj[u].w},
                                       make_float3(tj[u].x, tj[u].y, tj[u].z), A.sr, A.st);
-        const bool ok = jc[u] >= 0 && jc[u] < A.n && jc[u] != i;
-        key[u] = ok ? ((uint64_t)__float_as_uint(qv) << 32) | (uint32_t)jc[u] : none;
+        key[u] = ok[u] ? ((uint64_t)__float_as_uint(qv) << 32) | (uint32_t)jc[u] : none;
     }
     // entry r (behind the particle itself) ends up in lane r % 16
     uint64_t mine[2] = {none, none};
@@ -414,9 +424,10 @@ static RefreshArgs refresh_args(mp_filter f, int window) {
 static int refresh_rows(mp_filter f, int C) {
     // 16 lanes per particle while one lane each would leave most of the chip
     // waiting for its loads, and for windows whose candidates fit five a lane.
-    // K = 16, window 32, one lane / 16 lanes: 4096 particles 47 / 8.6 us,
-    // 65,536 58 / 39 us, 131,072 70 / 70 us, 262,144 94 / 132 us; spread over the
-    // map, whose lists are nearly empty, 32,768 18 / 15 us, 65,536 19 / 27 us.
+    // One lane / 16 lanes, K = 16 and window 32: 4096 particles 44 / 7.4 us, 65,536
+    // 53 / 29, 98,304 60 / 39, 131,072 63 / 51, 262,144 83 / 96; spread over a hall,
+    // whose lists are nearly empty, 32,768 20 / 9.3 us, 65,536 25 / 16, 98,304 29 / 21,
+    // 262,144 52 / 58.  K = 8 and window 16 lose from 131,072 on: 23 / 25 spread.
     const int64_t cands = (int64_t)C + f->K - 1;
     if (f->n > kRfMax || cands > 5 * kRfLanes) return 0;
     return cands <= 2 * kRfLanes ? 2 : (cands <= 3 * kRfLanes ? 3 : 5);
