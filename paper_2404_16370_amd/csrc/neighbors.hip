@@ -255,10 +255,10 @@ __device__ __forceinline__ void refresh_row(const RefreshArgs& A, int block) {
     for (int u = 0; u < R; ++u) {
         key[u] = none;
         if (!any[u]) continue;
-        // q >= +0: its bits order as its values do
+        // q >= 0: its bits order as its values do (weights of -0 give a q of -0: + 0)
         const float qv = mpdet::qdist(qi, ti, mpdet::quat{qj[u].x, qj[u].y, qj[u].z, qj[u].w},
                                       make_float3(tj[u].x, tj[u].y, tj[u].z), A.sr, A.st);
-        key[u] = ok[u] ? ((uint64_t)__float_as_uint(qv) << 32) | (uint32_t)jc[u] : none;
+        key[u] = ok[u] ? ((uint64_t)__float_as_uint(qv + 0.0f) << 32) | (uint32_t)jc[u] : none;
     }
     // entry r (behind the particle itself) ends up in lane r % 16
     uint64_t mine[2] = {none, none};

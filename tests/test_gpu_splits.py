@@ -401,3 +401,18 @@ def test_refresh_of_spread_particles_on_either_side_of_the_rule(k, window):
         ms.append(float(np.median(t)))
         f.close()
     assert ms[0] <= 1.05 * ms[1], ms
+
+
+@pytest.mark.parametrize("n,k,window", [(300, 8, 16), (300, 20, 40), (300, 32, 64)])
+@pytest.mark.parametrize("sr,st", [(-0.0, -0.0), (0.0, 0.0), (-0.0, 2.5)])
+def test_refresh_with_zero_weights(room, O, n, k, window, sr, st):
+    # distances of either zero: every candidate is at the same one, taken by its index
+    poses = S.gaussian_particles(n, S.pose8(*room["w"]["traj"][0]), 0.1, 0.3, n)
+    f = _filter(room, n, poses, k=k, window_c=window, lsh_bits=4, sigma_r=sr, sigma_t=st)
+    for stage in (M.MP_STAGE_LSH, M.MP_STAGE_SORT, M.MP_STAGE_REFRESH):
+        f.debug_stage(stage)
+    nbr, q, cnt = O.refresh(f.debug_get("poses"), f.debug_get("sorted"), f.debug_get("codes"), k, window, sr, st, None)
+    assert cnt.max() > 1
+    assert np.array_equal(f.debug_get("nbr").T, nbr) and np.array_equal(f.debug_get("cnt"), cnt)
+    assert np.allclose(f.debug_get("kval").T, np.where(nbr >= 0, np.exp(-q.astype(np.float64)), 0.0), rtol=1e-5)
+    f.close()
