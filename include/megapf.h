@@ -431,7 +431,7 @@ typedef struct {
  * likelihood kernels on their branch.  autotune != 0 times the queue kernel
  * for each gather batch (2, 4, 8) and keeps the fastest, and times the
  * likelihood launch of every other PLAIN instance for each (lik_layout,
- * lik_batch) candidate (PARTICLE with 2, 4, 8, 16; GROUPED with 2, 4, 8) and
+ * lik_batch) candidate (PARTICLE with 0, 2, 4, 8, 16; GROUPED with 2, 4, 8) and
  * keeps the fastest in its parameters (speed only: the per-point arithmetic is
  * the same; sums are ordered differently by the two layouts).  Every filter
  * needs a scan uploaded.  Errors: MP_E_ARG, MP_E_STATE (no scan, a filter

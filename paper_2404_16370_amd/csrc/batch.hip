@@ -297,8 +297,11 @@ void autotune(mp_filter f, hipStream_t s) {
     const int32_t keep_b = f->p.lik_batch, keep_l = f->p.lik_layout;
     int32_t best_b = keep_b, best_l = keep_l;
     float best_ms = 1e30f;
-    static const int32_t cand[][2] = {{MP_LIK_LAYOUT_PARTICLE, 2}, {MP_LIK_LAYOUT_PARTICLE, 4},
-                                      {MP_LIK_LAYOUT_PARTICLE, 8}, {MP_LIK_LAYOUT_PARTICLE, 16},
+    // (a gather batch of 0 leaves the choice to the launch: small PARTICLE passes
+    // take a lane per evaluation then, 256 x 300 10 us instead of 69)
+    static const int32_t cand[][2] = {{MP_LIK_LAYOUT_PARTICLE, 0}, {MP_LIK_LAYOUT_PARTICLE, 2},
+                                      {MP_LIK_LAYOUT_PARTICLE, 4}, {MP_LIK_LAYOUT_PARTICLE, 8},
+                                      {MP_LIK_LAYOUT_PARTICLE, 16},
                                       {MP_LIK_LAYOUT_GROUPED, 2},  {MP_LIK_LAYOUT_GROUPED, 4},
                                       {MP_LIK_LAYOUT_GROUPED, 8}};
     try {

@@ -137,3 +137,17 @@ def test_batch_errors(world):
         b.step(np.array([[1, 0, 0, 0, np.nan, 0, 0]], np.float32), None)
     b.step(None, None)
     b.close()
+
+
+def test_autotuned_small_pass_keeps_a_lane_per_evaluation(world):
+    # 256 x 300 on a hashed map: a lane per evaluation (lik_batch 0) takes a
+    # seventh of any gather batch's time
+    spec = ("hashed", 256, 1, 8, M.MP_SCORER_PLAIN, slice(0, 300))
+    f, alone = _make(world, spec, 31), _make(world, spec, 31, lik_layout=M.MP_LIK_LAYOUT_PARTICLE)
+    b = M.Batch([f], autotune=True)
+    info = b.info()
+    assert (info["lik_layout"][0], info["lik_batch"][0]) == (M.MP_LIK_LAYOUT_PARTICLE, 0)
+    b.step()
+    alone.step()
+    _assert_same(_state(f), _state(alone), "a lane per evaluation")
+    b.close()
