@@ -125,3 +125,22 @@ def test_odometry_errors(world, O):
     with pytest.raises(M.MegaPFError):
         f.odometry(init=np.array([1, 0, 0, 0, np.inf, 0, 0], np.float32))
     f.odometry(iterations=1)
+
+
+@pytest.mark.parametrize("iterations", [1, 3, 8])
+def test_terms_after_iterations_match_oracle(world, O, iterations):
+    # the final evaluation against the oracle's at the returned dT, whose matches
+    # come from those of the iterations before: the bounds of one evaluation, and
+    # the share of matches that the pose's rounding to FP32 may move
+    w = world["w"]
+    f, ((p0, c0), (p1, c1)) = _filter(world, w["scans"][:2], O)
+    res = f.odometry(iterations=iterations)
+    ref = O.gicp_terms(p0, c0, p1, c1, res["dT"], dmax=1.0)
+    moved = int(np.sum(f.debug_get("odo_nn") != ref["nn"]))
+    assert moved <= 1e-3 * len(p1)
+    assert abs(res["inliers"] - ref["ninl"]) <= moved and ref["ninl"] > 500
+    share = 1e-4 + moved / ref["ninl"]
+    assert abs(res["cost"] - ref["cost"]) <= share * ref["cost"]
+    assert np.abs(res["H21"] - ref["H21"]).max() <= share * np.abs(ref["H21"]).max()
+    diag = ref["H21"][[0, 6, 11, 15, 18, 20]]
+    assert np.all(np.abs(res["b"] - ref["b"]) <= share * np.sqrt(diag * ref["cost"]))
