@@ -708,10 +708,10 @@ VARIANTS = {
 def variants_leg(M, m, wl, minfo, scans, odo, warmup=1, steps=1):
     """One full-size filter step per accuracy variant of the neighbour search
     and the Stein update (same map, scans and seed); stage times of the last
-    step, and the SVGD kernel against its HBM roofline."""
+    step, and the SVGD kernel against its HBM roofline (bytes of the lists as
+    they stand after it)."""
     import torch
     n, K, it = wl["particles"], wl["k"], wl["svgd_iters"]
-    svgd_bytes = (28.0 + 8 * K + 56.0 * K + 28.0) * n * it   # algorithmic bytes, neighbour gathers included
     out = {}
     for name, kw in VARIANTS.items():
         p = M.mp_filter_default_params(n_particles=n, k=K, lsh_bits=wl["lsh_bits"], svgd_iters=it,
@@ -731,8 +731,11 @@ def variants_leg(M, m, wl, minfo, scans, odo, warmup=1, steps=1):
                 ms.append(e0.elapsed_time(e1))
         st = f.stage_times()
         sv = st["svgd"][0]
+        listed = list_lengths(f, wl)[0]
+        svgd_bytes = list_bytes(K, listed, 0.0, 0)["svgd"] * n * it
         out[name] = {"params": kw, "step_ms": round(float(np.median(ms)), 3),
                      "stage_ms": {k: round(st[k][0], 3) for k in ("lsh", "sort", "refresh", "svgd")},
+                     "mean_list": round(listed, 2),
                      "svgd_hbm_frac": round(svgd_bytes / PEAK_HBM / (sv * 1e-3), 4) if sv > 0 else None}
         f.close()
         torch.cuda.synchronize()
@@ -740,12 +743,31 @@ def variants_leg(M, m, wl, minfo, scans, odo, warmup=1, steps=1):
     return out
 
 
-def svgd_refresh_bytes(K):
-    """compulsory bytes per particle and launch: SVGD reads K neighbour ids and
-    kernel values, its own pose and psi, writes its pose; the refresh reads its
-    sorted slot, bucket bounds, pose and old list, writes list, kernel values
-    and count"""
-    return 8.0 * K + 96.0, 48.0 + 12.0 * K
+def list_lengths(f, wl):
+    """mean number of entries of the filter's neighbour lists, and of bucket
+    mates in their windows, as they stand"""
+    window = np.minimum(f.debug_get("end") - f.debug_get("head") - 1, wl["window_c"])
+    return float(f.debug_get("cnt").mean(dtype=np.float64)), float(window.mean(dtype=np.float64))
+
+
+def list_bytes(K, listed, window, rounds):
+    """algorithmic bytes per particle of the stages that walk the lists, gathers
+    included, for lists of `listed` entries (the particle itself among them) in K
+    places and windows of `window` mates: all K ids are read, kernel values, poses
+    and psi of the entries alone"""
+    return {"svgd": 28.0 + 4 * K + 60.0 * listed + 28.0,
+            "refresh": 28.0 + 4 * K + 32.0 * window + 28.0 * listed + 8 * K,
+            "posterior": 20.0 + rounds * (4.0 * K + 8.0 * listed + 4)}
+
+
+def compulsory_list_bytes(K, listed, rounds):
+    """bytes per particle that each launch must move once: SVGD reads K neighbour
+    ids, the entries' kernel values, its own pose and psi, writes its pose; the
+    refresh reads its sorted slot, bucket bounds, pose and old list, writes list,
+    kernel values and count; a posterior round reads ids, kernel values and a
+    probability and writes one"""
+    return {"svgd": 4.0 * K + 4.0 * listed + 96.0, "refresh": 48.0 + 12.0 * K,
+            "posterior": 36.0 + rounds * (4.0 * K + 4.0 * listed + 8)}
 
 
 def point_map_leg(M, xyz, wl, scans, odo, cell=0.2, radius=5, warmup=1, steps=2):
@@ -798,29 +820,27 @@ def _med_p90(v):
             "n": int(a.size)}
 
 
-def stage_roofline(stages, wl, lik_flops_launch, t_step):
+def stage_roofline(stages, wl, lik_flops_launch, t_step, listed, window):
     """Each stage of one filter step against the resource that bounds it.
     `frac` takes the algorithmic bytes per particle: what the method must
     move, neighbour gathers included (prediction 56 B per
     frame; LSH 36 B in the first iteration, later ones' codes are left by the
-    SVGD update, 12 B; sort 16 B per 8-bit pass + 12 B of bucket bounds;
-    refresh 28 + 4K + 32C + 32K + 8K; SVGD 28 + 8K + 56K; posterior 20 + R
-    (12K + 4)).  A fraction above 1 means the caches serve the gathers.
-    `frac_compulsory` takes the bytes each launch must move once, gathers
-    counted once.  The likelihood and the scan k-NN (all pairs, most of which
+    SVGD update, 12 B; sort 16 B per 8-bit pass + 12 B of bucket bounds; list
+    stages by list_bytes for the last iteration's lists and windows).  A fraction
+    above 1 means the caches serve the gathers.  `frac_compulsory` takes the bytes
+    each launch must move once, gathers counted once.  The likelihood and the scan k-NN (all pairs, most of which
     its index skips) are set against the FP32 peak.  `step` sums the stages' roofline times over the measured step time."""
-    n, it, K, C, R = wl["particles"], wl["svgd_iters"], wl["k"], wl["window_c"], wl["post_iters"]
+    n, it, K, R = wl["particles"], wl["svgd_iters"], wl["k"], wl["post_iters"]
     ns, passes = wl["scan_points"], (wl["lsh_bits"] + 7) // 8
-    svgd_c, refresh_c = svgd_refresh_bytes(K)
+    lists, once = list_bytes(K, listed, window, R), compulsory_list_bytes(K, listed, R)
     work = {
         "predict": ("hbm", 56.0 * n, 64.0 * n),
         "lsh": ("hbm", 36.0 * n, 44.0 * n),
         "sort": ("hbm", (16.0 * passes + 12.0) * n * it, (16.0 * passes + 12.0) * n * it),
-        "refresh": ("hbm", (28.0 + 4 * K + 32.0 * C + 32.0 * K + 8 * K) * n * it, refresh_c * n * it),
+        "refresh": ("hbm", lists["refresh"] * n * it, once["refresh"] * n * it),
         "likelihood": ("alu", lik_flops_launch * it, lik_flops_launch * it),
-        "svgd": ("hbm", (28.0 + 8 * K + 56.0 * K + 28.0) * n * it + 12.0 * n * (it - 1),
-                 svgd_c * n * it + 12.0 * n * (it - 1)),
-        "posterior": ("hbm", (20.0 + R * (12.0 * K + 4)) * n, (36.0 + R * (8.0 * K + 8)) * n),
+        "svgd": ("hbm", lists["svgd"] * n * it + 12.0 * n * (it - 1), once["svgd"] * n * it + 12.0 * n * (it - 1)),
+        "posterior": ("hbm", lists["posterior"] * n, once["posterior"] * n),
         "scan": ("alu", 8.0 * ns * (ns - 1), 8.0 * ns * (ns - 1)),
     }
     out, t_min = {}, 0.0
@@ -980,7 +1000,7 @@ def main():
         "stage_ms_last_step": {k: round(v[0], 3) for k, v in stages.items() if v[1]},
         "step_ms_events": {"with_scan_upload": _med_p90([a + b for a, b in zip(up_ms, step_ms)]),
                            "without_scan_upload": _med_p90(step_ms), "scan_upload": _med_p90(up_ms)},
-        "stage_roofline": stage_roofline(stages, wl, flops_launch, elapsed / args.steps),
+        "stage_roofline": stage_roofline(stages, wl, flops_launch, elapsed / args.steps, *list_lengths(f, wl)),
         "roofline": {"bound": "alu", "achieved": achieved / 1e12, "peak": PEAK_FP32 / 1e12, "unit": "TFLOP/s",
                      "frac": achieved / PEAK_FP32, "traffic": measured_traffic(args.workload),
                      "kernel": "k_lik_grp (grouped layout)", "launch_ms": t_launch * 1e3,
