@@ -17,6 +17,14 @@ __device__ __forceinline__ float mp_row_max(float v) {
     return fmaxf(v, __uint_as_float(mp_row_ror<1>(__float_as_uint(v))));
 }
 
+// minimum over the row
+__device__ __forceinline__ float mp_row_min(float v) {
+    v = fminf(v, __uint_as_float(mp_row_ror<8>(__float_as_uint(v))));
+    v = fminf(v, __uint_as_float(mp_row_ror<4>(__float_as_uint(v))));
+    v = fminf(v, __uint_as_float(mp_row_ror<2>(__float_as_uint(v))));
+    return fminf(v, __uint_as_float(mp_row_ror<1>(__float_as_uint(v))));
+}
+
 // the votes of this lane's row of 16
 __device__ __forceinline__ uint32_t mp_row_ballot(bool p) {
     return (uint32_t)(__ballot(p) >> (threadIdx.x & 48)) & 0xFFFFu;
