@@ -617,12 +617,19 @@ extern "C" mp_status mp_scan_upload(mp_filter f, const float* xyz, const float* 
             DevMem& orig = follows ? f->prev_orig : f->scan_orig;
             DevMem& idx = follows ? f->prev_idx : f->scan_idx;
             const size_t rec_bytes = sizeof(float) * 12 * (size_t)n, idx_bytes = mp_scan_index_bytes(n);
+            bool own = (verdict & 2u) != 0;
             {
                 DevMem walk_new, orig_new, idx_new, own_new;
                 if (f->scan.bytes < rec_bytes) walk_new.alloc(rec_bytes);
                 if (orig.bytes < rec_bytes) orig_new.alloc(rec_bytes);
                 if (idx.bytes < idx_bytes) idx_new.alloc(idx_bytes);
-                if ((verdict & 2u) && f->scan_own.bytes < rec_bytes) own_new.alloc(rec_bytes);
+                if (own && f->scan_own.bytes < rec_bytes) {
+                    try {
+                        own_new.alloc(rec_bytes);
+                    } catch (const MpError&) {
+                        own = false;   // no room: the index keeps the walk order
+                    }
+                }
                 if (walk_new.p) f->scan.swap(walk_new);
                 if (orig_new.p) orig.swap(orig_new);
                 if (idx_new.p) idx.swap(idx_new);
@@ -634,7 +641,7 @@ extern "C" mp_status mp_scan_upload(mp_filter f, const float* xyz, const float* 
                 f->prev_n = f->orig_n;
             }
             f->orig_n = n;
-            f->idx_own = (verdict & 2u) != 0;
+            f->idx_own = own;
             const int32_t* perm = P.idx;
             ScanRecords R{f->scan_orig.as<float4>(), f->scan.as<float4>(), nullptr, nullptr};
             if (f->idx_own) {
