@@ -166,8 +166,9 @@ typedef struct {
     float prior_floor;    /* prior probabilities below this are raised to it */
     float cov_eps;        /* GICP epsilon for scan covariances */
     int32_t lik_chunks;   /* scan-point chunks per particle tile in the likelihood launch; 0 = auto */
-    int32_t lik_batch;    /* scan points whose NNF cells are requested together per lane: 1..32 (power of 2);
-                             0 = 4 in the PARTICLE layout, 2 in the GROUPED one (GROUPED takes 2, 4 or 8) */
+    int32_t lik_batch;    /* scan points whose NNF cells are requested together per lane: 1..32 (power of 2;
+                             GROUPED takes 2, 4 or 8); 0 = by the pass: 4 in the PARTICLE layout, small passes of
+                             which take a lane per particle and point, 2 in the GROUPED one, 8 in its small passes */
     int32_t lik_layout;   /* MP_LIK_LAYOUT_*: lanes per particle in the likelihood launch */
     int32_t scorer;       /* MP_SCORER_*: per-point term of the likelihood */
     float sigma_s;        /* MP_SCORER_SCOREFIELD: isotropic sensor std of the score field, metres */
@@ -426,8 +427,8 @@ typedef struct {
 /* Instances with the PLAIN scorer on a dense-field map get lik_layout =
  * GROUPED: in every correction iteration their likelihood passes run as one
  * persistent launch (a fixed grid of workgroups taking tiles of at most 256
- * particles x 1024 scan points of all these instances, in instance order, from
- * an atomic work queue); the other instances launch their own
+ * particles x 1024 scan points of all these instances, those with the most
+ * points a tile first, from an atomic work queue); the other instances launch their own
  * likelihood kernels on their branch.  autotune != 0 times the queue kernel
  * for each gather batch (2, 4, 8) and keeps the fastest, and times the
  * likelihood launch of every other PLAIN instance for each (lik_layout,

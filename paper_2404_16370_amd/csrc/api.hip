@@ -537,7 +537,7 @@ extern "C" mp_status mp_filter_destroy(mp_filter f) {
 // The verdict of a scan's check, 15 us after the call on an idle stream: polled
 // for a while, as waiting for the stream costs as much again and would wait for
 // the sort as well.  (An upload of 300 points returned after 42 us and was done
-// after 85 with the verdict copied back before the sort; 22 and 60 us now.)
+// after 85 with the verdict copied back before the sort; 20 and 50 us now.)
 static uint32_t scan_verdict(const ScanPrep& P, hipStream_t s) {
     const auto read = [&]() { return __atomic_load_n(P.verdict, __ATOMIC_ACQUIRE); };
     const auto t0 = std::chrono::steady_clock::now();
@@ -588,8 +588,8 @@ extern "C" mp_status mp_scan_upload(mp_filter f, const float* xyz, const float* 
             // Walk order for the likelihood: Morton order of the points on a grid of half the
             // map voxel, so that consecutive points of one particle land in the same or
             // neighbouring voxels (the sum over points does not depend on the order).
-            // Only the verdict of the check comes back: the sort, which touches nothing that
-            // a refused scan must leave alone, runs while the host waits for it.
+            // Only the verdict of the check comes back: the sort runs while the host waits for
+            // it.  Nothing before it touches what a refused scan must leave alone.
             ScanPrep P;
             P.part = f->scan_work.as<float4>();
             P.start = reinterpret_cast<uint64_t*>(P.part + 2 * kPrepParts);

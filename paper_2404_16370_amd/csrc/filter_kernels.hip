@@ -446,7 +446,7 @@ struct PostArgs {
     float* __restrict__ p1;
     const int32_t* __restrict__ nbr;
     const float* __restrict__ kval;
-    double* __restrict__ part;      // 4 x nblocks partials
+    double* __restrict__ part;      // 3 x nblocks partials
     int* __restrict__ ipart;        // nblocks
     double* __restrict__ info;
     float* __restrict__ prior_out;

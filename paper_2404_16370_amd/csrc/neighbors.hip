@@ -6,16 +6,19 @@
 //                log(T_LSH^-1 T_i) (coupled SE(3) logarithm),
 //                cell = floor(zeta) (deterministic FP32), code =
 //                hash6(cell) & (2^bits - 1).  T^LSH is drawn from Philox for
-//                (frame, iteration); every lane derives it, lane 0 records it.
+//                (frame, iteration) by one lane of a workgroup.  The SVGD update
+//                leaves the codes of the iterations after the first.
 //   sort         stable radix sort of (code, index)  -> buckets as runs
-//   k_bucket_bounds  bucket head/end per sorted position (search of the runs)
-//   k_refresh    one lane per particle (its sorted position from a rank
-//                array): candidates = previous list U
+//   k_bucket_bounds  bucket head/end per sorted position (search of the runs);
+//                sorts in one workgroup leave them themselves
+//   k_refresh_row, k_refresh  16 lanes or one per particle (its sorted position
+//                from a rank array): candidates = previous list U
 //                window of up to C bucket-mates after the particle (cyclic in
 //                its bucket); each ranked by q_ij = d^T W^K d (deterministic
 //                FP32), the K-1 smallest (q, j) kept behind the particle itself
-//                in a register-resident insertion network; k_ij = exp(-q_ij)
-//                cached for the SVGD update and the posterior propagation.
+//                (row minima, or a register-resident insertion network);
+//                k_ij = exp(-q_ij) cached for the SVGD update and the posterior
+//                propagation.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>

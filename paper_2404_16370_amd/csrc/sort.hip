@@ -2,8 +2,8 @@
 //
 // The radix sorts distribute particles into LSH buckets (Alg. 1, distribute
 // loop), order the scan points for the likelihood's walk and group map points
-// by voxel.  Every pass handles one 8-bit digit and is stable, so the sort is
-// stable: equal keys keep ascending value order when the values start as
+// by voxel.  Every pass handles one digit (8 to 10 bits; 4 in the sort of few keys)
+// and is stable, so the sort is stable: equal keys keep ascending value order when the values start as
 // 0..n-1.
 //
 // 32-bit keys (the per-iteration sorts) take a one-sweep form: one launch

@@ -1,5 +1,6 @@
-"""Launch splits and pruned searches that must not change a result: every
-comparison here is bit for bit."""
+"""Launch splits and pruned searches that must not change a result: compared bit
+for bit, but for the posterior's weights (a bound from its FP32 roundings) and
+the odometry's sums and matches after its own iterations (bounds at the test)."""
 import numpy as np
 import pytest
 
